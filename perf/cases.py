@@ -162,3 +162,50 @@ def tolerance(case):
     # Against the same quantities in 64 bits, measured on the small shapes of every path: 2.3e-3 (bf16 probabilities and results), 2.5e-3
     # for the gradients, 2.6e-2 for the 8-bit path on its own codes (probabilities rounded to three mantissa bits).
     return {"rel": 1e-1} if case["path"] == "fp8" else {"rel": 1e-2}
+
+
+def _rows_of_classes(T, H, W, s, step):
+    """Token numbers of every class (p, q), p slow, in raster order; a class of the token-wise pattern has step 1, of the group-wise s."""
+    n = torch.arange(T * H * W, device="cuda").view(T, H, W)
+    h, w = torch.arange(H, device="cuda"), torch.arange(W, device="cuda")
+    return [n[:, h // step % s == p][:, :, w // step % s == q].reshape(-1) for p in range(s) for q in range(s)]
+
+
+def exact(case, seed):
+    """What run() returns, in 64 bits and plain torch: attention inside every class, its gradients by the textbook formulas.  The 8-bit
+    path is held against attention on the tensors before they are quantised."""
+    state = prepare(case, seed)
+    T, H, W, s, path = case["T"], case["H"], case["W"], case["s"], case["path"]
+    step = s if case["pattern"] == "group" else 1
+    if path == "rearrange" or work(case)["flops"] > 4e13:
+        return None  # rows that are moved; over about 20 seconds
+    q, k, v = state["q"], state["k"], state["v"]
+    out = torch.zeros(q.shape, dtype=torch.float64, device="cuda")
+    grads = [torch.zeros_like(out) for _ in range(3)] if path == "train" else []
+    scale = q.shape[3] ** -0.5
+    for rows in _rows_of_classes(T, H, W, s, step):
+        for b in range(q.shape[0]):
+            for a in range(q.shape[2]):
+                if not rows.numel():
+                    continue
+                qd, kd, vd = (t[b, rows, a].double() for t in (q, k, v))
+                kt, vt = kd.t().contiguous(), vd.t().contiguous()
+                od = torch.empty_like(qd)
+                dq, dk, dv = torch.empty_like(qd), torch.zeros_like(kd), torch.zeros_like(vd)
+                chunk = max(1, (1 << 27) // rows.numel())
+                for i in range(0, rows.numel(), chunk):
+                    prob = torch.softmax((qd[i : i + chunk] @ kt) * scale, dim=1)
+                    od[i : i + chunk] = prob @ vd
+                    if grads:
+                        do = state["dout"][b, rows[i : i + chunk], a].double()
+                        dv += prob.t().contiguous() @ do
+                        ds = prob * (do @ vt - (do * od[i : i + chunk]).sum(dim=1, keepdim=True))
+                        dq[i : i + chunk] = (ds @ kd) * scale
+                        dk += (ds.t().contiguous() @ qd[i : i + chunk]) * scale
+                out[b, rows, a] = od
+                for grad, part in zip(grads, (dq, dk, dv)):
+                    grad[b, rows, a] = part
+    if path == "chain":  # the other pattern's layout: subsequences slow, batch fast
+        other = _rows_of_classes(T, H, W, s, 1 if step == s else s)
+        return torch.cat([out[:, rows] for rows in other])
+    return (out, *grads) if path == "train" else out
