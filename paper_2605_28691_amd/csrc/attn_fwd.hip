@@ -5,9 +5,11 @@
 // without ever forming the N x N matrix: keys are walked in blocks of 32 with a running row maximum and row sum.
 //
 // Mapping onto the hardware
-//   * One workgroup = 8 wavefronts (two per SIMD), each owning 32 query rows for the whole key walk: 256 queries share
-//     every K/V tile that is brought into LDS, which halves the L2 -> LDS traffic per MFMA compared with 128 queries.
-//     One workgroup per CU (<= 256 VGPRs per lane, 64 KiB LDS).
+//   * One workgroup = NW wavefronts in KG key groups; a wavefront owns 32 query rows, the wavefronts of a group walk the same keys
+//     and share every K/V tile that is brought into LDS.  The shape for large problems is 8 wavefronts in one group: 256 queries
+//     a tile halve the L2 -> LDS traffic per MFMA compared with 128 (two wavefronts per SIMD, <= 256 VGPRs per lane, 64 KiB LDS).
+//     Small problems are bound by idle CUs and by the serial walk over the keys instead; they get smaller workgroups, and two
+//     groups that walk half of the keys each and merge (reference, sum, O) through LDS at the end: see pick_shape().
 //   * The products are formed transposed, S^T = K Q^T and O^T = V^T P^T, with v_mfma_f32_32x32x16_bf16.  In the
 //     32x32 accumulator layout lane l holds column l%32, so every lane owns ONE query: its 16 registers per 32-key
 //     block are 16 keys of that query, and the exponentiated accumulator registers, rounded to bf16, ARE the B operand
@@ -36,7 +38,7 @@
 //   * Row addresses come from the Skiparse index map: in the dense mode position j is row j, in the sparse modes it is
 //     the token the rearrangement (Algorithm 1) would have put at position j, so q, k, v are read and out is written in
 //     the original layout and no permuted copy exists.  The rows' byte offsets are formed 8 tiles ahead, one tile (64 rows,
-//     lane = row) per window by one wavefront in turn, and kept in a small ring in LDS from which every lane picks up the
+//     lane = row) per window by one wavefront of the group in turn, and kept in a small ring in LDS from which every lane picks up the
 //     two rows it fetches: the index arithmetic costs a wavefront one evaluation of the map per 8 tiles.
 //   * Workgroups are numbered so that the query tiles of one unit run on the same XCD (workgroup id mod 8 selects
 //     the XCD under round-robin dispatch; every XCD owns a contiguous eighth of the (unit, tile) order) and walk K/V in
@@ -59,23 +61,22 @@ typedef __attribute__((ext_vector_type(4))) unsigned int u32x4;
 #define LDS_PTR(T) __attribute__((address_space(3))) T*
 
 constexpr int KT = 64;          // keys per staged tile (two 32-key blocks)
-constexpr int NW = 8;            // wavefronts per workgroup: two per SIMD, all sharing one K/V tile in LDS
-constexpr int NTHREADS = 64 * NW;
 constexpr int ATTN_QT = 1;       // 32-query tiles per wavefront
-constexpr int RING_AHEAD = NW;   // row offsets are formed this many tiles ahead, by one wavefront per window in turn
+constexpr int RING_AHEAD = 8;    // row offsets are formed this many tiles ahead, by one wavefront per window in turn
 constexpr int RING = 16;         // tiles of row offsets (and key validity) kept in LDS: a slot is rewritten RING - RING_AHEAD windows after its last use
-static_assert((NW & (NW - 1)) == 0 && (RING & (RING - 1)) == 0 && RING >= RING_AHEAD + 4, "ring sizes");
+static_assert((RING & (RING - 1)) == 0 && RING >= RING_AHEAD + 4, "ring sizes");
 constexpr int LDS_AHEAD = 4;     // MFMA groups by which the LDS fragment reads run ahead in the steady state
 constexpr float RESCALE_LOG2 = 8.0f;  // the reference maximum is only raised when it grew by more than 2^8
 
-template <int D>
+// QW: wavefronts that share a tile (and fetch it together)
+template <int D, int QW>
 struct Tile {
     static constexpr int CH = D / 8;                     // 16-byte chunks per row
     static constexpr int RB = D * 2;                     // row bytes in LDS: rows are packed, bank conflicts are avoided by a swizzle
     static constexpr int RPI = 64 / CH;                  // rows covered by one direct-to-LDS instruction of a wavefront (64 chunks)
-    static constexpr int IPW = CH / NW;                  // such instructions per wavefront and 64-row tile
+    static constexpr int IPW = CH / QW;                  // such instructions per wavefront and 64-row tile
     static constexpr int TILE_BYTES = KT * RB;
-    static_assert(IPW >= 1 && IPW * NW == CH, "a tile is CH instructions, spread evenly over the wavefronts");
+    static_assert(IPW >= 1 && IPW * QW == CH, "a tile is CH instructions, spread evenly over the wavefronts");
     // chunk c of row r is stored at chunk position c ^ swz(r): see lds_layout.h
     __host__ __device__ static constexpr uint32_t swz(uint32_t r) { return lds_swizzle<D>(r); }
 };
@@ -123,22 +124,32 @@ __device__ inline size_t scattered_row(const AttnArgs& a, uint32_t sb, uint32_t 
     return ((size_t)(p * s + q) * B + b) * (uint32_t)gi.n_sub + r * (W / s) + ws;
 }
 
-template <int D, int QT, bool PAD>
-__global__ __launch_bounds__(NTHREADS, (QT == 1 && NW == 4 ? 2 : 1)) void attn_fwd_bf16_kernel(AttnArgs a, uint32_t q_tiles, uint32_t total, uint32_t per_xcd) {
-    using TL = Tile<D>;
+template <int D, int NW, int KG, bool PAD>
+__global__ __launch_bounds__(64 * NW, (NW == 4 && KG == 1 ? 2 : 1)) void attn_fwd_bf16_kernel(AttnArgs a, uint32_t q_tiles, uint32_t total, uint32_t per_xcd) {
+    constexpr int QT = ATTN_QT;
+    constexpr int QW = NW / KG;    // wavefronts of a key group: each owns 32 queries, all walk the same keys
+    static_assert((QW & (QW - 1)) == 0 && QW * KG == NW, "key groups are of equal size");
+    using TL = Tile<D, QW>;
     constexpr int KS = D / 16;     // MFMA steps along head_dim for S^T = K Q^T
     constexpr int MT = D / 32;     // 32-row blocks of O^T
-    constexpr int BR = 32 * NW * QT;   // query rows per workgroup: QT tiles of 32 per wavefront
+    constexpr int BR = 32 * QW * QT;   // query rows per workgroup: QT tiles of 32 per wavefront
     // four separate arrays: the compiler must be able to tell that the tile being filled is not the tile being read
-    __shared__ __attribute__((aligned(1024))) char kbuf0[TL::TILE_BYTES];
-    __shared__ __attribute__((aligned(1024))) char kbuf1[TL::TILE_BYTES];
-    __shared__ __attribute__((aligned(1024))) char vbuf0[TL::TILE_BYTES];
-    __shared__ __attribute__((aligned(1024))) char vbuf1[TL::TILE_BYTES];
-    __shared__ __attribute__((aligned(16))) uint32_t rowoff[RING][KT];        // byte offsets of the rows of the next tiles
-    __shared__ __attribute__((aligned(16))) float kbias[RING][KT];            // PAD only: logit bias per row of a K tile, 0 = real key, -inf = padding
+    __shared__ __attribute__((aligned(1024))) char kbuf0_all[KG * TL::TILE_BYTES];
+    __shared__ __attribute__((aligned(1024))) char kbuf1_all[KG * TL::TILE_BYTES];
+    __shared__ __attribute__((aligned(1024))) char vbuf0_all[KG * TL::TILE_BYTES];
+    __shared__ __attribute__((aligned(1024))) char vbuf1_all[KG * TL::TILE_BYTES];
+    __shared__ __attribute__((aligned(16))) uint32_t rowoff_all[KG][RING][KT];        // byte offsets of the rows of the next tiles
+    __shared__ __attribute__((aligned(16))) float kbias_all[KG][RING][KT];            // PAD only: logit bias per row of a K tile, 0 = real key, -inf = padding
 
     const uint32_t tid = threadIdx.x, lane = tid & 63u, wave = uniform(tid >> 6);
     const uint32_t lq = lane & 31u, h = lane >> 5;
+    const uint32_t kg = KG == 1 ? 0u : wave / QW, qw = KG == 1 ? wave : wave % QW;  // key group, wavefront of the group
+    char* const kbuf0 = kbuf0_all + kg * TL::TILE_BYTES;
+    char* const kbuf1 = kbuf1_all + kg * TL::TILE_BYTES;
+    char* const vbuf0 = vbuf0_all + kg * TL::TILE_BYTES;
+    char* const vbuf1 = vbuf1_all + kg * TL::TILE_BYTES;
+    uint32_t (*const rowoff)[KT] = rowoff_all[kg];
+    float (*const kbias)[KT] = kbias_all[kg];
 
     // workgroup -> (unit, query tile): id%8 is the XCD; each XCD owns a contiguous range of the (unit, tile) order, so that the
     // tiles of a unit run on one XCD (two at a range boundary) and the load is even for any number of units
@@ -168,7 +179,7 @@ __global__ __launch_bounds__(NTHREADS, (QT == 1 && NW == 4 ? 2 : 1)) void attn_f
     size_t q_row_off[QT];
 #pragma unroll
     for (int qi = 0; qi < QT; qi++) {
-        const uint32_t jq = qt * BR + (wave * QT + qi) * 32u + lq;
+        const uint32_t jq = qt * BR + (qw * QT + qi) * 32u + lq;
         q_valid[qi] = jq < n_seq;
         if (PAD) {
             bool real;
@@ -191,9 +202,13 @@ __global__ __launch_bounds__(NTHREADS, (QT == 1 && NW == 4 ? 2 : 1)) void attn_f
     // row, straight from the index map, and every lane of the workgroup later picks up the offsets of the rows it fetches.  The
     // index arithmetic thus costs each wavefront one evaluation per 8 tiles instead of one per tile and fetched row.
     const uint32_t row_bytes = (uint32_t)C * 2u;
+    // the key group's share of the tiles; tiles and 32-key blocks are numbered from its start below
+    const uint32_t all_tiles = (n_seq + KT - 1) / KT;
+    const uint32_t tile0 = KG == 1 ? 0u : kg * all_tiles / KG;
+    const uint32_t n_tiles = KG == 1 ? all_tiles : (kg + 1u) * all_tiles / KG - tile0;
     const uint32_t last_off = PAD ? 0u : src_token(a.g, p, q, n_seq - 1u) * row_bytes;  // rows past the end read the last valid row
     auto produce = [&](uint32_t tile) __attribute__((always_inline)) {
-        const uint32_t j = tile * KT + lane, jc = j < n_seq ? j : n_seq - 1u;
+        const uint32_t j = (tile0 + tile) * KT + lane, jc = j < n_seq ? j : n_seq - 1u;
         uint32_t off;
         if (PAD) {
             bool real;
@@ -209,7 +224,7 @@ __global__ __launch_bounds__(NTHREADS, (QT == 1 && NW == 4 ? 2 : 1)) void attn_f
     uint32_t st_row[TL::IPW], st_cb[TL::IPW];
 #pragma unroll
     for (int i = 0; i < TL::IPW; i++) {
-        st_row[i] = (wave * TL::IPW + i) * TL::RPI + lane / TL::CH;  // row of the tile
+        st_row[i] = (qw * TL::IPW + i) * TL::RPI + lane / TL::CH;  // row of the tile
         st_cb[i] = ((lane % TL::CH) ^ TL::swz(st_row[i])) * 16u;  // byte offset, inside the row, of the chunk this lane fetches
     }
     struct RowOffs {
@@ -226,7 +241,7 @@ __global__ __launch_bounds__(NTHREADS, (QT == 1 && NW == 4 ? 2 : 1)) void attn_f
 #pragma unroll
         for (int i = 0; i < TL::IPW; i++)
             __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)((const char*)g + o.off[i]),
-                                             (LDS_PTR(void))(buf + (wave * TL::IPW + i) * 1024u), 16, 0, 0);
+                                             (LDS_PTR(void))(buf + (qw * TL::IPW + i) * 1024u), 16, 0, 0);
     };
     auto issue_k = [&](char* buf, const RowOffs& o) __attribute__((always_inline)) { issue_tile(Kg, buf, o); };
     auto issue_v = [&](char* buf, const RowOffs& o) __attribute__((always_inline)) { issue_tile(Vg, buf, o); };
@@ -359,7 +374,7 @@ __global__ __launch_bounds__(NTHREADS, (QT == 1 && NW == 4 ? 2 : 1)) void attn_f
             if (decltype(MASK)::value && !PAD) {  // PAD: positions past the end carry the -inf bias like every padding position
 #pragma unroll
                 for (int r = 0; r < 16; r++) {
-                    const uint32_t key = blk * 32u + 8 * (r >> 2) + 4 * h + (r & 3);
+                    const uint32_t key = tile0 * KT + blk * 32u + 8 * (r >> 2) + 4 * h + (r & 3);
                     s[r] = key < n_seq ? s[r] : -INFINITY;
                 }
             }
@@ -498,25 +513,22 @@ __global__ __launch_bounds__(NTHREADS, (QT == 1 && NW == 4 ? 2 : 1)) void attn_f
     using P0 = std::integral_constant<int, 0>;
     using P1 = std::integral_constant<int, 1>;
 
-    const uint32_t n_tiles = (n_seq + KT - 1) / KT;
-
     // Staging schedule.  Window W reads K tile W and V tile W-1 from LDS.  Between its two steps it enqueues the direct loads of
     // K tile W+1 (into the K buffer that window W-1 read) and of V tile W (into the V buffer that window W-1 read); they have half
     // a window to land and are waited for just before the window's closing barrier.  The row offsets of tile W+2 are picked up
-    // from the ring in window W (so that the LDS read is not waited for), and tile W+RING_AHEAD's are formed by wavefront W%8.
+    // from the ring in window W (so that the LDS read is not waited for), and tile W+RING_AHEAD's are formed by wavefront W % QW of the group.
     // ---- prologue: offsets of tiles 0..RING_AHEAD, K tile 0
-    produce(wave);
-    if (wave == 0) produce(RING_AHEAD);
+    for (uint32_t t = qw; t <= (uint32_t)RING_AHEAD; t += QW) produce(t);
     __syncthreads();
     RowOffs off_v = read_offs(0);  // offsets of the tile whose V is fetched next
     issue_k(kbuf0, off_v);
-    RowOffs off_k = read_offs(1);  // offsets of the tile whose K is fetched next (rows past the end repeat the last row)
+    RowOffs off_k = read_offs(1);  // offsets of the tile whose K is fetched next (past the group's last tile: read, never used)
     tile_landed();
     __syncthreads();
 
     // ---- window 0: QK(0), then step 0 without PV
     {
-        issue_k(kbuf1, off_k);
+        if (n_tiles > 1) issue_k(kbuf1, off_k);
         issue_v(vbuf0, off_v);
         off_v = off_k;
         off_k = read_offs(2);
@@ -539,7 +551,7 @@ __global__ __launch_bounds__(NTHREADS, (QT == 1 && NW == 4 ? 2 : 1)) void attn_f
         // the L2 misses quadruple (measured: 2.4e8 instead of 5.7e7 per call, and 1.6 % more time); spreading the issues over the
         // MFMA groups is slower still (each issue stalls the wavefront).
         const RowOffs off_ahead = read_offs(Wn + 2u);
-        if (wave == (Wn & (uint32_t)(NW - 1))) produce(Wn + RING_AHEAD);
+        if (qw == (Wn & (uint32_t)(QW - 1))) produce(Wn + RING_AHEAD);
         const Frags pre = first_frags(P1{}, kb, vb);
         Frags mid, none;
         step_manual(P1{}, T_{}, kb, vb, 2 * Wn - 1, pre, mid);
@@ -579,6 +591,50 @@ __global__ __launch_bounds__(NTHREADS, (QT == 1 && NW == 4 ? 2 : 1)) void attn_f
         pv(vb, 1, preg[1]);
     }
 
+    // ---- key groups: the first one takes in the others' (reference, sum, O), through the LDS of the tiles
+    if constexpr (KG > 1) {
+        if (n_tiles < (all_tiles + KG - 1) / KG) __syncthreads();  // a group with one tile less has passed one barrier less
+        __syncthreads();                                           // every tile has been read
+        __shared__ float part_ml[KG][QW][2][64];
+        static_assert(MT * 4 * 1024 == TL::TILE_BYTES && QW <= 4, "the accumulators of a wavefront take a tile buffer");
+        char* const bufs[4] = {kbuf0_all, kbuf1_all, vbuf0_all, vbuf1_all};
+        if (kg != 0) {
+            char* dst = (qw == 0 ? kbuf0 : qw == 1 ? kbuf1 : qw == 2 ? vbuf0 : vbuf1) + lane * 16u;
+#pragma unroll
+            for (int mt = 0; mt < MT; mt++)
+#pragma unroll
+                for (int g = 0; g < 4; g++) {
+                    f32x4 o;
+#pragma unroll
+                    for (int e = 0; e < 4; e++) o[e] = oacc[0][mt][g * 4 + e];
+                    *(f32x4*)(dst + (mt * 4 + g) * 1024) = o;
+                }
+            part_ml[kg][qw][0][lane] = m_ref[0];
+            part_ml[kg][qw][1][lane] = l_run[0];
+        }
+        __syncthreads();
+        if (kg != 0) return;
+        const char* src = (qw == 0 ? bufs[0] : qw == 1 ? bufs[1] : qw == 2 ? bufs[2] : bufs[3]) + lane * 16u;
+#pragma unroll
+        for (int og = 1; og < KG; og++) {
+            const float mo = part_ml[og][qw][0][lane], lo = part_ml[og][qw][1][lane];
+            const float m_new = fmaxf(m_ref[0], mo);
+            // a group that saw nothing but padding has the reference -inf, l = 0 and O = 0
+            const float w0 = m_ref[0] == m_new ? 1.0f : __builtin_amdgcn_exp2f((m_ref[0] - m_new) * c);
+            const float w1 = mo == m_new ? 1.0f : __builtin_amdgcn_exp2f((mo - m_new) * c);
+            m_ref[0] = m_new;
+            l_run[0] = l_run[0] * w0 + lo * w1;
+#pragma unroll
+            for (int mt = 0; mt < MT; mt++)
+#pragma unroll
+                for (int g = 0; g < 4; g++) {
+                    const f32x4 o = *(const f32x4*)(src + og * TL::TILE_BYTES + (mt * 4 + g) * 1024);
+#pragma unroll
+                    for (int e = 0; e < 4; e++) oacc[0][mt][g * 4 + e] = oacc[0][mt][g * 4 + e] * w0 + o[e] * w1;
+                }
+        }
+    }
+
     // ---- epilogue: O = O^T / l, rounded to bf16; lane owns query lq, register r of block mt is channel 32*mt + 8*(r/4) + 4*h + r%4
 #pragma unroll
     for (int qi = 0; qi < QT; qi++) {
@@ -587,14 +643,14 @@ __global__ __launch_bounds__(NTHREADS, (QT == 1 && NW == 4 ? 2 : 1)) void attn_f
         const float inv = 1.0f / (llo + lhi);
         if (a.lse != nullptr && h == 0) {
             // log-sum-exp of the scaled logits: the reference is in raw logit units, the sum is relative to it
-            const uint32_t jq = qt * BR + (wave * QT + qi) * 32u + lq;
+            const uint32_t jq = qt * BR + (qw * QT + qi) * 32u + lq;
             if (jq < n_seq) a.lse[(size_t)unit * n_seq + jq] = q_valid[qi] ? m_ref[qi] * a.scale + __logf(llo + lhi) : 0.f;
         }
         if (q_valid[qi]) {
             __bf16* orow = Og + q_row_off[qi];
             if (a.out_kind != OUT_AS_INPUT) {
                 // the input is a sparse layout: bb is the subsequence (p, q, b) and this lane's query sits at position jq of it
-                const uint32_t jq = qt * BR + (wave * QT + qi) * 32u + lq;
+                const uint32_t jq = qt * BR + (qw * QT + qi) * 32u + lq;
                 orow = (__bf16*)a.out + scattered_row(a, bb, jq) * C + (size_t)head * D;
             }
 #pragma unroll
@@ -610,22 +666,72 @@ __global__ __launch_bounds__(NTHREADS, (QT == 1 && NW == 4 ? 2 : 1)) void attn_f
     }
 }
 
-template <int D, int QT, bool PAD>
-static hipError_t launch_t(const AttnArgs& a, hipStream_t stream) {
-    const uint32_t s2 = a.g.mode == MODE_DENSE ? 1u : (uint32_t)(a.g.s * a.g.s);
-    const uint32_t n_units = (uint32_t)a.B * s2 * (uint32_t)a.heads;
-    const uint32_t q_tiles = ((uint32_t)a.g.n_sub + 32u * NW * QT - 1u) / (32u * NW * QT);
+template <int D, int NW, int KG, bool PAD>
+static hipError_t launch_t(const AttnArgs& a, uint32_t n_units, hipStream_t stream) {
+    constexpr uint32_t BR = 32u * (NW / KG) * ATTN_QT;
+    const uint32_t q_tiles = ((uint32_t)a.g.n_sub + BR - 1u) / BR;
     const uint64_t total = (uint64_t)n_units * q_tiles;
     if (total > 0x7ffffff0ull) return hipErrorInvalidConfiguration;
     const uint32_t per_xcd = (uint32_t)((total + 7u) / 8u);
-    attn_fwd_bf16_kernel<D, QT, PAD><<<8u * per_xcd, NTHREADS, 0, stream>>>(a, q_tiles, (uint32_t)total, per_xcd);
+    attn_fwd_bf16_kernel<D, NW, KG, PAD><<<8u * per_xcd, 64 * NW, 0, stream>>>(a, q_tiles, (uint32_t)total, per_xcd);
     return hipGetLastError();
+}
+
+// Which workgroup shape a call gets.  A workgroup of NW wavefronts in KG key groups takes 32 * NW / KG queries:
+//   0  8 wavefronts, 1 group:  256 queries share every tile; the least L2 -> LDS traffic per MFMA, the best once the chip is full
+//   1  4 wavefronts, 1 group:  128 queries, two (head_dim 64: three) workgroups per CU; twice as many, finer-grained workgroups
+//   2  4 wavefronts, 2 groups:  64 queries, each group walks half of the keys: four times the workgroups, half the serial chain
+//   3  8 wavefronts, 2 groups: 128 queries, half the chain at two wavefronts per SIMD
+// Small problems leave compute units idle or a last round nearly empty, so the shape with the smallest estimated time is taken:
+// rounds over the 256 CUs, each as long as `fixed` plus, per 32-key block, the cost with k workgroups on a CU.  The costs (in units
+// of 0.1 us) were fitted to launches of every shape over 1..160 units of 32..8190 tokens; measured, before (always shape 0) -> after, us at
+// head_dim 128, units x tokens: 8x250 13.4 -> 8.2, 48x390 18.7 -> 13.7, 160x960 101 -> 88, 24x2600 134 -> 85, 48x2600 213 -> 165,
+// 4x5000 109 -> 66, 1x5000 107 -> 60; 48x960 (32) and 48x8190 (1390) keep shape 0.  At head_dim 64: 24x2600 88 -> 52, 160x4000 804 -> 708.
+struct ShapeCost {
+    int max_k;          // workgroups of this shape that one CU holds
+    float fixed;        // prologue, pipeline fill, epilogue (and the merge of key groups)
+    float block[3];     // per 32-key block of the sequence with k = 1..max_k workgroups on a CU
+};
+constexpr int N_SHAPES = 4;
+constexpr int SHAPE_QUERIES[N_SHAPES] = {256, 128, 64, 128};
+constexpr ShapeCost COST_128[N_SHAPES] = {{1, 40.f, {9.0f}}, {2, 20.f, {5.5f, 10.0f}}, {1, 25.f, {3.9f}}, {1, 45.f, {4.7f}}};
+constexpr ShapeCost COST_64[N_SHAPES] = {{1, 30.f, {5.2f}}, {3, 15.f, {3.6f, 5.7f, 8.0f}}, {2, 15.f, {2.4f, 3.7f}}, {1, 30.f, {2.9f}}};
+
+static int pick_shape(const ShapeCost* cost, uint32_t n_units, uint32_t n_sub) {
+    constexpr uint64_t CUS = 256;
+    const float blocks = (float)((n_sub + 31u) / 32u);
+    int best = 0;
+    float best_t = 0.f;
+    for (int v = 0; v < N_SHAPES; v++) {
+        if (v >= 2 && n_sub <= (uint32_t)KT) continue;  // a key group needs a tile of its own
+        const uint64_t wgs = (uint64_t)n_units * ((n_sub + SHAPE_QUERIES[v] - 1u) / SHAPE_QUERIES[v]);
+        const uint64_t per_round = CUS * cost[v].max_k, rounds = wgs / per_round, rem = wgs % per_round;
+        float t = (float)rounds * (cost[v].fixed + blocks * cost[v].block[cost[v].max_k - 1]);
+        if (rem != 0) t += cost[v].fixed + blocks * cost[v].block[(rem - 1u) / CUS];
+        if (v == 0 || t < best_t) {
+            best = v;
+            best_t = t;
+        }
+    }
+    return best;
+}
+
+template <int D, bool PAD>
+static hipError_t launch_shape(const AttnArgs& a, hipStream_t stream) {
+    const uint32_t s2 = a.g.mode == MODE_DENSE ? 1u : (uint32_t)(a.g.s * a.g.s);
+    const uint32_t n_units = (uint32_t)a.B * s2 * (uint32_t)a.heads;
+    switch (pick_shape(D == 128 ? COST_128 : COST_64, n_units, (uint32_t)a.g.n_sub)) {
+        case 1: return launch_t<D, 4, 1, PAD>(a, n_units, stream);
+        case 2: return launch_t<D, 4, 2, PAD>(a, n_units, stream);
+        case 3: return launch_t<D, 8, 2, PAD>(a, n_units, stream);
+        default: return launch_t<D, 8, 1, PAD>(a, n_units, stream);
+    }
 }
 
 hipError_t launch_attn_bf16(const AttnArgs& a, hipStream_t stream) {
     // one kernel serves the token-wise, group-wise and dense index maps: the map is only evaluated when the offset ring is filled
-    if (a.head_dim == 128) return a.pad ? launch_t<128, ATTN_QT, true>(a, stream) : launch_t<128, ATTN_QT, false>(a, stream);
-    if (a.head_dim == 64) return a.pad ? launch_t<64, ATTN_QT, true>(a, stream) : launch_t<64, ATTN_QT, false>(a, stream);
+    if (a.head_dim == 128) return a.pad ? launch_shape<128, true>(a, stream) : launch_shape<128, false>(a, stream);
+    if (a.head_dim == 64) return a.pad ? launch_shape<64, true>(a, stream) : launch_shape<64, false>(a, stream);
     return hipErrorInvalidValue;
 }
 

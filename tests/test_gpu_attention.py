@@ -264,3 +264,40 @@ def test_largest_admitted_batch_element_sampled_rows():
     p = [ctypes.c_void_p(t.data_ptr()) for t in (q, k, v, out)]
     rc = sk.lib().skiparse_attn_fwd(*p, 1, heads, T, 120, 168, D, s, 0, ctypes.c_float(0.0), 0, 1, None, 0, None)
     assert rc == -2
+
+
+# The forward's workgroup shape follows the problem's size: 64, 128 or 256 queries a workgroup, the keys walked by one group of
+# wavefronts or by two that are merged at the end.  Edges of all of them: one key tile more than a group, uneven halves, last query
+# tile of one row, many and few units, halves of the keys that hold nothing but padding.
+@pytest.mark.parametrize("heads,N", [(1, 65), (2, 128), (1, 129), (3, 321), (80, 65), (200, 129), (300, 33), (4, 1921), (90, 449), (12, 2497)])
+@pytest.mark.parametrize("D", [64, 128])
+def test_workgroup_shapes(heads, N, D):
+    import paper_2605_28691_amd as sk
+
+    w = si.make_shape("shapes", 1, heads, D, 1, 1, N, 1, seed=N + heads)
+    q, k, v = si.make_qkv(w)
+    q = (q.float() * 2.0).to(torch.bfloat16)  # references of the two key groups that differ by several powers of two
+    rng = np.random.default_rng(N)
+    ns = np.concatenate([rng.integers(0, N, 12), [0, N - 1]])
+    rows = np.array([(0, int(h), int(n)) for h in sorted({0, heads // 2, heads - 1}) for n in ns], dtype=np.int64)
+    want = oracle.skiparse_attention_rows(*oracle_inputs(q, k, v), rows, 1, 1, N, 1, "token", w.scale)
+    out, lse = sk.skiparse_attn_fwd_lse(*_gpu((q, k, v)), 1, 1, N, 1, "token", scale=w.scale)
+    assert_close_bf16(gather_rows(out, rows), want, f"heads {heads} N {N}")
+    # log-sum-exp of one head against float64 (bf16 products are exact in float32, so its error is that of exp and log in 32 bits)
+    logits = to_np64(q[0, :, heads - 1]) @ to_np64(k[0, :, heads - 1]).T * w.scale
+    m = logits.max(-1, keepdims=True)
+    assert np.abs(to_np64(lse[0, heads - 1]) - (m + np.log(np.exp(logits - m).sum(-1, keepdims=True)))[:, 0]).max() <= 5e-3
+
+
+@pytest.mark.parametrize("D", [64, 128])
+@pytest.mark.parametrize("pattern", ["token", "group"])
+@pytest.mark.parametrize("T,H,W,s", [(1, 17, 64, 4), (1, 9, 33, 3), (3, 17, 21, 2)])
+def test_key_groups_of_padding(T, H, W, s, pattern, D):
+    import paper_2605_28691_amd as sk
+
+    w = si.make_shape("padgroups", 1, 2, D, T, H, W, s, seed=5)
+    q, k, v = si.make_qkv(w)
+    rows = np.array([(0, h, n) for h in range(2) for n in range(T * H * W)], dtype=np.int64)
+    want = oracle.skiparse_attention_rows_padded(*oracle_inputs(q, k, v), rows, T, H, W, s, pattern, w.scale)
+    out = sk.skiparse_attn_fwd(*_gpu((q, k, v)), T, H, W, s, pattern, scale=w.scale, pad=True)
+    assert_close_bf16(gather_rows(out, rows), want, f"padded {pattern}")
