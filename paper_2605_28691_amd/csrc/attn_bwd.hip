@@ -47,8 +47,8 @@ constexpr int BRING_AHEAD = BNW;   // row offsets are formed this many tiles ahe
 constexpr int BRING = 16;          // tiles of row offsets kept in LDS
 static_assert((BNW & (BNW - 1)) == 0 && (BRING & (BRING - 1)) == 0 && BRING >= BRING_AHEAD + 4, "ring sizes");
 
-// PAD: any-resolution mode (Sec. 3.2): positions run over the grid padded to multiples of s*s; a padding position is skipped as an
-// owner and contributes nothing as a streamed row (a -inf bias as the initial accumulator of the logits in both launches).
+// PAD: any-resolution mode (Sec. 3.2): the kernel walks the real tokens of the class only (ClassMap), so that a padding position is
+// never met; log-sum-exp and delta are laid out over the padded grid.
 template <int D, int MODE, bool PAD>
 __global__ __launch_bounds__(BNT) void attn_bwd_kernel(BwdArgs a, uint32_t o_tiles, uint32_t total, uint32_t per_xcd) {
     constexpr int KS = D / 16;   // MFMA steps along head_dim
@@ -86,10 +86,9 @@ __global__ __launch_bounds__(BNT) void attn_bwd_kernel(BwdArgs a, uint32_t o_til
     __shared__ __attribute__((aligned(1024))) char s2buf0[TILE_BYTES];
     __shared__ __attribute__((aligned(1024))) char s2buf1[TILE_BYTES];
     __shared__ __attribute__((aligned(1024))) char own2buf[DKV ? 32 * BNW * RB : 16];  // DKV: V rows of the 256 owners, swizzled like a tile
-    __shared__ __attribute__((aligned(16))) float row_l[2][BT];  // initial M1 per streamed row: dK+dV -L/scale of the query; dQ (PAD) 0 / -inf
+    __shared__ __attribute__((aligned(16))) float row_l[2][BT];  // initial M1 per streamed row, dK+dV: -L/scale of the query
     __shared__ __attribute__((aligned(16))) float row_d[2][BT];  // initial M2 per streamed row: dK+dV -delta of the query
     __shared__ __attribute__((aligned(16))) uint32_t rowoff[BRING][BT];     // byte offsets of the streamed rows of the next tiles
-    __shared__ __attribute__((aligned(16))) unsigned char rowok[BRING][BT]; // PAD only: 1 = the row is a real token
 
     const uint32_t tid = threadIdx.x, lane = tid & 63u, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const uint32_t lq = lane & 31u, h = lane >> 5;
@@ -97,7 +96,12 @@ __global__ __launch_bounds__(BNT) void attn_bwd_kernel(BwdArgs a, uint32_t o_til
     const uint32_t lin = xcd * per_xcd + idx;  // each XCD owns a contiguous range of the (unit, owner tile) order
     if (lin >= total) return;
     const uint32_t unit = lin / o_tiles, ot = lin - unit * o_tiles;  // unit = (subsequence or batch element) * heads + head
-    const uint32_t bb = unit / (uint32_t)a.heads, head = unit - bb * (uint32_t)a.heads;
+    uint32_t bb = unit / (uint32_t)a.heads, head = unit - bb * (uint32_t)a.heads;
+    if (PAD) {  // classes differ in size: neighbouring units belong to different classes, so that every XCD gets its share of each
+        const uint32_t n_bb = (uint32_t)a.B * (uint32_t)(a.g.s * a.g.s);
+        head = unit / n_bb;
+        bb = unit - head * n_bb;
+    }
     uint32_t p = 0, q = 0, b0 = bb;
     if (a.g.mode != MODE_DENSE) {
         const uint32_t pq = bb / (uint32_t)a.B;
@@ -105,11 +109,15 @@ __global__ __launch_bounds__(BNT) void attn_bwd_kernel(BwdArgs a, uint32_t o_til
         p = pq / (uint32_t)a.g.s;
         q = pq - p * (uint32_t)a.g.s;
     }
-    const uint32_t n_seq = (uint32_t)a.g.n_sub;
+    ClassMap cm = {};
+    if (PAD) cm = make_class_map(a.g, p, q);
+    const uint32_t n_seq = PAD ? __builtin_amdgcn_readfirstlane(cm.n) : (uint32_t)a.g.n_sub;
+    if (PAD && ot * (32u * BNW) >= n_seq) return;  // the grid is sized for the largest class
     const size_t C = (size_t)a.heads * D;
     const size_t unit_off = (size_t)b0 * (uint32_t)a.g.n_tok * C + (size_t)head * D;  // elements
-    const float* lse_u = a.lse + (size_t)unit * n_seq;
-    const float* delta_u = a.delta + (size_t)unit * n_seq;
+    const size_t row_unit = (size_t)(bb * (uint32_t)a.heads + head) * (uint32_t)a.g.n_sub;
+    const float* lse_u = a.lse + row_unit;
+    const float* delta_u = a.delta + row_unit;
 
     // tensors by role
     const __bf16* own1_g = (const __bf16*)(MODE == BWD_DQ ? a.q : a.k) + unit_off;
@@ -121,17 +129,14 @@ __global__ __launch_bounds__(BNT) void attn_bwd_kernel(BwdArgs a, uint32_t o_til
 
     // ---- owner row: operands in registers (B operands: lane = owner lq, 8 consecutive channels starting at 16*ks + 8*h)
     const uint32_t jo = ot * (32u * BNW) + wave * 32u + lq;
-    // token at position j of this unit and whether it is a real one (always, outside the any-resolution mode)
-    auto token_at = [&](uint32_t j, bool* real) __attribute__((always_inline)) -> uint32_t {
-        if (PAD) return src_token_padded(a.g, p, q, j, real);
-        *real = true;
-        return src_token(a.g, p, q, j);
+    // token at position j of this unit, and where its log-sum-exp and delta are
+    auto token_at = [&](uint32_t j) __attribute__((always_inline)) -> uint32_t {
+        return PAD ? src_token_real(a.g, cm, p, q, j) : src_token(a.g, p, q, j);
     };
+    auto value_at = [&](uint32_t j) __attribute__((always_inline)) -> uint32_t { return PAD ? padded_position(a.g, cm, j) : j; };
     const uint32_t jo_c = jo < n_seq ? jo : n_seq - 1u;
-    bool own_real;
-    const uint32_t own_tok = token_at(jo_c, &own_real);
-    const bool own_valid = jo < n_seq && own_real;
-    const size_t own_off = (size_t)(own_real ? own_tok : 0u) * C;  // a padding owner reads token 0 and stores nothing
+    const bool own_valid = jo < n_seq;
+    const size_t own_off = (size_t)token_at(jo_c) * C;
     bf16x8 own1[KS], own2[DKV ? 1 : KS];
 #pragma unroll
     for (int ks = 0; ks < KS; ks++) {
@@ -140,8 +145,8 @@ __global__ __launch_bounds__(BNT) void attn_bwd_kernel(BwdArgs a, uint32_t o_til
     }
     float own_l = 0.f, own_d = 0.f;  // dQ: the owner is a query
     if (MODE == BWD_DQ) {
-        own_l = lse_u[jo_c] * LOG2E;
-        own_d = delta_u[jo_c];
+        own_l = lse_u[value_at(jo_c)] * LOG2E;
+        own_d = delta_u[value_at(jo_c)];
     }
     const float c = a.scale * LOG2E;  // exp(x*scale - L) = exp2(x*c - L*log2e)
     const float inv_scale = 1.0f / a.scale;
@@ -157,10 +162,7 @@ __global__ __launch_bounds__(BNT) void attn_bwd_kernel(BwdArgs a, uint32_t o_til
     const uint32_t row_bytes = (uint32_t)C * 2u;
     auto produce = [&](uint32_t tile) __attribute__((always_inline)) {
         const uint32_t j = tile * BT + lane;
-        bool real;
-        const uint32_t tok = token_at(j < n_seq ? j : n_seq - 1u, &real);  // rows past the end repeat the last row
-        rowoff[tile % BRING][lane] = real ? tok * row_bytes : 0u;          // padding rows read token 0
-        if (PAD) rowok[tile % BRING][lane] = real ? 1 : 0;
+        rowoff[tile % BRING][lane] = token_at(j < n_seq ? j : n_seq - 1u) * row_bytes;  // rows past the end repeat the last row
     };
     uint32_t st_row[IPW], st_cb[IPW];
 #pragma unroll
@@ -186,21 +188,18 @@ __global__ __launch_bounds__(BNT) void attn_bwd_kernel(BwdArgs a, uint32_t o_til
             __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)(st2_g + o.off[i]),
                                              (LDS_PTR(void))(b2 + (wave * IPW + i) * 1024u), 16, 0, 0);
         }
-        if ((DKV || PAD) && tid < BT) {  // per-row values of the streamed rows; rows past the end contribute nothing
+        if (DKV && tid < BT) {
+            // per-row values of the streamed queries: the INITIAL accumulators of the two products, so that they cost no arithmetic of
+            // their own.  Raw logit - L/scale, times c = s*c - L*log2e; -inf for a row past the end, which contributes nothing (P = 0).
             const uint32_t jj = t * BT + tid;
-            const bool ok = jj < n_seq && (!PAD || rowok[t % BRING][tid] != 0);
-            // The values are the INITIAL accumulators of the two products, so that they cost no arithmetic of their own:
-            if (MODE == BWD_DQ) {
-                rl = ok ? 0.f : -INFINITY;  // streamed keys: a bias on the raw logit
-            } else {
-                // streamed queries: raw logit - L/scale, times c = s*c - L*log2e; -inf for a row that contributes nothing (P = 0)
-                rl = ok ? -lse_u[jj] * inv_scale : -INFINITY;
-                rd = ok ? -delta_u[jj] : 0.f;  // dP - delta
-            }
+            const bool ok = jj < n_seq;
+            const uint32_t at = value_at(ok ? jj : n_seq - 1u);
+            rl = ok ? -lse_u[at] * inv_scale : -INFINITY;
+            rd = ok ? -delta_u[at] : 0.f;  // dP - delta
         }
     };
     auto store_rowvals = [&](uint32_t buf) __attribute__((always_inline)) {
-        if ((DKV || PAD) && tid < BT) {
+        if (DKV && tid < BT) {
             row_l[buf][tid] = rl;
             row_d[buf][tid] = rd;
         }
@@ -247,9 +246,7 @@ __global__ __launch_bounds__(BNT) void attn_bwd_kernel(BwdArgs a, uint32_t o_til
         for (int i = 0; i < 32 / RPI; i++) {
             const uint32_t r = (uint32_t)i * RPI + lane / CH;  // row of the wavefront's block
             const uint32_t j = ot * (32u * BNW) + wave * 32u + r;
-            bool real;
-            const uint32_t tok = token_at(j < n_seq ? j : n_seq - 1u, &real);
-            const uint32_t off = (real ? tok : 0u) * row_bytes + (((lane % CH) ^ swz(r)) * 16u);
+            const uint32_t off = token_at(j < n_seq ? j : n_seq - 1u) * row_bytes + (((lane % CH) ^ swz(r)) * 16u);
             __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)((const char*)own2_g + off),
                                              (LDS_PTR(void))(own2buf + wave * 32u * RB + (uint32_t)i * 1024u), 16, 0, 0);
         }
@@ -274,7 +271,7 @@ __global__ __launch_bounds__(BNT) void attn_bwd_kernel(BwdArgs a, uint32_t o_til
         const RowOffs off_now = off_next;
         off_next = read_offs(t + 2u);  // picked up a tile early so that the LDS read is not waited for
         if (wave == (t & (uint32_t)(BNW - 1))) produce(t + BRING_AHEAD);
-        const bool tail = MODE == BWD_DQ && !PAD && !more && (n_seq % BT) != 0;  // dQ: streamed keys past the end are masked
+        const bool tail = MODE == BWD_DQ && !more && (n_seq % BT) != 0;  // dQ: streamed keys past the end are masked
 #pragma unroll
         for (int blk = 0; blk < 2; blk++) {
             // The next tile's loads are enqueued halfway through this one on purpose: with a whole tile of slack even L2 misses are
@@ -285,7 +282,7 @@ __global__ __launch_bounds__(BNT) void attn_bwd_kernel(BwdArgs a, uint32_t o_til
 #pragma unroll
             for (int g = 0; g < 4; g++) {
                 f32x4 i1 = {0.f, 0.f, 0.f, 0.f}, i2 = {0.f, 0.f, 0.f, 0.f};
-                if (DKV || PAD) i1 = *(const f32x4*)&row_l[PARITY][blk * 32 + 8 * g + 4 * h];
+                if (DKV) i1 = *(const f32x4*)&row_l[PARITY][blk * 32 + 8 * g + 4 * h];
                 if (DKV) i2 = *(const f32x4*)&row_d[PARITY][blk * 32 + 8 * g + 4 * h];
 #pragma unroll
                 for (int e = 0; e < 4; e++) {
@@ -464,7 +461,8 @@ template <int D, int MODE, bool PAD>
 static hipError_t launch_mode(const BwdArgs& a, hipStream_t stream) {
     const uint32_t s2 = a.g.mode == MODE_DENSE ? 1u : (uint32_t)(a.g.s * a.g.s);
     const uint32_t n_units = (uint32_t)a.B * s2 * (uint32_t)a.heads;
-    const uint32_t o_tiles = ((uint32_t)a.g.n_sub + 32u * BNW - 1u) / (32u * BNW);
+    const uint32_t n_max = PAD ? make_class_map(a.g, 0, 0).n : (uint32_t)a.g.n_sub;  // the first class has the most real tokens
+    const uint32_t o_tiles = (n_max + 32u * BNW - 1u) / (32u * BNW);
     const uint64_t total = (uint64_t)n_units * o_tiles;
     if (total > 0x7ffffff0ull) return hipErrorInvalidConfiguration;
     const uint32_t per_xcd = (uint32_t)((total + 7u) / 8u);

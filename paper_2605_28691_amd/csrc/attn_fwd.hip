@@ -98,8 +98,6 @@ __device__ inline size_t uniform(size_t x) {
     return ((size_t)uniform((uint32_t)(x >> 32)) << 32) | uniform((uint32_t)x);
 }
 
-// PAD selects the any-resolution mode (Sec. 3.2): positions run over the grid padded to multiples of s*s, padding positions
-// are masked as keys (a 0 / -inf logit bias per staged row in LDS, from which the logits' accumulators start) and skipped as queries.
 // Row of `out` for position j of subsequence sb of the input's sparse layout: the token's row in the original layout, or its
 // row in the sparse layout of the other pattern (Alg. 1: tsa_to_orig / gsa_to_orig, tsa_to_gsa / gsa_to_tsa).
 __device__ inline size_t scattered_row(const AttnArgs& a, uint32_t sb, uint32_t j) {
@@ -124,6 +122,9 @@ __device__ inline size_t scattered_row(const AttnArgs& a, uint32_t sb, uint32_t 
     return ((size_t)(p * s + q) * B + b) * (uint32_t)gi.n_sub + r * (W / s) + ws;
 }
 
+// PAD selects the any-resolution mode (Sec. 3.2), where the subsequences are those of the grid padded to multiples of s*s with the
+// padding masked: the kernel walks the real tokens of the class only (ClassMap), so that a masked key is one that is never met.  Only
+// the log-sum-exp is laid out over the padded grid (zero at the padding).
 template <int D, int NW, int KG, bool PAD>
 __global__ __launch_bounds__(64 * NW, (NW == 4 && KG == 1 ? 2 : 1)) void attn_fwd_bf16_kernel(AttnArgs a, uint32_t q_tiles, uint32_t total, uint32_t per_xcd) {
     constexpr int QT = ATTN_QT;
@@ -139,7 +140,6 @@ __global__ __launch_bounds__(64 * NW, (NW == 4 && KG == 1 ? 2 : 1)) void attn_fw
     __shared__ __attribute__((aligned(1024))) char vbuf0_all[KG * TL::TILE_BYTES];
     __shared__ __attribute__((aligned(1024))) char vbuf1_all[KG * TL::TILE_BYTES];
     __shared__ __attribute__((aligned(16))) uint32_t rowoff_all[KG][RING][KT];        // byte offsets of the rows of the next tiles
-    __shared__ __attribute__((aligned(16))) float kbias_all[KG][RING][KT];            // PAD only: logit bias per row of a K tile, 0 = real key, -inf = padding
 
     const uint32_t tid = threadIdx.x, lane = tid & 63u, wave = uniform(tid >> 6);
     const uint32_t lq = lane & 31u, h = lane >> 5;
@@ -149,7 +149,6 @@ __global__ __launch_bounds__(64 * NW, (NW == 4 && KG == 1 ? 2 : 1)) void attn_fw
     char* const vbuf0 = vbuf0_all + kg * TL::TILE_BYTES;
     char* const vbuf1 = vbuf1_all + kg * TL::TILE_BYTES;
     uint32_t (*const rowoff)[KT] = rowoff_all[kg];
-    float (*const kbias)[KT] = kbias_all[kg];
 
     // workgroup -> (unit, query tile): id%8 is the XCD; each XCD owns a contiguous range of the (unit, tile) order, so that the
     // tiles of a unit run on one XCD (two at a range boundary) and the load is even for any number of units
@@ -157,7 +156,12 @@ __global__ __launch_bounds__(64 * NW, (NW == 4 && KG == 1 ? 2 : 1)) void attn_fw
     const uint32_t lin = xcd * per_xcd + idx;
     if (lin >= total) return;
     const uint32_t unit = lin / q_tiles, qt = lin - unit * q_tiles;
-    const uint32_t bb = unit / (uint32_t)a.heads, head = unit - bb * (uint32_t)a.heads;
+    uint32_t bb = unit / (uint32_t)a.heads, head = unit - bb * (uint32_t)a.heads;
+    if (PAD) {  // classes differ in size: neighbouring units belong to different classes, so that every XCD gets its share of each
+        const uint32_t n_bb = (uint32_t)a.B * (uint32_t)(a.g.s * a.g.s);
+        head = unit / n_bb;
+        bb = unit - head * n_bb;
+    }
     uint32_t p = 0, q = 0, b0 = bb;
     if (a.g.mode != MODE_DENSE) {
         const uint32_t pq = bb / (uint32_t)a.B;
@@ -165,7 +169,22 @@ __global__ __launch_bounds__(64 * NW, (NW == 4 && KG == 1 ? 2 : 1)) void attn_fw
         p = pq / (uint32_t)a.g.s;
         q = pq - p * (uint32_t)a.g.s;
     }
-    const uint32_t n_seq = (uint32_t)a.g.n_sub;
+    ClassMap cm = {};
+    if (PAD) cm = make_class_map(a.g, p, q);
+    const uint32_t n_seq = PAD ? uniform(cm.n) : (uint32_t)a.g.n_sub;
+    float* const lse_u = a.lse + (size_t)(bb * (uint32_t)a.heads + head) * (uint32_t)a.g.n_sub;
+    if (PAD) {
+        if (a.lse != nullptr)
+            for (uint32_t j = qt * (64u * NW) + tid; j < (uint32_t)a.g.n_sub; j += q_tiles * (64u * NW)) {
+                bool real;
+                (void)src_token_padded(a.g, p, q, j, &real);
+                if (!real) lse_u[j] = 0.f;
+            }
+        if (qt * BR >= n_seq) return;  // the grid is sized for the largest class
+    }
+    auto token_at = [&](uint32_t j) __attribute__((always_inline)) -> uint32_t {
+        return PAD ? src_token_real(a.g, cm, p, q, j) : src_token(a.g, p, q, j);
+    };
     const size_t C = (size_t)a.heads * D;
     const size_t unit_off = uniform((size_t)b0 * (uint32_t)a.g.n_tok * C + (size_t)head * D);  // elements
     const __bf16* Qg = (const __bf16*)a.q + unit_off;
@@ -181,14 +200,7 @@ __global__ __launch_bounds__(64 * NW, (NW == 4 && KG == 1 ? 2 : 1)) void attn_fw
     for (int qi = 0; qi < QT; qi++) {
         const uint32_t jq = qt * BR + (qw * QT + qi) * 32u + lq;
         q_valid[qi] = jq < n_seq;
-        if (PAD) {
-            bool real;
-            const uint32_t tok = src_token_padded(a.g, p, q, q_valid[qi] ? jq : 0u, &real);
-            q_valid[qi] = q_valid[qi] && real;
-            q_row_off[qi] = q_valid[qi] ? (size_t)tok * C : 0;  // padding queries read token 0 and store nothing
-        } else {
-            q_row_off[qi] = (size_t)src_token(a.g, p, q, q_valid[qi] ? jq : n_seq - 1u) * C;
-        }
+        q_row_off[qi] = (size_t)token_at(q_valid[qi] ? jq : n_seq - 1u) * C;
 #pragma unroll
         for (int ks = 0; ks < KS; ks++) qf[qi][ks] = *(const bf16x8*)(Qg + q_row_off[qi] + ks * 16 + 8 * h);
     }
@@ -206,20 +218,9 @@ __global__ __launch_bounds__(64 * NW, (NW == 4 && KG == 1 ? 2 : 1)) void attn_fw
     const uint32_t all_tiles = (n_seq + KT - 1) / KT;
     const uint32_t tile0 = KG == 1 ? 0u : kg * all_tiles / KG;
     const uint32_t n_tiles = KG == 1 ? all_tiles : (kg + 1u) * all_tiles / KG - tile0;
-    const uint32_t last_off = PAD ? 0u : src_token(a.g, p, q, n_seq - 1u) * row_bytes;  // rows past the end read the last valid row
     auto produce = [&](uint32_t tile) __attribute__((always_inline)) {
-        const uint32_t j = (tile0 + tile) * KT + lane, jc = j < n_seq ? j : n_seq - 1u;
-        uint32_t off;
-        if (PAD) {
-            bool real;
-            const uint32_t tok = src_token_padded(a.g, p, q, jc, &real);
-            const bool valid = j < n_seq && real;
-            off = valid ? tok * row_bytes : 0u;  // padding rows read token 0; their logits are masked
-            kbias[tile % RING][lane] = valid ? 0.f : -INFINITY;
-        } else {
-            off = j < n_seq ? src_token(a.g, p, q, jc) * row_bytes : last_off;
-        }
-        rowoff[tile % RING][lane] = off;
+        const uint32_t j = (tile0 + tile) * KT + lane;
+        rowoff[tile % RING][lane] = token_at(j < n_seq ? j : n_seq - 1u) * row_bytes;  // rows past the end read the last valid row
     };
     uint32_t st_row[TL::IPW], st_cb[TL::IPW];
 #pragma unroll
@@ -296,24 +297,13 @@ __global__ __launch_bounds__(64 * NW, (NW == 4 && KG == 1 ? 2 : 1)) void attn_fw
             v_rd[sec][mt] = row * TL::RB + ((ch ^ TL::swz(row)) * 16u) + 8 * (li & 1u);
         }
 
-    // Initial accumulator of the logits of 32-key block blkq: zero, or in the any-resolution mode the keys' bias (0 / -inf), which
-    // masks the padding positions without any arithmetic of its own.  Register r of the block is key 8*(r/4) + 4*h + r%4.
-    auto s_init = [&](uint32_t blkq) __attribute__((always_inline)) -> f32x16 {
-        f32x16 v;
-#pragma unroll
-        for (int i = 0; i < 4; i++) {
-            f32x4 b4 = {0.f, 0.f, 0.f, 0.f};
-            if (PAD) b4 = *(const f32x4*)&kbias[(blkq >> 1) % RING][(blkq & 1u) * 32u + 8 * i + 4 * h];
-#pragma unroll
-            for (int e = 0; e < 4; e++) v[4 * i + e] = b4[e];
-        }
-        return v;
-    };
-    // S(block blkq) = K(block) Q^T from K tile buffer kb, 32-key half `half`; each K fragment feeds all QT query tiles
-    auto qk = [&](const char* kb, int half, f32x16 (&s)[QT], uint32_t blkq) __attribute__((always_inline)) {
+    // S(block) = K(block) Q^T from K tile buffer kb, 32-key half `half`; each K fragment feeds all QT query tiles
+    auto qk = [&](const char* kb, int half, f32x16 (&s)[QT]) __attribute__((always_inline)) {
         f32x16 acc[QT];
 #pragma unroll
-        for (int qi = 0; qi < QT; qi++) acc[qi] = s_init(blkq);
+        for (int qi = 0; qi < QT; qi++)
+#pragma unroll
+            for (int r = 0; r < 16; r++) acc[qi][r] = 0.f;
 #pragma unroll
         for (int ks = 0; ks < KS; ks++) {
             const bf16x8 kf = *(const bf16x8*)(kb + k_rd[ks] + half * 32 * TL::RB);
@@ -366,12 +356,12 @@ __global__ __launch_bounds__(64 * NW, (NW == 4 && KG == 1 ? 2 : 1)) void attn_fw
     auto step = [&](auto DO_QK, auto DO_PV, auto MASK, auto PARC, uint32_t blk, const char* kb, const char* vb) __attribute__((always_inline)) {
         constexpr int PAR = decltype(PARC)::value;
         apply_pending();
-        if (decltype(DO_QK)::value) qk(kb, PAR ^ 1, sreg[PAR ^ 1], blk + 1u);
+        if (decltype(DO_QK)::value) qk(kb, PAR ^ 1, sreg[PAR ^ 1]);
         unsigned long long grow_mask = 0;
 #pragma unroll
         for (int qi = 0; qi < QT; qi++) {
             f32x16& s = sreg[PAR][qi];
-            if (decltype(MASK)::value && !PAD) {  // PAD: positions past the end carry the -inf bias like every padding position
+            if (decltype(MASK)::value) {
 #pragma unroll
                 for (int r = 0; r < 16; r++) {
                     const uint32_t key = tile0 * KT + blk * 32u + 8 * (r >> 2) + 4 * h + (r & 3);
@@ -403,8 +393,6 @@ __global__ __launch_bounds__(64 * NW, (NW == 4 && KG == 1 ? 2 : 1)) void attn_fw
     // wavefront takes the rare path, which finds the true maximum, redoes the block's exponentials against it and rescales
     // O and l.  Probabilities up to 2^16 are harmless: bf16 keeps their relative precision and O, l are fp32.
     // LDS fragments are read two MFMA groups ahead and every fragment feeds the MFMAs of all QT query tiles.
-    // In the any-resolution mode (PAD) the logits start from the keys' bias instead of zero (see s_init), nothing else differs;
-    // `blk` is the block whose softmax this step does (the logits it forms are those of block blk + 1).
     // MFMA groups of a step alternate between the two products (PV, QK, PV, QK, ...: as many of each), so consecutive MFMAs never
     // depend on each other: group g is PV group g/2 when g is even and QK group g/2 when g is odd.
     constexpr int NPV = 2 * MT, NQK = KS, NG = NPV + NQK;
@@ -433,7 +421,7 @@ __global__ __launch_bounds__(64 * NW, (NW == 4 && KG == 1 ? 2 : 1)) void attn_fw
     // `pre`: the step's first LDS_AHEAD fragments, already on their way.  With NEXT the step's last groups fetch, instead of
     // nothing, the first fragments of the FOLLOWING step on the same tiles (the other parity) into `nxt`, so that the LDS
     // latency is exposed once per window instead of once per step.
-    auto step_manual = [&](auto PARC, auto NEXTC, const char* kb, const char* vb, uint32_t blk, const Frags& pre, Frags& nxt) __attribute__((always_inline)) {
+    auto step_manual = [&](auto PARC, auto NEXTC, const char* kb, const char* vb, const Frags& pre, Frags& nxt) __attribute__((always_inline)) {
         constexpr int PAR = decltype(PARC)::value;
         constexpr bool NEXT = decltype(NEXTC)::value;
         using PARN = std::integral_constant<int, PAR ^ 1>;
@@ -460,7 +448,9 @@ __global__ __launch_bounds__(64 * NW, (NW == 4 && KG == 1 ? 2 : 1)) void attn_fw
                 if (g % 2 == 0) {
                     oacc[qi][i % MT] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fr[g], preg[PAR ^ 1][qi][i / MT], oacc[qi][i % MT], 0, 0, 0);
                 } else {
-                    if (i == 0) acc[qi] = s_init(blk + 1u);
+                    if (i == 0)
+#pragma unroll
+                        for (int r = 0; r < 16; r++) acc[qi][r] = 0.f;
                     acc[qi] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fr[g], qf[qi][i], acc[qi], 0, 0, 0);
                 }
             }
@@ -532,7 +522,7 @@ __global__ __launch_bounds__(64 * NW, (NW == 4 && KG == 1 ? 2 : 1)) void attn_fw
         issue_v(vbuf0, off_v);
         off_v = off_k;
         off_k = read_offs(2);
-        qk(kbuf0, 0, sreg[0], 0u);
+        qk(kbuf0, 0, sreg[0]);
         step(T_{}, F_{}, T_{}, P0{}, 0u, kbuf0, vbuf0);
         tile_landed();
         __syncthreads();
@@ -554,10 +544,10 @@ __global__ __launch_bounds__(64 * NW, (NW == 4 && KG == 1 ? 2 : 1)) void attn_fw
         if (qw == (Wn & (uint32_t)(QW - 1))) produce(Wn + RING_AHEAD);
         const Frags pre = first_frags(P1{}, kb, vb);
         Frags mid, none;
-        step_manual(P1{}, T_{}, kb, vb, 2 * Wn - 1, pre, mid);
+        step_manual(P1{}, T_{}, kb, vb, pre, mid);
         issue_k(kb_fill, off_k);
         issue_v(vb_fill, off_v);
-        step_manual(P0{}, F_{}, kb, vb, 2 * Wn, mid, none);
+        step_manual(P0{}, F_{}, kb, vb, mid, none);
         off_v = off_k;
         off_k = off_ahead;
         tile_landed();
@@ -619,7 +609,6 @@ __global__ __launch_bounds__(64 * NW, (NW == 4 && KG == 1 ? 2 : 1)) void attn_fw
         for (int og = 1; og < KG; og++) {
             const float mo = part_ml[og][qw][0][lane], lo = part_ml[og][qw][1][lane];
             const float m_new = fmaxf(m_ref[0], mo);
-            // a group that saw nothing but padding has the reference -inf, l = 0 and O = 0
             const float w0 = m_ref[0] == m_new ? 1.0f : __builtin_amdgcn_exp2f((m_ref[0] - m_new) * c);
             const float w1 = mo == m_new ? 1.0f : __builtin_amdgcn_exp2f((mo - m_new) * c);
             m_ref[0] = m_new;
@@ -644,7 +633,7 @@ __global__ __launch_bounds__(64 * NW, (NW == 4 && KG == 1 ? 2 : 1)) void attn_fw
         if (a.lse != nullptr && h == 0) {
             // log-sum-exp of the scaled logits: the reference is in raw logit units, the sum is relative to it
             const uint32_t jq = qt * BR + (qw * QT + qi) * 32u + lq;
-            if (jq < n_seq) a.lse[(size_t)unit * n_seq + jq] = q_valid[qi] ? m_ref[qi] * a.scale + __logf(llo + lhi) : 0.f;
+            if (jq < n_seq) lse_u[PAD ? padded_position(a.g, cm, jq) : jq] = m_ref[qi] * a.scale + __logf(llo + lhi);
         }
         if (q_valid[qi]) {
             __bf16* orow = Og + q_row_off[qi];
@@ -667,9 +656,9 @@ __global__ __launch_bounds__(64 * NW, (NW == 4 && KG == 1 ? 2 : 1)) void attn_fw
 }
 
 template <int D, int NW, int KG, bool PAD>
-static hipError_t launch_t(const AttnArgs& a, uint32_t n_units, hipStream_t stream) {
+static hipError_t launch_t(const AttnArgs& a, uint32_t n_units, uint32_t n_max, hipStream_t stream) {
     constexpr uint32_t BR = 32u * (NW / KG) * ATTN_QT;
-    const uint32_t q_tiles = ((uint32_t)a.g.n_sub + BR - 1u) / BR;
+    const uint32_t q_tiles = (n_max + BR - 1u) / BR;
     const uint64_t total = (uint64_t)n_units * q_tiles;
     if (total > 0x7ffffff0ull) return hipErrorInvalidConfiguration;
     const uint32_t per_xcd = (uint32_t)((total + 7u) / 8u);
@@ -697,13 +686,14 @@ constexpr int SHAPE_QUERIES[N_SHAPES] = {256, 128, 64, 128};
 constexpr ShapeCost COST_128[N_SHAPES] = {{1, 40.f, {9.0f}}, {2, 20.f, {5.5f, 10.0f}}, {1, 25.f, {3.9f}}, {1, 45.f, {4.7f}}};
 constexpr ShapeCost COST_64[N_SHAPES] = {{1, 30.f, {5.2f}}, {3, 15.f, {3.6f, 5.7f, 8.0f}}, {2, 15.f, {2.4f, 3.7f}}, {1, 30.f, {2.9f}}};
 
-static int pick_shape(const ShapeCost* cost, uint32_t n_units, uint32_t n_sub) {
+// n_sub: tokens of the largest unit, n_min: of the smallest
+static int pick_shape(const ShapeCost* cost, uint32_t n_units, uint32_t n_sub, uint32_t n_min) {
     constexpr uint64_t CUS = 256;
     const float blocks = (float)((n_sub + 31u) / 32u);
     int best = 0;
     float best_t = 0.f;
     for (int v = 0; v < N_SHAPES; v++) {
-        if (v >= 2 && n_sub <= (uint32_t)KT) continue;  // a key group needs a tile of its own
+        if (v >= 2 && n_min <= (uint32_t)KT) continue;  // a key group needs a tile of its own
         const uint64_t wgs = (uint64_t)n_units * ((n_sub + SHAPE_QUERIES[v] - 1u) / SHAPE_QUERIES[v]);
         const uint64_t per_round = CUS * cost[v].max_k, rounds = wgs / per_round, rem = wgs % per_round;
         float t = (float)rounds * (cost[v].fixed + blocks * cost[v].block[cost[v].max_k - 1]);
@@ -720,11 +710,15 @@ template <int D, bool PAD>
 static hipError_t launch_shape(const AttnArgs& a, hipStream_t stream) {
     const uint32_t s2 = a.g.mode == MODE_DENSE ? 1u : (uint32_t)(a.g.s * a.g.s);
     const uint32_t n_units = (uint32_t)a.B * s2 * (uint32_t)a.heads;
-    switch (pick_shape(D == 128 ? COST_128 : COST_64, n_units, (uint32_t)a.g.n_sub)) {
-        case 1: return launch_t<D, 4, 1, PAD>(a, n_units, stream);
-        case 2: return launch_t<D, 4, 2, PAD>(a, n_units, stream);
-        case 3: return launch_t<D, 8, 2, PAD>(a, n_units, stream);
-        default: return launch_t<D, 8, 1, PAD>(a, n_units, stream);
+    // any-resolution mode: the first class has the most real tokens, the last one the fewest
+    const uint32_t last = (uint32_t)a.g.s - 1u;
+    const uint32_t n_max = PAD ? make_class_map(a.g, 0, 0).n : (uint32_t)a.g.n_sub;
+    const uint32_t n_min = PAD ? make_class_map(a.g, last, last).n : n_max;
+    switch (pick_shape(D == 128 ? COST_128 : COST_64, n_units, n_max, n_min)) {
+        case 1: return launch_t<D, 4, 1, PAD>(a, n_units, n_max, stream);
+        case 2: return launch_t<D, 4, 2, PAD>(a, n_units, n_max, stream);
+        case 3: return launch_t<D, 8, 2, PAD>(a, n_units, n_max, stream);
+        default: return launch_t<D, 8, 1, PAD>(a, n_units, n_max, stream);
     }
 }
 

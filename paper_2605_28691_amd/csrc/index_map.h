@@ -49,6 +49,7 @@ struct GridMap {
     int W;         // original row length
     int n_tok;     // tokens per batch element in the original layout (T*H*W)
     int n_sub;     // tokens per subsequence
+    int T;         // frames
     uint32_t a;    // f(x) = x*a + (x/s)*b + c, see above
     uint32_t b;
     uint32_t cmul; // c = p*cmul (rows) or q*cmul (columns)
@@ -82,6 +83,55 @@ __host__ __device__ inline uint32_t src_token_padded(const GridMap& g, uint32_t 
     return (t * (uint32_t)g.H_real + h) * (uint32_t)g.W + w;
 }
 
+// Any-resolution mode without the padding.  The padding sits at the end of H and W, so the real positions of a class are a prefix
+// along either axis (both maps are monotone in hs and ws): a (T, hr, wr) grid of its own.  The attention kernels walk that grid,
+// "dense" positions 0 .. n-1 with no padding among them, so that nothing is computed and masked away.
+struct ClassMap {
+    uint32_t n;  // real tokens of the class (0 if the unpadded grid has none)
+    FastDiv w;   // division by the real columns of the class
+    FastDiv h;   // division by the real rows of the class
+};
+
+// make_fastdiv in 32-bit arithmetic: the same multiplier except at powers of two, where 2^32 / d is exact (e = 0)
+__host__ __device__ inline FastDiv make_fastdiv32(uint32_t d) {
+    FastDiv f;
+    f.d = d;
+    f.mul = d <= 1u ? 0u : 0xffffffffu / d + 1u;
+    f.one = d <= 1u ? 1u : 0u;
+    return f;
+}
+
+// number of hs (or ws) of class p (or q) that lie inside the n real rows (or columns)
+__host__ __device__ inline uint32_t class_extent(const GridMap& g, uint32_t n, uint32_t p) {
+    const uint32_t s = (uint32_t)g.s;
+    if (g.b == 0) return n > p ? (n - p + s - 1u) / s : 0u;  // token-wise: hs*s + p < n
+    const uint32_t full = n / (s * s), rest = n - full * s * s, first = p * s;  // group-wise: runs of s rows, one every s*s
+    return full * s + (rest > first ? (rest - first < s ? rest - first : s) : 0u);
+}
+
+__host__ __device__ inline ClassMap make_class_map(const GridMap& g, uint32_t p, uint32_t q) {
+    const uint32_t hr = class_extent(g, (uint32_t)g.H_real, p), wr = class_extent(g, (uint32_t)g.W, q);
+    ClassMap c;
+    c.n = (uint32_t)g.T * hr * wr;
+    c.w = make_fastdiv32(wr);
+    c.h = make_fastdiv32(hr);
+    return c;
+}
+
+// token number of dense position j of class (p, q), and the position on the padded grid that it stands for
+__host__ __device__ inline uint32_t src_token_real(const GridMap& g, const ClassMap& c, uint32_t p, uint32_t q, uint32_t j) {
+    const uint32_t r = c.w.div(j), ws = j - r * c.w.d;
+    const uint32_t t = c.h.div(r), hs = r - t * c.h.d;
+    const uint32_t h = hs * g.a + g.sdiv.div(hs) * g.b + p * g.cmul;
+    const uint32_t w = ws * g.a + g.sdiv.div(ws) * g.b + q * g.cmul;
+    return (t * (uint32_t)g.H_real + h) * (uint32_t)g.W + w;
+}
+__host__ __device__ inline uint32_t padded_position(const GridMap& g, const ClassMap& c, uint32_t j) {
+    const uint32_t r = c.w.div(j), ws = j - r * c.w.d;
+    const uint32_t t = c.h.div(r), hs = r - t * c.h.d;
+    return (t * g.sdiv.div(g.hpad.d) + hs) * g.ws.d + ws;
+}
+
 // Host side: the map of a grid.  `group` selects the group-wise pattern; `pad` the any-resolution mode, in which the
 // subsequences are those of the grid padded at the end of H and W to the next multiples of s*s.
 inline GridMap make_dense_gridmap(size_t n) {
@@ -91,6 +141,7 @@ inline GridMap make_dense_gridmap(size_t n) {
     g.W = 0;
     g.n_tok = (int)n;
     g.n_sub = (int)n;
+    g.T = 1;
     g.a = 1;
     g.b = 0;
     g.cmul = 0;
@@ -112,6 +163,7 @@ inline GridMap make_gridmap(int T, int H, int W, int s, bool group, bool pad = f
     g.W = W;
     g.n_tok = n_tok;
     g.n_sub = T * Hp * Wp / (s * s);
+    g.T = T;
     g.a = group ? 1u : (uint32_t)s;
     g.b = group ? (uint32_t)(s * s - s) : 0u;
     g.cmul = group ? (uint32_t)s : 1u;

@@ -1,6 +1,7 @@
 // Host-side check of the device index map (paper_2605_28691_amd/csrc/index_map.h): src_token() with its multiply-high
 // divisions must equal the plain integer formulas of Algorithm 1 for every position of a grid, and src_token_padded() (the
-// any-resolution map, Sec. 3.2) the plain pad-then-index formulas on grids that are not multiples of s*s.  Built and run by
+// any-resolution map, Sec. 3.2) the plain pad-then-index formulas on grids that are not multiples of s*s;
+// src_token_real() must enumerate exactly the real positions of src_token_padded(), in their order.  Built and run by
 // tests/test_host_logic.py with hipcc (host pass only); exits non-zero on the first mismatch.
 #include <cstdio>
 #include <cstdlib>
@@ -37,7 +38,7 @@ int main() {
     // any-resolution mode (Sec. 3.2): pad the END of H and W to multiples of s*s, index the padded grid with Algorithm 1's
     // formulas, and call a position real when it lies inside the unpadded grid; its token number is then counted on the
     // unpadded grid.  Every real token must be met exactly once over all classes.
-    const int pad_shapes[][4] = {{2, 7, 9, 2}, {3, 5, 6, 2}, {1, 10, 11, 3}, {2, 3, 3, 2}, {1, 17, 13, 4}, {4, 8, 10, 2}, {2, 9, 9, 3}, {21, 45, 80, 2}, {3, 8, 8, 2}};
+    const int pad_shapes[][4] = {{2, 7, 9, 2}, {3, 5, 6, 2}, {1, 10, 11, 3}, {2, 3, 3, 2}, {1, 17, 13, 4}, {4, 8, 10, 2}, {2, 9, 9, 3}, {21, 45, 80, 2}, {3, 8, 8, 2}, {2, 1, 1, 3}, {1, 2, 33, 4}, {3, 16, 17, 4}};
     for (auto& sh : pad_shapes) {
         const int T = sh[0], H = sh[1], W = sh[2], s = sh[3];
         const int Hp = (H + s * s - 1) / (s * s) * (s * s), Wp = (W + s * s - 1) / (s * s) * (s * s);
@@ -66,13 +67,35 @@ int main() {
                         }
                         checked++;
                     }
+            // the real positions of a class as a dense sequence: the same tokens in the same order, and the padded positions they stand for
+            for (int p = 0; p < s; p++)
+                for (int q = 0; q < s; q++) {
+                    const ClassMap c = make_class_map(g, (uint32_t)p, (uint32_t)q);
+                    uint32_t k = 0;
+                    for (int j = 0; j < g.n_sub; j++) {
+                        bool real = false;
+                        const uint32_t tok = src_token_padded(g, (uint32_t)p, (uint32_t)q, (uint32_t)j, &real);
+                        if (!real) continue;
+                        if (k >= c.n || src_token_real(g, c, (uint32_t)p, (uint32_t)q, k) != tok || padded_position(g, c, k) != (uint32_t)j) {
+                            printf("dense map mismatch T%d H%d W%d s%d group%d p%d q%d position %u\n", T, H, W, s, group, p, q, k);
+                            return 1;
+                        }
+                        k++;
+                        checked++;
+                    }
+                    if (k != c.n || c.n > make_class_map(g, 0, 0).n || c.n < make_class_map(g, (uint32_t)s - 1, (uint32_t)s - 1).n) {
+                        printf("dense map: class %d %d has %u real tokens, the map says %u\n", p, q, k, c.n);
+                        return 1;
+                    }
+                }
             free(seen);
             if (n_real != (long)T * H * W) { printf("padded map: %ld real positions, want %d\n", n_real, T * H * W); return 1; }
         }
     }
     // the multiply-high division over its whole admissible range for a few divisors: n * d < 2^32
-    for (uint32_t d : {1u, 2u, 3u, 7u, 40u, 641u, 65535u}) {
-        const FastDiv f = make_fastdiv(d);
+    for (uint32_t d : {1u, 2u, 3u, 7u, 40u, 64u, 641u, 65535u}) {
+        for (int narrow = 0; narrow < 2; narrow++) {
+        const FastDiv f = narrow ? make_fastdiv32(d) : make_fastdiv(d);
         const uint64_t limit = (1ull << 32) / d;
         for (uint64_t n = 0; n < limit; n += (limit > 5000000 ? limit / 4999999 : 1)) {
             if (f.div((uint32_t)n) != (uint32_t)(n / d)) { printf("fastdiv %u fails at %llu\n", d, (unsigned long long)n); return 1; }
@@ -80,6 +103,7 @@ int main() {
         }
         const uint32_t last = (uint32_t)(limit - 1);
         if (f.div(last) != last / d) { printf("fastdiv %u fails at the top of its range\n", d); return 1; }
+        }
     }
     printf("ok %ld checks\n", checked);
     return 0;
