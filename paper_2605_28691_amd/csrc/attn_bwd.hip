@@ -1,7 +1,7 @@
 // bf16 flash-attention backward for gfx950 with the Skiparse row addressing folded in (the layer is fine-tuned, Sec. 4.1, so
 // it needs gradients).  For every attention unit (a subsequence and a head), with P = softmax(scale Q K^T) recomputed from
 // the forward's log-sum-exp L:
-//     delta_i = sum_d dO_id O_id                      (= sum_j P_ij dP_ij; one small kernel)
+//     delta_i = sum_d dO_id O_id                      (= sum_j P_ij dP_ij; formed by the dQ launch, whose owner rows hold dO)
 //     dP = dO V^T,  dS = P o (dP - delta 1^T)
 //     dQ = scale dS K,   dK = scale dS^T Q,   dV = P^T dO
 // Two launches of one kernel template, each the forward kernel's scheme with the roles of the tensors exchanged: a lane OWNS
@@ -14,7 +14,10 @@
 // As in the forward kernel the 32x32 accumulator layout gives every lane one owner column, so R's registers are directly the
 // B operand of the last product, and the owner's gradient rows are accumulated in registers and written once: no atomics, the
 // result is deterministic.  dK and dV share one launch (S and dP are formed once for both: 7 matrix products in all against the
-// 5 of the definition); their two accumulators take 128 registers at head_dim 128, so the owner's V rows are kept in LDS there.
+// 5 of the definition); their two accumulators take 128 registers at head_dim 128, so the owner's V rows are kept in LDS where two
+// wavefronts share a SIMD.
+//   * Small problems get smaller workgroups, and two groups of wavefronts that walk half of the streamed rows each and add their
+//     accumulators through LDS at the end (in a fixed order, so the result stays deterministic): see the table at the launch.
 //   * log-sum-exp and delta are per QUERY: per-lane constants in the dQ launch; in the dK+dV launch per-streamed-row values,
 //     staged in LDS next to the tile as -L/scale and -delta and used as the INITIAL accumulators of M1 and M2, so that
 //     P = exp2(M1 * c) and dS = P o M2 need no further arithmetic (-inf / 0 for rows that must contribute nothing).
@@ -26,6 +29,7 @@
 
 #include "kernels.h"
 #include "lds_layout.h"
+#include "wg_shape.h"
 
 namespace skiparse {
 
@@ -35,63 +39,58 @@ typedef __attribute__((ext_vector_type(2))) __bf16 bf16x2;
 typedef __attribute__((ext_vector_type(2))) float f32x2;
 typedef __attribute__((ext_vector_type(4))) float f32x4;
 typedef __attribute__((ext_vector_type(16))) float f32x16;
-typedef __attribute__((ext_vector_type(4))) unsigned int u32x4;
 
 #define LDS_PTR(T) __attribute__((address_space(3))) T*
 
 constexpr int BT = 64;             // streamed rows per tile
-constexpr int BNW = 8;             // wavefronts per workgroup: 256 owners share every streamed tile
-constexpr int BNT = 64 * BNW;
 constexpr float LOG2E = 1.4426950408889634f;
-constexpr int BRING_AHEAD = BNW;   // row offsets are formed this many tiles ahead, by one wavefront per tile in turn
+constexpr int BRING_AHEAD = 8;   // row offsets are formed this many tiles ahead, by one wavefront per tile in turn
 constexpr int BRING = 16;          // tiles of row offsets kept in LDS
-static_assert((BNW & (BNW - 1)) == 0 && (BRING & (BRING - 1)) == 0 && BRING >= BRING_AHEAD + 4, "ring sizes");
+static_assert((BRING & (BRING - 1)) == 0 && BRING >= BRING_AHEAD + 4, "ring sizes");
 
 // PAD: any-resolution mode (Sec. 3.2): the kernel walks the real tokens of the class only (ClassMap), so that a padding position is
 // never met; log-sum-exp and delta are laid out over the padded grid.
-template <int D, int MODE, bool PAD>
-__global__ __launch_bounds__(BNT) void attn_bwd_kernel(BwdArgs a, uint32_t o_tiles, uint32_t total, uint32_t per_xcd) {
+template <int D, int MODE, int NW, int KG, bool PAD>
+__global__ __launch_bounds__(64 * NW, (NW == 4 && KG == 1 && (MODE == BWD_DQ || D == 64) ? 2 : 1)) void attn_bwd_kernel(BwdArgs a, uint32_t o_tiles, uint32_t total, uint32_t per_xcd) {
     constexpr int KS = D / 16;   // MFMA steps along head_dim
     constexpr int MT = D / 32;   // 32-channel blocks of the gradient row
     constexpr int CH = D / 8;    // 16-byte chunks per row
     constexpr int RB = D * 2;    // row bytes in LDS (packed rows, swizzled chunk positions)
     constexpr int RPI = 64 / CH; // rows filled by one direct-to-LDS instruction of a wavefront
-    constexpr int IPW = CH / BNW;  // such instructions per wavefront, tensor and tile
-    constexpr bool DKV = MODE == BWD_DKV; // dK and dV together: two accumulators, the owner's second operand (V) lives in LDS
-    // LDS fragments are read a few MFMA groups before their use and the order is pinned with scheduling fences, so that an MFMA
-    // waits only for its own operands (left to itself the compiler issues each read right before the MFMA that needs it).  The dQ
-    // launch reads 4 groups ahead (-7 %).  The dK+dV launch has almost no registers to spare: 1 group ahead in the first two
-    // products and 2 in the last two is what fits without spilling into the MFMA chains (-2 %; deeper variants spill and measure
-    // 2-14 % slower).  The depths of the dK+dV launch can be overridden at build time for measurements.
-#ifndef BWD_DKV_MAN_A
-#define BWD_DKV_MAN_A 1
-#endif
-#ifndef BWD_DKV_MAN_C
-#define BWD_DKV_MAN_C 1
-#endif
-#ifndef BWD_DKV_AH_A
-#define BWD_DKV_AH_A 1
-#endif
-#ifndef BWD_DKV_AH_C
-#define BWD_DKV_AH_C 2
-#endif
-    constexpr int AH_A = DKV ? BWD_DKV_AH_A : 4, AH_C = DKV ? BWD_DKV_AH_C : 4;
-    constexpr bool MAN_A = DKV ? (BWD_DKV_MAN_A != 0) : true, MAN_C = DKV ? (BWD_DKV_MAN_C != 0) : true;
+    constexpr int QW = NW / KG;  // wavefronts of a group: each owns 32 rows, all walk the same streamed rows
+    constexpr int IPW = CH / QW; // such instructions per wavefront, tensor and tile
+    constexpr int WGO = 32 * QW;         // owners per workgroup
+    constexpr bool DKV = MODE == BWD_DKV; // dK and dV together: two accumulators
+    constexpr bool OWN2_LDS = DKV && NW == 8;  // the owners' second operand (V) lives in LDS
+    // LDS fragments are read AH MFMA groups before their use and the order is pinned with scheduling fences, so that an MFMA
+    // waits only for its own operands (left to itself the compiler issues each read right before the MFMA that needs it).
+    // The dK+dV launch with 8 wavefronts has almost no registers to spare: 1 group ahead in the first two products and 2 in the last
+    // two is what fits without spilling into the MFMA chains (deeper variants measure 2-14 % slower).
+    constexpr int AH_A = OWN2_LDS ? 1 : 4, AH_C = OWN2_LDS ? 2 : 4;
     constexpr int TILE_BYTES = BT * RB;
-    static_assert(IPW >= 1 && IPW * BNW == CH, "a tile is CH instructions, spread evenly over the wavefronts");
+    static_assert(IPW >= 1 && IPW * QW == CH, "a tile is CH instructions, spread evenly over the wavefronts");
     // two streamed tensors, double buffered; separate arrays so that the compiler can tell the tile being filled from the one
     // being read
-    __shared__ __attribute__((aligned(1024))) char s1buf0[TILE_BYTES];
-    __shared__ __attribute__((aligned(1024))) char s1buf1[TILE_BYTES];
-    __shared__ __attribute__((aligned(1024))) char s2buf0[TILE_BYTES];
-    __shared__ __attribute__((aligned(1024))) char s2buf1[TILE_BYTES];
-    __shared__ __attribute__((aligned(1024))) char own2buf[DKV ? 32 * BNW * RB : 16];  // DKV: V rows of the 256 owners, swizzled like a tile
-    __shared__ __attribute__((aligned(16))) float row_l[2][BT];  // initial M1 per streamed row, dK+dV: -L/scale of the query
-    __shared__ __attribute__((aligned(16))) float row_d[2][BT];  // initial M2 per streamed row: dK+dV -delta of the query
-    __shared__ __attribute__((aligned(16))) uint32_t rowoff[BRING][BT];     // byte offsets of the streamed rows of the next tiles
+    __shared__ __attribute__((aligned(1024))) char s1buf0_all[KG * TILE_BYTES];
+    __shared__ __attribute__((aligned(1024))) char s1buf1_all[KG * TILE_BYTES];
+    __shared__ __attribute__((aligned(1024))) char s2buf0_all[KG * TILE_BYTES];
+    __shared__ __attribute__((aligned(1024))) char s2buf1_all[KG * TILE_BYTES];
+    __shared__ __attribute__((aligned(1024))) char own2buf[OWN2_LDS ? WGO * RB : 16];  // V rows of the owners, swizzled like a tile
+    __shared__ __attribute__((aligned(16))) float row_l_all[KG][2][BT];  // initial M1 per streamed row, dK+dV: -L/scale of the query
+    __shared__ __attribute__((aligned(16))) float row_d_all[KG][2][BT];  // initial M2 per streamed row: dK+dV -delta of the query
+    __shared__ __attribute__((aligned(16))) uint32_t rowoff_all[KG][BRING][BT];     // byte offsets of the streamed rows of the next tiles
 
     const uint32_t tid = threadIdx.x, lane = tid & 63u, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const uint32_t lq = lane & 31u, h = lane >> 5;
+    const uint32_t kg = KG == 1 ? 0u : wave / QW, ow = KG == 1 ? wave : wave % QW;  // group, wavefront of the group
+    const uint32_t gtid = tid - kg * (64u * QW);
+    char* const s1buf0 = s1buf0_all + kg * TILE_BYTES;
+    char* const s1buf1 = s1buf1_all + kg * TILE_BYTES;
+    char* const s2buf0 = s2buf0_all + kg * TILE_BYTES;
+    char* const s2buf1 = s2buf1_all + kg * TILE_BYTES;
+    float (*const row_l)[BT] = row_l_all[kg];
+    float (*const row_d)[BT] = row_d_all[kg];
+    uint32_t (*const rowoff)[BT] = rowoff_all[kg];
     const uint32_t xcd = blockIdx.x & 7u, idx = blockIdx.x >> 3;
     const uint32_t lin = xcd * per_xcd + idx;  // each XCD owns a contiguous range of the (unit, owner tile) order
     if (lin >= total) return;
@@ -112,12 +111,12 @@ __global__ __launch_bounds__(BNT) void attn_bwd_kernel(BwdArgs a, uint32_t o_til
     ClassMap cm = {};
     if (PAD) cm = make_class_map(a.g, p, q);
     const uint32_t n_seq = PAD ? __builtin_amdgcn_readfirstlane(cm.n) : (uint32_t)a.g.n_sub;
-    if (PAD && ot * (32u * BNW) >= n_seq) return;  // the grid is sized for the largest class
+    if (PAD && ot * (uint32_t)WGO >= n_seq) return;  // the grid is sized for the largest class
     const size_t C = (size_t)a.heads * D;
     const size_t unit_off = (size_t)b0 * (uint32_t)a.g.n_tok * C + (size_t)head * D;  // elements
     const size_t row_unit = (size_t)(bb * (uint32_t)a.heads + head) * (uint32_t)a.g.n_sub;
     const float* lse_u = a.lse + row_unit;
-    const float* delta_u = a.delta + row_unit;
+    float* delta_u = a.delta + row_unit;
 
     // tensors by role
     const __bf16* own1_g = (const __bf16*)(MODE == BWD_DQ ? a.q : a.k) + unit_off;
@@ -128,25 +127,35 @@ __global__ __launch_bounds__(BNT) void attn_bwd_kernel(BwdArgs a, uint32_t o_til
     __bf16* grad2_g = (__bf16*)a.dv + unit_off;  // DKV: the second gradient
 
     // ---- owner row: operands in registers (B operands: lane = owner lq, 8 consecutive channels starting at 16*ks + 8*h)
-    const uint32_t jo = ot * (32u * BNW) + wave * 32u + lq;
+    const uint32_t jo = ot * (uint32_t)WGO + ow * 32u + lq;
     // token at position j of this unit, and where its log-sum-exp and delta are
     auto token_at = [&](uint32_t j) __attribute__((always_inline)) -> uint32_t {
         return PAD ? src_token_real(a.g, cm, p, q, j) : src_token(a.g, p, q, j);
     };
     auto value_at = [&](uint32_t j) __attribute__((always_inline)) -> uint32_t { return PAD ? padded_position(a.g, cm, j) : j; };
-    const uint32_t jo_c = jo < n_seq ? jo : n_seq - 1u;
-    const bool own_valid = jo < n_seq;
+    const uint32_t jo_c = jo < n_seq ? jo : n_seq - 1u;  // an owner past the end reads the last row and stores nothing
     const size_t own_off = (size_t)token_at(jo_c) * C;
-    bf16x8 own1[KS], own2[DKV ? 1 : KS];
+    bf16x8 own1[KS], own2[OWN2_LDS ? 1 : KS];
 #pragma unroll
     for (int ks = 0; ks < KS; ks++) {
         own1[ks] = *(const bf16x8*)(own1_g + own_off + ks * 16 + 8 * h);
-        if (!DKV) own2[ks] = *(const bf16x8*)(own2_g + own_off + ks * 16 + 8 * h);
+        if (!OWN2_LDS) own2[OWN2_LDS ? 0 : ks] = *(const bf16x8*)(own2_g + own_off + ks * 16 + 8 * h);
     }
     float own_l = 0.f, own_d = 0.f;  // dQ: the owner is a query
     if (MODE == BWD_DQ) {
-        own_l = lse_u[value_at(jo_c)] * LOG2E;
-        own_d = delta_u[value_at(jo_c)];
+        // delta of the row: its dO is here, O is read for nothing else.  Kept for the dK+dV launch, which streams the queries.
+        const __bf16* o_g = (const __bf16*)a.out + unit_off + own_off;
+        float sum = 0.f;
+#pragma unroll
+        for (int ks = 0; ks < KS; ks++) {
+            const bf16x8 of = *(const bf16x8*)(o_g + ks * 16 + 8 * h);
+#pragma unroll
+            for (int e = 0; e < 8; e++) sum = fmaf((float)of[e], (float)own2[OWN2_LDS ? 0 : ks][e], sum);
+        }
+        const uint32_t at = value_at(jo_c);
+        own_d = sum + __shfl_xor(sum, 32);
+        own_l = lse_u[at] * LOG2E;
+        if (jo < n_seq && h == 0 && kg == 0) delta_u[at] = own_d;
     }
     const float c = a.scale * LOG2E;  // exp(x*scale - L) = exp2(x*c - L*log2e)
     const float inv_scale = 1.0f / a.scale;
@@ -160,14 +169,18 @@ __global__ __launch_bounds__(BNT) void attn_bwd_kernel(BwdArgs a, uint32_t o_til
     // ring in LDS filled BRING_AHEAD tiles ahead: for every tile ONE wavefront (they take turns) evaluates the index map for the 64
     // rows of a tile, lane = row, and every lane later picks up the offsets of the rows it fetches.
     const uint32_t row_bytes = (uint32_t)C * 2u;
+    // the group's share of the streamed tiles; tiles are numbered from its start below
+    const uint32_t all_t = (n_seq + BT - 1) / BT;
+    const uint32_t tile0 = KG == 1 ? 0u : kg * all_t / KG;
+    const uint32_t n_t = KG == 1 ? all_t : (kg + 1u) * all_t / KG - tile0;
     auto produce = [&](uint32_t tile) __attribute__((always_inline)) {
-        const uint32_t j = tile * BT + lane;
+        const uint32_t j = (tile0 + tile) * BT + lane;
         rowoff[tile % BRING][lane] = token_at(j < n_seq ? j : n_seq - 1u) * row_bytes;  // rows past the end repeat the last row
     };
     uint32_t st_row[IPW], st_cb[IPW];
 #pragma unroll
     for (int i = 0; i < IPW; i++) {
-        st_row[i] = (wave * IPW + i) * RPI + lane / CH;
+        st_row[i] = (ow * IPW + i) * RPI + lane / CH;
         st_cb[i] = ((lane % CH) ^ swz(st_row[i])) * 16u;
     }
     struct RowOffs {
@@ -184,14 +197,14 @@ __global__ __launch_bounds__(BNT) void attn_bwd_kernel(BwdArgs a, uint32_t o_til
 #pragma unroll
         for (int i = 0; i < IPW; i++) {
             __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)(st1_g + o.off[i]),
-                                             (LDS_PTR(void))(b1 + (wave * IPW + i) * 1024u), 16, 0, 0);
+                                             (LDS_PTR(void))(b1 + (ow * IPW + i) * 1024u), 16, 0, 0);
             __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)(st2_g + o.off[i]),
-                                             (LDS_PTR(void))(b2 + (wave * IPW + i) * 1024u), 16, 0, 0);
+                                             (LDS_PTR(void))(b2 + (ow * IPW + i) * 1024u), 16, 0, 0);
         }
-        if (DKV && tid < BT) {
+        if (DKV && gtid < BT) {
             // per-row values of the streamed queries: the INITIAL accumulators of the two products, so that they cost no arithmetic of
             // their own.  Raw logit - L/scale, times c = s*c - L*log2e; -inf for a row past the end, which contributes nothing (P = 0).
-            const uint32_t jj = t * BT + tid;
+            const uint32_t jj = (tile0 + t) * BT + gtid;
             const bool ok = jj < n_seq;
             const uint32_t at = value_at(ok ? jj : n_seq - 1u);
             rl = ok ? -lse_u[at] * inv_scale : -INFINITY;
@@ -199,9 +212,9 @@ __global__ __launch_bounds__(BNT) void attn_bwd_kernel(BwdArgs a, uint32_t o_til
         }
     };
     auto store_rowvals = [&](uint32_t buf) __attribute__((always_inline)) {
-        if (DKV && tid < BT) {
-            row_l[buf][tid] = rl;
-            row_d[buf][tid] = rd;
+        if (DKV && gtid < BT) {
+            row_l[buf][gtid] = rl;
+            row_d[buf][gtid] = rd;
         }
     };
     auto tile_landed = [&]() __attribute__((always_inline)) { asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); };
@@ -238,21 +251,20 @@ __global__ __launch_bounds__(BNT) void attn_bwd_kernel(BwdArgs a, uint32_t o_til
             t_rd[sec][mt] = row * RB + ((ch ^ swz(row)) * 16u) + 8 * (li & 1u);
         }
 
-    const uint32_t n_t = (n_seq + BT - 1) / BT;
-    if (DKV) {
-        // the wavefront's 32 owner rows of V go straight into LDS (one instruction fills RPI rows; same swizzle as the tiles, so
-        // the fragment of MFMA step ks sits at a_rd(ks) of the wavefront's 32-row block); waited for with tile 0
+    if (OWN2_LDS) {
+        // the wavefront's owner rows of V go straight into LDS (one instruction fills RPI rows; same swizzle as the tiles, so
+        // the fragment of MFMA step ks sits at a_rd(ks) of a 32-row block); waited for with tile 0
 #pragma unroll
         for (int i = 0; i < 32 / RPI; i++) {
             const uint32_t r = (uint32_t)i * RPI + lane / CH;  // row of the wavefront's block
-            const uint32_t j = ot * (32u * BNW) + wave * 32u + r;
+            const uint32_t j = ot * (uint32_t)WGO + wave * 32u + r;
             const uint32_t off = token_at(j < n_seq ? j : n_seq - 1u) * row_bytes + (((lane % CH) ^ swz(r)) * 16u);
             __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)((const char*)own2_g + off),
                                              (LDS_PTR(void))(own2buf + wave * 32u * RB + (uint32_t)i * 1024u), 16, 0, 0);
         }
     }
-    const char* const own2_lds = own2buf + (DKV ? wave * 32u * RB : 0u);
-    produce(wave);  // tiles 0 .. BRING_AHEAD-1
+    const char* const own2_lds = own2buf + (OWN2_LDS ? wave * 32u * RB : 0u);
+    for (uint32_t t = ow; t < (uint32_t)BRING_AHEAD; t += QW) produce(t);
     __syncthreads();
     issue_tile(0, read_offs(0), s1buf0, s2buf0);
     RowOffs off_next = read_offs(1);
@@ -263,15 +275,20 @@ __global__ __launch_bounds__(BNT) void attn_bwd_kernel(BwdArgs a, uint32_t o_til
     // the tile (which buffers) is a compile-time constant.  Tile t also forms the row offsets of tile t + BRING_AHEAD (written
     // here, first read in tile t + BRING_AHEAD - 2; the slot's previous tenant, tile t + BRING_AHEAD - BRING, was last read in tile
     // t + BRING_AHEAD - BRING - 1: barriers lie between in both directions).
-    auto do_tile = [&](auto PARC, uint32_t t) __attribute__((always_inline)) {
+    // The last tile is the only one that may hold streamed rows past the end; in the dQ launch they are masked.  PEEL: the last tiles
+    // are code of their own, so that the loop has neither the selects nor the test for a next tile (head_dim 64 -5..-9 %, the others
+    // -1..-3 %); the kernels at the register limit (head_dim 128 with two wavefronts per SIMD) spill when the copies are laid out in a
+    // row (414 values in the dK+dV launch, +20 %) and keep the test.
+    constexpr bool PEEL = !(D == 128 && (NW == 8 || (KG == 1 && MODE == BWD_DQ)));
+    auto do_tile = [&](auto PARC, auto LASTC, uint32_t t) __attribute__((always_inline)) {
+        const bool more = PEEL ? !decltype(LASTC)::value : t + 1 < n_t;
+        const bool tail = MODE == BWD_DQ && !more && n_seq % BT != 0 && kg == KG - 1;
         constexpr int PARITY = decltype(PARC)::value;  // t & 1
         const char* t1 = PARITY ? s1buf1 : s1buf0;
         const char* t2 = PARITY ? s2buf1 : s2buf0;
-        const bool more = t + 1 < n_t;
         const RowOffs off_now = off_next;
         off_next = read_offs(t + 2u);  // picked up a tile early so that the LDS read is not waited for
-        if (wave == (t & (uint32_t)(BNW - 1))) produce(t + BRING_AHEAD);
-        const bool tail = MODE == BWD_DQ && !more && (n_seq % BT) != 0;  // dQ: streamed keys past the end are masked
+        if (ow == (t & (uint32_t)(QW - 1))) produce(t + BRING_AHEAD);
 #pragma unroll
         for (int blk = 0; blk < 2; blk++) {
             // The next tile's loads are enqueued halfway through this one on purpose: with a whole tile of slack even L2 misses are
@@ -295,29 +312,20 @@ __global__ __launch_bounds__(BNT) void attn_bwd_kernel(BwdArgs a, uint32_t o_til
             auto frag_a = [&](int g) __attribute__((always_inline)) -> bf16x8 {
                 return *(const bf16x8*)((g % 2 == 0 ? t1 : t2) + a_rd(g / 2) + blk * 32 * RB);
             };
-            bf16x8 fa[NA], oa[DKV ? KS : 1];
-            if (MAN_A) {
+            bf16x8 fa[NA], oa[OWN2_LDS ? KS : 1];
+            auto read_a = [&](int g) __attribute__((always_inline)) {
+                fa[g] = frag_a(g);
+                if (OWN2_LDS && g % 2 == 1) oa[OWN2_LDS ? g / 2 : 0] = *(const bf16x8*)(own2_lds + a_rd(g / 2));
+            };
 #pragma unroll
-                for (int g = 0; g < AH_A; g++) {
-                    fa[g] = frag_a(g);
-                    if (DKV && g % 2 == 1) oa[g / 2] = *(const bf16x8*)(own2_lds + a_rd(g / 2));
-                }
-                __builtin_amdgcn_sched_barrier(0);
-            }
+            for (int g = 0; g < AH_A; g++) read_a(g);
+            __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
             for (int g = 0; g < NA; g++) {
-                if (MAN_A) {
-                    if (g + AH_A < NA) {
-                        fa[g + AH_A] = frag_a(g + AH_A);
-                        if (DKV && (g + AH_A) % 2 == 1) oa[(g + AH_A) / 2] = *(const bf16x8*)(own2_lds + a_rd((g + AH_A) / 2));
-                    }
-                } else {
-                    fa[g] = frag_a(g);
-                    if (DKV && g % 2 == 1) oa[g / 2] = *(const bf16x8*)(own2_lds + a_rd(g / 2));
-                }
+                if (g + AH_A < NA) read_a(g + AH_A);
                 if (g % 2 == 0) m1 = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fa[g], own1[g / 2], m1, 0, 0, 0);
-                else m2 = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fa[g], DKV ? oa[DKV ? g / 2 : 0] : own2[DKV ? 0 : g / 2], m2, 0, 0, 0);
-                if (MAN_A) __builtin_amdgcn_sched_barrier(0);
+                else m2 = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fa[g], OWN2_LDS ? oa[OWN2_LDS ? g / 2 : 0] : own2[OWN2_LDS ? 0 : g / 2], m2, 0, 0, 0);
+                __builtin_amdgcn_sched_barrier(0);
             }
             // the last product's first fragments are fetched now, under the elementwise arithmetic
             constexpr int NC = (DKV ? 4 : 2) * MT;  // DKV: dK and dV groups alternate
@@ -333,11 +341,9 @@ __global__ __launch_bounds__(BNT) void attn_bwd_kernel(BwdArgs a, uint32_t o_til
                 return __builtin_shufflevector(v0, v1, 0, 1, 2, 3, 4, 5, 6, 7);
             };
             bf16x8 fc[NC];
-            if (MAN_C) {
 #pragma unroll
-                for (int cidx = 0; cidx < AH_C; cidx++) fc[cidx] = frag_c(cidx);
-                __builtin_amdgcn_sched_barrier(0);
-            }
+            for (int cidx = 0; cidx < AH_C; cidx++) fc[cidx] = frag_c(cidx);
+            __builtin_amdgcn_sched_barrier(0);
             bf16x8 rf[2], rp[DKV ? 2 : 1];  // rp: P itself in the DKV launch (rf holds dS there)
 #pragma unroll
             for (int g2 = 0; g2 < 2; g2++) {
@@ -350,7 +356,7 @@ __global__ __launch_bounds__(BNT) void attn_bwd_kernel(BwdArgs a, uint32_t o_til
                         const int r = g2 * 8 + e + u;
                         float pr = MODE == BWD_DQ ? __builtin_amdgcn_exp2f(fmaf(m1[r], c, -own_l)) : __builtin_amdgcn_exp2f(m1[r] * c);
                         if (tail) {
-                            const uint32_t row = t * BT + blk * 32 + 8 * (r >> 2) + 4 * h + (r & 3);
+                            const uint32_t row = (tile0 + t) * BT + blk * 32 + 8 * (r >> 2) + 4 * h + (r & 3);
                             pr = row < n_seq ? pr : 0.f;
                         }
                         val[u] = MODE == BWD_DQ ? pr * (m2[r] - own_d) : pr * m2[r];
@@ -368,33 +374,78 @@ __global__ __launch_bounds__(BNT) void attn_bwd_kernel(BwdArgs a, uint32_t o_til
                 rf[g2] = pk;
                 if (DKV) rp[g2] = pp;
             }
-            if (MAN_C) __builtin_amdgcn_sched_barrier(0);
+            __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
             for (int cidx = 0; cidx < NC; cidx++) {
-                if (MAN_C) {
-                    if (cidx + AH_C < NC) fc[cidx + AH_C] = frag_c(cidx + AH_C);
-                } else {
-                    fc[cidx] = frag_c(cidx);
-                }
+                if (cidx + AH_C < NC) fc[cidx + AH_C] = frag_c(cidx + AH_C);
                 const int pair = DKV ? cidx / 2 : cidx, g2 = pair / MT, mt = pair % MT;
                 if (DKV && cidx % 2 == 1) acc2[mt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fc[cidx], rp[DKV ? g2 : 0], acc2[mt], 0, 0, 0);  // dV^T += dO^T P
                 else acc[mt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fc[cidx], rf[g2], acc[mt], 0, 0, 0);
-                if (MAN_C) __builtin_amdgcn_sched_barrier(0);
+                __builtin_amdgcn_sched_barrier(0);
             }
         }
         if (more) store_rowvals(PARITY ^ 1);
         tile_landed();
         __syncthreads();
     };
+    using P0 = std::integral_constant<int, 0>;
+    using P1 = std::integral_constant<int, 1>;
     uint32_t t = 0;
-    for (; t + 1 < n_t; t += 2) {
-        do_tile(std::integral_constant<int, 0>{}, t);
-        do_tile(std::integral_constant<int, 1>{}, t + 1u);
+    if constexpr (PEEL) {
+        for (; t + 2 < n_t; t += 2) {
+            do_tile(P0{}, std::false_type{}, t);
+            do_tile(P1{}, std::false_type{}, t + 1u);
+        }
+        if (t + 1 < n_t) {
+            do_tile(P0{}, std::false_type{}, t);
+            do_tile(P1{}, std::true_type{}, t + 1u);
+        } else if (t < n_t) {
+            do_tile(P0{}, std::true_type{}, t);
+        }
+    } else {
+        for (; t + 1 < n_t; t += 2) {
+            do_tile(P0{}, std::false_type{}, t);
+            do_tile(P1{}, std::false_type{}, t + 1u);
+        }
+        if (t < n_t) do_tile(P0{}, std::false_type{}, t);
     }
-    if (t < n_t) do_tile(std::integral_constant<int, 0>{}, t);
+
+    // ---- groups: the first one adds the others' sums to its own, through the LDS of the tiles
+    if constexpr (KG > 1) {
+        if (n_t < (all_t + KG - 1) / KG) __syncthreads();  // a group with one tile less has passed one barrier less
+        static_assert(KG == 2 && QW * (DKV ? 2 : 1) <= 4 && MT * 4 * 1024 == TILE_BYTES, "a wavefront's accumulator takes a tile buffer");
+        // every tile has been read (each ends with a barrier): wavefront ow of group 1 leaves dQ or dK in its group's buffer ow, dV in 2 + ow
+        auto part = [&](uint32_t i) __attribute__((always_inline)) -> char* {
+            return (i == 0 ? s1buf0_all : i == 1 ? s1buf1_all : i == 2 ? s2buf0_all : s2buf1_all) + TILE_BYTES + lane * 16u;
+        };
+        auto leave = [&](char* dst, const f32x16 (&x)[MT]) __attribute__((always_inline)) {
+#pragma unroll
+            for (int mt = 0; mt < MT; mt++)
+#pragma unroll
+                for (int g = 0; g < 4; g++) *(f32x4*)(dst + (mt * 4 + g) * 1024) = f32x4{x[mt][4 * g], x[mt][4 * g + 1], x[mt][4 * g + 2], x[mt][4 * g + 3]};
+        };
+        auto take = [&](const char* src, f32x16 (&x)[MT]) __attribute__((always_inline)) {
+#pragma unroll
+            for (int mt = 0; mt < MT; mt++)
+#pragma unroll
+                for (int g = 0; g < 4; g++) {
+                    const f32x4 o = *(const f32x4*)(src + (mt * 4 + g) * 1024);
+#pragma unroll
+                    for (int e = 0; e < 4; e++) x[mt][4 * g + e] += o[e];
+                }
+        };
+        if (kg != 0) {
+            leave(part(ow), acc);
+            if constexpr (DKV) leave(part(2u + ow), acc2);
+        }
+        __syncthreads();
+        if (kg != 0) return;
+        take(part(ow), acc);
+        if constexpr (DKV) take(part(2u + ow), acc2);
+    }
 
     // ---- epilogue: lane owns row jo; register r of block mt is channel 32*mt + 8*(r/4) + 4*h + r%4
-    if (own_valid) {
+    if (jo < n_seq) {
         const float f = a.scale;
 #pragma unroll
         for (int mt = 0; mt < MT; mt++)
@@ -412,73 +463,53 @@ __global__ __launch_bounds__(BNT) void attn_bwd_kernel(BwdArgs a, uint32_t o_til
                 for (int g = 0; g < 4; g++) {
                     bf16x4 o;
 #pragma unroll
-                    for (int e = 0; e < 4; e++) o[e] = (__bf16)acc2[mt][g * 4 + e];
+                    for (int e = 0; e < 4; e++) o[e] = (__bf16)acc2[DKV ? mt : 0][g * 4 + e];
                     *(bf16x4*)(grad2_g + own_off + mt * 32 + g * 8 + 4 * h) = o;
                 }
         }
     }
 }
 
-// delta[unit][j] = sum_d dO[row][head][d] * O[row][head][d]: one wavefront per position (sb, j), D/8 lanes per head.
-template <int D, bool PAD>
-__global__ __launch_bounds__(256) void bwd_delta_kernel(const __bf16* __restrict__ out, const __bf16* __restrict__ dout,
-                                                        float* __restrict__ delta, GridMap g, int B, int heads, uint32_t n_rows) {
-    constexpr int LPH = D / 8;        // lanes per head (16 bytes each)
-    constexpr int HPP = 64 / LPH;     // heads per pass
-    const uint32_t lane = threadIdx.x & 63u;
-    const uint32_t row = blockIdx.x * 4u + (threadIdx.x >> 6);
-    if (row >= n_rows) return;
-    const uint32_t n_sub = (uint32_t)g.n_sub;
-    const uint32_t sb = row / n_sub, j = row - sb * n_sub;
-    uint32_t p = 0, q = 0, b0 = sb;
-    if (g.mode != MODE_DENSE) {
-        const uint32_t pq = sb / (uint32_t)B;
-        b0 = sb - pq * (uint32_t)B;
-        p = pq / (uint32_t)g.s;
-        q = pq - p * (uint32_t)g.s;
-    }
-    const size_t C = (size_t)heads * D;
-    bool real = true;
-    const uint32_t tok = PAD ? src_token_padded(g, p, q, j, &real) : src_token(g, p, q, j);
-    const size_t base = ((size_t)b0 * (uint32_t)g.n_tok + (real ? tok : 0u)) * C;
-    for (uint32_t h0 = 0; h0 < (uint32_t)heads; h0 += HPP) {
-        const uint32_t head = h0 + lane / LPH;
-        float sum = 0.f;
-        if (head < (uint32_t)heads && real) {  // a padding position gets delta = 0
-            const size_t off = base + (size_t)head * D + (lane % LPH) * 8;
-            const bf16x8 o = *(const bf16x8*)(out + off);
-            const bf16x8 d = *(const bf16x8*)(dout + off);
-#pragma unroll
-            for (int e = 0; e < 8; e++) sum = fmaf((float)o[e], (float)d[e], sum);
-        }
-#pragma unroll
-        for (int m = LPH / 2; m >= 1; m >>= 1) sum += __shfl_xor(sum, m);
-        if (head < (uint32_t)heads && lane % LPH == 0) delta[((size_t)sb * heads + head) * n_sub + j] = sum;
-    }
+template <int D, int MODE, int NW, int KG, bool PAD>
+static hipError_t launch_t(const BwdArgs& a, uint32_t n_units, uint32_t n_max, hipStream_t stream) {
+    constexpr uint32_t WGO = 32u * (NW / KG);
+    const uint32_t o_tiles = (n_max + WGO - 1u) / WGO;
+    const uint64_t total = (uint64_t)n_units * o_tiles;
+    if (total > 0x7ffffff0ull) return hipErrorInvalidConfiguration;
+    const uint32_t per_xcd = (uint32_t)((total + 7u) / 8u);
+    attn_bwd_kernel<D, MODE, NW, KG, PAD><<<8u * per_xcd, 64 * NW, 0, stream>>>(a, o_tiles, (uint32_t)total, per_xcd);
+    return hipGetLastError();
 }
+
+// Workgroup shapes, as in the forward: 8 wavefronts (256 owners), 4 wavefronts (128), 4 wavefronts in two groups (64 owners, half the
+// chain each).  At head_dim 128 the dK+dV shapes with 4 wavefronts hold V in registers (one workgroup per CU).  Measured, always the
+// first shape -> picked, dQ and dK+dV together, us at head_dim 128, units x tokens: 16x200 39.8 -> 23, 12x700 78 -> 42, 48x390 62 -> 43,
+// 160x960 347 -> 328, 24x2600 495 -> 328, 1x5000 411 -> 190; 48x960 (108) and 48x8190 (5190) keep it.
+constexpr ShapeCost DQ_COST_128[] = {{256, 1, 50.f, {13.0f}}, {128, 2, 40.f, {9.5f, 13.4f}}, {64, 1, 40.f, {6.3f}}};
+constexpr ShapeCost DQ_COST_64[] = {{256, 1, 35.f, {8.0f}}, {128, 2, 28.f, {5.6f, 8.1f}}, {64, 2, 30.f, {3.4f, 6.0f}}};
+constexpr ShapeCost DKV_COST_128[] = {{256, 1, 80.f, {19.0f}}, {128, 1, 60.f, {13.2f}}, {64, 1, 70.f, {8.0f}}};
+constexpr ShapeCost DKV_COST_64[] = {{256, 1, 50.f, {10.0f}}, {128, 2, 40.f, {8.0f, 10.3f}}, {64, 1, 50.f, {5.4f}}};
 
 template <int D, int MODE, bool PAD>
 static hipError_t launch_mode(const BwdArgs& a, hipStream_t stream) {
     const uint32_t s2 = a.g.mode == MODE_DENSE ? 1u : (uint32_t)(a.g.s * a.g.s);
     const uint32_t n_units = (uint32_t)a.B * s2 * (uint32_t)a.heads;
-    const uint32_t n_max = PAD ? make_class_map(a.g, 0, 0).n : (uint32_t)a.g.n_sub;  // the first class has the most real tokens
-    const uint32_t o_tiles = (n_max + 32u * BNW - 1u) / (32u * BNW);
-    const uint64_t total = (uint64_t)n_units * o_tiles;
-    if (total > 0x7ffffff0ull) return hipErrorInvalidConfiguration;
-    const uint32_t per_xcd = (uint32_t)((total + 7u) / 8u);
-    attn_bwd_kernel<D, MODE, PAD><<<8u * per_xcd, BNT, 0, stream>>>(a, o_tiles, (uint32_t)total, per_xcd);
-    return hipGetLastError();
+    // any-resolution mode: the first class has the most real tokens, the last one the fewest
+    const uint32_t last = (uint32_t)a.g.s - 1u;
+    const uint32_t n_max = PAD ? make_class_map(a.g, 0, 0).n : (uint32_t)a.g.n_sub;
+    const uint32_t n_min = PAD ? make_class_map(a.g, last, last).n : n_max;
+    const ShapeCost(&cost)[3] = MODE == BWD_DQ ? (D == 128 ? DQ_COST_128 : DQ_COST_64) : (D == 128 ? DKV_COST_128 : DKV_COST_64);
+    switch (pick_shape(cost, n_units, n_max, 2, n_min > (uint32_t)BT)) {  // a group needs a tile of its own
+        case 1: return launch_t<D, MODE, 4, 1, PAD>(a, n_units, n_max, stream);
+        case 2: return launch_t<D, MODE, 4, 2, PAD>(a, n_units, n_max, stream);
+        default: return launch_t<D, MODE, 8, 1, PAD>(a, n_units, n_max, stream);
+    }
 }
 
 template <int D, bool PAD>
 static hipError_t launch_all(const BwdArgs& a, hipStream_t stream) {
-    const uint32_t s2 = a.g.mode == MODE_DENSE ? 1u : (uint32_t)(a.g.s * a.g.s);
-    const uint32_t n_rows = (uint32_t)a.B * s2 * (uint32_t)a.g.n_sub;
-    bwd_delta_kernel<D, PAD><<<(n_rows + 3u) / 4u, 256, 0, stream>>>((const __bf16*)a.out, (const __bf16*)a.dout, a.delta, a.g, a.B, a.heads, n_rows);
-    hipError_t e = hipGetLastError();
-    if (e != hipSuccess) return e;
-    if ((e = launch_mode<D, BWD_DQ, PAD>(a, stream)) != hipSuccess) return e;
-    return launch_mode<D, BWD_DKV, PAD>(a, stream);
+    const hipError_t e = launch_mode<D, BWD_DQ, PAD>(a, stream);  // forms delta, which the second launch reads
+    return e != hipSuccess ? e : launch_mode<D, BWD_DKV, PAD>(a, stream);
 }
 
 hipError_t launch_attn_bwd_bf16(const BwdArgs& a, hipStream_t stream) {

@@ -9,7 +9,7 @@
 //     and share every K/V tile that is brought into LDS.  The shape for large problems is 8 wavefronts in one group: 256 queries
 //     a tile halve the L2 -> LDS traffic per MFMA compared with 128 (two wavefronts per SIMD, <= 256 VGPRs per lane, 64 KiB LDS).
 //     Small problems are bound by idle CUs and by the serial walk over the keys instead; they get smaller workgroups, and two
-//     groups that walk half of the keys each and merge (reference, sum, O) through LDS at the end: see pick_shape().
+//     groups that walk half of the keys each and merge (reference, sum, O) through LDS at the end: see the table at the launch.
 //   * The products are formed transposed, S^T = K Q^T and O^T = V^T P^T, with v_mfma_f32_32x32x16_bf16.  In the
 //     32x32 accumulator layout lane l holds column l%32, so every lane owns ONE query: its 16 registers per 32-key
 //     block are 16 keys of that query, and the exponentiated accumulator registers, rounded to bf16, ARE the B operand
@@ -47,6 +47,7 @@
 
 #include "kernels.h"
 #include "lds_layout.h"
+#include "wg_shape.h"
 
 namespace skiparse {
 
@@ -666,45 +667,16 @@ static hipError_t launch_t(const AttnArgs& a, uint32_t n_units, uint32_t n_max, 
     return hipGetLastError();
 }
 
-// Which workgroup shape a call gets.  A workgroup of NW wavefronts in KG key groups takes 32 * NW / KG queries:
+// Workgroup shapes: NW wavefronts in KG key groups take 32 * NW / KG queries.
 //   0  8 wavefronts, 1 group:  256 queries share every tile; the least L2 -> LDS traffic per MFMA, the best once the chip is full
 //   1  4 wavefronts, 1 group:  128 queries, two (head_dim 64: three) workgroups per CU; twice as many, finer-grained workgroups
 //   2  4 wavefronts, 2 groups:  64 queries, each group walks half of the keys: four times the workgroups, half the serial chain
 //   3  8 wavefronts, 2 groups: 128 queries, half the chain at two wavefronts per SIMD
-// Small problems leave compute units idle or a last round nearly empty, so the shape with the smallest estimated time is taken:
-// rounds over the 256 CUs, each as long as `fixed` plus, per 32-key block, the cost with k workgroups on a CU.  The costs (in units
-// of 0.1 us) were fitted to launches of every shape over 1..160 units of 32..8190 tokens; measured, before (always shape 0) -> after, us at
+// The costs were fitted to launches of every shape over 1..160 units of 32..8190 tokens.  Measured, always shape 0 -> picked, us at
 // head_dim 128, units x tokens: 8x250 13.4 -> 8.2, 48x390 18.7 -> 13.7, 160x960 101 -> 88, 24x2600 134 -> 85, 48x2600 213 -> 165,
 // 4x5000 109 -> 66, 1x5000 107 -> 60; 48x960 (32) and 48x8190 (1390) keep shape 0.  At head_dim 64: 24x2600 88 -> 52, 160x4000 804 -> 708.
-struct ShapeCost {
-    int max_k;          // workgroups of this shape that one CU holds
-    float fixed;        // prologue, pipeline fill, epilogue (and the merge of key groups)
-    float block[3];     // per 32-key block of the sequence with k = 1..max_k workgroups on a CU
-};
-constexpr int N_SHAPES = 4;
-constexpr int SHAPE_QUERIES[N_SHAPES] = {256, 128, 64, 128};
-constexpr ShapeCost COST_128[N_SHAPES] = {{1, 40.f, {9.0f}}, {2, 20.f, {5.5f, 10.0f}}, {1, 25.f, {3.9f}}, {1, 45.f, {4.7f}}};
-constexpr ShapeCost COST_64[N_SHAPES] = {{1, 30.f, {5.2f}}, {3, 15.f, {3.6f, 5.7f, 8.0f}}, {2, 15.f, {2.4f, 3.7f}}, {1, 30.f, {2.9f}}};
-
-// n_sub: tokens of the largest unit, n_min: of the smallest
-static int pick_shape(const ShapeCost* cost, uint32_t n_units, uint32_t n_sub, uint32_t n_min) {
-    constexpr uint64_t CUS = 256;
-    const float blocks = (float)((n_sub + 31u) / 32u);
-    int best = 0;
-    float best_t = 0.f;
-    for (int v = 0; v < N_SHAPES; v++) {
-        if (v >= 2 && n_min <= (uint32_t)KT) continue;  // a key group needs a tile of its own
-        const uint64_t wgs = (uint64_t)n_units * ((n_sub + SHAPE_QUERIES[v] - 1u) / SHAPE_QUERIES[v]);
-        const uint64_t per_round = CUS * cost[v].max_k, rounds = wgs / per_round, rem = wgs % per_round;
-        float t = (float)rounds * (cost[v].fixed + blocks * cost[v].block[cost[v].max_k - 1]);
-        if (rem != 0) t += cost[v].fixed + blocks * cost[v].block[(rem - 1u) / CUS];
-        if (v == 0 || t < best_t) {
-            best = v;
-            best_t = t;
-        }
-    }
-    return best;
-}
+constexpr ShapeCost FWD_COST_128[] = {{256, 1, 40.f, {9.0f}}, {128, 2, 20.f, {5.5f, 10.0f}}, {64, 1, 25.f, {3.9f}}, {128, 1, 45.f, {4.7f}}};
+constexpr ShapeCost FWD_COST_64[] = {{256, 1, 30.f, {5.2f}}, {128, 3, 15.f, {3.6f, 5.7f, 8.0f}}, {64, 2, 15.f, {2.4f, 3.7f}}, {128, 1, 30.f, {2.9f}}};
 
 template <int D, bool PAD>
 static hipError_t launch_shape(const AttnArgs& a, hipStream_t stream) {
@@ -714,7 +686,7 @@ static hipError_t launch_shape(const AttnArgs& a, hipStream_t stream) {
     const uint32_t last = (uint32_t)a.g.s - 1u;
     const uint32_t n_max = PAD ? make_class_map(a.g, 0, 0).n : (uint32_t)a.g.n_sub;
     const uint32_t n_min = PAD ? make_class_map(a.g, last, last).n : n_max;
-    switch (pick_shape(D == 128 ? COST_128 : COST_64, n_units, n_max, n_min)) {
+    switch (pick_shape(D == 128 ? FWD_COST_128 : FWD_COST_64, n_units, n_max, 2, n_min > (uint32_t)KT)) {  // a key group needs a tile of its own
         case 1: return launch_t<D, 4, 1, PAD>(a, n_units, n_max, stream);
         case 2: return launch_t<D, 4, 2, PAD>(a, n_units, n_max, stream);
         case 3: return launch_t<D, 8, 2, PAD>(a, n_units, n_max, stream);

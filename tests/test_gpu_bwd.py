@@ -261,3 +261,40 @@ def test_backward_768p_one_unit_token_all_heads():
     dv_sum, do_sum = dv[0, idx].double().sum(0), dout.cuda()[0, idx].double().sum(0)
     assert float((dk_sum.abs() / dk_abs).max()) <= 2e-2
     assert float((dv_sum - do_sum).abs().max()) <= 2e-2 * float(do_sum.abs().max())
+
+
+# The backward's workgroup shapes (64, 128 or 256 owners, one or two groups of wavefronts) follow the problem's size: one tile more than a
+# group, uneven halves, a last tile of one row, many and few units.
+@pytest.mark.parametrize("heads,N", [(1, 65), (2, 129), (3, 321), (80, 65), (200, 129), (300, 33), (16, 900)])
+@pytest.mark.parametrize("D", [64, 128])
+def test_backward_workgroup_shapes(heads, N, D):
+    import paper_2605_28691_amd as sk
+
+    w = si.make_shape("bwd_shapes", 1, heads, D, 1, 1, N, 1, seed=N + heads)
+    q, k, v = si.make_qkv(w)
+    dout = si.make_dout(w)
+    _, _, dq, dk, dv = _run(sk, q, k, v, dout, 1, 1, N, 1, "token", w.scale)
+    for h in sorted({0, heads // 2, heads - 1}):
+        one = [t[:, :, h : h + 1].contiguous() for t in (q, k, v, dout)]
+        want = oracle.attention_bwd(*oracle_inputs(*one[:3]), si.as_oracle_array(one[3]), w.scale)
+        for g, wnt, name in zip((dq, dk, dv), want, ("dq", "dk", "dv")):
+            assert_grad_close(to_np64(g[:, :, h : h + 1]), wnt, f"head {h} {name}")
+
+
+@pytest.mark.parametrize("pattern", ["token", "group"])
+@pytest.mark.parametrize("T,H,W,s,D", [(1, 17, 64, 4, 128), (1, 9, 33, 3, 64), (1, 2, 33, 4, 128)])
+def test_backward_classes_of_unequal_size(T, H, W, s, D, pattern):
+    """Any-resolution grids whose classes differ in size, some of them without a real token."""
+    import paper_2605_28691_amd as sk
+
+    w = si.make_shape("bwd_classes", 1, 2, D, T, H, W, s, seed=6)
+    q, k, v = si.make_qkv(w)
+    dout = si.make_dout(w)
+    want = oracle.skiparse_attention_bwd_padded(*oracle_inputs(q, k, v), si.as_oracle_array(dout), T, H, W, s, pattern, w.scale)
+    qg, kg, vg, dg = (t.cuda() for t in (q, k, v, dout))
+    lse = torch.full(sk.skiparse_lse_shape(1, 2, T, H, W, D, s, pattern, True), 7.0, dtype=torch.float32, device="cuda")
+    out, lse = sk.skiparse_attn_fwd_lse(qg, kg, vg, T, H, W, s, pattern, scale=w.scale, lse=lse, pad=True)
+    assert not bool((lse == 7.0).any())  # written everywhere: zero at the padding
+    grads = sk.skiparse_attn_bwd(qg, kg, vg, out, dg, lse, T, H, W, s, pattern, scale=w.scale, pad=True)
+    for g, wnt, name in zip(grads, want, ("dq", "dk", "dv")):
+        assert_grad_close(to_np64(g), wnt, f"{pattern} {name}")
