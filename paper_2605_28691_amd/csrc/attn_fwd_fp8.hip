@@ -36,8 +36,10 @@ typedef __attribute__((ext_vector_type(4))) float f32x4;
 
 constexpr int KT8 = 64;            // keys per tile = contraction depth of one PV MFMA
 constexpr int NW8 = 4;             // wavefronts per workgroup: 128 queries (one scale block) share each K/V tile
-constexpr int WAVES_PER_SIMD8 = 3; // three workgroups per compute unit: the kernel is not software-pipelined, the overlap of one
-                                   // wavefront's exponentials with another's MFMAs comes from occupancy (needs <= 168 VGPRs)
+// Wavefronts per SIMD that the registers are allotted for: the kernel is not software-pipelined, the overlap of one wavefront's
+// exponentials with another's MFMAs comes from occupancy.  Three at head_dim 128 (<= 168 VGPRs), four at head_dim 64 (<= 128; against
+// three: 48 units of 8190 tokens 653 -> 622 us, 160 of 4000 555 -> 527, 1000 of 100 14.4 -> 12.5).
+constexpr int waves_per_simd8(int D) { return D == 64 ? 4 : 3; }
 constexpr int NT8 = 64 * NW8;
 constexpr float P_GAIN = 16.0f;    // probabilities are multiplied by (sv / sv_max) * 16 before the E4M3 cast
 
@@ -53,7 +55,7 @@ __device__ inline void lane_pair_f(float x, float& lo, float& hi) {
 // padding positions); a padding position is a masked key (a -inf bias per staged row, formed a tile ahead by one wavefront and added
 // to the logits) and a skipped query.
 template <int D, bool PAD>
-__attribute__((amdgpu_waves_per_eu(WAVES_PER_SIMD8, WAVES_PER_SIMD8)))
+__attribute__((amdgpu_waves_per_eu(waves_per_simd8(D), waves_per_simd8(D))))
 __global__ __launch_bounds__(NT8) void attn_fwd_fp8_kernel(Fp8AttnArgs a, uint32_t q_tiles, uint32_t total, uint32_t per_xcd) {
     constexpr int NJ = D / 64;         // 64-channel MFMA steps of S^T = K Q^T
     constexpr int MT = D / 32;         // 32-channel blocks of O^T
@@ -83,11 +85,14 @@ __global__ __launch_bounds__(NT8) void attn_fwd_fp8_kernel(Fp8AttnArgs a, uint32
     const uint32_t n_seq = (uint32_t)a.g.n_sub, n_blk = a.n_blk;
     const uint32_t pq_ = sb / (uint32_t)a.B, b0_ = sb - pq_ * (uint32_t)a.B;
     const uint32_t p_ = a.g.mode == MODE_DENSE ? 0u : pq_ / (uint32_t)a.g.s, q_ = a.g.mode == MODE_DENSE ? 0u : pq_ - p_ * (uint32_t)a.g.s;
-    // one wavefront (they take turns) marks the keys of a tile: lane = key
+    // one wavefront (they take turns) marks the keys of a tile: lane = key.  The padding sits at the end of H and W, so the real rows
+    // and columns of a class are a prefix: two divisions a key instead of the whole index map, on the path of every tile.
+    const uint32_t h_real = PAD ? class_extent(a.g, (uint32_t)a.g.H_real, p_) : 0u, w_real = PAD ? class_extent(a.g, (uint32_t)a.g.W, q_) : 0u;
+    const FastDiv hs_div = make_fastdiv32(PAD ? a.g.sdiv.div(a.g.hpad.d) : 1u);  // rows of a class on the padded grid
     auto mark_keys = [&](uint32_t t) __attribute__((always_inline)) {
         const uint32_t j = t * KT8 + lane;
-        bool real = false;
-        if (j < n_seq) (void)src_token_padded(a.g, p_, q_, j, &real);
+        const uint32_t r = a.g.ws.div(j), ws = j - r * a.g.ws.d, hs = r - hs_div.div(r) * hs_div.d;
+        const bool real = j < n_seq && ws < w_real && hs < h_real;
         kbias[t & 1u][lane] = real ? 0.f : -INFINITY;
         const unsigned long long pads = __builtin_amdgcn_ballot_w64(!real);
         if (lane == 0) kany[t & 1u] = pads != 0 ? 1u : 0u;
