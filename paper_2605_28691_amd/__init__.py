@@ -7,6 +7,7 @@ built library, or on a bad argument, a call raises.
 from __future__ import annotations
 
 import ctypes
+import functools
 import os
 
 import torch
@@ -89,14 +90,17 @@ def lib() -> ctypes.CDLL:
     return _lib
 
 
-def _stream() -> ctypes.c_void_p:
-    return ctypes.c_void_p(torch.cuda.current_stream().cuda_stream)
+# A small call is bound by what it costs to issue it (a kernel of 4 us behind 10 us of Python), so the marshalling keeps to plain
+# integers: addresses and the stream handle are converted once, by ctypes, and no Stream or c_void_p object is made for them.
+def _stream() -> int:
+    """Handle of torch's current stream on the current device."""
+    return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
 
 
-def _dev(t: torch.Tensor, name: str) -> ctypes.c_void_p:
+def _dev(t: torch.Tensor, name: str) -> int:
     if not t.is_cuda or not t.is_contiguous():
         raise ValueError(f"{name} must be a contiguous device tensor")
-    return ctypes.c_void_p(t.data_ptr())
+    return t.data_ptr()
 
 
 def _check(code: int, what: str) -> None:
@@ -209,7 +213,7 @@ def skiparse_attn_fwd(q, k, v, T: int, H: int, W: int, s: int, pattern: str, sca
     B, heads, D = _dims(q, T, H, W)
     if out is None:
         out = torch.empty_like(q)
-    ws_ptr, ws_bytes = ctypes.c_void_p(0), 0
+    ws_ptr, ws_bytes = None, 0
     if not fused:
         need = skiparse_workspace_bytes(B, heads, T, H, W, D, s, False)
         if workspace is None:
@@ -243,9 +247,19 @@ def skiparse_attn_fwd_sparse(q, k, v, T: int, H: int, W: int, s: int, pattern: s
     return out
 
 
+@functools.lru_cache(maxsize=256)
+def _lse_bytes(B, heads, T, H, W, D, s, pattern: int, flags: int) -> int:
+    return int(lib().skiparse_lse_bytes(B, heads, T, H, W, D, s, pattern, flags))
+
+
+@functools.lru_cache(maxsize=256)
+def _bwd_workspace_bytes(B, heads, T, H, W, D, s, pattern: int, flags: int) -> int:
+    return int(lib().skiparse_bwd_workspace_bytes(B, heads, T, H, W, D, s, pattern, flags))
+
+
 def skiparse_lse_shape(B, heads, T, H, W, D, s, pattern: str, pad: bool = False):
     """Shape of the log-sum-exp tensor: [s*s*B][heads][positions per subsequence] (positions of the padded grid with pad=True)."""
-    n = int(lib().skiparse_lse_bytes(B, heads, T, H, W, D, s, PATTERNS[pattern], PAD if pad else 0)) // 4
+    n = _lse_bytes(B, heads, T, H, W, D, s, PATTERNS[pattern], PAD if pad else 0) // 4
     if n == 0:
         raise ValueError("grid does not fit the pattern (use pad=True for the any-resolution mode)")
     return (s * s * B, heads, n // (s * s * B * heads))
@@ -268,7 +282,7 @@ def skiparse_attn_fwd_lse(q, k, v, T: int, H: int, W: int, s: int, pattern: str,
 
 
 def skiparse_bwd_workspace_bytes(B, heads, T, H, W, D, s, pattern: str, pad: bool = False) -> int:
-    return int(lib().skiparse_bwd_workspace_bytes(B, heads, T, H, W, D, s, PATTERNS[pattern], PAD if pad else 0))
+    return _bwd_workspace_bytes(B, heads, T, H, W, D, s, PATTERNS[pattern], PAD if pad else 0)
 
 
 def skiparse_attn_bwd(q, k, v, out, dout, lse, T: int, H: int, W: int, s: int, pattern: str, scale: float = 0.0,
