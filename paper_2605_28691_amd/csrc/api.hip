@@ -205,7 +205,7 @@ int skiparse_switch_pattern(const void* src, void* dst, int B, int heads, int T,
     if (s == 1) return finish(launch_permute(src, dst, B, make_gridmap(T, H, W, 1, SKIPARSE_TOKEN), row_bytes, 1, (hipStream_t)stream));
     const int to_pattern = from_pattern == SKIPARSE_TOKEN ? SKIPARSE_GROUP : SKIPARSE_TOKEN;
     const GridMap g_to = make_gridmap(T, H, W, s, to_pattern);
-    return finish(launch_switch(src, dst, B, g_to, from_pattern == SKIPARSE_GROUP, H, row_bytes, (hipStream_t)stream));
+    return finish(launch_switch(src, dst, B, g_to, row_bytes, (hipStream_t)stream));
 }
 
 int dense_attn_fwd(const void* q, const void* k, const void* v, void* out, int B, int heads, int T, int H, int W,

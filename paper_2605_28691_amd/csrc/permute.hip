@@ -1,20 +1,27 @@
 // Row gather/scatter between the original and the sparse token order (Algorithm 1, orig_to_tsa / orig_to_gsa and
-// their inverses).  Bound by HBM bandwidth: every row of heads*head_dim elements is contiguous in both layouts, so
-// one wavefront moves one row with 16-byte accesses per lane (1 KiB contiguous per wavefront instruction) and the
-// index arithmetic is done once per row.
+// their inverses), and between the two sparse orders.  Bound by HBM bandwidth: every row of heads*head_dim elements is contiguous in
+// both layouts.  The wavefronts enumerate DESTINATION rows and find each row's source with the index map or its inverse: contiguous
+// writes with gathered reads measure faster than the reverse.
+//   * Rows of 1 KiB and more: one wavefront moves one row with 16-byte accesses per lane (1 KiB contiguous per instruction).
+//   * Shorter rows: one wavefront moves a batch of rows.  A wavefront a row leaves most lanes idle and spends the index arithmetic, some
+//     ten integer divisions, on a few hundred bytes; here lane i finds the source of row i, one evaluation for the whole batch, and
+//     the batch is moved as one run of 16-byte chunks.  Permute, switch and unpermute together, us: 80,640 rows of 384 B 68.9 -> 45.1,
+//     32,256 rows of 128 B 28.4 -> 12.8.  From 1 KiB on a wavefront a row is the better one (1,280 B: 110 against 121; 10 KiB: 879
+//     against 887, and longer batches lose more).
 #include "kernels.h"
 
 namespace skiparse {
 
 typedef __attribute__((ext_vector_type(4))) unsigned int u32x4;
 
-constexpr int PERMUTE_WAVES = 4;  // rows per workgroup
+constexpr int PERMUTE_WAVES = 4;  // wavefronts per workgroup
 
-// BY_ORIG = false: the wavefronts enumerate the rows of the SPARSE layout (consecutive wavefronts touch consecutive sparse rows) and
-// find each row's place in the original layout with the index map; BY_ORIG = true: they enumerate the rows of the ORIGINAL layout
-// and find each token's class and position with the inverse formulas.  Either serves both directions; what differs is which
-// side of the copy is contiguous across wavefronts.  Contiguous WRITES with gathered reads measure faster than the reverse, so
-// the permute (writes the sparse layout) enumerates sparse rows and the unpermute (writes the original layout) original rows.
+enum RowMap : int {
+    TO_SPARSE = 0,  // destination: the sparse layout, source: the original one
+    TO_ORIGINAL = 1,  // the inverse
+    SWITCH = 2      // destination: the sparse layout of g's pattern, source: that of the other pattern
+};
+
 // ssp_G > 0 (Sparse Sequence Parallelism, Alg. 1 sparse_sequence_parallel, step 3): the sparse side is a buffer as it arrives from the
 // all-to-all, [source rank][my subsequence g'][source's subsequence g][b][position]; the algorithm's axis swap to
 // [source rank][g][g'][b] = "(p q b')" order is folded into the row number instead of being a pass of its own.
@@ -25,50 +32,50 @@ __device__ inline uint32_t ssp_received_sb(uint32_t sb, uint32_t B, uint32_t G) 
     return ((r * G + gd) * G + gs) * b + bb;
 }
 
-template <int UNROLL, bool BY_ORIG>
-__global__ __launch_bounds__(PERMUTE_WAVES * 64) void permute_rows_kernel(const u32x4* __restrict__ src, u32x4* __restrict__ dst,
-                                                                          int B, GridMap g, uint32_t chunks_per_row,
-                                                                          uint32_t n_rows, int to_sparse, uint32_t ssp_G) {
+// token (b, t*H + h, w) -> its row in the sparse layout of one pattern (Alg. 1 read backwards; H and W are multiples of s for the
+// token-wise pattern and of s*s for the group-wise one, so t*H + h splits like h)
+__device__ inline uint32_t sparse_row_of(bool group, uint32_t s, uint32_t W, uint32_t n_sub, uint32_t B, uint32_t b, uint32_t n, uint32_t ssp_G) {
+    const uint32_t th = n / W, w = n - th * W;
+    uint32_t p, q, r, ws;
+    if (group) {
+        p = (th / s) % s;
+        q = (w / s) % s;
+        r = (th / (s * s)) * s + th % s;
+        ws = (w / (s * s)) * s + w % s;
+    } else {
+        p = th % s;
+        q = w % s;
+        r = th / s;
+        ws = w / s;
+    }
+    uint32_t sb = (p * s + q) * B + b;
+    if (ssp_G) sb = ssp_received_sb(sb, B, ssp_G);
+    return sb * n_sub + r * (W / s) + ws;
+}
+
+// row number in the source of destination row `row`
+template <int MAP>
+__device__ inline uint32_t source_row(const GridMap& g, uint32_t B, uint32_t row, uint32_t ssp_G) {
+    const uint32_t s = (uint32_t)g.s, W = (uint32_t)g.W, n_sub = (uint32_t)g.n_sub;
+    if (MAP == TO_ORIGINAL) {
+        if (g.mode == MODE_DENSE) return row;
+        const uint32_t b = row / (uint32_t)g.n_tok;
+        return sparse_row_of(g.mode == MODE_GROUP, s, W, n_sub, B, b, row - b * (uint32_t)g.n_tok, ssp_G);
+    }
+    const uint32_t sb = row / n_sub, j = row - sb * n_sub;
+    const uint32_t pq = sb / B, b = sb - pq * B;
+    const uint32_t p = pq / s, tok = src_token(g, p, pq - p * s, j);
+    return MAP == SWITCH ? sparse_row_of(g.mode != MODE_GROUP, s, W, n_sub, B, b, tok, 0u) : b * (uint32_t)g.n_tok + tok;
+}
+
+template <int MAP, int UNROLL>
+__global__ __launch_bounds__(PERMUTE_WAVES * 64) void move_rows_kernel(const u32x4* __restrict__ src, u32x4* __restrict__ dst, int B, GridMap g,
+                                                                       uint32_t chunks_per_row, uint32_t n_rows, uint32_t ssp_G) {
     const uint32_t lane = threadIdx.x & 63u;
     const uint32_t row = blockIdx.x * PERMUTE_WAVES + (threadIdx.x >> 6);
     if (row >= n_rows) return;
-    uint32_t sparse_row, orig_row;
-    if (!BY_ORIG) {
-        // sparse row -> (sb, j) -> (p, q, b) -> row number in the original layout
-        const uint32_t n_sub = (uint32_t)g.n_sub;
-        const uint32_t sb = row / n_sub, j = row - sb * n_sub;
-        const uint32_t pq = sb / (uint32_t)B, b = sb - pq * (uint32_t)B;
-        const uint32_t p = pq / (uint32_t)g.s, q = pq - p * (uint32_t)g.s;
-        orig_row = b * (uint32_t)g.n_tok + src_token(g, p, q, j);
-        sparse_row = ssp_G ? ssp_received_sb(sb, (uint32_t)B, ssp_G) * n_sub + j : row;
-    } else {
-        // original row -> (b, t*H + h, w) -> class (p, q) and position (Alg. 1 read backwards; H and W are multiples of s for the
-        // token-wise pattern and of s*s for the group-wise one, so t*H + h splits like h)
-        orig_row = row;
-        sparse_row = row;
-        if (g.mode != MODE_DENSE) {
-            const uint32_t s = (uint32_t)g.s, W = (uint32_t)g.W;
-            const uint32_t b = row / (uint32_t)g.n_tok, n = row - b * (uint32_t)g.n_tok;
-            const uint32_t th = n / W, w = n - th * W;
-            uint32_t p, q, r, ws;
-            if (g.mode == MODE_GROUP) {
-                p = (th / s) % s;
-                q = (w / s) % s;
-                r = (th / (s * s)) * s + th % s;
-                ws = (w / (s * s)) * s + w % s;
-            } else {
-                p = th % s;
-                q = w % s;
-                r = th / s;
-                ws = w / s;
-            }
-            uint32_t sb = (p * s + q) * (uint32_t)B + b;
-            if (ssp_G) sb = ssp_received_sb(sb, (uint32_t)B, ssp_G);
-            sparse_row = sb * (uint32_t)g.n_sub + r * (W / s) + ws;
-        }
-    }
-    const u32x4* s = src + (size_t)(to_sparse ? orig_row : sparse_row) * chunks_per_row;
-    u32x4* d = dst + (size_t)(to_sparse ? sparse_row : orig_row) * chunks_per_row;
+    const u32x4* s = src + (size_t)source_row<MAP>(g, (uint32_t)B, row, ssp_G) * chunks_per_row;
+    u32x4* d = dst + (size_t)row * chunks_per_row;
     uint32_t c = lane;
     for (; c + (UNROLL - 1) * 64u < chunks_per_row; c += UNROLL * 64u) {
         u32x4 tmp[UNROLL];
@@ -80,91 +87,71 @@ __global__ __launch_bounds__(PERMUTE_WAVES * 64) void permute_rows_kernel(const 
     for (; c < chunks_per_row; c += 64u) __builtin_nontemporal_store(__builtin_nontemporal_load(s + c), d + c);
 }
 
-// Direct switch between the two sparse layouts (Algorithm 1, tsa_to_gsa / gsa_to_tsa): one row move per token instead of
-// an unpermute followed by a permute.  The destination row (sb', j') of pattern g_to holds token n; the source row is where
-// the other pattern keeps n.  Plain integer divisions: they run once per row of heads*head_dim elements.
-template <int UNROLL>
-__global__ __launch_bounds__(PERMUTE_WAVES * 64) void switch_rows_kernel(const u32x4* __restrict__ src, u32x4* __restrict__ dst, int B,
-                                                                         GridMap g_to, int from_group, uint32_t H, uint32_t chunks_per_row,
-                                                                         uint32_t n_rows) {
+constexpr uint32_t BATCH_CHUNKS = 1024;  // 16-byte chunks of a batch of short rows
+constexpr int BATCH_UNROLL = 5;
+
+template <int MAP>
+__global__ __launch_bounds__(PERMUTE_WAVES * 64) void move_short_rows_kernel(const u32x4* __restrict__ src, u32x4* __restrict__ dst, int B, GridMap g,
+                                                                             FastDiv chunks, uint32_t n_rows, uint32_t batch, uint32_t ssp_G) {
     const uint32_t lane = threadIdx.x & 63u;
-    const uint32_t row = blockIdx.x * PERMUTE_WAVES + (threadIdx.x >> 6);  // row number in the destination layout
-    if (row >= n_rows) return;
-    const uint32_t n_sub = (uint32_t)g_to.n_sub, s = (uint32_t)g_to.s, W = (uint32_t)g_to.W;
-    const uint32_t sb = row / n_sub, j = row - sb * n_sub;
-    const uint32_t pq = sb / (uint32_t)B, b = sb - pq * (uint32_t)B;
-    const uint32_t n = src_token(g_to, pq / s, pq % s, j);
-    // position of token n in the other pattern: class (p, q) and index r*Ws + ws inside it
-    const uint32_t th = n / W, w = n - th * W;  // th = t*H + h
-    uint32_t p, q, r, ws;
-    if (from_group) {
-        p = (th / s) % s;
-        q = (w / s) % s;
-        r = (th / (s * s)) * s + th % s;
-        ws = (w / (s * s)) * s + w % s;
-    } else {
-        p = th % s;
-        q = w % s;
-        r = th / s;
-        ws = w / s;
-    }
-    (void)H;
-    const uint32_t src_row = ((p * s + q) * (uint32_t)B + b) * n_sub + r * (W / s) + ws;
-    const u32x4* sp = src + (size_t)src_row * chunks_per_row;
-    u32x4* dp = dst + (size_t)row * chunks_per_row;
-    uint32_t c = lane;
-    for (; c + (UNROLL - 1) * 64u < chunks_per_row; c += UNROLL * 64u) {
-        u32x4 tmp[UNROLL];
+    const uint32_t row0 = (blockIdx.x * PERMUTE_WAVES + (threadIdx.x >> 6)) * batch;  // n_rows < 2^31: no overflow
+    if (row0 >= n_rows) return;
+    const uint32_t n = n_rows - row0 < batch ? n_rows - row0 : batch;  // at most 64
+    const uint32_t from = source_row<MAP>(g, (uint32_t)B, row0 + (lane < n ? lane : n - 1u), ssp_G);
+    u32x4* const d = dst + (size_t)row0 * chunks.d;
+    const uint32_t total = n * chunks.d;  // at most BATCH_CHUNKS: the division below is exact
+    for (uint32_t u0 = 0; u0 < total; u0 += BATCH_UNROLL * 64u) {  // wave-uniform: every lane takes part in the shuffles
+        u32x4 tmp[BATCH_UNROLL];
 #pragma unroll
-        for (int u = 0; u < UNROLL; u++) tmp[u] = __builtin_nontemporal_load(sp + c + u * 64u);
+        for (int k = 0; k < BATCH_UNROLL; k++) {
+            const uint32_t u = u0 + k * 64u + lane, uc = u < total ? u : total - 1u;  // lanes past the end repeat the last chunk and store nothing
+            const uint32_t i = chunks.div(uc), c = uc - i * chunks.d;
+            tmp[k] = __builtin_nontemporal_load(src + (size_t)(uint32_t)__shfl((int)from, (int)i) * chunks.d + c);
+        }
 #pragma unroll
-        for (int u = 0; u < UNROLL; u++) __builtin_nontemporal_store(tmp[u], dp + c + u * 64u);
+        for (int k = 0; k < BATCH_UNROLL; k++) {
+            const uint32_t u = u0 + k * 64u + lane;
+            if (u < total) __builtin_nontemporal_store(tmp[k], d + u);
+        }
     }
-    for (; c < chunks_per_row; c += 64u) __builtin_nontemporal_store(__builtin_nontemporal_load(sp + c), dp + c);
 }
 
-hipError_t launch_switch(const void* src, void* dst, int B, const GridMap& g_to, int from_group, int H, size_t row_bytes,
-                         hipStream_t stream) {
-    const uint32_t chunks = (uint32_t)(row_bytes / 16);
-    const uint32_t n_rows = (uint32_t)B * (uint32_t)(g_to.s * g_to.s) * (uint32_t)g_to.n_sub;
+template <int MAP, int UNROLL>
+static void launch_long(const void* src, void* dst, int B, const GridMap& g, uint32_t chunks, uint32_t n_rows, uint32_t ssp_G, hipStream_t stream) {
     const uint32_t blocks = (n_rows + PERMUTE_WAVES - 1) / PERMUTE_WAVES;
-    if (chunks >= 5 * 64)
-        switch_rows_kernel<5><<<blocks, PERMUTE_WAVES * 64, 0, stream>>>((const u32x4*)src, (u32x4*)dst, B, g_to, from_group, (uint32_t)H, chunks, n_rows);
-    else
-        switch_rows_kernel<1><<<blocks, PERMUTE_WAVES * 64, 0, stream>>>((const u32x4*)src, (u32x4*)dst, B, g_to, from_group, (uint32_t)H, chunks, n_rows);
+    move_rows_kernel<MAP, UNROLL><<<blocks, PERMUTE_WAVES * 64, 0, stream>>>((const u32x4*)src, (u32x4*)dst, B, g, chunks, n_rows, ssp_G);
+}
+
+template <int MAP>
+static hipError_t launch_rows(const void* src, void* dst, int B, const GridMap& g, size_t row_bytes, uint32_t ssp_G, hipStream_t stream) {
+    const uint32_t chunks = (uint32_t)(row_bytes / 16);
+    const uint32_t s2 = g.mode == MODE_DENSE ? 1u : (uint32_t)(g.s * g.s);
+    const uint32_t n_rows = (uint32_t)B * s2 * (uint32_t)g.n_sub;
+    // batches only where they leave 2048 wavefronts (two a SIMD); on fewer rows a wavefront each is as good or better (128 rows of 256 B:
+    // 6.9 us against 7.3)
+    uint32_t batch = chunks < 64u ? BATCH_CHUNKS / chunks : 1u;
+    batch = batch > 64u ? 64u : batch;
+    while (batch > 1u && n_rows / batch < 2048u) batch /= 2u;
+    if (batch > 1u) {
+        const uint32_t per_block = batch * PERMUTE_WAVES, blocks = (n_rows + per_block - 1) / per_block;
+        move_short_rows_kernel<MAP><<<blocks, PERMUTE_WAVES * 64, 0, stream>>>((const u32x4*)src, (u32x4*)dst, B, g, make_fastdiv32(chunks), n_rows, batch, ssp_G);
+    } else if (chunks >= 5 * 64) {
+        launch_long<MAP, 5>(src, dst, B, g, chunks, n_rows, ssp_G, stream);
+    } else if (chunks >= 3 * 64) {
+        launch_long<MAP, 3>(src, dst, B, g, chunks, n_rows, ssp_G, stream);
+    } else {
+        launch_long<MAP, 1>(src, dst, B, g, chunks, n_rows, ssp_G, stream);
+    }
     return hipGetLastError();
 }
 
-#ifndef SKIPARSE_UNPERMUTE_BY_ORIG
-#define SKIPARSE_UNPERMUTE_BY_ORIG 1
-#endif
-#ifndef SKIPARSE_PERMUTE_BY_ORIG
-#define SKIPARSE_PERMUTE_BY_ORIG 0
-#endif
-
-template <int UNROLL>
-static void launch_rows(const void* src, void* dst, int B, const GridMap& g, uint32_t chunks, uint32_t n_rows, int to_sparse,
-                        uint32_t ssp_G, hipStream_t stream) {
-    const uint32_t blocks = (n_rows + PERMUTE_WAVES - 1) / PERMUTE_WAVES;
-    const bool by_orig = to_sparse ? SKIPARSE_PERMUTE_BY_ORIG : SKIPARSE_UNPERMUTE_BY_ORIG;
-    if (by_orig)
-        permute_rows_kernel<UNROLL, true><<<blocks, PERMUTE_WAVES * 64, 0, stream>>>((const u32x4*)src, (u32x4*)dst, B, g, chunks, n_rows, to_sparse, ssp_G);
-    else
-        permute_rows_kernel<UNROLL, false><<<blocks, PERMUTE_WAVES * 64, 0, stream>>>((const u32x4*)src, (u32x4*)dst, B, g, chunks, n_rows, to_sparse, ssp_G);
+hipError_t launch_switch(const void* src, void* dst, int B, const GridMap& g_to, size_t row_bytes, hipStream_t stream) {
+    return launch_rows<SWITCH>(src, dst, B, g_to, row_bytes, 0u, stream);
 }
 
 hipError_t launch_permute(const void* src, void* dst, int B, const GridMap& g, size_t row_bytes, int to_sparse,
                           hipStream_t stream, int ssp_G) {
-    const uint32_t chunks = (uint32_t)(row_bytes / 16);
-    const uint32_t s2 = g.mode == MODE_DENSE ? 1u : (uint32_t)(g.s * g.s);
-    const uint32_t n_rows = (uint32_t)B * s2 * (uint32_t)g.n_sub;
-    if (chunks >= 5 * 64)
-        launch_rows<5>(src, dst, B, g, chunks, n_rows, to_sparse, (uint32_t)ssp_G, stream);
-    else if (chunks >= 3 * 64)
-        launch_rows<3>(src, dst, B, g, chunks, n_rows, to_sparse, (uint32_t)ssp_G, stream);
-    else
-        launch_rows<1>(src, dst, B, g, chunks, n_rows, to_sparse, (uint32_t)ssp_G, stream);
-    return hipGetLastError();
+    return to_sparse ? launch_rows<TO_SPARSE>(src, dst, B, g, row_bytes, 0u, stream) : launch_rows<TO_ORIGINAL>(src, dst, B, g, row_bytes, (uint32_t)ssp_G, stream);
 }
 
 }  // namespace skiparse

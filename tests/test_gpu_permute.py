@@ -111,3 +111,29 @@ def test_switch_pattern_768p_equals_two_step():
     gsa = sk.skiparse_permute(x, w.T, w.H, w.W, w.s, "group")
     assert torch.equal(sk.skiparse_switch_pattern(tsa, w.T, w.H, w.W, w.s, "token").view(torch.int16), gsa.view(torch.int16))
     assert torch.equal(sk.skiparse_switch_pattern(gsa, w.T, w.H, w.W, w.s, "group").view(torch.int16), tsa.view(torch.int16))
+
+
+# Rows below 1 KiB are moved in batches by one wavefront: rows of 1 to 63 chunks of 16 bytes, batches that do not divide the number of
+# rows, s = 1 (a copy), all three directions, canaries behind the destination.
+@pytest.mark.parametrize("row_bytes", [16, 48, 128, 336, 496, 1008])
+@pytest.mark.parametrize("B,T,H,W,s", [(1, 5, 36, 36, 2), (1, 7, 36, 36, 3), (3, 5, 32, 16, 4), (1, 41, 11, 13, 1), (1, 260, 16, 16, 2)])
+def test_short_rows_bit_exact(row_bytes, B, T, H, W, s):
+    import paper_2605_28691_amd as sk
+
+    x = _random_bits((B, T * H * W, 1, row_bytes), torch.uint8, seed=row_bytes + s)
+    xd = x.cuda()
+    pad = 4096
+    for pattern, other in (("token", "group"), ("group", "token")):
+        want = oracle.permute(x.numpy().reshape(B, T * H * W, row_bytes), T, H, W, s, pattern)
+        want_other = oracle.permute(x.numpy().reshape(B, T * H * W, row_bytes), T, H, W, s, other)
+        shape = (s * s * B, T * H * W // (s * s), 1, row_bytes)
+        bufs = [torch.full((x.numel() + pad,), 7, dtype=torch.uint8, device="cuda") for _ in range(3)]
+        y, z = (b[: x.numel()].view(shape) for b in bufs[:2])
+        back = bufs[2][: x.numel()].view(x.shape)
+        sk.skiparse_permute(xd, T, H, W, s, pattern, out=y)
+        sk.skiparse_switch_pattern(y, T, H, W, s, pattern, out=z)
+        sk.skiparse_unpermute(z, T, H, W, s, other, out=back)
+        assert np.array_equal(y.cpu().numpy().reshape(want.shape), want)
+        assert np.array_equal(z.cpu().numpy().reshape(want_other.shape), want_other)
+        assert torch.equal(back.cpu(), x)
+        assert all(bool((b[x.numel() :] == 7).all()) for b in bufs)
