@@ -676,7 +676,7 @@ static hipError_t launch_t(const AttnArgs& a, uint32_t n_units, uint32_t n_max, 
 // head_dim 128, units x tokens: 8x250 13.4 -> 8.2, 48x390 18.7 -> 13.7, 160x960 101 -> 88, 24x2600 134 -> 85, 48x2600 213 -> 165,
 // 4x5000 109 -> 66, 1x5000 107 -> 60; 48x960 (32) and 48x8190 (1390) keep shape 0.  At head_dim 64: 24x2600 88 -> 52, 160x4000 804 -> 708.
 constexpr ShapeCost FWD_COST_128[] = {{256, 1, 40.f, {9.0f}}, {128, 2, 20.f, {5.5f, 10.0f}}, {64, 1, 25.f, {3.9f}}, {128, 1, 45.f, {4.7f}}};
-constexpr ShapeCost FWD_COST_64[] = {{256, 1, 30.f, {5.2f}}, {128, 3, 15.f, {3.6f, 5.7f, 8.0f}}, {64, 2, 15.f, {2.4f, 3.7f}}, {128, 1, 30.f, {2.9f}}};
+constexpr ShapeCost FWD_COST_64[] = {{256, 1, 30.f, {5.2f}}, {128, 3, 15.f, {3.6f, 5.7f, 7.6f}}, {64, 2, 15.f, {2.4f, 3.7f}}, {128, 1, 30.f, {2.9f}}};
 
 template <int D, bool PAD>
 static hipError_t launch_shape(const AttnArgs& a, hipStream_t stream) {
