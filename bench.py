@@ -326,7 +326,7 @@ def main() -> int:
         extras["chain_token_to_group_tflops"] = round(flops / c_ms / 1e9, 2)
         del qs, ks, vs, os_
     if "bwd" in sections:
-        # training step of the layer: forward that keeps the log-sum-exp, then dQ, dK, dV (delta + two launches)
+        # training step of the layer: forward that keeps the log-sum-exp, then dQ (with delta) and dK, dV (two launches)
         dout = si.make_dout(w).cuda()
         lse = torch.empty((s * s * w.B, w.heads, w.Nsub), dtype=torch.float32, device="cuda")
         grads = [torch.empty_like(qd) for _ in range(3)]

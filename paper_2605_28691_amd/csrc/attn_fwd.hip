@@ -5,7 +5,7 @@
 // without ever forming the N x N matrix: keys are walked in blocks of 32 with a running row maximum and row sum.
 //
 // Mapping onto the hardware
-//   * One workgroup = NW wavefronts in KG key groups; a wavefront owns 32 query rows, the wavefronts of a group walk the same keys
+//   * One workgroup = 4 or 8 wavefronts in one or two key groups; a wavefront owns 32 query rows, the wavefronts of a group walk the same keys
 //     and share every K/V tile that is brought into LDS.  The shape for large problems is 8 wavefronts in one group: 256 queries
 //     a tile halve the L2 -> LDS traffic per MFMA compared with 128 (two wavefronts per SIMD, <= 256 VGPRs per lane, 64 KiB LDS).
 //     Small problems are bound by idle CUs and by the serial walk over the keys instead; they get smaller workgroups, and two
@@ -123,11 +123,22 @@ __device__ inline size_t scattered_row(const AttnArgs& a, uint32_t sb, uint32_t 
     return ((size_t)(p * s + q) * B + b) * (uint32_t)gi.n_sub + r * (W / s) + ws;
 }
 
+// Workgroup shapes: NW wavefronts in KG key groups take 32 * NW / KG queries.
+enum FwdShape : int {
+    Q256 = 1,        // 8 wavefronts, 1 group: 256 queries share every tile; the least L2 -> LDS traffic per MFMA, the best once the chip is full
+    Q128 = 2,        // 4 wavefronts, 1 group: two (head_dim 64: three) workgroups per CU; twice as many, finer-grained workgroups
+    Q64_SPLIT = 3,   // 4 wavefronts, 2 groups: four times the workgroups, half the serial chain
+    Q128_SPLIT = 4,  // 8 wavefronts, 2 groups: half the chain at two wavefronts per SIMD
+};
+constexpr int fwd_waves(int shape) { return shape == Q256 || shape == Q128_SPLIT ? 8 : 4; }
+constexpr int fwd_groups(int shape) { return shape >= Q64_SPLIT ? 2 : 1; }
+
 // PAD selects the any-resolution mode (Sec. 3.2), where the subsequences are those of the grid padded to multiples of s*s with the
 // padding masked: the kernel walks the real tokens of the class only (ClassMap), so that a masked key is one that is never met.  Only
 // the log-sum-exp is laid out over the padded grid (zero at the padding).
-template <int D, int NW, int KG, bool PAD>
-__global__ __launch_bounds__(64 * NW, (NW == 4 && KG == 1 ? 2 : 1)) void attn_fwd_bf16_kernel(AttnArgs a, uint32_t q_tiles, uint32_t total, uint32_t per_xcd) {
+template <int D, int SHAPE, bool PAD>
+__global__ __launch_bounds__(64 * fwd_waves(SHAPE), (SHAPE == Q128 ? 2 : 1)) void attn_fwd_bf16_kernel(AttnArgs a, uint32_t q_tiles, uint32_t total, uint32_t per_xcd) {
+    constexpr int NW = fwd_waves(SHAPE), KG = fwd_groups(SHAPE);
     constexpr int QT = ATTN_QT;
     constexpr int QW = NW / KG;    // wavefronts of a key group: each owns 32 queries, all walk the same keys
     static_assert((QW & (QW - 1)) == 0 && QW * KG == NW, "key groups are of equal size");
@@ -656,25 +667,22 @@ __global__ __launch_bounds__(64 * NW, (NW == 4 && KG == 1 ? 2 : 1)) void attn_fw
     }
 }
 
-template <int D, int NW, int KG, bool PAD>
+template <int D, int SHAPE, bool PAD>
 static hipError_t launch_t(const AttnArgs& a, uint32_t n_units, uint32_t n_max, hipStream_t stream) {
-    constexpr uint32_t BR = 32u * (NW / KG) * ATTN_QT;
+    constexpr int NW = fwd_waves(SHAPE);
+    constexpr uint32_t BR = 32u * (NW / fwd_groups(SHAPE)) * ATTN_QT;
     const uint32_t q_tiles = (n_max + BR - 1u) / BR;
     const uint64_t total = (uint64_t)n_units * q_tiles;
     if (total > 0x7ffffff0ull) return hipErrorInvalidConfiguration;
     const uint32_t per_xcd = (uint32_t)((total + 7u) / 8u);
-    attn_fwd_bf16_kernel<D, NW, KG, PAD><<<8u * per_xcd, 64 * NW, 0, stream>>>(a, q_tiles, (uint32_t)total, per_xcd);
+    attn_fwd_bf16_kernel<D, SHAPE, PAD><<<8u * per_xcd, 64 * NW, 0, stream>>>(a, q_tiles, (uint32_t)total, per_xcd);
     return hipGetLastError();
 }
 
-// Workgroup shapes: NW wavefronts in KG key groups take 32 * NW / KG queries.
-//   0  8 wavefronts, 1 group:  256 queries share every tile; the least L2 -> LDS traffic per MFMA, the best once the chip is full
-//   1  4 wavefronts, 1 group:  128 queries, two (head_dim 64: three) workgroups per CU; twice as many, finer-grained workgroups
-//   2  4 wavefronts, 2 groups:  64 queries, each group walks half of the keys: four times the workgroups, half the serial chain
-//   3  8 wavefronts, 2 groups: 128 queries, half the chain at two wavefronts per SIMD
-// The costs were fitted to launches of every shape over 1..160 units of 32..8190 tokens.  Measured, always shape 0 -> picked, us at
+// Costs of the shapes, in the order of FwdShape.
+// The costs were fitted to launches of every shape over 1..160 units of 32..8190 tokens.  Measured, always Q256 -> picked, us at
 // head_dim 128, units x tokens: 8x250 13.4 -> 8.2, 48x390 18.7 -> 13.7, 160x960 101 -> 88, 24x2600 134 -> 85, 48x2600 213 -> 165,
-// 4x5000 109 -> 66, 1x5000 107 -> 60; 48x960 (32) and 48x8190 (1390) keep shape 0.  At head_dim 64: 24x2600 88 -> 52, 160x4000 804 -> 708.
+// 4x5000 109 -> 66, 1x5000 107 -> 60; 48x960 (32) and 48x8190 (1390) keep Q256.  At head_dim 64: 24x2600 88 -> 52, 160x4000 804 -> 708.
 constexpr ShapeCost FWD_COST_128[] = {{256, 1, 40.f, {9.0f}}, {128, 2, 20.f, {5.5f, 10.0f}}, {64, 1, 25.f, {3.9f}}, {128, 1, 45.f, {4.7f}}};
 constexpr ShapeCost FWD_COST_64[] = {{256, 1, 30.f, {5.2f}}, {128, 3, 15.f, {3.6f, 5.7f, 7.6f}}, {64, 2, 15.f, {2.4f, 3.7f}}, {128, 1, 30.f, {2.9f}}};
 
@@ -687,10 +695,10 @@ static hipError_t launch_shape(const AttnArgs& a, hipStream_t stream) {
     const uint32_t n_max = PAD ? make_class_map(a.g, 0, 0).n : (uint32_t)a.g.n_sub;
     const uint32_t n_min = PAD ? make_class_map(a.g, last, last).n : n_max;
     switch (pick_shape(D == 128 ? FWD_COST_128 : FWD_COST_64, n_units, n_max, 2, n_min > (uint32_t)KT)) {  // a key group needs a tile of its own
-        case 1: return launch_t<D, 4, 1, PAD>(a, n_units, n_max, stream);
-        case 2: return launch_t<D, 4, 2, PAD>(a, n_units, n_max, stream);
-        case 3: return launch_t<D, 8, 2, PAD>(a, n_units, n_max, stream);
-        default: return launch_t<D, 8, 1, PAD>(a, n_units, n_max, stream);
+        case 1: return launch_t<D, Q128, PAD>(a, n_units, n_max, stream);
+        case 2: return launch_t<D, Q64_SPLIT, PAD>(a, n_units, n_max, stream);
+        case 3: return launch_t<D, Q128_SPLIT, PAD>(a, n_units, n_max, stream);
+        default: return launch_t<D, Q256, PAD>(a, n_units, n_max, stream);
     }
 }
 

@@ -69,7 +69,7 @@ __device__ inline uint32_t source_row(const GridMap& g, uint32_t B, uint32_t row
 }
 
 template <int MAP, int UNROLL>
-__global__ __launch_bounds__(PERMUTE_WAVES * 64) void move_rows_kernel(const u32x4* __restrict__ src, u32x4* __restrict__ dst, int B, GridMap g,
+__global__ __launch_bounds__(PERMUTE_WAVES * 64) void permute_rows_kernel(const u32x4* __restrict__ src, u32x4* __restrict__ dst, int B, GridMap g,
                                                                        uint32_t chunks_per_row, uint32_t n_rows, uint32_t ssp_G) {
     const uint32_t lane = threadIdx.x & 63u;
     const uint32_t row = blockIdx.x * PERMUTE_WAVES + (threadIdx.x >> 6);
@@ -91,7 +91,7 @@ constexpr uint32_t BATCH_CHUNKS = 1024;  // 16-byte chunks of a batch of short r
 constexpr int BATCH_UNROLL = 5;
 
 template <int MAP>
-__global__ __launch_bounds__(PERMUTE_WAVES * 64) void move_short_rows_kernel(const u32x4* __restrict__ src, u32x4* __restrict__ dst, int B, GridMap g,
+__global__ __launch_bounds__(PERMUTE_WAVES * 64) void permute_short_rows_kernel(const u32x4* __restrict__ src, u32x4* __restrict__ dst, int B, GridMap g,
                                                                              FastDiv chunks, uint32_t n_rows, uint32_t batch, uint32_t ssp_G) {
     const uint32_t lane = threadIdx.x & 63u;
     const uint32_t row0 = (blockIdx.x * PERMUTE_WAVES + (threadIdx.x >> 6)) * batch;  // n_rows < 2^31: no overflow
@@ -119,7 +119,7 @@ __global__ __launch_bounds__(PERMUTE_WAVES * 64) void move_short_rows_kernel(con
 template <int MAP, int UNROLL>
 static void launch_long(const void* src, void* dst, int B, const GridMap& g, uint32_t chunks, uint32_t n_rows, uint32_t ssp_G, hipStream_t stream) {
     const uint32_t blocks = (n_rows + PERMUTE_WAVES - 1) / PERMUTE_WAVES;
-    move_rows_kernel<MAP, UNROLL><<<blocks, PERMUTE_WAVES * 64, 0, stream>>>((const u32x4*)src, (u32x4*)dst, B, g, chunks, n_rows, ssp_G);
+    permute_rows_kernel<MAP, UNROLL><<<blocks, PERMUTE_WAVES * 64, 0, stream>>>((const u32x4*)src, (u32x4*)dst, B, g, chunks, n_rows, ssp_G);
 }
 
 template <int MAP>
@@ -134,7 +134,7 @@ static hipError_t launch_rows(const void* src, void* dst, int B, const GridMap& 
     while (batch > 1u && n_rows / batch < 2048u) batch /= 2u;
     if (batch > 1u) {
         const uint32_t per_block = batch * PERMUTE_WAVES, blocks = (n_rows + per_block - 1) / per_block;
-        move_short_rows_kernel<MAP><<<blocks, PERMUTE_WAVES * 64, 0, stream>>>((const u32x4*)src, (u32x4*)dst, B, g, make_fastdiv32(chunks), n_rows, batch, ssp_G);
+        permute_short_rows_kernel<MAP><<<blocks, PERMUTE_WAVES * 64, 0, stream>>>((const u32x4*)src, (u32x4*)dst, B, g, make_fastdiv32(chunks), n_rows, batch, ssp_G);
     } else if (chunks >= 5 * 64) {
         launch_long<MAP, 5>(src, dst, B, g, chunks, n_rows, ssp_G, stream);
     } else if (chunks >= 3 * 64) {
