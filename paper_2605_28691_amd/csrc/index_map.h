@@ -43,6 +43,24 @@ inline FastDiv make_fastdiv(uint32_t d) {
     return f;
 }
 
+// make_fastdiv in 32-bit arithmetic: the same multiplier except at powers of two, where 2^32 / d is exact (e = 0)
+__host__ __device__ inline FastDiv make_fastdiv32(uint32_t d) {
+    FastDiv f;
+    f.d = d;
+    f.mul = d <= 1u ? 0u : 0xffffffffu / d + 1u;
+    f.one = d <= 1u ? 1u : 0u;
+    return f;
+}
+
+// Real rows (or columns) of every class along one axis in the any-resolution mode: `below` for classes under `at`, `mid` for class
+// `at`, `above` for the others.  Three values serve every class: in the token-wise pattern the first n % s classes have one row more than
+// the others; in the group-wise one the last, incomplete run of s*s rows gives s rows to some classes, the rest to one, none to others.
+struct ClassAxis {
+    uint32_t at;
+    FastDiv below, mid, above;
+    __host__ __device__ inline FastDiv of(uint32_t p) const { return p < at ? below : p == at ? mid : above; }
+};
+
 struct GridMap {
     int mode;      // MODE_DENSE: position j is token j
     int s;         // sparse ratio
@@ -59,6 +77,8 @@ struct GridMap {
     // H_real rows of every H_pad are real, and columns below W (the real row length above) are real.
     int H_real;
     FastDiv hpad;  // division by the padded H
+    FastDiv hs;    // division by the padded H / s, the rows of a class on the padded grid
+    ClassAxis hc, wc;  // real rows and columns of the classes
 };
 
 __host__ __device__ inline uint32_t src_token(const GridMap& g, uint32_t p, uint32_t q, uint32_t j) {
@@ -92,29 +112,13 @@ struct ClassMap {
     FastDiv h;   // division by the real rows of the class
 };
 
-// make_fastdiv in 32-bit arithmetic: the same multiplier except at powers of two, where 2^32 / d is exact (e = 0)
-__host__ __device__ inline FastDiv make_fastdiv32(uint32_t d) {
-    FastDiv f;
-    f.d = d;
-    f.mul = d <= 1u ? 0u : 0xffffffffu / d + 1u;
-    f.one = d <= 1u ? 1u : 0u;
-    return f;
-}
-
-// number of hs (or ws) of class p (or q) that lie inside the n real rows (or columns)
-__host__ __device__ inline uint32_t class_extent(const GridMap& g, uint32_t n, uint32_t p) {
-    const uint32_t s = (uint32_t)g.s;
-    if (g.b == 0) return n > p ? (n - p + s - 1u) / s : 0u;  // token-wise: hs*s + p < n
-    const uint32_t full = n / (s * s), rest = n - full * s * s, first = p * s;  // group-wise: runs of s rows, one every s*s
-    return full * s + (rest > first ? (rest - first < s ? rest - first : s) : 0u);
-}
-
+// Selected from values that the host forms: extents and multipliers formed in the kernel put six integer divisions in a row in front of
+// every workgroup's first load (32 units of 10 tokens at head_dim 64, us a launch: 4.30 -> 4.20, in workgroups of 256 queries 4.91 -> 4.55).
 __host__ __device__ inline ClassMap make_class_map(const GridMap& g, uint32_t p, uint32_t q) {
-    const uint32_t hr = class_extent(g, (uint32_t)g.H_real, p), wr = class_extent(g, (uint32_t)g.W, q);
     ClassMap c;
-    c.n = (uint32_t)g.T * hr * wr;
-    c.w = make_fastdiv32(wr);
-    c.h = make_fastdiv32(hr);
+    c.w = g.wc.of(q);
+    c.h = g.hc.of(p);
+    c.n = (uint32_t)g.T * c.h.d * c.w.d;
     return c;
 }
 
@@ -129,13 +133,13 @@ __host__ __device__ inline uint32_t src_token_real(const GridMap& g, const Class
 __host__ __device__ inline uint32_t padded_position(const GridMap& g, const ClassMap& c, uint32_t j) {
     const uint32_t r = c.w.div(j), ws = j - r * c.w.d;
     const uint32_t t = c.h.div(r), hs = r - t * c.h.d;
-    return (t * g.sdiv.div(g.hpad.d) + hs) * g.ws.d + ws;
+    return (t * g.hs.d + hs) * g.ws.d + ws;
 }
 
 // Host side: the map of a grid.  `group` selects the group-wise pattern; `pad` the any-resolution mode, in which the
 // subsequences are those of the grid padded at the end of H and W to the next multiples of s*s.
 inline GridMap make_dense_gridmap(size_t n) {
-    GridMap g;
+    GridMap g = {};
     g.mode = MODE_DENSE;
     g.s = 1;
     g.W = 0;
@@ -152,12 +156,23 @@ inline GridMap make_dense_gridmap(size_t n) {
     return g;
 }
 
+inline ClassAxis make_class_axis(uint32_t n, uint32_t s, bool group) {
+    const uint32_t run = group ? s : 1u;  // rows of a class that lie next to each other
+    const uint32_t full = n / (s * run), rest = n - full * s * run;  // whole rounds over the classes; rows of the incomplete one
+    ClassAxis a;
+    a.at = rest / run;
+    a.below = make_fastdiv((full + 1u) * run);
+    a.mid = make_fastdiv(full * run + rest % run);
+    a.above = make_fastdiv(full * run);
+    return a;
+}
+
 inline GridMap make_gridmap(int T, int H, int W, int s, bool group, bool pad = false) {
     const int n_tok = T * H * W;
     if (s == 1) return make_dense_gridmap((size_t)n_tok);
     const int Hp = pad ? (H + s * s - 1) / (s * s) * (s * s) : H;
     const int Wp = pad ? (W + s * s - 1) / (s * s) * (s * s) : W;
-    GridMap g;
+    GridMap g = {};
     g.mode = group ? MODE_GROUP : MODE_TOKEN;
     g.s = s;
     g.W = W;
@@ -171,6 +186,9 @@ inline GridMap make_gridmap(int T, int H, int W, int s, bool group, bool pad = f
     g.sdiv = make_fastdiv((uint32_t)s);
     g.H_real = H;
     g.hpad = make_fastdiv((uint32_t)Hp);
+    g.hs = make_fastdiv((uint32_t)(Hp / s));
+    g.hc = make_class_axis((uint32_t)H, (uint32_t)s, group);
+    g.wc = make_class_axis((uint32_t)W, (uint32_t)s, group);
     return g;
 }
 

@@ -83,6 +83,14 @@ int main() {
                         k++;
                         checked++;
                     }
+                    // rows and columns of the class as the host hands them to the kernels
+                    uint32_t rows = 0, cols = 0;
+                    for (int h = 0; h < H; h++) rows += (group ? h / s : h) % s == p;
+                    for (int w = 0; w < W; w++) cols += (group ? w / s : w) % s == q;
+                    if (g.hc.of((uint32_t)p).d != rows || g.wc.of((uint32_t)q).d != cols || g.hs.d != (uint32_t)Hs) {
+                        printf("class extents T%d H%d W%d s%d group%d p%d q%d\n", T, H, W, s, group, p, q);
+                        return 1;
+                    }
                     if (k != c.n || c.n > make_class_map(g, 0, 0).n || c.n < make_class_map(g, (uint32_t)s - 1, (uint32_t)s - 1).n) {
                         printf("dense map: class %d %d has %u real tokens, the map says %u\n", p, q, k, c.n);
                         return 1;
