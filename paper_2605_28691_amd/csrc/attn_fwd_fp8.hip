@@ -88,9 +88,11 @@ __global__ __launch_bounds__(NT8) void attn_fwd_fp8_kernel(Fp8AttnArgs a, uint32
     // one wavefront (they take turns) marks the keys of a tile: lane = key.  The padding sits at the end of H and W, so the real rows
     // and columns of a class are a prefix: two divisions a key instead of the whole index map, on the path of every tile.
     const uint32_t h_real = PAD ? a.g.hc.of(p_).d : 0u, w_real = PAD ? a.g.wc.of(q_).d : 0u;
+    FastDiv hs_div = a.g.hs;  // rows of a class on the padded grid
+    hs_div.one = hs_div.d <= 1u ? 1u : 0u;  // two vector registers less than with the argument
     auto mark_keys = [&](uint32_t t) __attribute__((always_inline)) {
         const uint32_t j = t * KT8 + lane;
-        const uint32_t r = a.g.ws.div(j), ws = j - r * a.g.ws.d, hs = r - a.g.hs.div(r) * a.g.hs.d;
+        const uint32_t r = a.g.ws.div(j), ws = j - r * a.g.ws.d, hs = r - hs_div.div(r) * hs_div.d;
         const bool real = j < n_seq && ws < w_real && hs < h_real;
         kbias[t & 1u][lane] = real ? 0.f : -INFINITY;
         const unsigned long long pads = __builtin_amdgcn_ballot_w64(!real);
