@@ -145,6 +145,11 @@ __global__ __launch_bounds__(64 * fwd_waves(SHAPE), (SHAPE == Q128 ? 2 : 1)) voi
     using TL = Tile<D, QW>;
     constexpr int KS = D / 16;     // MFMA steps along head_dim for S^T = K Q^T
     constexpr int MT = D / 32;     // 32-row blocks of O^T
+    // Small calls: offsets are formed for the tiles that exist only (those past the group's last tile are read but address nothing), and
+    // keys are compared with the end only in the block that holds it: 1 to 6 % of a small launch (us, 103 units of 377 tokens at
+    // head_dim 64 12.3 -> 11.8, 144 of 160..176 in the any-resolution mode at head_dim 128 12.65 -> 12.3).  The kernel that the largest
+    // problems use is left without: it takes three registers more and 0.3 % more time there (110.8 -> 111.1 ms).
+    constexpr bool TRIM = PAD || D == 64 || SHAPE != Q256;
     constexpr int BR = 32 * QW * QT;   // query rows per workgroup: QT tiles of 32 per wavefront
     // four separate arrays: the compiler must be able to tell that the tile being filled is not the tile being read
     __shared__ __attribute__((aligned(1024))) char kbuf0_all[KG * TL::TILE_BYTES];
@@ -373,7 +378,7 @@ __global__ __launch_bounds__(64 * fwd_waves(SHAPE), (SHAPE == Q128 ? 2 : 1)) voi
 #pragma unroll
         for (int qi = 0; qi < QT; qi++) {
             f32x16& s = sreg[PAR][qi];
-            if (decltype(MASK)::value) {
+            if (decltype(MASK)::value && (!TRIM || tile0 * KT + blk * 32u + 32u > n_seq)) {  // wave-uniform: the block holds keys past the end
 #pragma unroll
                 for (int r = 0; r < 16; r++) {
                     const uint32_t key = tile0 * KT + blk * 32u + 8 * (r >> 2) + 4 * h + (r & 3);
@@ -520,7 +525,7 @@ __global__ __launch_bounds__(64 * fwd_waves(SHAPE), (SHAPE == Q128 ? 2 : 1)) voi
     // a window to land and are waited for just before the window's closing barrier.  The row offsets of tile W+2 are picked up
     // from the ring in window W (so that the LDS read is not waited for), and tile W+RING_AHEAD's are formed by wavefront W % QW of the group.
     // ---- prologue: offsets of tiles 0..RING_AHEAD, K tile 0
-    for (uint32_t t = qw; t <= (uint32_t)RING_AHEAD; t += QW) produce(t);
+    for (uint32_t t = qw; t <= (uint32_t)RING_AHEAD && (!TRIM || t < n_tiles); t += QW) produce(t);
     __syncthreads();
     RowOffs off_v = read_offs(0);  // offsets of the tile whose V is fetched next
     issue_k(kbuf0, off_v);
