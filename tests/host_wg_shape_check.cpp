@@ -1,0 +1,20 @@
+// Evaluates the rule that picks an attention launch's workgroup shape (paper_2605_28691_amd/csrc/wg_shape.h) on the host.  Reads calls from
+// stdin, one a line: launch (fwd, dq or dkv), head_dim, B, heads, T, H, W, s, group, pad; prints the number of the shape of each.  Built and
+// run by tests/test_wg_shape.py.
+#include <cstdio>
+#include <cstring>
+
+#include "../paper_2605_28691_amd/csrc/kernels.h"
+
+using namespace skiparse;
+
+int main() {
+    char launch[8];
+    int D, B, heads, T, H, W, s, group, pad;
+    while (scanf("%7s %d %d %d %d %d %d %d %d %d", launch, &D, &B, &heads, &T, &H, &W, &s, &group, &pad) == 10) {
+        const GridMap g = make_gridmap(T, H, W, s, group != 0, pad != 0);
+        const UnitSizes u = unit_sizes(g, pad != 0 && s > 1, (uint64_t)B * (uint64_t)heads);
+        printf("%d\n", strcmp(launch, "fwd") == 0 ? pick_fwd_shape(D, u) : pick_bwd_shape(strcmp(launch, "dkv") == 0, D, u));
+    }
+    return 0;
+}

@@ -1,0 +1,54 @@
+"""The rule that picks a launch's workgroup shape, evaluated on the host: what it picks for calls that every shape was measured on."""
+import os
+import subprocess
+
+import pytest
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+Q256, Q128, Q64_SPLIT, Q128_SPLIT = 1, 2, 3, 4  # FwdShape
+O256, O128, O64_SPLIT = 1, 2, 3                 # BwdShape
+
+
+@pytest.fixture(scope="module")
+def pick(tmp_path_factory):
+    """pick([(launch, D, B, heads, T, H, W, s, group, pad), ...]) -> shapes"""
+    exe = str(tmp_path_factory.mktemp("wg_shape") / "host_wg_shape_check")
+    src = os.path.join(ROOT, "tests", "host_wg_shape_check.cpp")
+    subprocess.check_call(["/opt/rocm/bin/hipcc", "-x", "hip", "--offload-arch=gfx950", "-O1", "-std=c++17",
+                           "-Wno-unused-command-line-argument", "-o", exe, src])
+
+    def run(calls):
+        text = "\n".join(" ".join(str(int(x)) if not isinstance(x, str) else x for x in c) for c in calls) + "\n"
+        out = subprocess.run([exe], input=text, stdout=subprocess.PIPE, text=True, check=True).stdout.split()
+        assert len(out) == len(calls)
+        return [int(x) for x in out]
+
+    return run
+
+
+def dense(launch, D, units, n):
+    return (launch, D, 1, units, 1, 1, n, 1, 0, 0)
+
+
+def test_two_key_groups_only_while_the_large_shape_leaves_the_chip_idle(pick):
+    """Splitting the keys pays while the 256-query shape has less than two rounds of workgroups; with more it lost 1 to 7 %."""
+    few = [(1, 8190), (2, 12000), (1, 20160), (4, 20160), (1, 32760), (8, 384), (24, 384)]
+    assert all(x in (Q64_SPLIT, Q128_SPLIT) for x in pick([dense("fwd", 128, *c) for c in few]))
+    many = [(20, 20160), (14, 30240), (10, 40320), (5, 80640), (63, 11340), (20, 8190), (40, 20160), (160, 20160)]
+    assert all(x in (Q256, Q128) for x in pick([dense("fwd", D, *c) for c in many for D in (64, 128)]))
+    # at six rounds and more Q256 is the best of the two at head_dim 128
+    assert pick([dense("fwd", 128, *c) for c in many[:5] + many[6:]]) == [Q256] * 7
+
+
+def test_one_round_of_the_large_shape_keeps_it_against_two_small_workgroups_a_cu(pick):
+    """Measured 1 to 10 % faster in one round of 256-query workgroups than in twice as many of 128 queries, two on most CUs."""
+    assert pick([dense("fwd", 128, *c) for c in ((192, 240), (84, 512), (225, 216), (96, 384), (148, 256), (48, 960))]) == [Q256] * 6
+    assert pick([dense("fwd", 64, 103, 377), dense("fwd", 64, 108, 384), ("fwd", 64, 3, 30, 1, 32, 21, 2, 1, 1)])[0] == Q256
+    # where the small workgroups are alone on their CUs, or the large ones would need a second round, they stay
+    assert pick([dense("fwd", 128, *c) for c in ((48, 390), (112, 144), (24, 2600), (48, 2600), (432, 64))]) == [Q128] * 5
+
+
+def test_classes_without_a_token_are_no_workgroups(pick):
+    """Any-resolution grid on which only 2 of 16 classes hold a token: 2 x 64 units, not 16 x 64, decide (4-wavefront workgroups win)."""
+    call = ("fwd", 64, 1, 64, 30, 2, 7, 4, 1, 1)
+    assert pick([call]) == pick([dense("fwd", 64, 128, 30 * 2 * 4)])
