@@ -17,7 +17,7 @@
 // 5 of the definition); their two accumulators take 128 registers at head_dim 128, so the owner's V rows are kept in LDS where two
 // wavefronts share a SIMD.
 //   * Small problems get smaller workgroups, and two groups of wavefronts that walk half of the streamed rows each and add their
-//     accumulators through LDS at the end (in a fixed order, so the result stays deterministic): see the table at the launch.
+//     accumulators through LDS at the end (in a fixed order, so the result stays deterministic): see wg_shape.h.
 //   * log-sum-exp and delta are per QUERY: per-lane constants in the dQ launch; in the dK+dV launch per-streamed-row values,
 //     staged in LDS next to the tile as -L/scale and -delta and used as the INITIAL accumulators of M1 and M2, so that
 //     P = exp2(M1 * c) and dS = P o M2 need no further arithmetic (-inf / 0 for rows that must contribute nothing).
@@ -29,7 +29,6 @@
 
 #include "kernels.h"
 #include "lds_layout.h"
-#include "wg_shape.h"
 
 namespace skiparse {
 
@@ -43,6 +42,7 @@ typedef __attribute__((ext_vector_type(16))) float f32x16;
 #define LDS_PTR(T) __attribute__((address_space(3))) T*
 
 constexpr int BT = 64;             // streamed rows per tile
+static_assert(GROUP_MIN_ROWS == BT, "a group needs a tile of its own");
 constexpr float LOG2E = 1.4426950408889634f;
 constexpr int BRING_AHEAD = 8;   // row offsets are formed this many tiles ahead, by one wavefront per tile in turn
 constexpr int BRING = 16;          // tiles of row offsets kept in LDS
@@ -51,7 +51,7 @@ static_assert((BRING & (BRING - 1)) == 0 && BRING >= BRING_AHEAD + 4, "ring size
 // PAD: any-resolution mode (Sec. 3.2): the kernel walks the real tokens of the class only (ClassMap), so that a padding position is
 // never met; log-sum-exp and delta are laid out over the padded grid.
 template <int D, int MODE, int NW, int KG, bool PAD>
-__global__ __launch_bounds__(64 * NW, (NW == 4 && KG == 1 && (MODE == BWD_DQ || D == 64) ? 2 : 1)) void attn_bwd_kernel(BwdArgs a, uint32_t o_tiles, uint32_t total, uint32_t per_xcd) {
+__global__ __launch_bounds__(64 * NW, (NW == 4 && KG == 1 && (MODE == BWD_DQ || D == 64) ? 2 : 1)) void attn_bwd_kernel(BwdArgs a, PadArg<PAD> pad_map, uint32_t o_tiles, uint32_t total, uint32_t per_xcd) {
     constexpr int KS = D / 16;   // MFMA steps along head_dim
     constexpr int MT = D / 32;   // 32-channel blocks of the gradient row
     constexpr int CH = D / 8;    // 16-byte chunks per row
@@ -108,8 +108,7 @@ __global__ __launch_bounds__(64 * NW, (NW == 4 && KG == 1 && (MODE == BWD_DQ || 
         p = pq / (uint32_t)a.g.s;
         q = pq - p * (uint32_t)a.g.s;
     }
-    ClassMap cm = {};
-    if (PAD) cm = make_class_map(a.g, p, q);
+    const ClassMap cm = make_class_map(a.g, pad_map, p, q);
     const uint32_t n_seq = PAD ? __builtin_amdgcn_readfirstlane(cm.n) : (uint32_t)a.g.n_sub;
     if (PAD && ot * (uint32_t)WGO >= n_seq) return;  // the grid is sized for the largest class
     const size_t C = (size_t)a.heads * D;
@@ -477,32 +476,21 @@ static hipError_t launch_t(const BwdArgs& a, uint32_t n_units, uint32_t n_max, h
     const uint64_t total = (uint64_t)n_units * o_tiles;
     if (total > 0x7ffffff0ull) return hipErrorInvalidConfiguration;
     const uint32_t per_xcd = (uint32_t)((total + 7u) / 8u);
-    attn_bwd_kernel<D, MODE, NW, KG, PAD><<<8u * per_xcd, 64 * NW, 0, stream>>>(a, o_tiles, (uint32_t)total, per_xcd);
+    PadArg<PAD> pad_map;
+    make_pad_arg(a.g, pad_map);
+    attn_bwd_kernel<D, MODE, NW, KG, PAD><<<8u * per_xcd, 64 * NW, 0, stream>>>(a, pad_map, o_tiles, (uint32_t)total, per_xcd);
     return hipGetLastError();
 }
-
-// Workgroup shapes, as in the forward: 8 wavefronts (256 owners), 4 wavefronts (128), 4 wavefronts in two groups (64 owners, half the
-// chain each).  At head_dim 128 the dK+dV shapes with 4 wavefronts hold V in registers (one workgroup per CU).  Measured, always the
-// first shape -> picked, dQ and dK+dV together, us at head_dim 128, units x tokens: 16x200 39.8 -> 23, 12x700 78 -> 42, 48x390 62 -> 43,
-// 160x960 347 -> 328, 24x2600 495 -> 328, 1x5000 411 -> 190; 48x960 (108) and 48x8190 (5190) keep it.
-constexpr ShapeCost DQ_COST_128[] = {{256, 1, 50.f, {13.0f}}, {128, 2, 40.f, {9.5f, 13.4f}}, {64, 1, 40.f, {6.3f}}};
-constexpr ShapeCost DQ_COST_64[] = {{256, 1, 35.f, {8.0f}}, {128, 2, 28.f, {5.6f, 8.1f}}, {64, 2, 30.f, {3.4f, 6.0f}}};
-constexpr ShapeCost DKV_COST_128[] = {{256, 1, 80.f, {19.0f}}, {128, 1, 60.f, {13.2f}}, {64, 1, 70.f, {8.0f}}};
-constexpr ShapeCost DKV_COST_64[] = {{256, 1, 50.f, {10.0f}}, {128, 2, 40.f, {8.0f, 10.3f}}, {64, 1, 50.f, {5.4f}}};
 
 template <int D, int MODE, bool PAD>
 static hipError_t launch_mode(const BwdArgs& a, hipStream_t stream) {
     const uint32_t s2 = a.g.mode == MODE_DENSE ? 1u : (uint32_t)(a.g.s * a.g.s);
     const uint32_t n_units = (uint32_t)a.B * s2 * (uint32_t)a.heads;
-    // any-resolution mode: the first class has the most real tokens, the last one the fewest
-    const uint32_t last = (uint32_t)a.g.s - 1u;
-    const uint32_t n_max = PAD ? make_class_map(a.g, 0, 0).n : (uint32_t)a.g.n_sub;
-    const uint32_t n_min = PAD ? make_class_map(a.g, last, last).n : n_max;
-    const ShapeCost(&cost)[3] = MODE == BWD_DQ ? (D == 128 ? DQ_COST_128 : DQ_COST_64) : (D == 128 ? DKV_COST_128 : DKV_COST_64);
-    switch (pick_shape(cost, n_units, n_max, 2, n_min > (uint32_t)BT)) {  // a group needs a tile of its own
-        case 1: return launch_t<D, MODE, 4, 1, PAD>(a, n_units, n_max, stream);
-        case 2: return launch_t<D, MODE, 4, 2, PAD>(a, n_units, n_max, stream);
-        default: return launch_t<D, MODE, 8, 1, PAD>(a, n_units, n_max, stream);
+    const UnitSizes u = unit_sizes(a.g, PAD, (uint64_t)a.B * (uint32_t)a.heads);
+    switch (pick_bwd_shape(MODE == BWD_DKV, D, u)) {
+        case O128: return launch_t<D, MODE, 4, 1, PAD>(a, n_units, u.n_max, stream);
+        case O64_SPLIT: return launch_t<D, MODE, 4, 2, PAD>(a, n_units, u.n_max, stream);
+        default: return launch_t<D, MODE, 8, 1, PAD>(a, n_units, u.n_max, stream);
     }
 }
 

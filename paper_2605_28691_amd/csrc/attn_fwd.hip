@@ -9,7 +9,7 @@
 //     and share every K/V tile that is brought into LDS.  The shape for large problems is 8 wavefronts in one group: 256 queries
 //     a tile halve the L2 -> LDS traffic per MFMA compared with 128 (two wavefronts per SIMD, <= 256 VGPRs per lane, 64 KiB LDS).
 //     Small problems are bound by idle CUs and by the serial walk over the keys instead; they get smaller workgroups, and two
-//     groups that walk half of the keys each and merge (reference, sum, O) through LDS at the end: see the table at the launch.
+//     groups that walk half of the keys each and merge (reference, sum, O) through LDS at the end: see wg_shape.h.
 //   * The products are formed transposed, S^T = K Q^T and O^T = V^T P^T, with v_mfma_f32_32x32x16_bf16.  In the
 //     32x32 accumulator layout lane l holds column l%32, so every lane owns ONE query: its 16 registers per 32-key
 //     block are 16 keys of that query, and the exponentiated accumulator registers, rounded to bf16, ARE the B operand
@@ -47,7 +47,6 @@
 
 #include "kernels.h"
 #include "lds_layout.h"
-#include "wg_shape.h"
 
 namespace skiparse {
 
@@ -62,6 +61,7 @@ typedef __attribute__((ext_vector_type(4))) unsigned int u32x4;
 #define LDS_PTR(T) __attribute__((address_space(3))) T*
 
 constexpr int KT = 64;          // keys per staged tile (two 32-key blocks)
+static_assert(GROUP_MIN_ROWS == KT, "a key group needs a tile of its own");
 constexpr int ATTN_QT = 1;       // 32-query tiles per wavefront
 constexpr int RING_AHEAD = 8;    // row offsets are formed this many tiles ahead, by one wavefront per window in turn
 constexpr int RING = 16;         // tiles of row offsets (and key validity) kept in LDS: a slot is rewritten RING - RING_AHEAD windows after its last use
@@ -123,13 +123,7 @@ __device__ inline size_t scattered_row(const AttnArgs& a, uint32_t sb, uint32_t 
     return ((size_t)(p * s + q) * B + b) * (uint32_t)gi.n_sub + r * (W / s) + ws;
 }
 
-// Workgroup shapes: NW wavefronts in KG key groups take 32 * NW / KG queries.
-enum FwdShape : int {
-    Q256 = 1,        // 8 wavefronts, 1 group: 256 queries share every tile; the least L2 -> LDS traffic per MFMA, the best once the chip is full
-    Q128 = 2,        // 4 wavefronts, 1 group: two (head_dim 64: three) workgroups per CU; twice as many, finer-grained workgroups
-    Q64_SPLIT = 3,   // 4 wavefronts, 2 groups: four times the workgroups, half the serial chain
-    Q128_SPLIT = 4,  // 8 wavefronts, 2 groups: half the chain at two wavefronts per SIMD
-};
+// Workgroup shapes (FwdShape): NW wavefronts in KG key groups take 32 * NW / KG queries.
 constexpr int fwd_waves(int shape) { return shape == Q256 || shape == Q128_SPLIT ? 8 : 4; }
 constexpr int fwd_groups(int shape) { return shape >= Q64_SPLIT ? 2 : 1; }
 
@@ -137,7 +131,7 @@ constexpr int fwd_groups(int shape) { return shape >= Q64_SPLIT ? 2 : 1; }
 // padding masked: the kernel walks the real tokens of the class only (ClassMap), so that a masked key is one that is never met.  Only
 // the log-sum-exp is laid out over the padded grid (zero at the padding).
 template <int D, int SHAPE, bool PAD>
-__global__ __launch_bounds__(64 * fwd_waves(SHAPE), (SHAPE == Q128 ? 2 : 1)) void attn_fwd_bf16_kernel(AttnArgs a, uint32_t q_tiles, uint32_t total, uint32_t per_xcd) {
+__global__ __launch_bounds__(64 * fwd_waves(SHAPE), (SHAPE == Q128 ? 2 : 1)) void attn_fwd_bf16_kernel(AttnArgs a, PadArg<PAD> pad_map, uint32_t q_tiles, uint32_t total, uint32_t per_xcd) {
     constexpr int NW = fwd_waves(SHAPE), KG = fwd_groups(SHAPE);
     constexpr int QT = ATTN_QT;
     constexpr int QW = NW / KG;    // wavefronts of a key group: each owns 32 queries, all walk the same keys
@@ -186,8 +180,7 @@ __global__ __launch_bounds__(64 * fwd_waves(SHAPE), (SHAPE == Q128 ? 2 : 1)) voi
         p = pq / (uint32_t)a.g.s;
         q = pq - p * (uint32_t)a.g.s;
     }
-    ClassMap cm = {};
-    if (PAD) cm = make_class_map(a.g, p, q);
+    const ClassMap cm = make_class_map(a.g, pad_map, p, q);
     const uint32_t n_seq = PAD ? uniform(cm.n) : (uint32_t)a.g.n_sub;
     float* const lse_u = a.lse + (size_t)(bb * (uint32_t)a.heads + head) * (uint32_t)a.g.n_sub;
     if (PAD) {
@@ -603,7 +596,7 @@ __global__ __launch_bounds__(64 * fwd_waves(SHAPE), (SHAPE == Q128 ? 2 : 1)) voi
         if (n_tiles < (all_tiles + KG - 1) / KG) __syncthreads();  // a group with one tile less has passed one barrier less
         __syncthreads();                                           // every tile has been read
         __shared__ float part_ml[KG][QW][2][64];
-        static_assert(MT * 4 * 1024 == TL::TILE_BYTES && QW <= 4, "the accumulators of a wavefront take a tile buffer");
+        static_assert(QT == 1 && MT * 4 * 1024 == TL::TILE_BYTES && QW <= 4, "the accumulators of a wavefront take a tile buffer");
         char* const bufs[4] = {kbuf0_all, kbuf1_all, vbuf0_all, vbuf1_all};
         if (kg != 0) {
             char* dst = (qw == 0 ? kbuf0 : qw == 1 ? kbuf1 : qw == 2 ? vbuf0 : vbuf1) + lane * 16u;
@@ -680,30 +673,22 @@ static hipError_t launch_t(const AttnArgs& a, uint32_t n_units, uint32_t n_max, 
     const uint64_t total = (uint64_t)n_units * q_tiles;
     if (total > 0x7ffffff0ull) return hipErrorInvalidConfiguration;
     const uint32_t per_xcd = (uint32_t)((total + 7u) / 8u);
-    attn_fwd_bf16_kernel<D, SHAPE, PAD><<<8u * per_xcd, 64 * NW, 0, stream>>>(a, q_tiles, (uint32_t)total, per_xcd);
+    PadArg<PAD> pad_map;
+    make_pad_arg(a.g, pad_map);
+    attn_fwd_bf16_kernel<D, SHAPE, PAD><<<8u * per_xcd, 64 * NW, 0, stream>>>(a, pad_map, q_tiles, (uint32_t)total, per_xcd);
     return hipGetLastError();
 }
-
-// Costs of the shapes, in the order of FwdShape.
-// The costs were fitted to launches of every shape over 1..160 units of 32..8190 tokens.  Measured, always Q256 -> picked, us at
-// head_dim 128, units x tokens: 8x250 13.4 -> 8.2, 48x390 18.7 -> 13.7, 160x960 101 -> 88, 24x2600 134 -> 85, 48x2600 213 -> 165,
-// 4x5000 109 -> 66, 1x5000 107 -> 60; 48x960 (32) and 48x8190 (1390) keep Q256.  At head_dim 64: 24x2600 88 -> 52, 160x4000 804 -> 708.
-constexpr ShapeCost FWD_COST_128[] = {{256, 1, 40.f, {9.0f}}, {128, 2, 20.f, {5.5f, 10.0f}}, {64, 1, 25.f, {3.9f}}, {128, 1, 45.f, {4.7f}}};
-constexpr ShapeCost FWD_COST_64[] = {{256, 1, 30.f, {5.2f}}, {128, 3, 15.f, {3.6f, 5.7f, 7.6f}}, {64, 2, 15.f, {2.4f, 3.7f}}, {128, 1, 30.f, {2.9f}}};
 
 template <int D, bool PAD>
 static hipError_t launch_shape(const AttnArgs& a, hipStream_t stream) {
     const uint32_t s2 = a.g.mode == MODE_DENSE ? 1u : (uint32_t)(a.g.s * a.g.s);
     const uint32_t n_units = (uint32_t)a.B * s2 * (uint32_t)a.heads;
-    // any-resolution mode: the first class has the most real tokens, the last one the fewest
-    const uint32_t last = (uint32_t)a.g.s - 1u;
-    const uint32_t n_max = PAD ? make_class_map(a.g, 0, 0).n : (uint32_t)a.g.n_sub;
-    const uint32_t n_min = PAD ? make_class_map(a.g, last, last).n : n_max;
-    switch (pick_shape(D == 128 ? FWD_COST_128 : FWD_COST_64, n_units, n_max, 2, n_min > (uint32_t)KT)) {  // a key group needs a tile of its own
-        case 1: return launch_t<D, Q128, PAD>(a, n_units, n_max, stream);
-        case 2: return launch_t<D, Q64_SPLIT, PAD>(a, n_units, n_max, stream);
-        case 3: return launch_t<D, Q128_SPLIT, PAD>(a, n_units, n_max, stream);
-        default: return launch_t<D, Q256, PAD>(a, n_units, n_max, stream);
+    const UnitSizes u = unit_sizes(a.g, PAD, (uint64_t)a.B * (uint32_t)a.heads);
+    switch (pick_fwd_shape(D, u)) {
+        case Q128: return launch_t<D, Q128, PAD>(a, n_units, u.n_max, stream);
+        case Q64_SPLIT: return launch_t<D, Q64_SPLIT, PAD>(a, n_units, u.n_max, stream);
+        case Q128_SPLIT: return launch_t<D, Q128_SPLIT, PAD>(a, n_units, u.n_max, stream);
+        default: return launch_t<D, Q256, PAD>(a, n_units, u.n_max, stream);
     }
 }
 

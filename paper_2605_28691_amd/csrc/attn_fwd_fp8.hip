@@ -56,7 +56,7 @@ __device__ inline void lane_pair_f(float x, float& lo, float& hi) {
 // to the logits) and a skipped query.
 template <int D, bool PAD>
 __attribute__((amdgpu_waves_per_eu(waves_per_simd8(D), waves_per_simd8(D))))
-__global__ __launch_bounds__(NT8) void attn_fwd_fp8_kernel(Fp8AttnArgs a, uint32_t q_tiles, uint32_t total, uint32_t per_xcd) {
+__global__ __launch_bounds__(NT8) void attn_fwd_fp8_kernel(Fp8AttnArgs a, PadArg<PAD> pad_map, uint32_t q_tiles, uint32_t total, uint32_t per_xcd) {
     constexpr int NJ = D / 64;         // 64-channel MFMA steps of S^T = K Q^T
     constexpr int MT = D / 32;         // 32-channel blocks of O^T
     constexpr int RB = D;              // row bytes in LDS (packed rows, swizzled chunk positions)
@@ -87,13 +87,11 @@ __global__ __launch_bounds__(NT8) void attn_fwd_fp8_kernel(Fp8AttnArgs a, uint32
     const uint32_t p_ = a.g.mode == MODE_DENSE ? 0u : pq_ / (uint32_t)a.g.s, q_ = a.g.mode == MODE_DENSE ? 0u : pq_ - p_ * (uint32_t)a.g.s;
     // one wavefront (they take turns) marks the keys of a tile: lane = key.  The padding sits at the end of H and W, so the real rows
     // and columns of a class are a prefix: two divisions a key instead of the whole index map, on the path of every tile.
-    const uint32_t h_real = PAD ? a.g.hc.of(p_).d : 0u, w_real = PAD ? a.g.wc.of(q_).d : 0u;
-    FastDiv hs_div = a.g.hs;  // rows of a class on the padded grid
-    hs_div.one = hs_div.d <= 1u ? 1u : 0u;  // two vector registers less than with the argument
+    const ClassMap cm = make_class_map(a.g, pad_map, p_, q_);
     auto mark_keys = [&](uint32_t t) __attribute__((always_inline)) {
         const uint32_t j = t * KT8 + lane;
-        const uint32_t r = a.g.ws.div(j), ws = j - r * a.g.ws.d, hs = r - hs_div.div(r) * hs_div.d;
-        const bool real = j < n_seq && ws < w_real && hs < h_real;
+        const uint32_t r = a.g.ws.div(j), ws = j - r * a.g.ws.d, hs = r - cm.hs.div(r) * cm.hs.d;
+        const bool real = j < n_seq && ws < cm.w.d && hs < cm.h.d;
         kbias[t & 1u][lane] = real ? 0.f : -INFINITY;
         const unsigned long long pads = __builtin_amdgcn_ballot_w64(!real);
         if (lane == 0) kany[t & 1u] = pads != 0 ? 1u : 0u;
@@ -355,7 +353,9 @@ static hipError_t launch_fp8_t(const Fp8AttnArgs& a, hipStream_t stream) {
     const uint64_t total = (uint64_t)n_units * q_tiles;
     if (total > 0x7ffffff0ull) return hipErrorInvalidConfiguration;
     const uint32_t per_xcd = (uint32_t)((total + 7u) / 8u);
-    attn_fwd_fp8_kernel<D, PAD><<<8u * per_xcd, NT8, 0, stream>>>(a, q_tiles, (uint32_t)total, per_xcd);
+    PadArg<PAD> pad_map;
+    make_pad_arg(a.g, pad_map);
+    attn_fwd_fp8_kernel<D, PAD><<<8u * per_xcd, NT8, 0, stream>>>(a, pad_map, q_tiles, (uint32_t)total, per_xcd);
     return hipGetLastError();
 }
 

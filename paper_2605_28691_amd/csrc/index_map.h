@@ -52,23 +52,6 @@ __host__ __device__ inline FastDiv make_fastdiv32(uint32_t d) {
     return f;
 }
 
-// Real rows (or columns) of every class along one axis in the any-resolution mode: entry 0 for the classes under `at`, 1 for class
-// `at`, 2 for the others.  Three values serve every class: in the token-wise pattern the first n % s classes have one row more than
-// the others; in the group-wise one the last, incomplete run of s*s rows gives s rows to some classes, the rest to one, none to others.
-struct ClassAxis {
-    uint32_t at;
-    uint32_t n[3], mul[3];  // rows and FastDiv multiplier
-    __host__ __device__ inline FastDiv of(uint32_t p) const {
-        FastDiv f;
-        f.d = p < at ? n[0] : p == at ? n[1] : n[2];
-        f.mul = p < at ? mul[0] : p == at ? mul[1] : mul[2];
-        // Formed here: kept in the arguments and selected like the others it makes the dK+dV launch (head_dim 128) spill 22 values
-        // instead of 11, and the whole training step at 720P takes 115.7 ms instead of 111.2.
-        f.one = f.d <= 1u ? 1u : 0u;
-        return f;
-    }
-};
-
 struct GridMap {
     int mode;      // MODE_DENSE: position j is token j
     int s;         // sparse ratio
@@ -85,8 +68,6 @@ struct GridMap {
     // H_real rows of every H_pad are real, and columns below W (the real row length above) are real.
     int H_real;
     FastDiv hpad;  // division by the padded H
-    FastDiv hs;    // division by the padded H / s, the rows of a class on the padded grid
-    ClassAxis hc, wc;  // real rows and columns of the classes
 };
 
 __host__ __device__ inline uint32_t src_token(const GridMap& g, uint32_t p, uint32_t q, uint32_t j) {
@@ -111,6 +92,37 @@ __host__ __device__ inline uint32_t src_token_padded(const GridMap& g, uint32_t 
     return (t * (uint32_t)g.H_real + h) * (uint32_t)g.W + w;
 }
 
+// Real rows (or columns) of every class along one axis in the any-resolution mode: entry 0 for the classes under `at`, 1 for class
+// `at`, 2 for the others.  Three values serve every class: in the token-wise pattern the first n % s classes have one row more than
+// the others; in the group-wise one the last, incomplete run of s*s rows gives s rows to some classes, the rest to one, none to others.
+struct ClassAxis {
+    uint32_t at;
+    uint32_t n[3], mul[3];  // rows and FastDiv multiplier
+    __host__ __device__ inline FastDiv of(uint32_t p) const {
+        FastDiv f;
+        f.d = p < at ? n[0] : p == at ? n[1] : n[2];
+        f.mul = p < at ? mul[0] : p == at ? mul[1] : mul[2];
+        // Formed here: kept in the arguments and selected like the others it makes the dK+dV launch (head_dim 128) spill 22 values
+        // instead of 11, and the whole training step at 720P takes 115.7 ms instead of 111.2.
+        f.one = f.d <= 1u ? 1u : 0u;
+        return f;
+    }
+};
+
+// What the kernels of the any-resolution mode need beside the GridMap; formed on the host and an argument of these kernels only, not a
+// part of the map that every launch carries (a small 8-bit any-resolution call of four launches: 80.7 us with it there, 80.2).
+struct PadMap {
+    FastDiv hs;        // division by the padded H / s, the rows of a class on the padded grid
+    ClassAxis hc, wc;  // real rows and columns of the classes
+};
+struct NoPadMap {};
+template <bool PAD>
+struct PadArgOf { typedef NoPadMap type; };
+template <>
+struct PadArgOf<true> { typedef PadMap type; };
+template <bool PAD>
+using PadArg = typename PadArgOf<PAD>::type;
+
 // Any-resolution mode without the padding.  The padding sits at the end of H and W, so the real positions of a class are a prefix
 // along either axis (both maps are monotone in hs and ws): a (T, hr, wr) grid of its own.  The attention kernels walk that grid,
 // "dense" positions 0 .. n-1 with no padding among them, so that nothing is computed and masked away.
@@ -118,15 +130,21 @@ struct ClassMap {
     uint32_t n;  // real tokens of the class (0 if the unpadded grid has none)
     FastDiv w;   // division by the real columns of the class
     FastDiv h;   // division by the real rows of the class
+    FastDiv hs;  // division by its rows on the padded grid
 };
 
 // Selected from values that the host forms: extents and multipliers formed in the kernel put six integer divisions in a row in front of
 // every workgroup's first load (32 units of 10 tokens at head_dim 64, us a launch: 4.30 -> 4.20, in workgroups of 256 queries 4.91 -> 4.55).
-__host__ __device__ inline ClassMap make_class_map(const GridMap& g, uint32_t p, uint32_t q) {
+__host__ __device__ inline ClassMap make_class_map(const GridMap& g, const NoPadMap&, uint32_t, uint32_t) {
+    return {(uint32_t)g.n_sub, {}, {}, {}};
+}
+__host__ __device__ inline ClassMap make_class_map(const GridMap& g, const PadMap& m, uint32_t p, uint32_t q) {
     ClassMap c;
-    c.w = g.wc.of(q);
-    c.h = g.hc.of(p);
+    c.w = m.wc.of(q);
+    c.h = m.hc.of(p);
     c.n = (uint32_t)g.T * c.h.d * c.w.d;
+    c.hs = m.hs;
+    c.hs.one = c.hs.d <= 1u ? 1u : 0u;  // formed, as in ClassAxis
     return c;
 }
 
@@ -141,13 +159,13 @@ __host__ __device__ inline uint32_t src_token_real(const GridMap& g, const Class
 __host__ __device__ inline uint32_t padded_position(const GridMap& g, const ClassMap& c, uint32_t j) {
     const uint32_t r = c.w.div(j), ws = j - r * c.w.d;
     const uint32_t t = c.h.div(r), hs = r - t * c.h.d;
-    return (t * g.hs.d + hs) * g.ws.d + ws;
+    return (t * g.sdiv.div(g.hpad.d) + hs) * g.ws.d + ws;  // (with c.hs.d the dK+dV launch of head_dim 128 spills 17 values instead of 11)
 }
 
 // Host side: the map of a grid.  `group` selects the group-wise pattern; `pad` the any-resolution mode, in which the
 // subsequences are those of the grid padded at the end of H and W to the next multiples of s*s.
 inline GridMap make_dense_gridmap(size_t n) {
-    GridMap g = {};
+    GridMap g;
     g.mode = MODE_DENSE;
     g.s = 1;
     g.W = 0;
@@ -164,25 +182,12 @@ inline GridMap make_dense_gridmap(size_t n) {
     return g;
 }
 
-inline ClassAxis make_class_axis(uint32_t n, uint32_t s, bool group) {
-    const uint32_t run = group ? s : 1u;  // rows of a class that lie next to each other
-    const uint32_t full = n / (s * run), rest = n - full * s * run;  // whole rounds over the classes; rows of the incomplete one
-    const uint32_t len[3] = {(full + 1u) * run, full * run + rest % run, full * run};
-    ClassAxis a;
-    a.at = rest / run;
-    for (int i = 0; i < 3; i++) {
-        a.n[i] = len[i];
-        a.mul[i] = make_fastdiv(len[i]).mul;
-    }
-    return a;
-}
-
 inline GridMap make_gridmap(int T, int H, int W, int s, bool group, bool pad = false) {
     const int n_tok = T * H * W;
     if (s == 1) return make_dense_gridmap((size_t)n_tok);
     const int Hp = pad ? (H + s * s - 1) / (s * s) * (s * s) : H;
     const int Wp = pad ? (W + s * s - 1) / (s * s) * (s * s) : W;
-    GridMap g = {};
+    GridMap g;
     g.mode = group ? MODE_GROUP : MODE_TOKEN;
     g.s = s;
     g.W = W;
@@ -196,10 +201,34 @@ inline GridMap make_gridmap(int T, int H, int W, int s, bool group, bool pad = f
     g.sdiv = make_fastdiv((uint32_t)s);
     g.H_real = H;
     g.hpad = make_fastdiv((uint32_t)Hp);
-    g.hs = make_fastdiv((uint32_t)(Hp / s));
-    g.hc = make_class_axis((uint32_t)H, (uint32_t)s, group);
-    g.wc = make_class_axis((uint32_t)W, (uint32_t)s, group);
     return g;
 }
+
+// Real rows (columns) of every class: n real rows in all.
+inline ClassAxis make_class_axis(uint32_t n, uint32_t s, bool group) {
+    const uint32_t run = group ? s : 1u;  // rows of a class that lie next to each other
+    const uint32_t full = n / (s * run), rest = n - full * s * run;  // whole rounds over the classes; rows of the incomplete one
+    const uint32_t len[3] = {(full + 1u) * run, full * run + rest % run, full * run};
+    ClassAxis a;
+    a.at = rest / run;
+    for (int i = 0; i < 3; i++) {
+        a.n[i] = len[i];
+        a.mul[i] = make_fastdiv(len[i]).mul;
+    }
+    return a;
+}
+
+// The second map of an any-resolution grid (g made with pad = true).
+inline PadMap make_pad_map(const GridMap& g) {
+    const uint32_t s = (uint32_t)g.s;
+    PadMap m;
+    m.hs = make_fastdiv(g.hpad.d / s);
+    m.hc = make_class_axis((uint32_t)g.H_real, s, g.mode == MODE_GROUP);
+    m.wc = make_class_axis((uint32_t)g.W, s, g.mode == MODE_GROUP);
+    return m;
+}
+inline void make_pad_arg(const GridMap&, NoPadMap&) {}
+inline void make_pad_arg(const GridMap& g, PadMap& m) { m = make_pad_map(g); }
+inline ClassMap make_class_map(const GridMap& g, uint32_t p, uint32_t q) { return make_class_map(g, make_pad_map(g), p, q); }
 
 }  // namespace skiparse

@@ -6,8 +6,22 @@
 #include <stdint.h>
 
 #include "index_map.h"
+#include "wg_shape.h"
 
 namespace skiparse {
+
+// Sizes of the units of a launch over map g, `per_class` units (batch elements x heads) a class.
+inline UnitSizes unit_sizes(const GridMap& g, bool pad, uint64_t per_class) {
+    if (!pad) return {per_class * (g.mode == MODE_DENSE ? 1u : (uint32_t)(g.s * g.s)), (uint32_t)g.n_sub, (uint32_t)g.n_sub};
+    const uint32_t s = (uint32_t)g.s;
+    const PadMap m = make_pad_map(g);
+    uint32_t rows = 0, cols = 0;  // classes that have any along either axis
+    for (uint32_t p = 0; p < s; p++) {
+        rows += m.hc.of(p).d != 0;
+        cols += m.wc.of(p).d != 0;
+    }
+    return {per_class * rows * cols, make_class_map(g, m, 0, 0).n, make_class_map(g, m, s - 1u, s - 1u).n};
+}
 
 // Row gather/scatter between the original and the sparse layout.  `to_sparse` != 0: dst is sparse.  ssp_G > 0: the sparse side is an
 // all-to-all receive buffer of Sparse Sequence Parallelism with ssp_G subsequences per rank (Alg. 1, sparse_sequence_parallel, step 3).

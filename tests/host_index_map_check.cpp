@@ -83,11 +83,11 @@ int main() {
                         k++;
                         checked++;
                     }
-                    // rows and columns of the class as the host hands them to the kernels
+                    // rows and columns of the class, as selected from what the host hands to the kernels
                     uint32_t rows = 0, cols = 0;
                     for (int h = 0; h < H; h++) rows += (group ? h / s : h) % s == p;
                     for (int w = 0; w < W; w++) cols += (group ? w / s : w) % s == q;
-                    if (g.hc.of((uint32_t)p).d != rows || g.wc.of((uint32_t)q).d != cols || g.hs.d != (uint32_t)Hs) {
+                    if (c.h.d != rows || c.w.d != cols || c.hs.d != (uint32_t)Hs) {
                         printf("class extents T%d H%d W%d s%d group%d p%d q%d\n", T, H, W, s, group, p, q);
                         return 1;
                     }
