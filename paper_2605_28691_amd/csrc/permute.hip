@@ -2,12 +2,10 @@
 // their inverses), and between the two sparse orders.  Bound by HBM bandwidth: every row of heads*head_dim elements is contiguous in
 // both layouts.  The wavefronts enumerate DESTINATION rows and find each row's source with the index map or its inverse: contiguous
 // writes with gathered reads measure faster than the reverse.
-//   * Rows of 1 KiB and more: one wavefront moves one row with 16-byte accesses per lane (1 KiB contiguous per instruction).
-//   * Shorter rows: one wavefront moves a batch of rows.  A wavefront a row leaves most lanes idle and spends the index arithmetic, some
+//   * Longer rows: one wavefront moves one row with 16-byte accesses per lane (1 KiB contiguous per instruction).
+//   * Rows up to 768 B: one wavefront moves a batch of rows.  A wavefront a row leaves most lanes idle and spends the index arithmetic, some
 //     ten integer divisions, on a few hundred bytes; here lane i finds the source of row i, one evaluation for the whole batch, and
-//     the batch is moved as one run of 16-byte chunks.  Permute, switch and unpermute together, us: 80,640 rows of 384 B 68.9 -> 45.1,
-//     32,256 rows of 128 B 28.4 -> 12.8.  From 1 KiB on a wavefront a row is the better one (1,280 B: 110 against 121; 10 KiB: 879
-//     against 887, and longer batches lose more).
+//     the batch is moved as one run of 16-byte chunks.  The rule is row_batch() in wg_shape.h.
 #include "kernels.h"
 
 namespace skiparse {
@@ -87,8 +85,8 @@ __global__ __launch_bounds__(PERMUTE_WAVES * 64) void permute_rows_kernel(const 
     for (; c < chunks_per_row; c += 64u) __builtin_nontemporal_store(__builtin_nontemporal_load(s + c), d + c);
 }
 
-constexpr uint32_t BATCH_CHUNKS = 1024;  // 16-byte chunks of a batch of short rows
-constexpr int BATCH_UNROLL = 5;
+constexpr int BATCH_UNROLL = BATCH_CHUNKS / 64;  // a full batch in one round of loads
+static_assert(BATCH_UNROLL * 64 == BATCH_CHUNKS, "whole rounds of the wavefront");
 
 template <int MAP>
 __global__ __launch_bounds__(PERMUTE_WAVES * 64) void permute_short_rows_kernel(const u32x4* __restrict__ src, u32x4* __restrict__ dst, int B, GridMap g,
@@ -100,19 +98,17 @@ __global__ __launch_bounds__(PERMUTE_WAVES * 64) void permute_short_rows_kernel(
     const uint32_t from = source_row<MAP>(g, (uint32_t)B, row0 + (lane < n ? lane : n - 1u), ssp_G);
     u32x4* const d = dst + (size_t)row0 * chunks.d;
     const uint32_t total = n * chunks.d;  // at most BATCH_CHUNKS: the division below is exact
-    for (uint32_t u0 = 0; u0 < total; u0 += BATCH_UNROLL * 64u) {  // wave-uniform: every lane takes part in the shuffles
-        u32x4 tmp[BATCH_UNROLL];
+    u32x4 tmp[BATCH_UNROLL];
 #pragma unroll
-        for (int k = 0; k < BATCH_UNROLL; k++) {
-            const uint32_t u = u0 + k * 64u + lane, uc = u < total ? u : total - 1u;  // lanes past the end repeat the last chunk and store nothing
-            const uint32_t i = chunks.div(uc), c = uc - i * chunks.d;
-            tmp[k] = __builtin_nontemporal_load(src + (size_t)(uint32_t)__shfl((int)from, (int)i) * chunks.d + c);
-        }
+    for (int k = 0; k < BATCH_UNROLL; k++) {
+        const uint32_t u = k * 64u + lane, uc = u < total ? u : total - 1u;  // lanes past the end repeat the last chunk and store nothing
+        const uint32_t i = chunks.div(uc), c = uc - i * chunks.d;
+        tmp[k] = __builtin_nontemporal_load(src + (size_t)(uint32_t)__shfl((int)from, (int)i) * chunks.d + c);
+    }
 #pragma unroll
-        for (int k = 0; k < BATCH_UNROLL; k++) {
-            const uint32_t u = u0 + k * 64u + lane;
-            if (u < total) __builtin_nontemporal_store(tmp[k], d + u);
-        }
+    for (int k = 0; k < BATCH_UNROLL; k++) {
+        const uint32_t u = k * 64u + lane;
+        if (u < total) __builtin_nontemporal_store(tmp[k], d + u);
     }
 }
 
@@ -127,11 +123,7 @@ static hipError_t launch_rows(const void* src, void* dst, int B, const GridMap& 
     const uint32_t chunks = (uint32_t)(row_bytes / 16);
     const uint32_t s2 = g.mode == MODE_DENSE ? 1u : (uint32_t)(g.s * g.s);
     const uint32_t n_rows = (uint32_t)B * s2 * (uint32_t)g.n_sub;
-    // batches only where they leave 2048 wavefronts (two a SIMD); on fewer rows a wavefront each is as good or better (128 rows of 256 B:
-    // 6.9 us against 7.3)
-    uint32_t batch = chunks < 64u ? BATCH_CHUNKS / chunks : 1u;
-    batch = batch > 64u ? 64u : batch;
-    while (batch > 1u && n_rows / batch < 2048u) batch /= 2u;
+    const uint32_t batch = row_batch(chunks, n_rows);
     if (batch > 1u) {
         const uint32_t per_block = batch * PERMUTE_WAVES, blocks = (n_rows + per_block - 1) / per_block;
         permute_short_rows_kernel<MAP><<<blocks, PERMUTE_WAVES * 64, 0, stream>>>((const u32x4*)src, (u32x4*)dst, B, g, make_fastdiv32(chunks), n_rows, batch, ssp_G);

@@ -106,4 +106,19 @@ inline int pick_bwd_shape(bool dkv, int head_dim, const UnitSizes& u) {
     return pick_shape(head_dim == 128 ? DQ_COST_128 : DQ_COST_64, u, no_limit);
 }
 
+// ---- row moves: how many rows of `chunks` 16-byte chunks one wavefront moves.
+// Batches of 4 KiB, a single round of loads: larger ones leave less in flight and lose more the longer the rows are (16 KiB: 768 B rows 91.8 us
+// instead of the 87.5 of a wavefront a row, 1008 B 122 instead of 101).  Permute, switch and unpermute of 96,768 rows together, us, a wavefront
+// a row -> batches: 64 B 71.5 -> 14.8, 128 B 72.8 -> 17.7, 256 B 75 -> 31, 384 B 78.7 -> 46, 512 B 79.5 -> 55, 640 B 83.7 -> 68.5,
+// 768 B 87.5 -> 80.5; from 832 B on a wavefront a row is as good or better (1008 B 101 -> 105).  And only where they leave 2048
+// wavefronts, two a SIMD: with fewer rows a wavefront each is as good (128 rows of 256 B: 6.9 us against 7.3).
+constexpr uint32_t BATCH_CHUNKS = 256;
+constexpr uint32_t BATCH_MAX_ROW = 48;
+inline uint32_t row_batch(uint32_t chunks, uint32_t n_rows) {
+    uint32_t batch = chunks <= BATCH_MAX_ROW ? BATCH_CHUNKS / chunks : 1u;
+    batch = batch > 64u ? 64u : batch;  // lane i finds row i
+    while (batch > 1u && n_rows / batch < 2048u) batch /= 2u;
+    return batch;
+}
+
 }  // namespace skiparse

@@ -1,6 +1,6 @@
-// Evaluates the rule that picks an attention launch's workgroup shape (paper_2605_28691_amd/csrc/wg_shape.h) on the host.  Reads calls from
-// stdin, one a line: launch (fwd, dq or dkv), head_dim, B, heads, T, H, W, s, group, pad; prints the number of the shape of each.  Built and
-// run by tests/test_wg_shape.py.
+// Evaluates the rules that pick a launch's shape (paper_2605_28691_amd/csrc/wg_shape.h) on the host.  Reads calls from stdin, one a line:
+// launch (fwd, dq or dkv), head_dim, B, heads, T, H, W, s, group, pad; prints the number of the shape of each.  A launch named "rows" has the
+// bytes of a row in place of head_dim and prints the rows that a wavefront moves.  Built and run by tests/test_wg_shape.py.
 #include <cstdio>
 #include <cstring>
 
@@ -12,6 +12,10 @@ int main() {
     char launch[8];
     int D, B, heads, T, H, W, s, group, pad;
     while (scanf("%7s %d %d %d %d %d %d %d %d %d", launch, &D, &B, &heads, &T, &H, &W, &s, &group, &pad) == 10) {
+        if (strcmp(launch, "rows") == 0) {
+            printf("%u\n", row_batch((uint32_t)(D / 16), (uint32_t)(B * T * H * W)));
+            continue;
+        }
         const GridMap g = make_gridmap(T, H, W, s, group != 0, pad != 0);
         const UnitSizes u = unit_sizes(g, pad != 0 && s > 1, (uint64_t)B * (uint64_t)heads);
         printf("%d\n", strcmp(launch, "fwd") == 0 ? pick_fwd_shape(D, u) : pick_bwd_shape(strcmp(launch, "dkv") == 0, D, u));

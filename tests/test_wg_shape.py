@@ -1,4 +1,4 @@
-"""The rule that picks a launch's workgroup shape, evaluated on the host: what it picks for calls that every shape was measured on."""
+"""The rules that pick a launch's shape, evaluated on the host: what they pick for calls that every shape was measured on."""
 import os
 import subprocess
 
@@ -52,3 +52,18 @@ def test_classes_without_a_token_are_no_workgroups(pick):
     """Any-resolution grid on which only 2 of 16 classes hold a token: 2 x 64 units, not 16 x 64, decide (4-wavefront workgroups win)."""
     call = ("fwd", 64, 1, 64, 30, 2, 7, 4, 1, 1)
     assert pick([call]) == pick([dense("fwd", 64, 128, 30 * 2 * 4)])
+
+
+def rows(row_bytes, n):
+    return ("rows", row_bytes, 1, 1, 1, 1, n, 1, 0, 0)
+
+
+def test_row_batches(pick):
+    """A wavefront moves at most 4 KiB of rows in a batch, and rows above 768 B one by one: both measured slower than a wavefront a row."""
+    sizes = list(range(16, 1024, 16))
+    for n in (4608, 13824, 55296, 193536):
+        for row_bytes, batch in zip(sizes, pick([rows(b, n) for b in sizes])):
+            assert 1 <= batch <= 64
+            assert batch == 1 or (row_bytes <= 768 and batch * row_bytes <= 4096 and n // batch >= 2048)
+    assert pick([rows(b, 193536) for b in (16, 64, 128, 768, 784, 1008)]) == [64, 64, 32, 5, 1, 1]
+    assert pick([rows(128, 2000)]) == [1]
