@@ -113,7 +113,7 @@ def test_switch_pattern_768p_equals_two_step():
     assert torch.equal(sk.skiparse_switch_pattern(gsa, w.T, w.H, w.W, w.s, "group").view(torch.int16), tsa.view(torch.int16))
 
 
-# Rows below 1 KiB are moved in batches by one wavefront: rows of 1 to 63 chunks of 16 bytes, batches that do not divide the number of
+# Rows up to 768 B are moved in batches by one wavefront: rows of 1 to 63 chunks of 16 bytes, batches that do not divide the number of
 # rows, s = 1 (a copy), all three directions, canaries behind the destination.
 @pytest.mark.parametrize("row_bytes", [16, 48, 128, 336, 496, 1008])
 @pytest.mark.parametrize("B,T,H,W,s", [(1, 5, 36, 36, 2), (1, 7, 36, 36, 3), (3, 5, 32, 16, 4), (1, 41, 11, 13, 1), (1, 260, 16, 16, 2)])
@@ -137,3 +137,9 @@ def test_short_rows_bit_exact(row_bytes, B, T, H, W, s):
         assert np.array_equal(z.cpu().numpy().reshape(want_other.shape), want_other)
         assert torch.equal(back.cpu(), x)
         assert all(bool((b[x.numel() :] == 7).all()) for b in bufs)
+
+
+@pytest.mark.parametrize("row_bytes", [16, 48])
+def test_short_rows_in_full_batches(row_bytes):
+    """134,640 rows: batches of 64 rows, one a lane (fewer rows get smaller batches), the last of 48."""
+    test_short_rows_bit_exact(row_bytes, 1, 33, 68, 60, 2)

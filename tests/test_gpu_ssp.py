@@ -19,6 +19,7 @@ CASES = [  # b, heads, D, T, H, W, s, group_size
     (2, 1, 128, 1, 9, 9, 3, 9),
     (1, 2, 64, 1, 16, 32, 4, 8),
     (1, 1, 64, 3, 4, 4, 1, 1),     # s = 1: a copy
+    (2, 3, 64, 7, 48, 52, 2, 2),   # 17,472 local rows of 192 to 768 B: moved in batches of 5 that do not divide them, G = b = 2
 ]
 
 
