@@ -247,19 +247,25 @@ def skiparse_attn_fwd_sparse(q, k, v, T: int, H: int, W: int, s: int, pattern: s
     return out
 
 
-@functools.lru_cache(maxsize=256)
-def _lse_bytes(B, heads, T, H, W, D, s, pattern: int, flags: int) -> int:
-    return int(lib().skiparse_lse_bytes(B, heads, T, H, W, D, s, pattern, flags))
+_INTS = (int,) * 9
 
 
 @functools.lru_cache(maxsize=256)
-def _bwd_workspace_bytes(B, heads, T, H, W, D, s, pattern: int, flags: int) -> int:
-    return int(lib().skiparse_bwd_workspace_bytes(B, heads, T, H, W, D, s, pattern, flags))
+def _bytes_of_ints(name: str, *sizes: int) -> int:
+    return int(getattr(lib(), name)(*sizes))
+
+
+def _bytes(name: str, *sizes) -> int:
+    """A size that the library computes from (B, heads, T, H, W, D, s, pattern, flags).  Remembered for plain integers only: they are their
+    own value, while a one-element tensor is looked up by identity and may change, and 8.0, which the call refuses, is found under 8."""
+    if tuple(map(type, sizes)) == _INTS:
+        return _bytes_of_ints(name, *sizes)
+    return int(getattr(lib(), name)(*sizes))
 
 
 def skiparse_lse_shape(B, heads, T, H, W, D, s, pattern: str, pad: bool = False):
     """Shape of the log-sum-exp tensor: [s*s*B][heads][positions per subsequence] (positions of the padded grid with pad=True)."""
-    n = _lse_bytes(B, heads, T, H, W, D, s, PATTERNS[pattern], PAD if pad else 0) // 4
+    n = _bytes("skiparse_lse_bytes", B, heads, T, H, W, D, s, PATTERNS[pattern], PAD if pad else 0) // 4
     if n == 0:
         raise ValueError("grid does not fit the pattern (use pad=True for the any-resolution mode)")
     return (s * s * B, heads, n // (s * s * B * heads))
@@ -282,7 +288,7 @@ def skiparse_attn_fwd_lse(q, k, v, T: int, H: int, W: int, s: int, pattern: str,
 
 
 def skiparse_bwd_workspace_bytes(B, heads, T, H, W, D, s, pattern: str, pad: bool = False) -> int:
-    return _bwd_workspace_bytes(B, heads, T, H, W, D, s, PATTERNS[pattern], PAD if pad else 0)
+    return _bytes("skiparse_bwd_workspace_bytes", B, heads, T, H, W, D, s, PATTERNS[pattern], PAD if pad else 0)
 
 
 def skiparse_attn_bwd(q, k, v, out, dout, lse, T: int, H: int, W: int, s: int, pattern: str, scale: float = 0.0,
