@@ -91,10 +91,27 @@ def lib() -> ctypes.CDLL:
 
 
 # A small call is bound by what it costs to issue it (a kernel of 4 us behind 10 us of Python), so the marshalling keeps to plain
-# integers: addresses and the stream handle are converted once, by ctypes, and no Stream or c_void_p object is made for them.
+# integers: addresses and the stream handle are converted once, by ctypes, and no Stream or c_void_p object is made for them.  torch hands
+# out the bare handle under private names only; where a release has no such names the Stream object serves.
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+_get_device = getattr(torch._C, "_cuda_getDevice", None)
+
+
 def _stream() -> int:
     """Handle of torch's current stream on the current device."""
-    return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
+    if _raw_stream is None or _get_device is None:
+        return torch.cuda.current_stream().cuda_stream
+    return _raw_stream(_get_device())
+
+
+def _forked() -> None:
+    """The bare handle is given out without a look at where: in a forked child torch's public call decides, which refuses the GPU to the
+    child of a process that has used it."""
+    global _raw_stream
+    _raw_stream = None
+
+
+os.register_at_fork(after_in_child=_forked)
 
 
 def _dev(t: torch.Tensor, name: str) -> int:

@@ -1,5 +1,8 @@
 """The Python binding's own logic, without a GPU: sizes that the library computes, and the stream that calls go to."""
 import ctypes
+import os
+import subprocess
+import sys
 
 import numpy as np
 import pytest
@@ -7,11 +10,11 @@ import torch
 
 import paper_2605_28691_amd as sk
 
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+
 
 @pytest.fixture(scope="module", autouse=True)
 def built():
-    import os
-
     if not os.path.exists(sk._LIB_PATH):
         from paper_2605_28691_amd import build
 
@@ -39,3 +42,37 @@ def test_sizes_refuse_what_is_no_integer():
             sk.skiparse_lse_shape(1, 2, 2, bad, 8, 64, 2, "token")
         with pytest.raises(ctypes.ArgumentError):
             sk.skiparse_bwd_workspace_bytes(1, 2, 2, bad, 8, 64, 2, "token")
+
+
+def test_stream_of_a_forked_child_is_refused():
+    """torch refuses the GPU in a child forked from a process that has used it; so does a call whose tensors are all there already."""
+    code = """
+import os, torch
+torch._C._cuda_getDevice, torch._C._cuda_getCurrentRawStream = (lambda: 0), (lambda device: 7)
+import paper_2605_28691_amd as sk
+assert sk._stream() == 7
+pid = os.fork()
+if pid == 0:
+    torch.cuda._is_in_bad_fork = lambda: True  # what torch finds in such a child
+    try:
+        sk._stream()
+        os._exit(3)
+    except RuntimeError as e:
+        os._exit(0 if "fork" in str(e) else 4)
+_, status = os.waitpid(pid, 0)
+assert sk._stream() == 7
+raise SystemExit(os.WEXITSTATUS(status))
+"""
+    assert subprocess.run([sys.executable, "-c", code], cwd=ROOT).returncode == 0
+
+
+@pytest.mark.parametrize("missing", ["_raw_stream", "_get_device"])
+def test_stream_without_the_private_names(monkeypatch, missing):
+    """A torch without the private names for the bare handle serves through its public Stream object."""
+
+    class Stream:
+        cuda_stream = 11
+
+    monkeypatch.setattr(sk, missing, None)
+    monkeypatch.setattr(torch.cuda, "current_stream", lambda: Stream)
+    assert sk._stream() == 11
