@@ -12,7 +12,7 @@ from _util import assert_close_bf16, gather_rows, oracle_inputs, to_np64
 
 pytestmark = pytest.mark.gpu
 
-SMALL = [  # B, heads, D, T, H, W, s -- several query/key tiles and ragged tails (tiles are 128 queries x 64 keys)
+SMALL = [  # B, heads, D, T, H, W, s -- several query/key tiles and ragged tails (tiles are 64 to 256 queries x 64 keys)
     (1, 2, 64, 2, 8, 8, 2),      # the tiny workload's shape: 32 tokens per subsequence, a single partial tile
     (2, 3, 128, 3, 8, 12, 2),    # Nsub = 72: partial query tile, one full + one partial key tile
     (1, 2, 128, 5, 16, 20, 2),   # Nsub = 400: 4 query tiles, 7 key tiles, tail of 16
@@ -20,7 +20,7 @@ SMALL = [  # B, heads, D, T, H, W, s -- several query/key tiles and ragged tails
     (1, 9, 128, 4, 9, 18, 3),    # s = 3, 9 heads (unit count not a multiple of 8)
     (1, 1, 128, 1, 16, 48, 4),   # s = 4: 16 subsequences of 48 tokens
     (1, 2, 128, 7, 16, 16, 2),   # Nsub = 448 = 7 * 64: no key tail
-    (1, 1, 64, 9, 24, 28, 2),    # Nsub = 1512: 24 key tiles, more than the 16 slots of the row-offset ring, tail of 40
+    (1, 1, 64, 9, 24, 28, 2),    # Nsub = 1512: 24 key tiles, halved between two groups of wavefronts, tail of 40
     (2, 2, 64, 1, 2, 2, 2),      # one token per subsequence (token-wise only): out = v
 ]
 
@@ -173,7 +173,7 @@ PAD_CASES = [  # B, heads, D, T, H, W, s -- H or W not a multiple of s*s
     (1, 4, 128, 2, 11, 20, 3),
     (1, 2, 128, 6, 8, 12, 2),    # divisible: the padded mode must agree with the plain one
     (1, 1, 128, 9, 1, 33, 2),    # H = 1: the classes with p = 1 are empty
-    (1, 1, 64, 11, 21, 26, 2),   # padded grid 24 x 28: 1848 positions per class = 29 key tiles (ring wrap-around), rows of padding inside
+    (1, 1, 64, 11, 21, 26, 2),   # padded grid 24 x 28, 1573 real tokens in the largest class: two groups of wavefronts, uneven halves
 ]
 
 
@@ -268,8 +268,13 @@ def test_largest_admitted_batch_element_sampled_rows():
 
 # The forward's workgroup shape follows the problem's size: 64, 128 or 256 queries a workgroup, the keys walked by one group of
 # wavefronts or by two that are merged at the end.  Edges of all of them: one key tile more than a group, uneven halves, last query
-# tile of one row, many and few units, halves of the keys that hold nothing but padding.
-@pytest.mark.parametrize("heads,N", [(1, 65), (2, 128), (1, 129), (3, 321), (80, 65), (200, 129), (300, 33), (4, 1921), (90, 449), (12, 2497)])
+# tile of one row, many and few units, walks of more than the 16 tiles that the row-offset ring holds.  test_wg_shape.py says which
+# shape each takes.
+WORKGROUP_SHAPES = [(1, 65), (2, 128), (1, 129), (3, 321), (80, 65), (200, 129), (300, 33), (4, 1921), (90, 449), (12, 2497), (24, 700), (29, 1100),
+                    (52, 1100), (1, 2200), (8, 2100)]
+
+
+@pytest.mark.parametrize("heads,N", WORKGROUP_SHAPES)
 @pytest.mark.parametrize("D", [64, 128])
 def test_workgroup_shapes(heads, N, D):
     import paper_2605_28691_amd as sk
@@ -289,9 +294,13 @@ def test_workgroup_shapes(heads, N, D):
     assert np.abs(to_np64(lse[0, heads - 1]) - (m + np.log(np.exp(logits - m).sum(-1, keepdims=True)))[:, 0]).max() <= 5e-3
 
 
+# Any-resolution grids: classes of unequal size, a smallest one of exactly a tile or less (never split) and of more.
+PADDED_GROUPS = [(1, 17, 64, 4), (1, 9, 33, 3), (3, 17, 21, 2)]  # T, H, W, s; 2 heads
+
+
 @pytest.mark.parametrize("D", [64, 128])
 @pytest.mark.parametrize("pattern", ["token", "group"])
-@pytest.mark.parametrize("T,H,W,s", [(1, 17, 64, 4), (1, 9, 33, 3), (3, 17, 21, 2)])
+@pytest.mark.parametrize("T,H,W,s", PADDED_GROUPS)
 def test_key_groups_of_padding(T, H, W, s, pattern, D):
     import paper_2605_28691_amd as sk
 
@@ -300,4 +309,39 @@ def test_key_groups_of_padding(T, H, W, s, pattern, D):
     rows = np.array([(0, h, n) for h in range(2) for n in range(T * H * W)], dtype=np.int64)
     want = oracle.skiparse_attention_rows_padded(*oracle_inputs(q, k, v), rows, T, H, W, s, pattern, w.scale)
     out = sk.skiparse_attn_fwd(*_gpu((q, k, v)), T, H, W, s, pattern, scale=w.scale, pad=True)
+    assert_close_bf16(gather_rows(out, rows), want, f"padded {pattern}")
+
+
+PADDED_SHAPES = [  # heads, T, H, W, s, pattern: every workgroup shape in the any-resolution mode, some with walks of more than 16 tiles
+    (1, 1, 17, 21, 3, "token"),
+    (1, 1, 17, 21, 2, "token"),
+    (26, 3, 17, 21, 3, "group"),
+    (5, 5, 27, 21, 2, "token"),
+    (4, 7, 33, 37, 3, "group"),
+    (7, 7, 33, 37, 3, "group"),
+    (2, 7, 33, 37, 3, "token"),
+    (1, 11, 33, 37, 2, "token"),  # classes of 50, 53 and 56 key tiles in two groups: an odd count leaves one group a barrier short
+    (1, 21, 30, 33, 3, "token"),
+]
+
+
+@pytest.mark.parametrize("D", [64, 128])
+@pytest.mark.parametrize("heads,T,H,W,s,pattern", PADDED_SHAPES)
+def test_any_resolution_workgroup_shapes(heads, T, H, W, s, pattern, D):
+    import paper_2605_28691_amd as sk
+
+    w = si.make_shape("padshapes", 1, heads, D, T, H, W, s, seed=T + H)
+    q, k, v = si.make_qkv(w)
+    N = T * H * W
+    # the first and last token of every class, where the classes differ, and tokens at random
+    step = s if pattern == "group" else 1
+    n = np.arange(N)
+    cls = (n // W % H // step % s) * s + n % W // step % s
+    ns = np.concatenate([n[cls == c][[0, -1]] for c in range(s * s)] + [np.random.default_rng(N).integers(0, N, 24)])
+    rows = np.array([(0, h, i) for h in sorted({0, heads // 2, heads - 1}) for i in ns], dtype=np.int64)
+    want = oracle.skiparse_attention_rows_padded(*oracle_inputs(q, k, v), rows, T, H, W, s, pattern, w.scale)
+    guard = torch.full((q.numel() + 4096,), 5.0, dtype=torch.bfloat16, device="cuda")
+    out = guard[2048 : 2048 + q.numel()].view(q.shape)
+    sk.skiparse_attn_fwd(*_gpu((q, k, v)), T, H, W, s, pattern, scale=w.scale, pad=True, out=out)
+    assert bool((guard[:2048] == 5.0).all()) and bool((guard[2048 + q.numel() :] == 5.0).all())
     assert_close_bf16(gather_rows(out, rows), want, f"padded {pattern}")

@@ -19,11 +19,11 @@ BWD_MAX_REL = 3e-2
 SMALL = [  # B, heads, D, T, H, W, s
     (1, 2, 64, 2, 8, 8, 2),      # 32 tokens per subsequence: a single partial tile on both sides
     (2, 3, 128, 3, 8, 12, 2),    # Nsub = 72: one full + one partial streamed tile
-    (1, 2, 128, 5, 16, 20, 2),   # Nsub = 400: two owner tiles (256 + 144), 7 streamed tiles with a tail of 16
+    (1, 2, 128, 5, 16, 20, 2),   # Nsub = 400: 7 streamed tiles with a tail of 16
     (2, 2, 64, 5, 16, 20, 2),    # head_dim 64, batch of 2
     (1, 9, 128, 4, 9, 18, 3),    # s = 3, 9 heads
     (1, 2, 128, 7, 16, 16, 2),   # Nsub = 448 = 7 * 64: no tail
-    (1, 1, 64, 9, 24, 28, 2),    # Nsub = 1512: 24 streamed tiles, more than the 16 slots of the row-offset ring
+    (1, 1, 64, 9, 24, 28, 2),    # Nsub = 1512: 24 streamed tiles, halved between two groups of wavefronts
     (1, 1, 128, 1, 16, 48, 4),   # s = 4: 16 subsequences of 48 tokens
     (2, 2, 64, 1, 2, 2, 2),      # one token per subsequence (token-wise only): P = 1, dv = dout, dq = dk = 0
 ]
@@ -154,10 +154,10 @@ PAD_CASES = [  # B, heads, D, T, H, W, s -- any-resolution mode: H or W not a mu
     (2, 3, 128, 4, 10, 13, 2),   # padded grid 12 x 16: Nsub_pad = 192
     (1, 2, 64, 5, 6, 30, 2),
     (1, 4, 128, 2, 11, 20, 3),   # s = 3: padded to 18 x 27
-    (1, 2, 128, 9, 17, 21, 2),   # Nsub_pad = 9 * 5 * 6 = 270: two owner tiles, padding rows inside and at the end of tiles
+    (1, 2, 128, 9, 17, 21, 2),   # classes of 720 to 891 real tokens of 1080 positions
     (1, 1, 128, 9, 1, 33, 2),    # H = 1: the classes with p = 1 hold padding only
     (1, 2, 128, 6, 8, 12, 2),    # divisible: must agree bit for bit with the plain mode
-    (1, 1, 64, 11, 21, 26, 2),   # padded grid 24 x 28: 29 streamed tiles (ring wrap-around), rows of padding inside
+    (1, 1, 64, 11, 21, 26, 2),   # padded grid 24 x 28, 1573 real tokens in the largest class: two groups of wavefronts, uneven halves
 ]
 
 
@@ -264,8 +264,12 @@ def test_backward_768p_one_unit_token_all_heads():
 
 
 # The backward's workgroup shapes (64, 128 or 256 owners, one or two groups of wavefronts) follow the problem's size: one tile more than a
-# group, uneven halves, a last tile of one row, many and few units.
-@pytest.mark.parametrize("heads,N", [(1, 65), (2, 129), (3, 321), (80, 65), (200, 129), (300, 33), (16, 900)])
+# group, uneven halves, a last tile of one row, many and few units, walks of more than the 16 tiles that the row-offset ring holds.
+# test_wg_shape.py says which shape each takes.
+WORKGROUP_SHAPES = [(1, 65), (2, 129), (3, 321), (80, 65), (200, 129), (300, 33), (16, 900), (15, 1100), (29, 1100), (1, 2200), (13, 2497)]
+
+
+@pytest.mark.parametrize("heads,N", WORKGROUP_SHAPES)
 @pytest.mark.parametrize("D", [64, 128])
 def test_backward_workgroup_shapes(heads, N, D):
     import paper_2605_28691_amd as sk
@@ -298,3 +302,35 @@ def test_backward_classes_of_unequal_size(T, H, W, s, D, pattern):
     grads = sk.skiparse_attn_bwd(qg, kg, vg, out, dg, lse, T, H, W, s, pattern, scale=w.scale, pad=True)
     for g, wnt, name in zip(grads, want, ("dq", "dk", "dv")):
         assert_grad_close(to_np64(g), wnt, f"{pattern} {name}")
+
+
+PADDED_SHAPES = [  # heads, T, H, W, s, pattern: every workgroup shape in the any-resolution mode, most with walks of more than 16 tiles
+    (2, 7, 33, 37, 3, "group"),
+    (4, 7, 33, 37, 3, "group"),
+    (4, 7, 33, 37, 2, "token"),
+    (1, 11, 33, 37, 2, "token"),  # classes of 50, 53 and 56 streamed tiles in two groups: an odd count leaves one group a barrier short
+]
+
+
+@pytest.mark.parametrize("D", [64, 128])
+@pytest.mark.parametrize("heads,T,H,W,s,pattern", PADDED_SHAPES)
+def test_backward_any_resolution_workgroup_shapes(heads, T, H, W, s, pattern, D):
+    """Gradients of sampled tokens of the unit of the first and of the last class, which differ in size."""
+    import paper_2605_28691_amd as sk
+
+    w = si.make_shape("bwd_padshapes", 1, heads, D, T, H, W, s, seed=T + heads)
+    q, k, v = si.make_qkv(w)
+    dout = si.make_dout(w)
+    qg, kg, vg, dg = (t.cuda() for t in (q, k, v, dout))
+    out, lse = sk.skiparse_attn_fwd_lse(qg, kg, vg, T, H, W, s, pattern, scale=w.scale, pad=True)
+    grads = sk.skiparse_attn_bwd(qg, kg, vg, out, dg, lse, T, H, W, s, pattern, scale=w.scale, pad=True)
+    step = s if pattern == "group" else 1
+    n = np.arange(T * H * W)
+    cls = (n // W % H // step % s) * s + n % W // step % s
+    rng = np.random.default_rng(T * H)
+    for c, head in ((0, heads - 1), (s * s - 1, 0), (1, heads // 2)):
+        members = n[cls == c]
+        toks = [int(members[i]) for i in sorted({0, len(members) - 1, *(int(x) for x in rng.integers(0, len(members), 10))})]
+        want = oracle.skiparse_attention_bwd_unit_padded(*oracle_inputs(q, k, v), si.as_oracle_array(dout), 0, head, toks, T, H, W, s, pattern, w.scale)
+        for g, wnt, name in zip(grads, want, ("dq", "dk", "dv")):
+            assert_grad_close(to_np64(g[0, toks, head]), wnt, f"class {c} {name}")

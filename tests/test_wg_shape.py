@@ -54,6 +54,41 @@ def test_classes_without_a_token_are_no_workgroups(pick):
     assert pick([call]) == pick([dense("fwd", 64, 128, 30 * 2 * 4)])
 
 
+def _classes(n, s, group):
+    step = s if group else 1
+    return [sum(1 for x in range(n) if x // step % s == p) for p in range(s)]
+
+
+def test_gpu_tests_reach_every_shape(pick):
+    """Every kernel that a launch can take, at both head_dims, plain and in the any-resolution mode, and each with a walk that wraps the ring
+    of row offsets (more than 16 tiles of 64 rows a group), is taken by a test that compares it with the oracle: a refit of the tables that
+    moves the calls of those tests elsewhere fails here."""
+    import test_gpu_attention as fwd
+    import test_gpu_bwd as bwd
+
+    calls = []
+    for launches, module in ((("fwd",), fwd), (("dq", "dkv"), bwd)):
+        for launch in launches:
+            for D in (64, 128):
+                calls += [(launch, D, 1, heads, 1, 1, n, 1, 0, 0) for heads, n in module.WORKGROUP_SHAPES]
+                calls += [(launch, D, 1, heads, T, H, W, s, int(pattern == "group"), 1) for heads, T, H, W, s, pattern in module.PADDED_SHAPES]
+    for T, H, W, s in fwd.PADDED_GROUPS:
+        calls += [("fwd", D, 1, 2, T, H, W, s, group, 1) for D in (64, 128) for group in (0, 1)]
+    calls += [(launch, D, B, heads, T, H, W, s, group, 1) for launch in ("dq", "dkv") for B, heads, D, T, H, W, s in bwd.PAD_CASES for group in (0, 1)]
+    met, wrapped = set(), set()
+    for call, shape in zip(calls, pick(calls)):
+        launch, D, _, _, T, H, W, s, group, pad = call
+        largest = T * max(_classes(H, s, group)) * max(_classes(W, s, group)) if pad else T * H * W
+        groups = 2 if shape >= (Q64_SPLIT if launch == "fwd" else O64_SPLIT) else 1
+        met.add((launch, D, shape, pad))
+        if (largest + 63) // 64 // groups > 16:
+            wrapped.add((launch, D, shape, pad))
+    want = {("fwd", D, shape, pad) for D in (64, 128) for shape in (Q256, Q128, Q64_SPLIT, Q128_SPLIT) for pad in (0, 1)}
+    want |= {(launch, D, shape, pad) for launch in ("dq", "dkv") for D in (64, 128) for shape in (O256, O128, O64_SPLIT) for pad in (0, 1)}
+    assert met == want
+    assert wrapped == want
+
+
 def rows(row_bytes, n):
     return ("rows", row_bytes, 1, 1, 1, 1, n, 1, 0, 0)
 
