@@ -18,6 +18,11 @@
  *   - Shape rules: token-wise needs H % s == 0 and W % s == 0; group-wise needs H % (s*s) == 0 and
  *     W % (s*s) == 0 (Sec. 3.2: the smallest repeatable unit is s^2 x s^2).  s = 1 is legal: the permute is
  *     a copy and sparse attention equals full attention.
+ *   - Results are deterministic: the same call gives the same bits.  The bits of one (subsequence, head) of the bf16 attention may
+ *     depend on how many of them share the call: the number and length pick the kernel's workgroup shape, and calls of few long units
+ *     walk the keys in two halves, whose probabilities are rounded to bf16 against a reference of their own.  A batch and its
+ *     elements alone, or a layer and one rank's share of it, agree within the rounding of bf16 probabilities (2.6e-3 relative,
+ *     gradients 5e-5), not bit for bit.
  *   - Return value: SKIPARSE_OK or a negative error code.  Arguments are validated before the first HIP
  *     call, so a bad call touches no memory and launches nothing.
  */
@@ -104,7 +109,7 @@ int dense_attn_fwd(const void* q, const void* k, const void* v, void* out, int B
  *   flags = SKIPARSE_FUSED | SKIPARSE_PAD   any-resolution mode (Sec. 3.2): H and W may be arbitrary; the grid is treated as
  *                          padded at the END of H and W to the next multiples of s*s, padding positions are masked as keys
  *                          and skipped as queries.  q, k, v, out still hold only the T*H*W real tokens; no padded copy is
- *                          made (the padding is an address predicate of the fused kernel).  Without SKIPARSE_FUSED the
+ *                          made (the fused kernel walks the real tokens of every subsequence).  Without SKIPARSE_FUSED the
  *                          flag is rejected with SKIPARSE_EUNSUPPORTED.
  */
 int skiparse_attn_fwd(const void* q, const void* k, const void* v, void* out, int B, int heads, int T, int H, int W,

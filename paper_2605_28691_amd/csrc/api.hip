@@ -246,7 +246,7 @@ int skiparse_attn_fwd(const void* q, const void* k, const void* v, void* out, in
     int rc = check_shape(B, heads, T, H, W, head_dim, s, pattern, &sh, pad);
     if (rc != SKIPARSE_OK) return rc;
     if (elem_size(dtype) == 0) return SKIPARSE_EINVAL;
-    if (pad && !(flags & SKIPARSE_FUSED)) return SKIPARSE_EUNSUPPORTED;  // padding exists only as an address predicate of the fused kernel
+    if (pad && !(flags & SKIPARSE_FUSED)) return SKIPARSE_EUNSUPPORTED;  // only the fused kernel has the any-resolution walk
     if (dtype != SKIPARSE_BF16 || (head_dim != 64 && head_dim != 128)) return SKIPARSE_EUNSUPPORTED;
     const size_t bytes = sh.elems * 2;
     rc = check_attn_ranges(sh, W, 2);

@@ -64,7 +64,7 @@ constexpr int KT = 64;          // keys per staged tile (two 32-key blocks)
 static_assert(GROUP_MIN_ROWS == KT, "a key group needs a tile of its own");
 constexpr int ATTN_QT = 1;       // 32-query tiles per wavefront
 constexpr int RING_AHEAD = 8;    // row offsets are formed this many tiles ahead, by one wavefront per window in turn
-constexpr int RING = 16;         // tiles of row offsets (and key validity) kept in LDS: a slot is rewritten RING - RING_AHEAD windows after its last use
+constexpr int RING = 16;         // tiles of row offsets kept in LDS: a slot is rewritten RING - RING_AHEAD windows after its last use
 static_assert((RING & (RING - 1)) == 0 && RING >= RING_AHEAD + 4, "ring sizes");
 constexpr int LDS_AHEAD = 4;     // MFMA groups by which the LDS fragment reads run ahead in the steady state
 constexpr float RESCALE_LOG2 = 8.0f;  // the reference maximum is only raised when it grew by more than 2^8
@@ -386,10 +386,10 @@ __global__ __launch_bounds__(64 * fwd_waves(SHAPE), (SHAPE == Q128 ? 2 : 1)) voi
             const bool grow = (m_new - m_ref[qi]) * c > RESCALE_LOG2;  // same in lanes l and l^32
             grow_mask |= __builtin_amdgcn_ballot_w64(grow);
             const float m_use = grow ? m_new : m_ref[qi];
-            // 1 where the reference stays (also while it is still -inf: a block of nothing but masked keys), 0 on the first real block
+            // 1 where the reference stays, 0 on the first block (a group's first key is always a real one)
             alpha_pending[qi] = grow ? __builtin_amdgcn_exp2f((m_ref[qi] - m_use) * c) : 1.0f;
             m_ref[qi] = m_use;
-            // while no real key has been seen the reference is -inf: take 0 instead so that masked logits give exp2(-inf) = 0
+            // the reference is still -inf only if every logit so far has overflowed to -inf: take 0 instead so that they give exp2(-inf) = 0
             const float mc_use = m_use == -INFINITY ? 0.f : m_use * c;
             l_run[qi] = fmaf(l_run[qi], alpha_pending[qi], exps(s, mc_use, preg[PAR][qi]));
         }
@@ -497,8 +497,8 @@ __global__ __launch_bounds__(64 * fwd_waves(SHAPE), (SHAPE == Q128 ? 2 : 1)) voi
                 float lo, hi;
                 lane_pair(mx, lo, hi);
                 const float m_new = max3(m_ref[qi], lo, hi);
-                // while no real key has been seen (a block of nothing but padding) the reference stays -inf: factor 1, exponent 0
-                alpha_pending[qi] = m_new == -INFINITY ? 1.0f : __builtin_amdgcn_exp2f((m_ref[qi] - m_new) * c);  // 0 on the first real block
+                // -inf only if every logit so far has overflowed to -inf: factor 1, exponent 0
+                alpha_pending[qi] = m_new == -INFINITY ? 1.0f : __builtin_amdgcn_exp2f((m_ref[qi] - m_new) * c);  // 0 on the first block
                 m_ref[qi] = m_new;
                 l_run[qi] = fmaf(l_run[qi], alpha_pending[qi], exps(s, m_new == -INFINITY ? 0.f : m_new * c, preg[PAR][qi]));
             }

@@ -43,7 +43,7 @@ struct AttnArgs {
     int heads;
     int head_dim;
     float scale;    // multiplies the logits
-    bool pad;       // any-resolution mode: g describes the padded grid, padding positions are masked / skipped
+    bool pad;       // any-resolution mode: g describes the padded grid; the kernel walks the real tokens of a class only
     GridMap g;
     // Where the output rows go.  OUT_AS_INPUT: out is addressed like q.  OUT_ORIGINAL / OUT_OTHER_PATTERN: q, k, v are the
     // sparse layout of pattern g_in (so g is a dense map over its B*s*s subsequences) and the row of query (sb, j) is written
@@ -73,7 +73,7 @@ struct BwdArgs {
     int heads;
     int head_dim;
     float scale;
-    bool pad;           // any-resolution mode: g describes the padded grid; padding positions are masked keys and skipped rows
+    bool pad;           // any-resolution mode, as in AttnArgs; lse and delta are laid out over the padded grid
     GridMap g;
 };
 hipError_t launch_attn_bwd_bf16(const BwdArgs& a, hipStream_t stream);
