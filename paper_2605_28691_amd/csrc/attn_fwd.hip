@@ -141,9 +141,9 @@ __global__ __launch_bounds__(64 * fwd_waves(SHAPE), (SHAPE == Q128 ? 2 : 1)) voi
     constexpr int MT = D / 32;     // 32-row blocks of O^T
     // Small calls: offsets are formed for the tiles that exist only (those past the group's last tile are read but address nothing), and
     // keys are compared with the end only in the block that holds it: 1 to 6 % of a small launch (us, 103 units of 377 tokens at
-    // head_dim 64 12.3 -> 11.8, 144 of 160..176 in the any-resolution mode at head_dim 128 12.65 -> 12.3).  The kernel that the largest
-    // problems use is left without: it takes three registers more and 0.3 % more time there (110.8 -> 111.1 ms).
-    constexpr bool TRIM = PAD || D == 64 || SHAPE != Q256;
+    // head_dim 64 12.3 -> 11.8, 144 of 160..176 in the any-resolution mode at head_dim 128 12.65 -> 12.3).  The plain kernels of head_dim 128
+    // go without: three or four registers more cost 0.3 % at 768P (110.8 -> 111.1 ms) and 0.5 % of a 13.6 us layer of 390 tokens a unit.
+    constexpr bool TRIM = PAD || D == 64;
     constexpr int BR = 32 * QW * QT;   // query rows per workgroup: QT tiles of 32 per wavefront
     // four separate arrays: the compiler must be able to tell that the tile being filled is not the tile being read
     __shared__ __attribute__((aligned(1024))) char kbuf0_all[KG * TL::TILE_BYTES];
