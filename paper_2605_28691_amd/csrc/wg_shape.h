@@ -11,8 +11,10 @@ struct ShapeCost {
     int rows;        // rows of a workgroup
     bool split;      // two groups that walk half of the rows each
     int max_k;       // workgroups of this shape that one CU holds
-    float fixed[3];  // prologue, pipeline fill, epilogue and merge, with k = 1..max_k workgroups on a CU
-    float block[3];  // per 32-row block of the walk, the same
+    float first;     // us outside the walk (prologue, pipeline fill, epilogue, merge): the first round of workgroups,
+    float again;     // and every further one
+    float crowd;     // once, where workgroups share a CU: they start together and wait for the same loads
+    float block[4];  // us per 32-row block of the walk with 128 or fewer, 256, 512, 768 workgroups running
 };
 
 // The units of a launch: how many have any row, and the rows of the largest and of the smallest one (they differ in the any-resolution
@@ -20,31 +22,41 @@ struct ShapeCost {
 struct UnitSizes {
     uint64_t units;
     uint32_t n_max, n_min;
+    uint64_t workgroups(const ShapeCost& c) const { return units * ((n_max + (uint32_t)c.rows - 1u) / (uint32_t)c.rows); }
 };
 
+constexpr uint64_t CUS = 256;
 constexpr uint32_t GROUP_MIN_ROWS = 64;  // a group of wavefronts needs a tile of its own: units of this size or less are not split
 
-// The shape with the smallest estimated time: rounds over the 256 CUs, each as long as `fixed` plus the blocks of the walk at the cost
-// of that many workgroups per CU.  Every cost is in units of 0.1 us, fitted to launches of every shape (see the tables).  Shapes with two
-// groups are left out where the first shape, the largest, fills `split_rounds` rounds: see at the forward's tables.
-template <int N>
-inline int pick_shape(const ShapeCost (&cost)[N], const UnitSizes& u, float split_rounds) {
-    constexpr uint64_t CUS = 256;
+// us per block with `wgs` workgroups running: between the entries the cost is linear (the chip's clock falls as it fills, and CUs with two
+// workgroups slow down by and by), or with `step` that of the entry above.
+inline float block_cost(const ShapeCost& c, uint64_t wgs, bool step) {
+    const int hi = wgs <= CUS ? 1 : (int)((wgs - 1u) / CUS) + 1;
+    if (step) return c.block[hi];
+    if (wgs <= CUS / 2) return c.block[0];
+    const float from = hi == 1 ? CUS / 2 : (float)(CUS * (hi - 1)), width = hi == 1 ? CUS / 2 : CUS;
+    return c.block[hi - 1] + (c.block[hi] - c.block[hi - 1]) * ((float)wgs - from) / width;
+}
+
+// Estimated us of a launch: rounds over the CUs, the last one with what is left.
+inline float launch_cost(const ShapeCost& c, const UnitSizes& u, bool step) {
     const float blocks = (float)((u.n_max + 31u) / 32u);
-    auto workgroups = [&](int v) { return u.units * ((u.n_max + (uint32_t)cost[v].rows - 1u) / (uint32_t)cost[v].rows); };
-    const bool may_split = u.n_min > GROUP_MIN_ROWS && (float)workgroups(0) < split_rounds * (float)CUS;
+    const uint64_t wgs = u.workgroups(c), per_round = CUS * (uint64_t)c.max_k, rounds = wgs / per_round, rem = wgs % per_round;
+    float t = c.first + c.again * (float)(rounds + (rem != 0) - 1u) + (float)rounds * blocks * c.block[c.max_k];
+    if (rem != 0) t += blocks * block_cost(c, rem, step);
+    if (wgs > CUS) t += c.crowd * (wgs >= CUS + CUS / 12 ? 1.0f : 12.0f * (float)(wgs - CUS) / CUS);
+    return t;
+}
+
+// The shape with the smallest estimate among those that `admit` lets through; the first one always is.
+template <int N, typename Admit>
+inline int pick_shape(const ShapeCost (&cost)[N], const UnitSizes& u, bool step, Admit admit) {
     int best = 0;
-    float best_t = 0.f;
-    for (int v = 0; v < N; v++) {
-        if (cost[v].split && !may_split) continue;
-        const int k = cost[v].max_k;
-        const uint64_t wgs = workgroups(v), per_round = CUS * (uint64_t)k, rounds = wgs / per_round, rem = wgs % per_round;
-        float t = (float)rounds * (cost[v].fixed[k - 1] + blocks * cost[v].block[k - 1]);
-        if (rem != 0) {
-            const uint64_t last = (rem - 1u) / CUS;
-            t += cost[v].fixed[last] + blocks * cost[v].block[last];
-        }
-        if (v == 0 || t < best_t) {
+    float best_t = launch_cost(cost[0], u, step);
+    for (int v = 1; v < N; v++) {
+        if ((cost[v].split && u.n_min <= GROUP_MIN_ROWS) || !admit(cost[v])) continue;
+        const float t = launch_cost(cost[v], u, step);
+        if (t < best_t) {
             best = v;
             best_t = t;
         }
@@ -60,27 +72,32 @@ enum FwdShape : int {
     Q128_SPLIT = 4,  // 8 wavefronts, 2 groups: half the chain at two wavefronts per SIMD
 };
 
-// Costs fitted to launches of every shape over 4..1100 units of 8..80,640 tokens.  Measured, always Q256 -> picked, us at head_dim 128, units x
-// tokens: 48x390 18.6 -> 13.5, 160x960 101 -> 88, 24x2600 134 -> 85, 48x2600 213 -> 165, 1x8190 166 -> 96, 1x20160 401 -> 236, 4x20160
-// 948 -> 830; 192x240 (16.5), 84x512 (21.3), 48x960 (32) and 48x8190 (1400) keep it.  At head_dim 64: 24x2600 88 -> 52, 4x20160 640 -> 499,
-// 160x4000 865 -> 718, 160x20160 18,550 -> 17,220; 103x377 (11.8) keeps it.
-//   * Two Q128 workgroups that start together on a CU wait for the same loads, so the first round costs them more than one alone:
-//     their `fixed` is larger.  With one figure for both the rule took Q128 for 192x240 (17.3), 84x512 (22.5), 225x216 (17.7 against 16.8).
-//   * Two groups stream K and V at two places and move 4 % more per MFMA; what they gain is the idle part of the last round, and that
-//     counts only while there are few rounds: many are spread by the power limit (the clock rises as the chip empties).  In units of Q256
-//     rounds, Q256 / Q128_SPLIT, us: 1.2 948 / 830, 1.5 581 / 549, 2.5 1517 / 1509 (Q128: 1498), 6.2 3777 / 3885 (20x20160), 6.5 5738 / 6029
-//     (14x30240), 6.2 7649 / 7792 (10x40320), 6.2 15,380 / 15,590 (5x80640).  From two rounds on they are left out.
-constexpr ShapeCost FWD_COST_128[] = {{Q256, 256, false, 1, {40.f}, {9.0f}},
-                                      {Q128, 128, false, 2, {20.f, 40.f}, {5.5f, 10.0f}},
-                                      {Q64_SPLIT, 64, true, 1, {25.f}, {3.9f}},
-                                      {Q128_SPLIT, 128, true, 1, {45.f}, {4.7f}}};
-constexpr ShapeCost FWD_COST_64[] = {{Q256, 256, false, 1, {27.f}, {5.2f}},
-                                     {Q128, 128, false, 3, {15.f, 26.f, 26.f}, {3.6f, 5.7f, 7.6f}},
-                                     {Q64_SPLIT, 64, true, 2, {15.f, 15.f}, {2.4f, 3.7f}},
-                                     {Q128_SPLIT, 128, true, 1, {30.f}, {2.9f}}};
-constexpr float FWD_SPLIT_ROUNDS = 2.0f;
+// Costs fitted to 1100 calls timed in every shape (1..2700 units of 8..80,640 tokens, plain and any-resolution): the pick is 0.1 % above the
+// best shape on average and 8 % at worst (with one figure a round 0.5 % and 15 %).  Measured, always Q256 -> picked, us at
+// head_dim 128, units x tokens: 48x390 18.6 -> 13.5, 88x280 16.5 -> 14.7, 160x960 101 -> 88, 169x1550 246 -> 230, 24x2600 134 -> 85,
+// 48x2600 213 -> 165, 1x8190 166 -> 96, 1x20160 401 -> 236, 4x20160 948 -> 830; 192x240 (16.5), 34x900 (29), 84x512 (21.3), 48x960 (32),
+// 14x30240 (5740), 20x20160 (3780) and 48x8190 (1400) keep it.  At head_dim 64: 24x2600 88 -> 52, 4x20160 640 -> 499, 160x4000 865 -> 718,
+// 160x20160 18,550 -> 17,220; 103x377 (11.8) keeps it.
+//   * What a round costs depends on how full it is: a Q256 block takes 0.63 us with half of the CUs busy and 0.88 with all of them, the chip
+//     being at its power limit.  Without that the rule gave long sequences to Q128_SPLIT for a smaller last round: 14x30240 6025 us.
+//   * Two Q128 workgroups that start together on a CU wait for the same loads (`crowd`): 192x240 17.3 in that shape, 84x512 22.5.
+//   * Q64_SPLIT is for one round of its own: in a second one the traffic of four times the workgroups shows (34x900: 33.5).
+//   * The split shapes stream K and V at two places and move 4 % more per MFMA; what they gain is idle CUs, so they are left out from two
+//     rounds of Q256 on.
+constexpr ShapeCost FWD_COST_128[] = {{Q256, 256, false, 1, 4.0f, 7.3f, 0.f, {0.63f, 0.88f}},
+                                      {Q128, 128, false, 2, 3.6f, 2.6f, 2.3f, {0.40f, 0.66f, 0.96f}},
+                                      {Q64_SPLIT, 64, true, 1, 1.2f, 0.8f, 0.f, {0.29f, 0.37f}},
+                                      {Q128_SPLIT, 128, true, 1, 5.6f, 10.2f, 0.f, {0.30f, 0.46f}}};
+constexpr ShapeCost FWD_COST_64[] = {{Q256, 256, false, 1, 3.2f, 5.7f, 0.f, {0.32f, 0.524f}},
+                                     {Q128, 128, false, 3, 1.6f, 0.8f, 4.5f, {0.30f, 0.32f, 0.535f, 0.66f}},
+                                     {Q64_SPLIT, 64, true, 2, 1.8f, 1.1f, 0.f, {0.165f, 0.268f, 0.376f}},
+                                     {Q128_SPLIT, 128, true, 1, 3.2f, 6.2f, 0.f, {0.194f, 0.249f}}};
 inline int pick_fwd_shape(int head_dim, const UnitSizes& u) {
-    return pick_shape(head_dim == 128 ? FWD_COST_128 : FWD_COST_64, u, FWD_SPLIT_ROUNDS);
+    const auto& cost = head_dim == 128 ? FWD_COST_128 : FWD_COST_64;
+    return pick_shape(cost, u, false, [&](const ShapeCost& c) {
+        if (!c.split) return true;
+        return u.workgroups(cost[0]) < 2u * CUS && (c.shape != Q64_SPLIT || u.workgroups(c) <= CUS * (uint64_t)c.max_k);
+    });
 }
 
 // ---- backward.  The dQ launch's owners are queries, the dK+dV launch's keys.
@@ -93,17 +110,25 @@ enum BwdShape : int {
 // At head_dim 128 the dK+dV shapes with 4 wavefronts hold V in registers (one workgroup per CU).  Measured, always O256 -> picked, dQ and dK+dV
 // together, us at head_dim 128, units x tokens: 16x200 39.8 -> 23, 12x700 78 -> 42, 48x390 62 -> 43, 160x960 347 -> 328, 24x2600 495 -> 328,
 // 1x5000 411 -> 190, 1x20160 1534 -> 1150, 4x20160 3560 -> 3390; 48x960 (108), 30x8190 (3340), 12x20160 (7900) and 48x8190 (5190) keep it.
-constexpr ShapeCost DQ_COST_128[] = {{O256, 256, false, 1, {50.f}, {13.0f}}, {O128, 128, false, 2, {40.f, 40.f}, {9.5f, 13.4f}}, {O64_SPLIT, 64, true, 1, {40.f}, {6.3f}}};
-constexpr ShapeCost DQ_COST_64[] = {{O256, 256, false, 1, {35.f}, {8.0f}}, {O128, 128, false, 2, {28.f, 28.f}, {5.6f, 8.1f}}, {O64_SPLIT, 64, true, 2, {30.f, 30.f}, {3.4f, 6.0f}}};
-constexpr ShapeCost DKV_COST_128[] = {{O256, 256, false, 1, {80.f}, {19.0f}}, {O128, 128, false, 1, {60.f}, {13.2f}}, {O64_SPLIT, 64, true, 1, {70.f}, {8.0f}}};
-constexpr ShapeCost DKV_COST_64[] = {{O256, 256, false, 1, {50.f}, {10.0f}}, {O128, 128, false, 2, {40.f, 40.f}, {8.0f, 10.3f}}, {O64_SPLIT, 64, true, 1, {50.f}, {5.4f}}};
+constexpr ShapeCost DQ_COST_128[] = {{O256, 256, false, 1, 5.0f, 5.0f, 0.f, {0.f, 1.30f}},
+                                     {O128, 128, false, 2, 4.0f, 4.0f, 0.f, {0.f, 0.95f, 1.34f}},
+                                     {O64_SPLIT, 64, true, 1, 4.0f, 4.0f, 0.f, {0.f, 0.63f}}};
+constexpr ShapeCost DQ_COST_64[] = {{O256, 256, false, 1, 3.5f, 3.5f, 0.f, {0.f, 0.80f}},
+                                    {O128, 128, false, 2, 2.8f, 2.8f, 0.f, {0.f, 0.56f, 0.81f}},
+                                    {O64_SPLIT, 64, true, 2, 3.0f, 3.0f, 0.f, {0.f, 0.34f, 0.60f}}};
+constexpr ShapeCost DKV_COST_128[] = {{O256, 256, false, 1, 8.0f, 8.0f, 0.f, {0.f, 1.90f}},
+                                      {O128, 128, false, 1, 6.0f, 6.0f, 0.f, {0.f, 1.32f}},
+                                      {O64_SPLIT, 64, true, 1, 7.0f, 7.0f, 0.f, {0.f, 0.80f}}};
+constexpr ShapeCost DKV_COST_64[] = {{O256, 256, false, 1, 5.0f, 5.0f, 0.f, {0.f, 1.00f}},
+                                     {O128, 128, false, 2, 4.0f, 4.0f, 0.f, {0.f, 0.80f, 1.03f}},
+                                     {O64_SPLIT, 64, true, 1, 5.0f, 5.0f, 0.f, {0.f, 0.54f}}};
 
-// The split shape has no limit here: none of 80 random training steps took longer than with 256 owners alone, and a long walk gains by it
-// too (dK+dV of 1x80640, with dQ: 13.7 ms against 14.2).
+// Here one figure for a round is enough (picks 0.2 % above the best shape on average over 300 calls, 6 % at worst; with linear costs in between
+// 0.4 % and 13 %), and the split shape has no limit: none of 80 random training steps took longer than with 256 owners alone, and a
+// long walk gains by it too (dK+dV of 1x80640, with dQ: 13.7 ms against 14.2).
 inline int pick_bwd_shape(bool dkv, int head_dim, const UnitSizes& u) {
-    const float no_limit = 3.4e38f;
-    if (dkv) return pick_shape(head_dim == 128 ? DKV_COST_128 : DKV_COST_64, u, no_limit);
-    return pick_shape(head_dim == 128 ? DQ_COST_128 : DQ_COST_64, u, no_limit);
+    const auto& cost = dkv ? (head_dim == 128 ? DKV_COST_128 : DKV_COST_64) : (head_dim == 128 ? DQ_COST_128 : DQ_COST_64);
+    return pick_shape(cost, u, true, [](const ShapeCost&) { return true; });
 }
 
 // ---- row moves: how many rows of `chunks` 16-byte chunks one wavefront moves.

@@ -271,7 +271,7 @@ def test_largest_admitted_batch_element_sampled_rows():
 # tile of one row, many and few units, walks of more than the 16 tiles that the row-offset ring holds.  test_wg_shape.py says which
 # shape each takes.
 WORKGROUP_SHAPES = [(1, 65), (2, 128), (1, 129), (3, 321), (80, 65), (200, 129), (300, 33), (4, 1921), (90, 449), (12, 2497), (24, 700), (29, 1100),
-                    (52, 1100), (1, 2200), (8, 2100)]
+                    (30, 1100), (52, 1100), (1, 2200), (8, 2100)]
 
 
 @pytest.mark.parametrize("heads,N", WORKGROUP_SHAPES)
@@ -320,6 +320,7 @@ PADDED_SHAPES = [  # heads, T, H, W, s, pattern: every workgroup shape in the an
     (4, 7, 33, 37, 3, "group"),
     (7, 7, 33, 37, 3, "group"),
     (2, 7, 33, 37, 3, "token"),
+    (1, 7, 33, 37, 2, "token"),
     (1, 11, 33, 37, 2, "token"),  # classes of 50, 53 and 56 key tiles in two groups: an odd count leaves one group a barrier short
     (1, 21, 30, 33, 3, "token"),
 ]

@@ -32,20 +32,28 @@ def dense(launch, D, units, n):
 
 def test_two_key_groups_only_while_the_large_shape_leaves_the_chip_idle(pick):
     """Splitting the keys pays while the 256-query shape has less than two rounds of workgroups; with more it lost 1 to 7 %."""
-    few = [(1, 8190), (2, 12000), (1, 20160), (4, 20160), (1, 32760), (8, 384), (24, 384)]
-    assert all(x in (Q64_SPLIT, Q128_SPLIT) for x in pick([dense("fwd", 128, *c) for c in few]))
+    few = [(1, 8190), (2, 12000), (1, 20160), (1, 32760), (8, 384), (24, 384)]
+    assert all(x in (Q64_SPLIT, Q128_SPLIT) for x in pick([dense("fwd", D, *c) for c in few for D in (64, 128)]))
+    assert pick([dense("fwd", 128, 4, 20160)]) == [Q128_SPLIT]
     many = [(20, 20160), (14, 30240), (10, 40320), (5, 80640), (63, 11340), (20, 8190), (40, 20160), (160, 20160)]
     assert all(x in (Q256, Q128) for x in pick([dense("fwd", D, *c) for c in many for D in (64, 128)]))
-    # at six rounds and more Q256 is the best of the two at head_dim 128
+    # at six rounds and more Q256 is the better one at head_dim 128, Q128 at head_dim 64
     assert pick([dense("fwd", 128, *c) for c in many[:5] + many[6:]]) == [Q256] * 7
+    assert pick([dense("fwd", 64, *c) for c in many]) == [Q128] * 8
+
+
+def test_sixty_four_query_workgroups_only_in_one_round(pick):
+    """A second round of them is slower than half as many large workgroups (34 units of 900 tokens: 33.5 us against 29)."""
+    assert pick([dense("fwd", 128, *c) for c in ((34, 900), (33, 900), (55, 547), (29, 1061))]) == [Q256] * 4
+    assert pick([dense("fwd", 128, *c) for c in ((16, 900), (28, 576), (24, 384))]) == [Q64_SPLIT] * 3
 
 
 def test_one_round_of_the_large_shape_keeps_it_against_two_small_workgroups_a_cu(pick):
     """Measured 1 to 10 % faster in one round of 256-query workgroups than in twice as many of 128 queries, two on most CUs."""
-    assert pick([dense("fwd", 128, *c) for c in ((192, 240), (84, 512), (225, 216), (96, 384), (148, 256), (48, 960))]) == [Q256] * 6
-    assert pick([dense("fwd", 64, 103, 377), dense("fwd", 64, 108, 384), ("fwd", 64, 3, 30, 1, 32, 21, 2, 1, 1)])[0] == Q256
-    # where the small workgroups are alone on their CUs, or the large ones would need a second round, they stay
-    assert pick([dense("fwd", 128, *c) for c in ((48, 390), (112, 144), (24, 2600), (48, 2600), (432, 64))]) == [Q128] * 5
+    assert pick([dense("fwd", 128, *c) for c in ((192, 240), (84, 512), (225, 216), (152, 140), (148, 256), (48, 960))]) == [Q256] * 6
+    assert pick([dense("fwd", 64, *c) for c in ((103, 377), (108, 384), (180, 140))]) == [Q256] * 3
+    # where nearly all small workgroups are alone on their CUs, or the large ones would need another round, they stay
+    assert pick([dense("fwd", 128, *c) for c in ((48, 390), (88, 280), (112, 144), (24, 2600), (48, 2600), (432, 64), (169, 1550))]) == [Q128] * 7
 
 
 def test_classes_without_a_token_are_no_workgroups(pick):
