@@ -231,4 +231,97 @@ inline void make_pad_arg(const GridMap&, NoPadMap&) {}
 inline void make_pad_arg(const GridMap& g, PadMap& m) { m = make_pad_map(g); }
 inline ClassMap make_class_map(const GridMap& g, uint32_t p, uint32_t q) { return make_class_map(g, make_pad_map(g), p, q); }
 
+// ---- row moves: every row of one layout and where it is in another
+enum RowMap : int {
+    TO_SPARSE = 0,  // destination: the sparse layout, source: the original one
+    TO_ORIGINAL = 1,  // the inverse
+    SWITCH = 2      // destination: the sparse layout of g's pattern, source: that of the other pattern
+};
+
+// ssp_G > 0 (Sparse Sequence Parallelism, Alg. 1 sparse_sequence_parallel, step 3): the sparse side is a buffer as it arrives from the
+// all-to-all, [source rank][my subsequence g'][source's subsequence g][b][position]; the algorithm's axis swap to
+// [source rank][g][g'][b] = "(p q b')" order is folded into the row number instead of being a pass of its own.
+__host__ __device__ inline uint32_t ssp_received_sb(uint32_t sb, uint32_t B, uint32_t G) {
+    const uint32_t b = B / G;                        // batch elements per subsequence
+    const uint32_t pq = sb / B, bi = sb - pq * B;    // class of the source pattern; (g', batch element)
+    const uint32_t r = pq / G, gs = pq - r * G, gd = bi / b, bb = bi - gd * b;
+    return ((r * G + gd) * G + gs) * b + bb;
+}
+
+// Division of any 32-bit n by any run-time constant d: the high 64 bits of n * ceil(2^64 / d), exact without a condition on the sizes
+// (the multiplier is off by less than 1, the quotient by less than n / 2^64 < 1 / d).  Six scalar instructions where n is the same in every lane.
+struct Div32 {
+    uint32_t d, lo, hi, one;  // one: d = 1, whose multiplier would be 2^64
+    __host__ __device__ inline uint32_t div(uint32_t n) const {
+#if defined(__HIP_DEVICE_COMPILE__)
+        const uint32_t low = __umulhi(n, lo);
+#else
+        const uint32_t low = (uint32_t)(((uint64_t)n * lo) >> 32);
+#endif
+        return (uint32_t)(((uint64_t)n * hi + low) >> 32) + n * one;
+    }
+};
+inline Div32 make_div32(uint32_t d) {
+    const uint64_t m = d <= 1u ? 0u : ~0ull / d + 1u;
+    return {d, (uint32_t)m, (uint32_t)(m >> 32), d <= 1u ? 1u : 0u};
+}
+
+// What the row numbers of both sides are made of, for destination rows of one RowMap.
+struct RowArgs {
+    Div32 n_row;    // rows of a subsequence (destination sparse) or of a batch element (destination original)
+    Div32 row_len;  // W / s (destination sparse) or W
+    Div32 B, s;
+    uint32_t W, Ws, n_tok, n_sub;
+    int mode;
+};
+
+// Algorithm 1's index maps along one axis.  x = t*H + h or w (H and W are multiples of s, and of s*s for the group-wise pattern, so t*H + h
+// splits like h); (cls, pos) = the class and the place inside it.
+__host__ __device__ inline void split_axis(bool group, const Div32& s, uint32_t x, uint32_t& cls, uint32_t& pos) {
+    const uint32_t a = s.div(x), m = x - a * s.d;
+    if (!group) {
+        cls = m;
+        pos = a;
+        return;
+    }
+    const uint32_t a2 = s.div(a);
+    cls = a - a2 * s.d;
+    pos = a2 * s.d + m;
+}
+__host__ __device__ inline uint32_t join_axis(bool group, const Div32& s, uint32_t cls, uint32_t pos) {
+    if (!group) return pos * s.d + cls;
+    const uint32_t a = s.div(pos);
+    return (a * s.d + cls) * s.d + (pos - a * s.d);
+}
+
+// row number in the source of destination row `row`
+template <int MAP>
+__host__ __device__ inline uint32_t source_row(const RowArgs& g, uint32_t row, uint32_t ssp_G) {
+    if (g.mode == MODE_DENSE) return row;
+    const bool group = g.mode == MODE_GROUP;
+    const uint32_t o = g.n_row.div(row), j = row - o * g.n_row.d;  // outer number, row inside it
+    const uint32_t r = g.row_len.div(j), c = j - r * g.row_len.d;
+    uint32_t b = o, th = r, w = c;  // TO_ORIGINAL
+    if (MAP != TO_ORIGINAL) {
+        const uint32_t pq = g.B.div(o), p = g.s.div(pq);
+        b = o - pq * g.B.d;
+        th = join_axis(group, g.s, p, r);
+        w = join_axis(group, g.s, pq - p * g.s.d, c);
+        if (MAP == TO_SPARSE) return b * g.n_tok + th * g.W + w;
+    }
+    uint32_t p, q, pr, pc;
+    split_axis(MAP == SWITCH ? !group : group, g.s, th, p, pr);
+    split_axis(MAP == SWITCH ? !group : group, g.s, w, q, pc);
+    uint32_t sb = (p * g.s.d + q) * g.B.d + b;
+    if (MAP == TO_ORIGINAL && ssp_G) sb = ssp_received_sb(sb, g.B.d, ssp_G);
+    return sb * g.n_sub + pr * g.Ws + pc;
+}
+
+// Host side: g describes the destination's pattern for TO_SPARSE and SWITCH, the source's for TO_ORIGINAL.
+template <int MAP>
+inline RowArgs make_row_args(const GridMap& g, uint32_t B) {
+    const uint32_t W = (uint32_t)g.W, Ws = W / (uint32_t)g.s, n_tok = (uint32_t)g.n_tok, n_sub = (uint32_t)g.n_sub;
+    return {make_div32(MAP == TO_ORIGINAL ? n_tok : n_sub), make_div32(MAP == TO_ORIGINAL ? W : Ws), make_div32(B), make_div32((uint32_t)g.s), W, Ws, n_tok, n_sub, g.mode};
+}
+
 }  // namespace skiparse

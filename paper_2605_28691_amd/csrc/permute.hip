@@ -2,7 +2,11 @@
 // their inverses), and between the two sparse orders.  Bound by HBM bandwidth: every row of heads*head_dim elements is contiguous in
 // both layouts.  The wavefronts enumerate DESTINATION rows and find each row's source with the index map or its inverse: contiguous
 // writes with gathered reads measure faster than the reverse.
-//   * Longer rows: one wavefront moves one row with 16-byte accesses per lane (1 KiB contiguous per instruction).
+//   * Longer rows: one wavefront moves 1 KiB of a row, one 16-byte access a lane, and the next ones the rest of it.  What is in flight then
+//     lies close together (8 MB on the whole chip, not 80), and the copy runs at 6.5 TB/s; a wavefront a row of 10 KiB with five loads in
+//     flight reached 5.7, with two 6.2.  Every wavefront forms its row number anew, so the divisions are multiplications on the scalar unit
+//     (Div32): with the compiler's own they bound the copy (permute, switch and unpermute of 80,640 rows of 10 KiB 872 us, in parts of 1 KiB
+//     795, with Div32 756).  Rows that fill the last 1 KiB badly go in parts of up to 2 KiB: row_unroll() in wg_shape.h.
 //   * Rows up to 768 B: one wavefront moves a batch of rows.  A wavefront a row leaves most lanes idle and spends the index arithmetic, some
 //     ten integer divisions, on a few hundred bytes; here lane i finds the source of row i, one evaluation for the whole batch, and
 //     the batch is moved as one run of 16-byte chunks.  The rule is row_batch() in wg_shape.h.
@@ -14,88 +18,38 @@ typedef __attribute__((ext_vector_type(4))) unsigned int u32x4;
 
 constexpr int PERMUTE_WAVES = 4;  // wavefronts per workgroup
 
-enum RowMap : int {
-    TO_SPARSE = 0,  // destination: the sparse layout, source: the original one
-    TO_ORIGINAL = 1,  // the inverse
-    SWITCH = 2      // destination: the sparse layout of g's pattern, source: that of the other pattern
-};
-
-// ssp_G > 0 (Sparse Sequence Parallelism, Alg. 1 sparse_sequence_parallel, step 3): the sparse side is a buffer as it arrives from the
-// all-to-all, [source rank][my subsequence g'][source's subsequence g][b][position]; the algorithm's axis swap to
-// [source rank][g][g'][b] = "(p q b')" order is folded into the row number instead of being a pass of its own.
-__device__ inline uint32_t ssp_received_sb(uint32_t sb, uint32_t B, uint32_t G) {
-    const uint32_t b = B / G;                        // batch elements per subsequence
-    const uint32_t pq = sb / B, bi = sb - pq * B;    // class of the source pattern; (g', batch element)
-    const uint32_t r = pq / G, gs = pq - r * G, gd = bi / b, bb = bi - gd * b;
-    return ((r * G + gd) * G + gs) * b + bb;
-}
-
-// token (b, t*H + h, w) -> its row in the sparse layout of one pattern (Alg. 1 read backwards; H and W are multiples of s for the
-// token-wise pattern and of s*s for the group-wise one, so t*H + h splits like h)
-__device__ inline uint32_t sparse_row_of(bool group, uint32_t s, uint32_t W, uint32_t n_sub, uint32_t B, uint32_t b, uint32_t n, uint32_t ssp_G) {
-    const uint32_t th = n / W, w = n - th * W;
-    uint32_t p, q, r, ws;
-    if (group) {
-        p = (th / s) % s;
-        q = (w / s) % s;
-        r = (th / (s * s)) * s + th % s;
-        ws = (w / (s * s)) * s + w % s;
-    } else {
-        p = th % s;
-        q = w % s;
-        r = th / s;
-        ws = w / s;
-    }
-    uint32_t sb = (p * s + q) * B + b;
-    if (ssp_G) sb = ssp_received_sb(sb, B, ssp_G);
-    return sb * n_sub + r * (W / s) + ws;
-}
-
-// row number in the source of destination row `row`
-template <int MAP>
-__device__ inline uint32_t source_row(const GridMap& g, uint32_t B, uint32_t row, uint32_t ssp_G) {
-    const uint32_t s = (uint32_t)g.s, W = (uint32_t)g.W, n_sub = (uint32_t)g.n_sub;
-    if (MAP == TO_ORIGINAL) {
-        if (g.mode == MODE_DENSE) return row;
-        const uint32_t b = row / (uint32_t)g.n_tok;
-        return sparse_row_of(g.mode == MODE_GROUP, s, W, n_sub, B, b, row - b * (uint32_t)g.n_tok, ssp_G);
-    }
-    const uint32_t sb = row / n_sub, j = row - sb * n_sub;
-    const uint32_t pq = sb / B, b = sb - pq * B;
-    const uint32_t p = pq / s, tok = src_token(g, p, pq - p * s, j);
-    return MAP == SWITCH ? sparse_row_of(g.mode != MODE_GROUP, s, W, n_sub, B, b, tok, 0u) : b * (uint32_t)g.n_tok + tok;
-}
-
 template <int MAP, int UNROLL>
-__global__ __launch_bounds__(PERMUTE_WAVES * 64) void permute_rows_kernel(const u32x4* __restrict__ src, u32x4* __restrict__ dst, int B, GridMap g,
-                                                                       uint32_t chunks_per_row, uint32_t n_rows, uint32_t ssp_G) {
+__global__ __launch_bounds__(PERMUTE_WAVES * 64) void permute_rows_kernel(const u32x4* __restrict__ src, u32x4* __restrict__ dst, RowArgs g, Div32 parts,
+                                                                          uint32_t span, uint32_t chunks, uint32_t n_rows, uint32_t ssp_G) {
     const uint32_t lane = threadIdx.x & 63u;
-    const uint32_t row = blockIdx.x * PERMUTE_WAVES + (threadIdx.x >> 6);
+    const uint32_t id = __builtin_amdgcn_readfirstlane(blockIdx.x * PERMUTE_WAVES + (threadIdx.x >> 6));
+    const uint32_t row = parts.div(id), part = id - row * parts.d;
     if (row >= n_rows) return;
-    const u32x4* s = src + (size_t)source_row<MAP>(g, (uint32_t)B, row, ssp_G) * chunks_per_row;
-    u32x4* d = dst + (size_t)row * chunks_per_row;
-    uint32_t c = lane;
-    for (; c + (UNROLL - 1) * 64u < chunks_per_row; c += UNROLL * 64u) {
+    const u32x4* s = src + (size_t)source_row<MAP>(g, row, ssp_G) * chunks;
+    u32x4* d = dst + (size_t)row * chunks;
+    const uint32_t from = part * span, to = from + span < chunks ? from + span : chunks;
+    for (uint32_t c = from + lane; c < to; c += UNROLL * 64u) {  // one round, but for tensors of more than MAX_ROW_WAVES spans
         u32x4 tmp[UNROLL];
 #pragma unroll
-        for (int u = 0; u < UNROLL; u++) tmp[u] = __builtin_nontemporal_load(s + c + u * 64u);
+        for (int u = 0; u < UNROLL; u++)
+            if (u == 0 || c + u * 64u < to) tmp[u] = __builtin_nontemporal_load(s + c + u * 64u);
 #pragma unroll
-        for (int u = 0; u < UNROLL; u++) __builtin_nontemporal_store(tmp[u], d + c + u * 64u);
+        for (int u = 0; u < UNROLL; u++)
+            if (u == 0 || c + u * 64u < to) __builtin_nontemporal_store(tmp[u], d + c + u * 64u);
     }
-    for (; c < chunks_per_row; c += 64u) __builtin_nontemporal_store(__builtin_nontemporal_load(s + c), d + c);
 }
 
 constexpr int BATCH_UNROLL = BATCH_CHUNKS / 64;  // a full batch in one round of loads
 static_assert(BATCH_UNROLL * 64 == BATCH_CHUNKS, "whole rounds of the wavefront");
 
 template <int MAP>
-__global__ __launch_bounds__(PERMUTE_WAVES * 64) void permute_short_rows_kernel(const u32x4* __restrict__ src, u32x4* __restrict__ dst, int B, GridMap g,
+__global__ __launch_bounds__(PERMUTE_WAVES * 64) void permute_short_rows_kernel(const u32x4* __restrict__ src, u32x4* __restrict__ dst, RowArgs g,
                                                                              FastDiv chunks, uint32_t n_rows, uint32_t batch, uint32_t ssp_G) {
     const uint32_t lane = threadIdx.x & 63u;
     const uint32_t row0 = (blockIdx.x * PERMUTE_WAVES + (threadIdx.x >> 6)) * batch;  // n_rows < 2^31: no overflow
     if (row0 >= n_rows) return;
     const uint32_t n = n_rows - row0 < batch ? n_rows - row0 : batch;  // at most 64
-    const uint32_t from = source_row<MAP>(g, (uint32_t)B, row0 + (lane < n ? lane : n - 1u), ssp_G);
+    const uint32_t from = source_row<MAP>(g, row0 + (lane < n ? lane : n - 1u), ssp_G);
     u32x4* const d = dst + (size_t)row0 * chunks.d;
     const uint32_t total = n * chunks.d;  // at most BATCH_CHUNKS: the division below is exact
     u32x4 tmp[BATCH_UNROLL];
@@ -113,9 +67,10 @@ __global__ __launch_bounds__(PERMUTE_WAVES * 64) void permute_short_rows_kernel(
 }
 
 template <int MAP, int UNROLL>
-static void launch_long(const void* src, void* dst, int B, const GridMap& g, uint32_t chunks, uint32_t n_rows, uint32_t ssp_G, hipStream_t stream) {
-    const uint32_t blocks = (n_rows + PERMUTE_WAVES - 1) / PERMUTE_WAVES;
-    permute_rows_kernel<MAP, UNROLL><<<blocks, PERMUTE_WAVES * 64, 0, stream>>>((const u32x4*)src, (u32x4*)dst, B, g, chunks, n_rows, ssp_G);
+static void launch_long(const void* src, void* dst, const RowArgs& g, uint32_t chunks, uint32_t n_rows, uint32_t ssp_G, hipStream_t stream) {
+    const uint32_t span = row_span(chunks, n_rows, UNROLL), parts = (chunks + span - 1u) / span;
+    const uint32_t blocks = (n_rows * parts + PERMUTE_WAVES - 1) / PERMUTE_WAVES;
+    permute_rows_kernel<MAP, UNROLL><<<blocks, PERMUTE_WAVES * 64, 0, stream>>>((const u32x4*)src, (u32x4*)dst, g, make_div32(parts), span, chunks, n_rows, ssp_G);
 }
 
 template <int MAP>
@@ -124,15 +79,14 @@ static hipError_t launch_rows(const void* src, void* dst, int B, const GridMap& 
     const uint32_t s2 = g.mode == MODE_DENSE ? 1u : (uint32_t)(g.s * g.s);
     const uint32_t n_rows = (uint32_t)B * s2 * (uint32_t)g.n_sub;
     const uint32_t batch = row_batch(chunks, n_rows);
+    const RowArgs args = make_row_args<MAP>(g, (uint32_t)B);
     if (batch > 1u) {
         const uint32_t per_block = batch * PERMUTE_WAVES, blocks = (n_rows + per_block - 1) / per_block;
-        permute_short_rows_kernel<MAP><<<blocks, PERMUTE_WAVES * 64, 0, stream>>>((const u32x4*)src, (u32x4*)dst, B, g, make_fastdiv32(chunks), n_rows, batch, ssp_G);
-    } else if (chunks >= 5 * 64) {
-        launch_long<MAP, 5>(src, dst, B, g, chunks, n_rows, ssp_G, stream);
-    } else if (chunks >= 3 * 64) {
-        launch_long<MAP, 3>(src, dst, B, g, chunks, n_rows, ssp_G, stream);
+        permute_short_rows_kernel<MAP><<<blocks, PERMUTE_WAVES * 64, 0, stream>>>((const u32x4*)src, (u32x4*)dst, args, make_fastdiv32(chunks), n_rows, batch, ssp_G);
+    } else if (row_unroll(chunks) == 2u) {
+        launch_long<MAP, 2>(src, dst, args, chunks, n_rows, ssp_G, stream);
     } else {
-        launch_long<MAP, 1>(src, dst, B, g, chunks, n_rows, ssp_G, stream);
+        launch_long<MAP, 1>(src, dst, args, chunks, n_rows, ssp_G, stream);
     }
     return hipGetLastError();
 }

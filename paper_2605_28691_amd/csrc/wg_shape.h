@@ -146,4 +146,21 @@ inline uint32_t row_batch(uint32_t chunks, uint32_t n_rows) {
     return batch;
 }
 
+
+// Longer rows: parts of 64 chunks a wavefront, or of up to 128 (two loads in flight) where parts of 64 would leave more than a fifth of the
+// lanes idle.  Permute, switch and unpermute together, us, a wavefront a row / parts of 64 / of 128: 80,640 rows of 80 chunks 110 / 121 / 105,
+// 32,256 of 144 chunks 85.4 / 84.4 / 80.9, 81,648 of 112 chunks 150 / 147 / 153, 80,640 of 192 chunks 248 / 233 / 239, of 640 chunks
+// 872 / 757 / 830.
+inline uint32_t row_unroll(uint32_t chunks) {
+    const uint32_t lanes = (chunks + 63u) / 64u * 64u;
+    return chunks > 64u && 5u * chunks < 4u * lanes ? 2u : 1u;
+}
+constexpr uint32_t MAX_ROW_WAVES = 1u << 25;  // a grid holds fewer than 2^32 work items; more rows than that keep a wavefront each
+// chunks a wavefront moves: equal parts of whole 128-byte lines
+inline uint32_t row_span(uint32_t chunks, uint32_t n_rows, uint32_t unroll) {
+    uint32_t parts = (chunks + 64u * unroll - 1u) / (64u * unroll);
+    while (parts > 1u && (uint64_t)n_rows * parts > MAX_ROW_WAVES) parts = (parts + 1u) / 2u;
+    return ((chunks + parts - 1u) / parts + 7u) / 8u * 8u;
+}
+
 }  // namespace skiparse

@@ -143,3 +143,10 @@ def test_short_rows_bit_exact(row_bytes, B, T, H, W, s):
 def test_short_rows_in_full_batches(row_bytes):
     """134,640 rows: batches of 64 rows, one a lane (fewer rows get smaller batches), the last of 48."""
     test_short_rows_bit_exact(row_bytes, 1, 33, 68, 60, 2)
+
+
+# Longer rows are moved in parts: rows just above a batch, of one part, of one part and a chunk, of parts that are not full, of many.
+@pytest.mark.parametrize("row_bytes", [784, 1024, 1040, 1280, 1792, 2304, 10240, 10256])
+@pytest.mark.parametrize("B,T,H,W,s", [(1, 2, 16, 16, 2), (2, 1, 18, 9, 3), (1, 3, 5, 7, 1)])
+def test_long_rows_bit_exact(row_bytes, B, T, H, W, s):
+    test_short_rows_bit_exact(row_bytes, B, T, H, W, s)

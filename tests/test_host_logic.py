@@ -24,3 +24,14 @@ def test_lds_tile_layout_is_consistent_and_conflict_free(tmp_path):
     out = subprocess.run([exe], stdout=subprocess.PIPE, text=True)
     assert out.returncode == 0, out.stdout
     assert out.stdout.startswith("ok")
+
+
+def test_row_moves_match_plain_formulas(tmp_path):
+    """Source rows of the row moves, their division, and the parts that long rows are moved in (host check)."""
+    exe = str(tmp_path / "host_row_moves_check")
+    src = os.path.join(ROOT, "tests", "host_row_moves_check.cpp")
+    subprocess.check_call(["/opt/rocm/bin/hipcc", "-x", "hip", "--offload-arch=gfx950", "-O1", "-std=c++17",
+                           "-Wno-unused-command-line-argument", "-o", exe, src])
+    out = subprocess.run([exe], stdout=subprocess.PIPE, text=True)
+    assert out.returncode == 0, out.stdout
+    assert out.stdout.startswith("ok")
