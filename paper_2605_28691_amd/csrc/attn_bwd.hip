@@ -1,23 +1,25 @@
 // bf16 flash-attention backward for gfx950 with the Skiparse row addressing folded in (the layer is fine-tuned, Sec. 4.1, so
 // it needs gradients).  For every attention unit (a subsequence and a head), with P = softmax(scale Q K^T) recomputed from
 // the forward's log-sum-exp L:
-//     delta_i = sum_d dO_id O_id                      (= sum_j P_ij dP_ij; formed by the dQ launch, whose owner rows hold dO)
+//     delta_i = sum_d dO_id O_id                      (= sum_j P_ij dP_ij; formed by the dQ launch, whose owner rows hold dO, or beforehand)
 //     dP = dO V^T,  dS = P o (dP - delta 1^T)
 //     dQ = scale dS K,   dK = scale dS^T Q,   dV = P^T dO
-// Two launches of one kernel template, each the forward kernel's scheme with the roles of the tensors exchanged: a lane OWNS
-// one row (a query in the dQ launch, a key in the dK+dV launch) and the rows of the other side are STREAMED through LDS in
-// tiles of 64:
+// One scheme for both kinds of gradient, the forward kernel's with the roles of the tensors exchanged: a lane OWNS one row (a query for
+// dQ, a key for dK+dV) and the rows of the other side are STREAMED through LDS in tiles of 64 or 32:
 //     M1^T[streamed, owner] = A1 B1^T      (dQ: K Q^T;     dK+dV: Q K^T)         A1 from LDS, B1 = owner (registers)
 //     M2^T[streamed, owner] = A2 B2^T      (dQ: V dO^T;    dK+dV: dO V^T)        A2 from LDS, B2 = owner (dQ: registers, dK+dV: LDS)
 //     R = elementwise(M1, M2)              (dS; in the dK+dV launch also P)       registers, rounded to bf16
 //     acc^T[channel, owner] += A3^T R      (dQ: K^T dS^T;  dK: Q^T dS;  dV: dO^T P)   A3 read from LDS with the transposing read
 // As in the forward kernel the 32x32 accumulator layout gives every lane one owner column, so R's registers are directly the
 // B operand of the last product, and the owner's gradient rows are accumulated in registers and written once: no atomics, the
-// result is deterministic.  dK and dV share one launch (S and dP are formed once for both: 7 matrix products in all against the
+// result is deterministic.  dK and dV share one walk (S and dP are formed once for both: 7 matrix products in all against the
 // 5 of the definition); their two accumulators take 128 registers at head_dim 128, so the owner's V rows are kept in LDS where two
 // wavefronts share a SIMD.
-//   * Small problems get smaller workgroups, and two groups of wavefronts that walk half of the streamed rows each and add their
-//     accumulators through LDS at the end (in a fixed order, so the result stays deterministic): see wg_shape.h.
+//   * The large problems whose rounds of workgroups are full take a launch of each kind in workgroups of 256 owners, the least traffic per MFMA.
+//     All others take ONE launch in smaller workgroups, the dK+dV ones first: a launch of each kind leaves the chip half idle in its last
+//     round, which is the only one of a small problem, and two workgroups of different kinds on a CU overlap one's elementwise arithmetic
+//     with the other's MFMAs.  Few units walk the streamed rows in two groups of wavefronts, half each, that add their accumulators
+//     through LDS at the end (in a fixed order, so the result stays deterministic).  The rule and what it measured: wg_shape.h.
 //   * log-sum-exp and delta are per QUERY: per-lane constants in the dQ launch; in the dK+dV launch per-streamed-row values,
 //     staged in LDS next to the tile as -L/scale and -delta and used as the INITIAL accumulators of M1 and M2, so that
 //     P = exp2(M1 * c) and dS = P o M2 need no further arithmetic (-inf / 0 for rows that must contribute nothing).
@@ -41,59 +43,56 @@ typedef __attribute__((ext_vector_type(16))) float f32x16;
 
 #define LDS_PTR(T) __attribute__((address_space(3))) T*
 
-constexpr int BT = 64;             // streamed rows per tile
-static_assert(GROUP_MIN_ROWS == BT, "a group needs a tile of its own");
+constexpr int BT64 = 64;           // streamed rows per tile, but where LDS has to hold two workgroups
+static_assert(GROUP_MIN_ROWS == BT64, "a group needs a tile of its own");
 constexpr float LOG2E = 1.4426950408889634f;
-constexpr int BRING_AHEAD = 8;   // row offsets are formed this many tiles ahead, by one wavefront per tile in turn
-constexpr int BRING = 16;          // tiles of row offsets kept in LDS
+constexpr int BRING_AHEAD = 8;   // row offsets are formed this many groups of 64 rows ahead, by one wavefront per group in turn
+constexpr int BRING = 16;          // groups of 64 row offsets kept in LDS
 static_assert((BRING & (BRING - 1)) == 0 && BRING >= BRING_AHEAD + 4, "ring sizes");
+
+// LDS of a workgroup
+struct BwdLds {
+    char *s1buf0, *s1buf1, *s2buf0, *s2buf1;  // two streamed tensors, double buffered
+    char* own2;                               // the owners' second operand, where it lives in LDS
+    float *row_l, *row_d;                     // initial M1 and M2 per streamed row of both buffers (dK+dV)
+    uint32_t* rowoff;                         // byte offsets of the streamed rows of the next tiles
+};
 
 // PAD: any-resolution mode (Sec. 3.2): the kernel walks the real tokens of the class only (ClassMap), so that a padding position is
 // never met; log-sum-exp and delta are laid out over the padded grid.
-template <int D, int MODE, int NW, int KG, bool PAD>
-__global__ __launch_bounds__(64 * NW, (NW == 4 && KG == 1 && (MODE == BWD_DQ || D == 64) ? 2 : 1)) void attn_bwd_kernel(BwdArgs a, PadArg<PAD> pad_map, uint32_t o_tiles, uint32_t total, uint32_t per_xcd) {
+// lin: number of the workgroup in the (unit, owner tile) order.  DELTA: the dQ part forms delta (else it is there already).
+template <int D, int MODE, int NW, int KG, int BT, bool OWN2_LDS, bool DELTA, bool PAD>
+__device__ __attribute__((always_inline)) inline void bwd_part(const BwdArgs& a, const PadArg<PAD>& pad_map, uint32_t lin, uint32_t o_tiles, const BwdLds& lds) {
     constexpr int KS = D / 16;   // MFMA steps along head_dim
     constexpr int MT = D / 32;   // 32-channel blocks of the gradient row
     constexpr int CH = D / 8;    // 16-byte chunks per row
     constexpr int RB = D * 2;    // row bytes in LDS (packed rows, swizzled chunk positions)
     constexpr int RPI = 64 / CH; // rows filled by one direct-to-LDS instruction of a wavefront
     constexpr int QW = NW / KG;  // wavefronts of a group: each owns 32 rows, all walk the same streamed rows
-    constexpr int IPW = CH / QW; // such instructions per wavefront, tensor and tile
+    constexpr int IPW = BT / RPI / QW; // such instructions per wavefront, tensor and tile
     constexpr int WGO = 32 * QW;         // owners per workgroup
     constexpr bool DKV = MODE == BWD_DKV; // dK and dV together: two accumulators
-    constexpr bool OWN2_LDS = DKV && NW == 8;  // the owners' second operand (V) lives in LDS
     // LDS fragments are read AH MFMA groups before their use and the order is pinned with scheduling fences, so that an MFMA
     // waits only for its own operands (left to itself the compiler issues each read right before the MFMA that needs it).
     // The dK+dV launch with 8 wavefronts has almost no registers to spare: 1 group ahead in the first two products and 2 in the last
     // two is what fits without spilling into the MFMA chains (deeper variants measure 2-14 % slower).
     constexpr int AH_A = OWN2_LDS ? 1 : 4, AH_C = OWN2_LDS ? 2 : 4;
     constexpr int TILE_BYTES = BT * RB;
-    static_assert(IPW >= 1 && IPW * QW == CH, "a tile is CH instructions, spread evenly over the wavefronts");
-    // two streamed tensors, double buffered; separate arrays so that the compiler can tell the tile being filled from the one
-    // being read
-    __shared__ __attribute__((aligned(1024))) char s1buf0_all[KG * TILE_BYTES];
-    __shared__ __attribute__((aligned(1024))) char s1buf1_all[KG * TILE_BYTES];
-    __shared__ __attribute__((aligned(1024))) char s2buf0_all[KG * TILE_BYTES];
-    __shared__ __attribute__((aligned(1024))) char s2buf1_all[KG * TILE_BYTES];
-    __shared__ __attribute__((aligned(1024))) char own2buf[OWN2_LDS ? WGO * RB : 16];  // V rows of the owners, swizzled like a tile
-    __shared__ __attribute__((aligned(16))) float row_l_all[KG][2][BT];  // initial M1 per streamed row, dK+dV: -L/scale of the query
-    __shared__ __attribute__((aligned(16))) float row_d_all[KG][2][BT];  // initial M2 per streamed row: dK+dV -delta of the query
-    __shared__ __attribute__((aligned(16))) uint32_t rowoff_all[KG][BRING][BT];     // byte offsets of the streamed rows of the next tiles
-
+    static_assert(IPW >= 1 && IPW * QW * RPI == BT, "a tile's instructions are spread evenly over the wavefronts");
+    static_assert(BT == 64 || BT == 32, "tiles of one or two blocks of 32 rows");
     const uint32_t tid = threadIdx.x, lane = tid & 63u, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const uint32_t lq = lane & 31u, h = lane >> 5;
     const uint32_t kg = KG == 1 ? 0u : wave / QW, ow = KG == 1 ? wave : wave % QW;  // group, wavefront of the group
     const uint32_t gtid = tid - kg * (64u * QW);
-    char* const s1buf0 = s1buf0_all + kg * TILE_BYTES;
-    char* const s1buf1 = s1buf1_all + kg * TILE_BYTES;
-    char* const s2buf0 = s2buf0_all + kg * TILE_BYTES;
-    char* const s2buf1 = s2buf1_all + kg * TILE_BYTES;
-    float (*const row_l)[BT] = row_l_all[kg];
-    float (*const row_d)[BT] = row_d_all[kg];
-    uint32_t (*const rowoff)[BT] = rowoff_all[kg];
-    const uint32_t xcd = blockIdx.x & 7u, idx = blockIdx.x >> 3;
-    const uint32_t lin = xcd * per_xcd + idx;  // each XCD owns a contiguous range of the (unit, owner tile) order
-    if (lin >= total) return;
+    char* const s1buf0 = lds.s1buf0;
+    char* const s1buf1 = lds.s1buf1;
+    char* const s2buf0 = lds.s2buf0;
+    char* const s2buf1 = lds.s2buf1;
+    char* const own2buf = lds.own2;
+    const uint32_t grp = kg * (uint32_t)TILE_BYTES;  // the group's half of every tile buffer: a part of the lanes' read offsets, so that it costs no register
+    float (*const row_l)[BT] = (float (*)[BT])lds.row_l + kg * 2u;
+    float (*const row_d)[BT] = (float (*)[BT])lds.row_d + kg * 2u;
+    uint32_t* const rowoff = lds.rowoff + kg * (BRING * 64u);
     const uint32_t unit = lin / o_tiles, ot = lin - unit * o_tiles;  // unit = (subsequence or batch element) * heads + head
     uint32_t bb = unit / (uint32_t)a.heads, head = unit - bb * (uint32_t)a.heads;
     if (PAD) {  // classes differ in size: neighbouring units belong to different classes, so that every XCD gets its share of each
@@ -141,7 +140,12 @@ __global__ __launch_bounds__(64 * NW, (NW == 4 && KG == 1 && (MODE == BWD_DQ || 
         if (!OWN2_LDS) own2[OWN2_LDS ? 0 : ks] = *(const bf16x8*)(own2_g + own_off + ks * 16 + 8 * h);
     }
     float own_l = 0.f, own_d = 0.f;  // dQ: the owner is a query
-    if (MODE == BWD_DQ) {
+    if (MODE == BWD_DQ && !DELTA) {
+        const uint32_t at = value_at(jo_c);
+        own_d = delta_u[at];
+        own_l = lse_u[at] * LOG2E;
+    }
+    if (MODE == BWD_DQ && DELTA) {
         // delta of the row: its dO is here, O is read for nothing else.  Kept for the dK+dV launch, which streams the queries.
         const __bf16* o_g = (const __bf16*)a.out + unit_off + own_off;
         float sum = 0.f;
@@ -172,9 +176,9 @@ __global__ __launch_bounds__(64 * NW, (NW == 4 && KG == 1 && (MODE == BWD_DQ || 
     const uint32_t all_t = (n_seq + BT - 1) / BT;
     const uint32_t tile0 = KG == 1 ? 0u : kg * all_t / KG;
     const uint32_t n_t = KG == 1 ? all_t : (kg + 1u) * all_t / KG - tile0;
-    auto produce = [&](uint32_t tile) __attribute__((always_inline)) {
-        const uint32_t j = (tile0 + tile) * BT + lane;
-        rowoff[tile % BRING][lane] = token_at(j < n_seq ? j : n_seq - 1u) * row_bytes;  // rows past the end repeat the last row
+    auto produce = [&](uint32_t group) __attribute__((always_inline)) {
+        const uint32_t j = tile0 * BT + group * 64u + lane;
+        rowoff[group % BRING * 64u + lane] = token_at(j < n_seq ? j : n_seq - 1u) * row_bytes;  // rows past the end repeat the last row
     };
     uint32_t st_row[IPW], st_cb[IPW];
 #pragma unroll
@@ -188,7 +192,7 @@ __global__ __launch_bounds__(64 * NW, (NW == 4 && KG == 1 && (MODE == BWD_DQ || 
     auto read_offs = [&](uint32_t tile) __attribute__((always_inline)) -> RowOffs {
         RowOffs o;
 #pragma unroll
-        for (int i = 0; i < IPW; i++) o.off[i] = rowoff[tile % BRING][st_row[i]] + st_cb[i];
+        for (int i = 0; i < IPW; i++) o.off[i] = rowoff[tile * BT % (BRING * 64u) + st_row[i]] + st_cb[i];
         return o;
     };
     float rl = 0.f, rd = 0.f;
@@ -196,9 +200,9 @@ __global__ __launch_bounds__(64 * NW, (NW == 4 && KG == 1 && (MODE == BWD_DQ || 
 #pragma unroll
         for (int i = 0; i < IPW; i++) {
             __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)(st1_g + o.off[i]),
-                                             (LDS_PTR(void))(b1 + (ow * IPW + i) * 1024u), 16, 0, 0);
+                                             (LDS_PTR(void))(b1 + grp + (ow * IPW + i) * 1024u), 16, 0, 0);
             __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)(st2_g + o.off[i]),
-                                             (LDS_PTR(void))(b2 + (ow * IPW + i) * 1024u), 16, 0, 0);
+                                             (LDS_PTR(void))(b2 + grp + (ow * IPW + i) * 1024u), 16, 0, 0);
         }
         if (DKV && gtid < BT) {
             // per-row values of the streamed queries: the INITIAL accumulators of the two products, so that they cost no arithmetic of
@@ -231,7 +235,7 @@ __global__ __launch_bounds__(64 * NW, (NW == 4 && KG == 1 && (MODE == BWD_DQ || 
     // step 0 with ks*32 XORed in (the row part lies above the chunk bits), so one register and an XOR per read can replace the
     // table; the dK+dV launch, the tightest on registers, does that.
     constexpr bool ADDR_TABLE = !DKV;
-    const uint32_t a_rd0 = lq * RB + ((h ^ swz(lq)) * 16u);
+    const uint32_t a_rd0 = grp + lq * RB + ((h ^ swz(lq)) * 16u);
     uint32_t a_rd_tab[ADDR_TABLE ? KS : 1];
     if (ADDR_TABLE) {
 #pragma unroll
@@ -247,22 +251,22 @@ __global__ __launch_bounds__(64 * NW, (NW == 4 && KG == 1 && (MODE == BWD_DQ || 
         for (int mt = 0; mt < MT; mt++) {
             const uint32_t row = 4 * h + (li >> 2) + 8 * sec;  // adding 16*g2 + 32*blk does not change the swizzle (low 4 bits)
             const uint32_t ch = (uint32_t)(mt * 4) + lgrp * 2 + ((li & 3u) >> 1);
-            t_rd[sec][mt] = row * RB + ((ch ^ swz(row)) * 16u) + 8 * (li & 1u);
+            t_rd[sec][mt] = grp + row * RB + ((ch ^ swz(row)) * 16u) + 8 * (li & 1u);
         }
 
     if (OWN2_LDS) {
         // the wavefront's owner rows of V go straight into LDS (one instruction fills RPI rows; same swizzle as the tiles, so
         // the fragment of MFMA step ks sits at a_rd(ks) of a 32-row block); waited for with tile 0
 #pragma unroll
-        for (int i = 0; i < 32 / RPI; i++) {
-            const uint32_t r = (uint32_t)i * RPI + lane / CH;  // row of the wavefront's block
-            const uint32_t j = ot * (uint32_t)WGO + wave * 32u + r;
+        for (int i0 = 0; i0 < 32 / RPI; i0 += KG) {
+            const uint32_t i = (uint32_t)i0 + kg, r = i * RPI + lane / CH;  // row of the wavefront's block; the groups have the same owners
+            const uint32_t j = ot * (uint32_t)WGO + ow * 32u + r;
             const uint32_t off = token_at(j < n_seq ? j : n_seq - 1u) * row_bytes + (((lane % CH) ^ swz(r)) * 16u);
             __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)((const char*)own2_g + off),
-                                             (LDS_PTR(void))(own2buf + wave * 32u * RB + (uint32_t)i * 1024u), 16, 0, 0);
+                                             (LDS_PTR(void))(own2buf + ow * 32u * RB + i * 1024u), 16, 0, 0);
         }
     }
-    const char* const own2_lds = own2buf + (OWN2_LDS ? wave * 32u * RB : 0u);
+    const char* const own2_lds = own2buf + (OWN2_LDS ? ow * 32u * RB : 0u) - grp;  // read at a_rd()
     for (uint32_t t = ow; t < (uint32_t)BRING_AHEAD; t += QW) produce(t);
     __syncthreads();
     issue_tile(0, read_offs(0), s1buf0, s2buf0);
@@ -278,7 +282,7 @@ __global__ __launch_bounds__(64 * NW, (NW == 4 && KG == 1 && (MODE == BWD_DQ || 
     // are code of their own, so that the loop has neither the selects nor the test for a next tile (head_dim 64 -5..-9 %, the others
     // -1..-3 %); the kernels at the register limit (head_dim 128 with two wavefronts per SIMD) spill when the copies are laid out in a
     // row (414 values in the dK+dV launch, +20 %) and keep the test.
-    constexpr bool PEEL = !(D == 128 && (NW == 8 || (KG == 1 && MODE == BWD_DQ)));
+    constexpr bool PEEL = BT == 64 && !(D == 128 && (NW == 8 || (KG == 1 && MODE == BWD_DQ)));
     auto do_tile = [&](auto PARC, auto LASTC, uint32_t t) __attribute__((always_inline)) {
         const bool more = PEEL ? !decltype(LASTC)::value : t + 1 < n_t;
         const bool tail = MODE == BWD_DQ && !more && n_seq % BT != 0 && kg == KG - 1;
@@ -287,12 +291,16 @@ __global__ __launch_bounds__(64 * NW, (NW == 4 && KG == 1 && (MODE == BWD_DQ || 
         const char* t2 = PARITY ? s2buf1 : s2buf0;
         const RowOffs off_now = off_next;
         off_next = read_offs(t + 2u);  // picked up a tile early so that the LDS read is not waited for
-        if (ow == (t & (uint32_t)(QW - 1))) produce(t + BRING_AHEAD);
+        if (BT == 64) {
+            if (ow == (t & (uint32_t)(QW - 1))) produce(t + BRING_AHEAD);
+        } else if (PARITY == 0) {
+            if (ow == (t / 2u & (uint32_t)(QW - 1))) produce(t / 2u + BRING_AHEAD);
+        }
 #pragma unroll
-        for (int blk = 0; blk < 2; blk++) {
+        for (int blk = 0; blk < BT / 32; blk++) {
             // The next tile's loads are enqueued halfway through this one on purpose: with a whole tile of slack even L2 misses are
             // hidden, the workgroups that walk the same unit drift apart and stop sharing its tiles through the L2.
-            if (blk == 1 && more) issue_tile(t + 1, off_now, PARITY ? s1buf0 : s1buf1, PARITY ? s2buf0 : s2buf1);
+            if (blk == BT / 32 - 1 && more) issue_tile(t + 1, off_now, PARITY ? s1buf0 : s1buf1, PARITY ? s2buf0 : s2buf1);
             // register r of a block is streamed row 8*(r/4) + 4*h + r%4; the per-row values start the accumulators
             f32x16 m1, m2;
 #pragma unroll
@@ -412,10 +420,13 @@ __global__ __launch_bounds__(64 * NW, (NW == 4 && KG == 1 && (MODE == BWD_DQ || 
     // ---- groups: the first one adds the others' sums to its own, through the LDS of the tiles
     if constexpr (KG > 1) {
         if (n_t < (all_t + KG - 1) / KG) __syncthreads();  // a group with one tile less has passed one barrier less
-        static_assert(KG == 2 && QW * (DKV ? 2 : 1) <= 4 && MT * 4 * 1024 == TILE_BYTES, "a wavefront's accumulator takes a tile buffer");
-        // every tile has been read (each ends with a barrier): wavefront ow of group 1 leaves dQ or dK in its group's buffer ow, dV in 2 + ow
+        // every tile has been read (each ends with a barrier): a wavefront's accumulator takes 4 KiB per channel block of the tile buffers
+        constexpr uint32_t PART = MT * 4 * 1024, SLOTS = 4 * KG * TILE_BYTES / PART;
+        constexpr bool AT_ONCE = QW * (DKV ? 2 : 1) <= SLOTS;  // room for dK and dV together
+        static_assert(KG == 2 && QW <= SLOTS && KG * TILE_BYTES % PART == 0, "the tile buffers hold an accumulator of every wavefront of a group");
         auto part = [&](uint32_t i) __attribute__((always_inline)) -> char* {
-            return (i == 0 ? s1buf0_all : i == 1 ? s1buf1_all : i == 2 ? s2buf0_all : s2buf1_all) + TILE_BYTES + lane * 16u;
+            const uint32_t n = i % 4u;
+            return (n == 0 ? lds.s1buf0 : n == 1 ? lds.s1buf1 : n == 2 ? lds.s2buf0 : lds.s2buf1) + i / 4u * PART + lane * 16u;
         };
         auto leave = [&](char* dst, const f32x16 (&x)[MT]) __attribute__((always_inline)) {
 #pragma unroll
@@ -435,12 +446,20 @@ __global__ __launch_bounds__(64 * NW, (NW == 4 && KG == 1 && (MODE == BWD_DQ || 
         };
         if (kg != 0) {
             leave(part(ow), acc);
-            if constexpr (DKV) leave(part(2u + ow), acc2);
+            if constexpr (DKV && AT_ONCE) leave(part(QW + ow), acc2);
         }
         __syncthreads();
+        if (kg == 0) {
+            take(part(ow), acc);
+            if constexpr (DKV && AT_ONCE) take(part(QW + ow), acc2);
+        }
+        if constexpr (DKV && !AT_ONCE) {
+            __syncthreads();
+            if (kg != 0) leave(part(ow), acc2);
+            __syncthreads();
+            if (kg == 0) take(part(ow), acc2);
+        }
         if (kg != 0) return;
-        take(part(ow), acc);
-        if constexpr (DKV) take(part(2u + ow), acc2);
     }
 
     // ---- epilogue: lane owns row jo; register r of block mt is channel 32*mt + 8*(r/4) + 4*h + r%4
@@ -469,35 +488,129 @@ __global__ __launch_bounds__(64 * NW, (NW == 4 && KG == 1 && (MODE == BWD_DQ || 
     }
 }
 
-template <int D, int MODE, int NW, int KG, bool PAD>
+// A launch of one kind of owner.
+template <int D, int MODE, int NW, bool PAD>
+__global__ __launch_bounds__(64 * NW, (NW == 4 ? 2 : 1)) void attn_bwd_kernel(BwdArgs a, PadArg<PAD> pad_map, uint32_t o_tiles, uint32_t total, uint32_t per_xcd) {
+    constexpr bool OWN2_LDS = MODE == BWD_DKV;
+    constexpr int TILE = BT64 * D * 2;
+    // separate arrays so that the compiler can tell the tile being filled from the one being read
+    __shared__ __attribute__((aligned(1024))) char s1buf0[TILE], s1buf1[TILE], s2buf0[TILE], s2buf1[TILE];
+    __shared__ __attribute__((aligned(1024))) char own2[OWN2_LDS ? 32 * NW * D * 2 : 16];  // V rows of the owners, swizzled like a tile
+    __shared__ __attribute__((aligned(16))) float row_l[2 * BT64], row_d[2 * BT64];
+    __shared__ __attribute__((aligned(16))) uint32_t rowoff[BRING * 64];
+    const uint32_t lin = (blockIdx.x & 7u) * per_xcd + (blockIdx.x >> 3);  // each XCD owns a contiguous range of the (unit, owner tile) order
+    if (lin >= total) return;
+    bwd_part<D, MODE, NW, 1, BT64, OWN2_LDS, true, PAD>(a, pad_map, lin, o_tiles, {s1buf0, s1buf1, s2buf0, s2buf1, own2, row_l, row_d, rowoff});
+}
+
+// Both kinds in one launch.  At head_dim 128 with the owners' V in LDS, tiles of 32 rows leave room for two B128 workgroups on a CU (70 KiB each) and
+// for the two groups of B128_SPLIT; each kind fits 256 registers without a spill (4 to 6 in B128_SPLIT).  48 units of 400 tokens: 35 us with the
+// launch that forms delta, against 43 in a launch of each kind, 160 of 960: 312 against 344 (605 TFLOP/s on the definition's five products).
+constexpr int both_waves(int shape) { return shape == B128_SPLIT ? 8 : 4; }
+constexpr int both_groups(int shape) { return shape == B128 ? 1 : 2; }
+template <int D, int SHAPE, bool PAD>
+__global__ __launch_bounds__(64 * both_waves(SHAPE), (SHAPE == B128 || (SHAPE == B64_SPLIT && D == 64) ? 2 : 1)) void attn_bwd_both_kernel(BwdArgs a, PadArg<PAD> pad_map, uint32_t o_tiles, uint32_t total, uint32_t per_xcd) {
+    constexpr int NW = both_waves(SHAPE), KG = both_groups(SHAPE);
+    constexpr bool OWN2_LDS = D == 128 && SHAPE != B64_SPLIT;
+    constexpr int BT = OWN2_LDS ? 32 : BT64, TILE = BT * D * 2;
+    __shared__ __attribute__((aligned(1024))) char s1buf0[KG * TILE], s1buf1[KG * TILE], s2buf0[KG * TILE], s2buf1[KG * TILE];
+    __shared__ __attribute__((aligned(1024))) char own2[OWN2_LDS ? 32 * NW / KG * D * 2 : 16];
+    __shared__ __attribute__((aligned(16))) float row_l[KG * 2 * BT], row_d[KG * 2 * BT];
+    __shared__ __attribute__((aligned(16))) uint32_t rowoff[KG * BRING * 64];
+    const bool dkv = blockIdx.x < 8u * per_xcd;  // the longer workgroups first: what is left over at the end is short
+    const uint32_t id = dkv ? blockIdx.x : blockIdx.x - 8u * per_xcd, lin = (id & 7u) * per_xcd + (id >> 3);
+    if (lin >= total) return;
+    const BwdLds lds = {s1buf0, s1buf1, s2buf0, s2buf1, own2, row_l, row_d, rowoff};
+    if (dkv) bwd_part<D, BWD_DKV, NW, KG, BT, OWN2_LDS, false, PAD>(a, pad_map, lin, o_tiles, lds);
+    else bwd_part<D, BWD_DQ, NW, KG, BT, false, false, PAD>(a, pad_map, lin, o_tiles, lds);
+}
+
+// delta = rowsum(dO o O) of every query, for the launch of both kinds.  A wavefront takes 16 rows of a unit, lane i finding row i, with all loads
+// in flight at once.  HBM-bound where it is not a launch's latency: 160 units of 960 tokens at head_dim 128 take 14 us of 312.
+template <int D, bool PAD>
+__global__ __launch_bounds__(256) void attn_bwd_delta_kernel(BwdArgs a, PadArg<PAD> pad_map, uint32_t tiles, uint32_t total) {
+    constexpr int CH = D / 8, RPI = 64 / CH, N = 16 / RPI;  // lanes a row, rows an instruction, instructions
+    const uint32_t lane = threadIdx.x & 63u, id = __builtin_amdgcn_readfirstlane(blockIdx.x * 4u + (threadIdx.x >> 6));
+    if (id >= total) return;
+    const uint32_t unit = id / tiles, j0 = (id - unit * tiles) * 16u;
+    const uint32_t bb = unit / (uint32_t)a.heads, head = unit - bb * (uint32_t)a.heads;
+    uint32_t p = 0, q = 0, b0 = bb;
+    if (a.g.mode != MODE_DENSE) {
+        const uint32_t pq = bb / (uint32_t)a.B;
+        b0 = bb - pq * (uint32_t)a.B;
+        p = pq / (uint32_t)a.g.s;
+        q = pq - p * (uint32_t)a.g.s;
+    }
+    const ClassMap cm = make_class_map(a.g, pad_map, p, q);
+    const uint32_t n_seq = PAD ? cm.n : (uint32_t)a.g.n_sub;
+    if (j0 >= n_seq) return;
+    const uint32_t jl = j0 + (lane & 15u), jc = jl < n_seq ? jl : n_seq - 1u;
+    const uint32_t tok = PAD ? src_token_real(a.g, cm, p, q, jc) : src_token(a.g, p, q, jc), at = PAD ? padded_position(a.g, cm, jc) : jc;
+    const size_t C = (size_t)a.heads * D, base = (size_t)b0 * (uint32_t)a.g.n_tok * C + (size_t)head * D + lane % CH * 8u;
+    const __bf16 *o_g = (const __bf16*)a.out + base, *do_g = (const __bf16*)a.dout + base;
+    bf16x8 o[N], d[N];
+#pragma unroll
+    for (int i = 0; i < N; i++) {
+        const size_t row = (size_t)(uint32_t)__shfl((int)tok, (int)(i * RPI + lane / CH)) * C;
+        o[i] = *(const bf16x8*)(o_g + row);
+        d[i] = *(const bf16x8*)(do_g + row);
+    }
+    float* delta_u = a.delta + (size_t)unit * (uint32_t)a.g.n_sub;
+#pragma unroll
+    for (int i = 0; i < N; i++) {
+        float sum = 0.f;
+#pragma unroll
+        for (int e = 0; e < 8; e++) sum = fmaf((float)o[i][e], (float)d[i][e], sum);
+#pragma unroll
+        for (int off = 1; off < CH; off <<= 1) sum += __shfl_xor(sum, off);
+        const uint32_t r = i * RPI + lane / CH, pos = (uint32_t)__shfl((int)at, (int)r);
+        if (lane % CH == 0 && j0 + r < n_seq) delta_u[pos] = sum;
+    }
+}
+
+template <int D, int SHAPE, bool PAD>
+static hipError_t launch_both(const BwdArgs& a, uint32_t n_units, uint32_t n_max, hipStream_t stream) {
+    constexpr uint32_t NW = both_waves(SHAPE), WGO = 32u * NW / both_groups(SHAPE);
+    const uint32_t o_tiles = (n_max + WGO - 1u) / WGO, d_tiles = (n_max + 15u) / 16u;
+    const uint64_t total = (uint64_t)n_units * o_tiles, waves = (uint64_t)n_units * d_tiles;
+    if (total > 0x3ffffff0ull || waves > 0x7ffffff0ull) return hipErrorInvalidConfiguration;
+    const uint32_t per_xcd = (uint32_t)((total + 7u) / 8u);
+    PadArg<PAD> pad_map;
+    make_pad_arg(a.g, pad_map);
+    attn_bwd_delta_kernel<D, PAD><<<(uint32_t)((waves + 3u) / 4u), 256, 0, stream>>>(a, pad_map, d_tiles, (uint32_t)waves);
+    attn_bwd_both_kernel<D, SHAPE, PAD><<<16u * per_xcd, 64u * NW, 0, stream>>>(a, pad_map, o_tiles, (uint32_t)total, per_xcd);
+    return hipGetLastError();
+}
+
+template <int D, int MODE, int NW, bool PAD>
 static hipError_t launch_t(const BwdArgs& a, uint32_t n_units, uint32_t n_max, hipStream_t stream) {
-    constexpr uint32_t WGO = 32u * (NW / KG);
+    constexpr uint32_t WGO = 32u * NW;
     const uint32_t o_tiles = (n_max + WGO - 1u) / WGO;
     const uint64_t total = (uint64_t)n_units * o_tiles;
     if (total > 0x7ffffff0ull) return hipErrorInvalidConfiguration;
     const uint32_t per_xcd = (uint32_t)((total + 7u) / 8u);
     PadArg<PAD> pad_map;
     make_pad_arg(a.g, pad_map);
-    attn_bwd_kernel<D, MODE, NW, KG, PAD><<<8u * per_xcd, 64 * NW, 0, stream>>>(a, pad_map, o_tiles, (uint32_t)total, per_xcd);
+    attn_bwd_kernel<D, MODE, NW, PAD><<<8u * per_xcd, 64 * NW, 0, stream>>>(a, pad_map, o_tiles, (uint32_t)total, per_xcd);
     return hipGetLastError();
-}
-
-template <int D, int MODE, bool PAD>
-static hipError_t launch_mode(const BwdArgs& a, hipStream_t stream) {
-    const uint32_t s2 = a.g.mode == MODE_DENSE ? 1u : (uint32_t)(a.g.s * a.g.s);
-    const uint32_t n_units = (uint32_t)a.B * s2 * (uint32_t)a.heads;
-    const UnitSizes u = unit_sizes(a.g, PAD, (uint64_t)a.B * (uint32_t)a.heads);
-    switch (pick_bwd_shape(MODE == BWD_DKV, D, u)) {
-        case O128: return launch_t<D, MODE, 4, 1, PAD>(a, n_units, u.n_max, stream);
-        case O64_SPLIT: return launch_t<D, MODE, 4, 2, PAD>(a, n_units, u.n_max, stream);
-        default: return launch_t<D, MODE, 8, 1, PAD>(a, n_units, u.n_max, stream);
-    }
 }
 
 template <int D, bool PAD>
 static hipError_t launch_all(const BwdArgs& a, hipStream_t stream) {
-    const hipError_t e = launch_mode<D, BWD_DQ, PAD>(a, stream);  // forms delta, which the second launch reads
-    return e != hipSuccess ? e : launch_mode<D, BWD_DKV, PAD>(a, stream);
+    const uint32_t s2 = a.g.mode == MODE_DENSE ? 1u : (uint32_t)(a.g.s * a.g.s);
+    const uint32_t n_units = (uint32_t)a.B * s2 * (uint32_t)a.heads;
+    const UnitSizes u = unit_sizes(a.g, PAD, (uint64_t)a.B * (uint32_t)a.heads);
+    switch (pick_bwd_pair(D, u)) {
+        case B128: return launch_both<D, B128, PAD>(a, n_units, u.n_max, stream);
+        case B64_SPLIT: return launch_both<D, B64_SPLIT, PAD>(a, n_units, u.n_max, stream);
+        case B128_SPLIT: return launch_both<D, B128_SPLIT, PAD>(a, n_units, u.n_max, stream);
+        default: break;
+    }
+    // The dQ launch forms delta, which the second one reads.  Some of these calls have a better last round in workgroups of 128 queries (24 units of
+    // 2055 tokens at head_dim 64); the other shapes of pick_bwd_shape() are for calls that have been taken above.
+    const bool small = pick_bwd_shape(false, D, u) == O128;
+    const hipError_t e = small ? launch_t<D, BWD_DQ, 4, PAD>(a, n_units, u.n_max, stream) : launch_t<D, BWD_DQ, 8, PAD>(a, n_units, u.n_max, stream);
+    return e != hipSuccess ? e : launch_t<D, BWD_DKV, 8, PAD>(a, n_units, u.n_max, stream);
 }
 
 hipError_t launch_attn_bwd_bf16(const BwdArgs& a, hipStream_t stream) {

@@ -131,6 +131,49 @@ inline int pick_bwd_shape(bool dkv, int head_dim, const UnitSizes& u) {
     return pick_shape(cost, u, true, [](const ShapeCost&) { return true; });
 }
 
+// Both kinds of owner in ONE launch (after a small one that forms delta): the dK+dV workgroups first, the dQ workgroups fill the chip behind them,
+// so that there is one last round instead of two and a call of few units has twice the workgroups.
+enum BwdPair : int {
+    TWO_LAUNCHES = 0,  // not in one: a launch of each kind, 256 owners a workgroup (dQ also 128: pick_bwd_shape())
+    B128 = 1,          // 4 wavefronts, 1 group, two workgroups on a CU whatever their kind
+    B64_SPLIT = 2,     // 4 wavefronts, 2 groups
+    B128_SPLIT = 3,    // 8 wavefronts, 2 groups
+};
+// us, the mean of both kinds.  Fitted to 660 calls (1..1088 units of 24..30,000 tokens, plain and any-resolution) timed in every shape: the pick is 0.5 %
+// above the best on average and 12 % at worst, and 0.84 of the two launches' time on average (1.03 at worst).  Measured, two launches -> picked,
+// us, units x tokens, head_dim 128: 1x120 18.1 -> 12.4, 8x190 21.6 -> 14.5, 48x400 43 -> 35, 24x1000 75 -> 63.5, 1x6116 215 -> 134, 160x400 120 -> 93,
+// 160x960 344 -> 312, 1x11191 390 -> 370, 12x8190 1437 -> 1313, 4x20160 3387 -> 2704, 160x2600 2093 -> 1977; head_dim 64: 1x78 11.8 -> 8.1,
+// 48x400 25.9 -> 21.4, 24x1000 44.6 -> 33.8, 1x3955 94 -> 52, 4x5000 171 -> 115, 160x960 171 -> 165.
+constexpr ShapeCost PAIR_COST_128[] = {{B128, 128, false, 2, 8.9f, 8.3f, 4.7f, {1.285f, 1.505f, 1.616f}},
+                                       {B64_SPLIT, 64, true, 1, 10.8f, 4.0f, 0.f, {0.614f, 0.718f}},
+                                       {B128_SPLIT, 128, true, 1, 14.3f, 8.2f, 0.f, {0.975f, 0.930f}}};
+constexpr ShapeCost PAIR_COST_64[] = {{B128, 128, false, 2, 7.2f, 5.4f, 2.4f, {0.558f, 0.684f, 0.848f}},
+                                      {B64_SPLIT, 64, true, 2, 7.4f, 4.0f, 1.8f, {0.361f, 0.387f, 0.481f}},
+                                      {B128_SPLIT, 128, true, 1, 11.6f, 6.1f, 0.f, {0.372f, 0.426f}}};
+// Workgroups of 256 owners, in a launch of each kind, take 4 to 7 % less per row and block (head_dim 64: 1 to 4 %), but only their full rounds show
+// it: the share of the chip's rounds that holds owners has to be near one, or there is a single, largely filled round of a long walk.  Measured, one launch
+// in B128 -> two of 256 owners, us: 73x12282 1.00 -> 0.932, 192x4584 0.953, 48x8190 5295 -> 5081, 84x3740 2026 -> 1918, 582x2734 7870 -> 7700, 160x20160 105,350 -> 102,340, 6x7844 (162 workgroups)
+// 0.900; the other way 20x20160 13,570 -> 13,940, 39x5781 1.011, 414x1824 1.058, 74x385 1.246.
+inline bool bwd_full_rounds(int head_dim, const UnitSizes& u) {
+    const uint64_t wgs = u.units * ((u.n_max + 255u) / 256u), rounds = (wgs + CUS - 1u) / CUS;
+    const float fill = (float)(u.units * ((u.n_max + 127u) / 128u)) / (float)(2u * CUS * rounds);
+    // Classes of different sizes and many rounds (head_dim 128): the two launches stay 1 to 4 % ahead (972 units of 1596 to 2100 tokens 6530 -> 6340, 320 of
+    // 5000 tokens 15,155 -> 14,780), where equal units gain up to 7 % by the one.
+    if (head_dim == 128 && u.n_min != u.n_max && u.n_max >= 1500u && u.units * ((u.n_max + 127u) / 128u) >= 8u * CUS) return true;
+    if (rounds == 1u) return head_dim == 128 ? u.n_max >= 2300u && fill >= 0.70f : u.n_max >= 1600u && fill >= 0.78f;
+    if (head_dim == 128) return fill >= 0.955f ? u.n_max >= 2500u : u.n_max >= 4000u && fill >= 0.935f;
+    return u.n_max >= 4000u && rounds <= 6u && fill >= 0.955f;
+}
+inline int pick_bwd_pair(int head_dim, const UnitSizes& u) {
+    if (bwd_full_rounds(head_dim, u)) return TWO_LAUNCHES;
+    const UnitSizes both = {2u * u.units, u.n_max, u.n_min};
+    // more rounds of the split shapes than these were never the best
+    return pick_shape(head_dim == 128 ? PAIR_COST_128 : PAIR_COST_64, both, false, [&](const ShapeCost& c) {
+        const uint64_t most = c.shape == B64_SPLIT ? (head_dim == 128 ? 1u : 3u) : c.shape == B128_SPLIT ? (head_dim == 128 ? 2u : 4u) : ~0u;
+        return both.workgroups(c) <= most * CUS * (uint64_t)c.max_k;
+    });
+}
+
 // ---- row moves: how many rows of `chunks` 16-byte chunks one wavefront moves.
 // Batches of 4 KiB, a single round of loads: larger ones leave less in flight and lose more the longer the rows are (16 KiB: 768 B rows 91.8 us
 // instead of the 87.5 of a wavefront a row, 1008 B 122 instead of 101).  Permute, switch and unpermute of 96,768 rows together, us, a wavefront

@@ -334,3 +334,19 @@ def test_backward_any_resolution_workgroup_shapes(heads, T, H, W, s, pattern, D)
         want = oracle.skiparse_attention_bwd_unit_padded(*oracle_inputs(q, k, v), si.as_oracle_array(dout), 0, head, toks, T, H, W, s, pattern, w.scale)
         for g, wnt, name in zip(grads, want, ("dq", "dk", "dv")):
             assert_grad_close(to_np64(g[0, toks, head]), wnt, f"class {c} {name}")
+
+
+# Beside the shapes above, head_dim -> (heads, N): a launch of each kind of owner in 256-owner workgroups (also with 128 queries a workgroup for
+# dQ), long walks of the split shapes.
+PAIR_SHAPES = {64: [(23, 2211), (24, 2055), (2, 385)], 128: [(18, 2560), (4, 2200), (2, 385)]}
+PADDED_PAIR_SHAPES = {64: [(4, 11, 33, 37, 2, "token"), (8, 5, 33, 37, 2, "token"), (1, 7, 33, 37, 2, "token")], 128: [(4, 11, 33, 37, 2, "token"), (9, 21, 33, 37, 3, "group"), (1, 7, 33, 37, 2, "token"), (1, 5, 33, 37, 3, "token")]}
+
+
+@pytest.mark.parametrize("D,heads,N", [(D, *c) for D in PAIR_SHAPES for c in PAIR_SHAPES[D]])
+def test_backward_pair_shapes(D, heads, N):
+    test_backward_workgroup_shapes(heads, N, D)
+
+
+@pytest.mark.parametrize("D,case", [(D, c) for D in PADDED_PAIR_SHAPES for c in PADDED_PAIR_SHAPES[D]])
+def test_backward_any_resolution_pair_shapes(D, case):
+    test_backward_any_resolution_workgroup_shapes(*case, D)
