@@ -276,3 +276,20 @@ def test_fp8_720p_sampled_rows():
     print(f"fp8 720p: kernel max-abs {ma:.3e} rel-L2 {rl:.3e}; ideal max-abs {ma_i:.3e} rel-L2 {rl_i:.3e}")
     assert rl <= REL_L2_VS_IDEAL * rl_i and ma <= MAX_ABS_VS_IDEAL * ma_i
     assert ma <= FP8_MAX_ABS and rl <= FP8_REL_L2_BACKSTOP
+
+
+@pytest.mark.parametrize("D,heads,T,H,W,s,pad", [
+    (64, 13, 21, 64, 48, 2, False),   # 107 MB: past the size up to which loads are cached
+    (128, 27, 21, 39, 37, 3, True),   # 209 MB, padded to 45 x 45, a number of workgroups that the XCDs do not share evenly
+    (128, 35, 21, 64, 48, 2, False),  # 578 MB: both sides past the caches
+])
+def test_quantize_large_equals_its_heads(D, heads, T, H, W, s, pad):
+    """Heads do not see each other: a large tensor's codes and scales are those of its heads quantised alone (checked against the oracle above)."""
+    import paper_2605_28691_amd as sk
+
+    x = torch.randn((1, T * H * W, heads, D), generator=torch.Generator(device="cuda").manual_seed(heads), device="cuda").to(torch.bfloat16)
+    x[0, ::7] *= 6.0
+    x8, scales = sk.skiparse_quantize_fp8(x, T, H, W, s, "group" if pad else "token", pad=pad)
+    for h in (0, heads // 2, heads - 1):
+        one8, one_s = sk.skiparse_quantize_fp8(x[:, :, h : h + 1].contiguous(), T, H, W, s, "group" if pad else "token", pad=pad)
+        assert torch.equal(x8[:, :, h : h + 1], one8) and torch.equal(scales[:, h : h + 1], one_s)
