@@ -51,12 +51,18 @@ __device__ inline void lane_pair_f(float x, float& lo, float& hi) {
     hi = __uint_as_float(r1);
 }
 
-// PAD: any-resolution mode (Sec. 3.2): positions run over the grid padded to multiples of s*s (the quantiser has put zero codes at the
-// padding positions); a padding position is a masked key (a -inf bias per staged row, formed a tile ahead by one wavefront and added
-// to the logits) and a skipped query.
-template <int D, bool PAD>
+// Any-resolution mode (Sec. 3.2): positions run over the grid padded to multiples of s*s (the quantiser has put zero codes at the
+// padding positions); a padding position is a masked key (a -inf bias per staged row, formed a tile ahead by one wavefront) and a skipped
+// query.  The bias is the initial accumulator of the logits on every tile, or is added to them where a flag says that the tile holds any: the
+// former takes 8 LDS reads a tile, the latter a test and, where it is set, 32 additions as well.  The results are the same.  Attention alone, us, added
+// where needed -> initial accumulator: 2x16 heads of 64, 9x17x21 54.6 -> 49.3, 12 heads of 64, 21x30x45 783 -> 712, 4 heads of 128, 21x30x45
+// 371 -> 338; with rows whole and the last of 24 lines padded, at head_dim 128: 40 heads, 1x45x80 73.2 -> 75.6, 12 heads, 21x45x80 5359 -> 5396.
+enum Padding : int { NO_PADDING = 0, SOME_TILES = 1, MOST_TILES = 2 };
+
+template <int D, int PADDING>
 __attribute__((amdgpu_waves_per_eu(waves_per_simd8(D), waves_per_simd8(D))))
-__global__ __launch_bounds__(NT8) void attn_fwd_fp8_kernel(Fp8AttnArgs a, PadArg<PAD> pad_map, uint32_t q_tiles, uint32_t total, uint32_t per_xcd) {
+__global__ __launch_bounds__(NT8) void attn_fwd_fp8_kernel(Fp8AttnArgs a, PadArg<PADDING != NO_PADDING> pad_map, uint32_t q_tiles, uint32_t total, uint32_t per_xcd) {
+    constexpr bool PAD = PADDING != NO_PADDING, FLAG = PADDING == SOME_TILES;
     constexpr int NJ = D / 64;         // 64-channel MFMA steps of S^T = K Q^T
     constexpr int MT = D / 32;         // 32-channel blocks of O^T
     constexpr int RB = D;              // row bytes in LDS (packed rows, swizzled chunk positions)
@@ -73,7 +79,7 @@ __global__ __launch_bounds__(NT8) void attn_fwd_fp8_kernel(Fp8AttnArgs a, PadArg
     __shared__ __attribute__((aligned(1024))) char vbuf1[TILE_BYTES];
     __shared__ float sv_part[NW8];
     __shared__ __attribute__((aligned(16))) float kbias[2][KT8];  // PAD only: 0 for a real key of the tile, -inf for padding
-    __shared__ uint32_t kany[2];                                  // PAD only: non-zero if the tile holds any padding (most hold none)
+    __shared__ uint32_t kany[2];                                  // FLAG only: non-zero if the tile holds any padding
 
     const uint32_t tid = threadIdx.x, lane = tid & 63u, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const uint32_t lq = lane & 31u, h = lane >> 5;
@@ -93,8 +99,10 @@ __global__ __launch_bounds__(NT8) void attn_fwd_fp8_kernel(Fp8AttnArgs a, PadArg
         const uint32_t r = a.g.ws.div(j), ws = j - r * a.g.ws.d, hs = r - cm.hs.div(r) * cm.hs.d;
         const bool real = j < n_seq && ws < cm.w.d && hs < cm.h.d;
         kbias[t & 1u][lane] = real ? 0.f : -INFINITY;
-        const unsigned long long pads = __builtin_amdgcn_ballot_w64(!real);
-        if (lane == 0) kany[t & 1u] = pads != 0 ? 1u : 0u;
+        if (FLAG) {
+            const unsigned long long pads = __builtin_amdgcn_ballot_w64(!real);
+            if (lane == 0) kany[t & 1u] = pads != 0 ? 1u : 0u;
+        }
     };
     const size_t C = (size_t)a.heads * D;  // bytes per position in the sparse layout
     const size_t unit_off = ((size_t)sb * n_seq) * C + (size_t)head * D;
@@ -201,12 +209,17 @@ __global__ __launch_bounds__(NT8) void attn_fwd_fp8_kernel(Fp8AttnArgs a, PadArg
             sv_nxt = svp[nb];
         }
 
-        // S^T = K Q^T: two blocks of 32 keys
+        // S^T = K Q^T: two blocks of 32 keys; register r of block kt is key 32*kt + 8*(r/4) + 4*h + r%4 (positions past the end carry -inf as well)
+        auto bias = [&](int kt, int i) __attribute__((always_inline)) -> f32x4 { return *(const f32x4*)&kbias[PARITY][kt * 32 + 8 * i + 4 * h]; };
         f32x16 sacc[2];
 #pragma unroll
         for (int kt = 0; kt < 2; kt++) {
 #pragma unroll
-            for (int r = 0; r < 16; r++) sacc[kt][r] = 0.f;
+            for (int i = 0; i < 4; i++) {
+                const f32x4 b4 = PADDING == MOST_TILES ? bias(kt, i) : f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+                for (int e = 0; e < 4; e++) sacc[kt][4 * i + e] = b4[e];
+            }
 #pragma unroll
             for (int j = 0; j < NJ; j++) {
                 const i32x4 k0 = *(const i32x4*)(kb + (k_rd0 ^ (uint32_t)((4 * j) * 16)) + kt * 32 * RB);
@@ -215,13 +228,12 @@ __global__ __launch_bounds__(NT8) void attn_fwd_fp8_kernel(Fp8AttnArgs a, PadArg
                 sacc[kt] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(kf, qf[j], sacc[kt], 0, 0, 0, 0, 0, 0);
             }
         }
-        if (PAD && __builtin_amdgcn_readfirstlane(kany[PARITY]) != 0) {
-            // register r of block kt is key 32*kt + 8*(r/4) + 4*h + r%4; positions past the end carry -inf as well
+        if (FLAG && __builtin_amdgcn_readfirstlane(kany[PARITY]) != 0) {
 #pragma unroll
             for (int kt = 0; kt < 2; kt++)
 #pragma unroll
                 for (int i = 0; i < 4; i++) {
-                    const f32x4 b4 = *(const f32x4*)&kbias[PARITY][kt * 32 + 8 * i + 4 * h];
+                    const f32x4 b4 = bias(kt, i);
 #pragma unroll
                     for (int e = 0; e < 4; e++) sacc[kt][4 * i + e] += b4[e];
                 }
@@ -345,7 +357,7 @@ __global__ __launch_bounds__(NT8) void attn_fwd_fp8_kernel(Fp8AttnArgs a, PadArg
     }
 }
 
-template <int D, bool PAD>
+template <int D, int PADDING>
 static hipError_t launch_fp8_t(const Fp8AttnArgs& a, hipStream_t stream) {
     const uint32_t s2 = a.g.mode == MODE_DENSE ? 1u : (uint32_t)(a.g.s * a.g.s);
     const uint32_t n_units = (uint32_t)a.B * s2 * (uint32_t)a.heads;
@@ -353,15 +365,21 @@ static hipError_t launch_fp8_t(const Fp8AttnArgs& a, hipStream_t stream) {
     const uint64_t total = (uint64_t)n_units * q_tiles;
     if (total > 0x7ffffff0ull) return hipErrorInvalidConfiguration;
     const uint32_t per_xcd = (uint32_t)((total + 7u) / 8u);
-    PadArg<PAD> pad_map;
+    PadArg<PADDING != NO_PADDING> pad_map;
     make_pad_arg(a.g, pad_map);
-    attn_fwd_fp8_kernel<D, PAD><<<8u * per_xcd, NT8, 0, stream>>>(a, pad_map, q_tiles, (uint32_t)total, per_xcd);
+    attn_fwd_fp8_kernel<D, PADDING><<<8u * per_xcd, NT8, 0, stream>>>(a, pad_map, q_tiles, (uint32_t)total, per_xcd);
     return hipGetLastError();
 }
 
+template <int D>
+static hipError_t launch_fp8_d(const Fp8AttnArgs& a, hipStream_t stream) {
+    if (!a.pad) return launch_fp8_t<D, NO_PADDING>(a, stream);
+    return pads_most_tiles(a.g) ? launch_fp8_t<D, MOST_TILES>(a, stream) : launch_fp8_t<D, SOME_TILES>(a, stream);
+}
+
 hipError_t launch_attn_fp8(const Fp8AttnArgs& a, hipStream_t stream) {
-    if (a.head_dim == 128) return a.pad ? launch_fp8_t<128, true>(a, stream) : launch_fp8_t<128, false>(a, stream);
-    if (a.head_dim == 64) return a.pad ? launch_fp8_t<64, true>(a, stream) : launch_fp8_t<64, false>(a, stream);
+    if (a.head_dim == 128) return launch_fp8_d<128>(a, stream);
+    if (a.head_dim == 64) return launch_fp8_d<64>(a, stream);
     return hipErrorInvalidValue;
 }
 

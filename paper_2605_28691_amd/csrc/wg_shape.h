@@ -174,6 +174,12 @@ inline int pick_bwd_pair(int head_dim, const UnitSizes& u) {
     });
 }
 
+// ---- 8-bit attention, any-resolution mode: do most tiles of 64 positions hold padding?  Where the columns are padded every line of positions ends in
+// some (lines of more than two tiles aside); where only lines are, every frame does, once in frame / 64 tiles.
+inline bool pads_most_tiles(uint32_t line, uint32_t frame, bool cols_padded, bool lines_padded) {
+    return (cols_padded && line <= 128u) || (lines_padded && frame <= 128u);
+}
+
 // ---- row moves: how many rows of `chunks` 16-byte chunks one wavefront moves.
 // Batches of 4 KiB, a single round of loads: larger ones leave less in flight and lose more the longer the rows are (16 KiB: 768 B rows 91.8 us
 // instead of the 87.5 of a wavefront a row, 1008 B 122 instead of 101).  Permute, switch and unpermute of 96,768 rows together, us, a wavefront

@@ -293,3 +293,11 @@ def test_quantize_large_equals_its_heads(D, heads, T, H, W, s, pad):
     for h in (0, heads // 2, heads - 1):
         one8, one_s = sk.skiparse_quantize_fp8(x[:, :, h : h + 1].contiguous(), T, H, W, s, "group" if pad else "token", pad=pad)
         assert torch.equal(x8[:, :, h : h + 1], one8) and torch.equal(scales[:, h : h + 1], one_s)
+
+
+# Padding in few of the key tiles: whole lines at the end of long frames, the end of long lines; and a grid whose padding sits in every tile.
+@pytest.mark.parametrize("D", [64, 128])
+@pytest.mark.parametrize("T,H,W", [(2, 22, 24), (1, 4, 261), (1, 6, 258), (5, 9, 22)])
+@pytest.mark.parametrize("pattern", ["token", "group"])
+def test_fp8_any_resolution_padding_in_some_tiles(T, H, W, pattern, D):
+    test_fp8_any_resolution_small(1, 2, D, T, H, W, 2, pattern)
