@@ -125,6 +125,49 @@ def _check(code: int, what: str) -> None:
         raise SkiparseError(code, what)
 
 
+# Where the tensors of a call stand in the C function's arguments, and what they are called when one is refused.
+_QKVO = ((0, "q"), (1, "k"), (2, "v"), (3, "out"))
+_TENSORS = {
+    "skiparse_permute": ((0, "x"), (1, "out")),
+    "skiparse_unpermute": ((0, "y"), (1, "out")),
+    "skiparse_switch_pattern": ((0, "y"), (1, "out")),
+    "skiparse_ssp_pack": ((0, "x"), (1, "out")),
+    "skiparse_ssp_unpack": ((0, "recv"), (1, "out")),
+    "dense_attn_fwd": _QKVO,
+    "skiparse_attn_fwd": (*_QKVO, (15, "workspace")),
+    "skiparse_attn_fwd_sparse": _QKVO,
+    "skiparse_attn_fwd_lse": (*_QKVO, (4, "lse")),
+    "skiparse_attn_bwd": (*_QKVO, (4, "dout"), (5, "lse"), (6, "dq"), (7, "dk"), (8, "dv"), (20, "workspace")),
+    "skiparse_attn_bwd_static": (*_QKVO, (4, "dout"), (5, "lse"), (6, "dq"), (7, "dk"), (8, "dv")),
+    "skiparse_quantize_fp8_ex": ((0, "x"), (1, "x8"), (2, "scales")),
+    "skiparse_attn_fwd_fp8_ex": ((0, "q8"), (1, "k8"), (2, "v8"), (3, "sq"), (4, "sk"), (5, "sv"), (6, "out")),
+}
+
+
+def _failed(code: int, name: str) -> None:
+    _check(code, name.removesuffix("_ex"))
+
+
+def _general(name: str, *args) -> None:
+    """The call by way of ctypes, which takes every integer-like argument and names what it refuses."""
+    args = list(args)
+    for i, what in _TENSORS[name]:
+        if not (args[i] is None and (name, what) == ("skiparse_attn_fwd", "workspace")):  # the fused form needs none
+            args[i] = _dev(args[i], what)
+    _failed(getattr(lib(), name)(*args), name)
+
+
+# The entry points themselves: natively marshalled where the module is there (it is built for one torch and one Python), by ctypes otherwise.
+try:
+    from . import _marshal
+except ImportError:
+    _marshal = None
+else:
+    _marshal.set_up(_general, _failed)
+for _name in _TENSORS:
+    globals()["_" + _name] = functools.partial(_general, _name) if _marshal is None else getattr(_marshal, _name)
+
+
 def _dims(x: torch.Tensor, T: int, H: int, W: int):
     B, N, heads, D = x.shape
     if N != T * H * W:
@@ -137,10 +180,7 @@ def skiparse_permute(x: torch.Tensor, T: int, H: int, W: int, s: int, pattern: s
     B, heads, D = _dims(x, T, H, W)
     if out is None:
         out = torch.empty((s * s * B, (T * H * W) // (s * s), heads, D), dtype=x.dtype, device=x.device)
-    _check(
-        lib().skiparse_permute(_dev(x, "x"), _dev(out, "out"), B, heads, T, H, W, D, s, PATTERNS[pattern], _DTYPES[x.dtype], _stream()),
-        "skiparse_permute",
-    )
+    _skiparse_permute(x, out, B, heads, T, H, W, D, s, PATTERNS[pattern], _DTYPES[x.dtype], _stream())
     return out
 
 
@@ -152,10 +192,7 @@ def skiparse_unpermute(y: torch.Tensor, T: int, H: int, W: int, s: int, pattern:
         raise ValueError("sparse-layout shape does not match the grid")
     if out is None:
         out = torch.empty((B, T * H * W, heads, D), dtype=y.dtype, device=y.device)
-    _check(
-        lib().skiparse_unpermute(_dev(y, "y"), _dev(out, "out"), B, heads, T, H, W, D, s, PATTERNS[pattern], _DTYPES[y.dtype], _stream()),
-        "skiparse_unpermute",
-    )
+    _skiparse_unpermute(y, out, B, heads, T, H, W, D, s, PATTERNS[pattern], _DTYPES[y.dtype], _stream())
     return out
 
 
@@ -167,10 +204,7 @@ def skiparse_switch_pattern(y: torch.Tensor, T: int, H: int, W: int, s: int, fro
         raise ValueError("sparse-layout shape does not match the grid")
     if out is None:
         out = torch.empty_like(y)
-    _check(
-        lib().skiparse_switch_pattern(_dev(y, "y"), _dev(out, "out"), B, heads, T, H, W, D, s, PATTERNS[from_pattern], _DTYPES[y.dtype], _stream()),
-        "skiparse_switch_pattern",
-    )
+    _skiparse_switch_pattern(y, out, B, heads, T, H, W, D, s, PATTERNS[from_pattern], _DTYPES[y.dtype], _stream())
     return out
 
 
@@ -183,10 +217,7 @@ def skiparse_ssp_pack(x: torch.Tensor, T: int, H: int, W: int, s: int, group_siz
         raise ValueError("shard shape does not match the grid and the group")
     if out is None:
         out = torch.empty((group_size, G, Bl, n_local // (s * s), heads, D), dtype=x.dtype, device=x.device)
-    _check(
-        lib().skiparse_ssp_pack(_dev(x, "x"), _dev(out, "out"), Bl // G, heads, T, H, W, D, s, group_size, _DTYPES[x.dtype], _stream()),
-        "skiparse_ssp_pack",
-    )
+    _skiparse_ssp_pack(x, out, Bl // G, heads, T, H, W, D, s, group_size, _DTYPES[x.dtype], _stream())
     return out
 
 
@@ -198,10 +229,7 @@ def skiparse_ssp_unpack(recv: torch.Tensor, T: int, H: int, W: int, s: int, grou
         raise ValueError("receive-buffer shape does not match the grid and the group")
     if out is None:
         out = torch.empty((Bl, base * s * s, heads, D), dtype=recv.dtype, device=recv.device)
-    _check(
-        lib().skiparse_ssp_unpack(_dev(recv, "recv"), _dev(out, "out"), Bl // G, heads, T, H, W, D, s, group_size, _DTYPES[recv.dtype], _stream()),
-        "skiparse_ssp_unpack",
-    )
+    _skiparse_ssp_unpack(recv, out, Bl // G, heads, T, H, W, D, s, group_size, _DTYPES[recv.dtype], _stream())
     return out
 
 
@@ -210,11 +238,7 @@ def dense_attn_fwd(q, k, v, T: int, H: int, W: int, scale: float = 0.0, out: tor
     B, heads, D = _dims(q, T, H, W)
     if out is None:
         out = torch.empty_like(q)
-    _check(
-        lib().dense_attn_fwd(_dev(q, "q"), _dev(k, "k"), _dev(v, "v"), _dev(out, "out"), B, heads, T, H, W, D, float(scale),
-                             _DTYPES[q.dtype], _stream()),
-        "dense_attn_fwd",
-    )
+    _dense_attn_fwd(q, k, v, out, B, heads, T, H, W, D, float(scale), _DTYPES[q.dtype], _stream())
     return out
 
 
@@ -230,18 +254,16 @@ def skiparse_attn_fwd(q, k, v, T: int, H: int, W: int, s: int, pattern: str, sca
     B, heads, D = _dims(q, T, H, W)
     if out is None:
         out = torch.empty_like(q)
-    ws_ptr, ws_bytes = None, 0
-    if not fused:
+    ws_bytes = 0
+    if fused:
+        workspace = None
+    else:
         need = skiparse_workspace_bytes(B, heads, T, H, W, D, s, False)
         if workspace is None:
             workspace = torch.empty(max(need, 1), dtype=torch.uint8, device=q.device)
-        ws_ptr, ws_bytes = _dev(workspace, "workspace"), workspace.numel() * workspace.element_size()
-    _check(
-        lib().skiparse_attn_fwd(_dev(q, "q"), _dev(k, "k"), _dev(v, "v"), _dev(out, "out"), B, heads, T, H, W, D, s,
-                                PATTERNS[pattern], float(scale), _DTYPES[q.dtype], (FUSED if fused else 0) | (PAD if pad else 0), ws_ptr, ws_bytes,
-                                _stream()),
-        "skiparse_attn_fwd",
-    )
+        ws_bytes = workspace.numel() * workspace.element_size()
+    _skiparse_attn_fwd(q, k, v, out, B, heads, T, H, W, D, s, PATTERNS[pattern], float(scale), _DTYPES[q.dtype],
+                       (FUSED if fused else 0) | (PAD if pad else 0), workspace, ws_bytes, _stream())
     return out
 
 
@@ -256,11 +278,8 @@ def skiparse_attn_fwd_sparse(q, k, v, T: int, H: int, W: int, s: int, pattern: s
     if out is None:
         shape = (B, T * H * W, heads, D) if out_layout == "original" else tuple(q.shape)
         out = torch.empty(shape, dtype=q.dtype, device=q.device)
-    _check(
-        lib().skiparse_attn_fwd_sparse(_dev(q, "q"), _dev(k, "k"), _dev(v, "v"), _dev(out, "out"), B, heads, T, H, W, D, s,
-                                       PATTERNS[pattern], OUT_LAYOUTS[out_layout], float(scale), _DTYPES[q.dtype], _stream()),
-        "skiparse_attn_fwd_sparse",
-    )
+    _skiparse_attn_fwd_sparse(q, k, v, out, B, heads, T, H, W, D, s, PATTERNS[pattern], OUT_LAYOUTS[out_layout], float(scale),
+                              _DTYPES[q.dtype], _stream())
     return out
 
 
@@ -296,11 +315,8 @@ def skiparse_attn_fwd_lse(q, k, v, T: int, H: int, W: int, s: int, pattern: str,
         out = torch.empty_like(q)
     if lse is None:
         lse = torch.empty(skiparse_lse_shape(B, heads, T, H, W, D, s, pattern, pad), dtype=torch.float32, device=q.device)
-    _check(
-        lib().skiparse_attn_fwd_lse(_dev(q, "q"), _dev(k, "k"), _dev(v, "v"), _dev(out, "out"), _dev(lse, "lse"), B, heads, T, H, W, D, s,
-                                    PATTERNS[pattern], float(scale), _DTYPES[q.dtype], PAD if pad else 0, _stream()),
-        "skiparse_attn_fwd_lse",
-    )
+    _skiparse_attn_fwd_lse(q, k, v, out, lse, B, heads, T, H, W, D, s, PATTERNS[pattern], float(scale), _DTYPES[q.dtype], PAD if pad else 0,
+                           _stream())
     return out, lse
 
 
@@ -318,13 +334,8 @@ def skiparse_attn_bwd(q, k, v, out, dout, lse, T: int, H: int, W: int, s: int, p
     dv = torch.empty_like(q) if dv is None else dv
     if workspace is None:
         workspace = torch.empty(max(skiparse_bwd_workspace_bytes(B, heads, T, H, W, D, s, pattern, pad), 1), dtype=torch.uint8, device=q.device)
-    _check(
-        lib().skiparse_attn_bwd(_dev(q, "q"), _dev(k, "k"), _dev(v, "v"), _dev(out, "out"), _dev(dout, "dout"), _dev(lse, "lse"),
-                                _dev(dq, "dq"), _dev(dk, "dk"), _dev(dv, "dv"), B, heads, T, H, W, D, s, PATTERNS[pattern], float(scale),
-                                _DTYPES[q.dtype], PAD if pad else 0, _dev(workspace, "workspace"),
-                                workspace.numel() * workspace.element_size(), _stream()),
-        "skiparse_attn_bwd",
-    )
+    _skiparse_attn_bwd(q, k, v, out, dout, lse, dq, dk, dv, B, heads, T, H, W, D, s, PATTERNS[pattern], float(scale), _DTYPES[q.dtype],
+                       PAD if pad else 0, workspace, workspace.numel() * workspace.element_size(), _stream())
     return dq, dk, dv
 
 
@@ -333,12 +344,8 @@ def skiparse_attn_bwd_static(q, k, v, out, dout, lse, dq, dk, dv, T: int, H: int
     """skiparse_attn_bwd for callers that cannot allocate: the delta workspace is the library's static device array, and this
     wrapper allocates nothing either (dq, dk, dv must be passed).  Problems above the array's size raise (code -4)."""
     B, heads, D = _dims(q, T, H, W)
-    _check(
-        lib().skiparse_attn_bwd_static(_dev(q, "q"), _dev(k, "k"), _dev(v, "v"), _dev(out, "out"), _dev(dout, "dout"), _dev(lse, "lse"),
-                                       _dev(dq, "dq"), _dev(dk, "dk"), _dev(dv, "dv"), B, heads, T, H, W, D, s, PATTERNS[pattern],
-                                       float(scale), _DTYPES[q.dtype], PAD if pad else 0, _stream()),
-        "skiparse_attn_bwd_static",
-    )
+    _skiparse_attn_bwd_static(q, k, v, out, dout, lse, dq, dk, dv, B, heads, T, H, W, D, s, PATTERNS[pattern], float(scale),
+                              _DTYPES[q.dtype], PAD if pad else 0, _stream())
     return dq, dk, dv
 
 
@@ -352,11 +359,7 @@ def skiparse_quantize_fp8(x: torch.Tensor, T: int, H: int, W: int, s: int, patte
     nsub = skiparse_lse_shape(B, heads, T, H, W, D, s, pattern, pad)[2]
     x8 = torch.empty((s * s * B, nsub, heads, D), dtype=torch.uint8, device=x.device)
     scales = torch.empty((s * s * B, heads, (nsub + 127) // 128), dtype=torch.float32, device=x.device)
-    _check(
-        lib().skiparse_quantize_fp8_ex(_dev(x, "x"), _dev(x8, "x8"), _dev(scales, "scales"), B, heads, T, H, W, D, s,
-                                       PATTERNS[pattern], PAD if pad else 0, _stream()),
-        "skiparse_quantize_fp8",
-    )
+    _skiparse_quantize_fp8_ex(x, x8, scales, B, heads, T, H, W, D, s, PATTERNS[pattern], PAD if pad else 0, _stream())
     return x8, scales
 
 
@@ -370,9 +373,6 @@ def skiparse_attn_fwd_fp8(q8, k8, v8, sq, sk, sv, T: int, H: int, W: int, s: int
         raise ValueError("sparse-layout shape does not match the grid")
     if out is None:
         out = torch.empty((B, T * H * W, heads, D), dtype=torch.bfloat16, device=q8.device)
-    _check(
-        lib().skiparse_attn_fwd_fp8_ex(_dev(q8, "q8"), _dev(k8, "k8"), _dev(v8, "v8"), _dev(sq, "sq"), _dev(sk, "sk"), _dev(sv, "sv"),
-                                       _dev(out, "out"), B, heads, T, H, W, D, s, PATTERNS[pattern], float(scale), PAD if pad else 0, _stream()),
-        "skiparse_attn_fwd_fp8",
-    )
+    _skiparse_attn_fwd_fp8_ex(q8, k8, v8, sq, sk, sv, out, B, heads, T, H, W, D, s, PATTERNS[pattern], float(scale), PAD if pad else 0,
+                              _stream())
     return out

@@ -1,14 +1,16 @@
-"""Compiles the HIP sources under csrc/ (gfx950 only), in-tree: libskiparse.so, the attention library, and
-libskiparse_probe.so, the measurement micro-kernels the benchmark times."""
+"""Compiles the sources under csrc/ in-tree: libskiparse.so, the attention library, and libskiparse_probe.so, the measurement
+micro-kernels the benchmark times (HIP, gfx950 only), and _marshal.so, the binding's native calls (host C++)."""
 from __future__ import annotations
 
 import os
 import subprocess
+import sysconfig
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libskiparse.so")
 SOURCES = ["api.hip", "permute.hip", "attn_fwd.hip", "attn_bwd.hip", "quant_fp8.hip", "attn_fwd_fp8.hip"]
+MARSHAL = os.path.join(HERE, "_marshal.so")
 PROBE_LIB = os.path.join(HERE, "libskiparse_probe.so")
 PROBE_SOURCES = ["mfma_probe.hip"]
 FLAGS = [
@@ -24,9 +26,28 @@ FLAGS = [
 
 
 def build(verbose: bool = False, save_temps: bool = False) -> str:
-    """Builds both libraries; returns the path of the attention library."""
+    """Builds everything; returns the path of the attention library."""
     _build_one(PROBE_LIB, PROBE_SOURCES, verbose, False)
-    return _build_one(LIB, SOURCES, verbose, save_temps)
+    _build_one(LIB, SOURCES, verbose, save_temps)
+    _build_marshal(verbose)
+    return LIB
+
+
+def _build_marshal(verbose: bool) -> str:
+    """The CPython module: compiled against torch's headers, linked to the attention library beside it."""
+    import torch
+
+    root = os.path.dirname(torch.__file__)
+    cmd = [os.environ.get("CXX", "g++"), "-O2", "-std=c++17", "-fPIC", "-shared", "-fvisibility=hidden",
+           f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}",
+           "-isystem", os.path.join(root, "include"), "-isystem", os.path.join(root, "include", "torch", "csrc", "api", "include"),
+           "-isystem", sysconfig.get_paths()["include"],
+           os.path.join(CSRC, "marshal.cpp"), "-o", MARSHAL + ".tmp",
+           "-L" + HERE, "-l:" + os.path.basename(LIB), "-Wl,-rpath,$ORIGIN",
+           "-L" + os.path.join(root, "lib"), "-ltorch_python", "-ltorch_cpu", "-lc10"]
+    _run(cmd, verbose)
+    os.replace(MARSHAL + ".tmp", MARSHAL)
+    return MARSHAL
 
 
 def _build_one(lib: str, sources, verbose: bool, save_temps: bool) -> str:
@@ -40,15 +61,19 @@ def _build_one(lib: str, sources, verbose: bool, save_temps: bool) -> str:
     else:
         out = lib + ".tmp"
     cmd += ["-o", out] + [os.path.join(CSRC, s) for s in sources]
+    _run(cmd, verbose)
+    os.replace(out, lib)
+    return lib
+
+
+def _run(cmd, verbose: bool) -> None:
     res = subprocess.run(cmd, stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True)
     # the host pass does not know the packed-fp32 target feature and says so; that is harmless
     log = "\n".join(l for l in res.stdout.splitlines() if "packed-fp32-ops" not in l)
     if res.returncode != 0:
-        raise RuntimeError("hipcc failed:\n" + log)
+        raise RuntimeError(os.path.basename(cmd[0]) + " failed:\n" + log)
     if verbose and log.strip():
         print(log)
-    os.replace(out, lib)
-    return lib
 
 
 if __name__ == "__main__":

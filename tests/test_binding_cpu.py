@@ -76,3 +76,40 @@ def test_stream_without_the_private_names(monkeypatch, missing):
     monkeypatch.setattr(sk, missing, None)
     monkeypatch.setattr(torch.cuda, "current_stream", lambda: Stream)
     assert sk._stream() == 11
+
+
+def test_native_marshalling_passes_on_what_is_not_plain():
+    """Everything but plain tensors on the GPU, int and float goes to the general way, as it came; nothing is read from it before."""
+    native = sk._marshal
+    assert native is not None, "the module is built with the library"
+    q = torch.zeros(1, 128, 2, 64, dtype=torch.bfloat16)
+    seen = []
+    native.set_up(lambda *args: seen.append(args), sk._failed)
+    try:
+        for name, tensors in sk._TENSORS.items():
+            n = len(getattr(sk.lib(), name).argtypes)
+            slots = dict(tensors)
+            args = [q if i in slots else 1 for i in range(n)]
+            for call in (args, args[:-1], [], [5] * n, [None] * n, [1.0] * n):
+                getattr(native, name)(*call)
+                assert seen.pop() == (name, *call)
+    finally:
+        native.set_up(sk._general, sk._failed)
+    assert not seen
+
+
+@pytest.mark.parametrize("bad, error", [((5,), AttributeError), ((None,), AttributeError), ((torch.zeros(1, 128, 2, 64, dtype=torch.bfloat16),), ValueError)])
+def test_refused_tensors(monkeypatch, bad, error):
+    monkeypatch.setattr(sk, "_stream", lambda: 0)
+    good = torch.zeros(1, 128, 2, 64, dtype=torch.bfloat16)
+    with pytest.raises(ValueError if error is AttributeError else error):  # q comes first, and is on the CPU
+        sk.skiparse_attn_fwd(good, *bad, good, 2, 8, 8, 2, "token")
+    with pytest.raises(error):
+        sk._skiparse_attn_fwd(bad[0], good, good, good, 1, 2, 2, 8, 8, 64, 2, 0, 0.0, 0, 1, None, 0, 0)
+
+
+def test_every_entry_point_is_marshalled_in_the_order_of_the_c_function():
+    """The table of tensor arguments against the types that ctypes converts: a tensor stands exactly where the C function takes a device pointer."""
+    for name, tensors in sk._TENSORS.items():
+        types = getattr(sk.lib(), name).argtypes
+        assert [i for i, t in enumerate(types) if t is ctypes.c_void_p] == [i for i, _ in tensors] + [len(types) - 1]

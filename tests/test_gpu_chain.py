@@ -5,6 +5,9 @@ The expected value is the oracle's Skiparse attention (original layout) moved, w
 the call writes.  Tolerance (bf16 path): max |diff| <= 2e-2 and relative L2 error <= 5e-3.  Row placement is also checked
 bit for bit against the library's separate rearrangement calls (same arithmetic, only the destination row differs).
 """
+import ctypes
+import gc
+
 import numpy as np
 import pytest
 import torch
@@ -95,3 +98,39 @@ def test_calls_follow_the_current_stream():
     side.synchronize()
     assert torch.equal(got, want)
     assert torch.equal(sk.skiparse_unpermute(y, T, H, W, s, "group"), want)
+
+
+def test_native_and_general_marshalling_agree():
+    """Plain arguments are marshalled natively, integer-like ones and tensor subclasses by way of ctypes: the same results, and the same refusals."""
+    import paper_2605_28691_amd as sk
+
+    class Sub(torch.Tensor):
+        pass
+
+    gen = torch.Generator(device="cuda").manual_seed(1)
+    q, k, v = (torch.randn((1, 256, 2, 64), generator=gen, device="cuda").to(torch.bfloat16) for _ in range(3))
+    n = np.int64
+    for fused in (True, False):
+        want = sk.skiparse_attn_fwd(q, k, v, 4, 8, 8, 2, "token", fused=fused)
+        assert torch.equal(want, sk.skiparse_attn_fwd(q, k, v, n(4), n(8), torch.tensor(8), n(2), "token", fused=fused))
+        assert torch.equal(want, sk.skiparse_attn_fwd(q.as_subclass(Sub), k, v, 4, 8, 8, 2, "token", fused=fused).as_subclass(torch.Tensor))
+    out, lse = sk.skiparse_attn_fwd_lse(q, k, v, 4, 8, 8, 2, "group")
+    out2, lse2 = sk.skiparse_attn_fwd_lse(q, k, v, 4, n(8), 8, 2, "group")
+    assert torch.equal(out, out2) and torch.equal(lse, lse2)
+    for a, b in zip(sk.skiparse_attn_bwd(q, k, v, out, q, lse, 4, 8, 8, 2, "group"), sk.skiparse_attn_bwd(q, k, v, out, q, lse, 4, n(8), 8, 2, "group")):
+        assert torch.equal(a, b)
+    for a, b in zip(sk.skiparse_quantize_fp8(q, 4, 8, 8, 2, "group"), sk.skiparse_quantize_fp8(q, 4, n(8), 8, 2, "group")):
+        assert torch.equal(a, b)
+    strided = torch.empty((1, 256, 2, 128), dtype=torch.bfloat16, device="cuda")[..., ::2]
+    for bad, error in ((k.cpu(), ValueError), (strided, ValueError), (5, AttributeError), (None, AttributeError)):
+        with pytest.raises(error):
+            sk.skiparse_attn_fwd(q, bad, v, 4, 8, 8, 2, "token")
+    with pytest.raises(sk.SkiparseError, match="skiparse_attn_fwd: grid not divisible"):
+        sk.skiparse_attn_fwd(q, k, v, 4, 64, 1, 2, "token")
+    with pytest.raises(ctypes.ArgumentError):
+        sk.skiparse_attn_fwd(q, k, v, 4, 8.0, 8, 2, "token")
+    with pytest.raises(sk.SkiparseError) as e:
+        sk.skiparse_attn_fwd(q, k, v, 4, 8, 8, 2, "token", out=q)
+    assert e.value.code == -1
+    del e
+    gc.collect()  # the tracebacks hold tensors, and a later test looks at the memory allocated
