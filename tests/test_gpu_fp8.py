@@ -301,3 +301,28 @@ def test_quantize_large_equals_its_heads(D, heads, T, H, W, s, pad):
 @pytest.mark.parametrize("pattern", ["token", "group"])
 def test_fp8_any_resolution_padding_in_some_tiles(T, H, W, pattern, D):
     test_fp8_any_resolution_small(1, 2, D, T, H, W, 2, pattern)
+
+
+# The queries of the any-resolution mode are the real positions only, 128 a workgroup whatever scale block they come from: classes of exactly two
+# workgroups (256 real positions of 384) and of two and a remainder (258), fewer than a wavefront, classes with no column at all, s = 4; the
+# queries' magnitude changes along the sequence, so that every scale block has a scale of its own.
+@pytest.mark.parametrize("T,H,W,s,pattern", [(16, 9, 7, 2, "token"), (43, 5, 3, 2, "group"), (1, 5, 6, 2, "token"), (40, 9, 1, 3, "token"), (7, 20, 13, 4, "group")])
+@pytest.mark.parametrize("D", [64, 128])
+def test_fp8_any_resolution_queries(T, H, W, s, pattern, D):
+    import paper_2605_28691_amd as sk
+
+    w = si.make_shape("p8q", 2, 3, D, T, H, W, s, seed=71)
+    q, k, v = si.make_qkv(w)
+    N = T * H * W
+    q = q * torch.pow(2.0, torch.arange(N) * 5 // N - 2).view(1, N, 1, 1).to(q.dtype)  # powers of two: q stays in bf16
+    c = [sk.skiparse_quantize_fp8(t.cuda(), T, H, W, s, pattern, pad=True) for t in (q, k, v)]
+    out = sk.skiparse_attn_fwd_fp8(c[0][0], c[1][0], c[2][0], c[0][1], c[1][1], c[2][1], T, H, W, s, pattern, scale=w.scale, pad=True)
+    rows = _all_rows(2, 3, N)
+    exact = oracle.skiparse_attention_rows_padded(*oracle_inputs(q, k, v), rows, T, H, W, s, pattern, w.scale)
+    ideal = emu.ideal_attention_rows_padded(*oracle_inputs(q, k, v), rows, T, H, W, s, pattern, w.scale)
+    got = gather_rows(out, rows)
+    assert np.isfinite(got).all()
+    ma, rl = errors(got, exact)
+    ma_i, rl_i = errors(ideal, exact)
+    print(f"kernel max-abs {ma:.3e} rel-L2 {rl:.3e}; ideal max-abs {ma_i:.3e} rel-L2 {rl_i:.3e}")
+    assert rl <= REL_L2_VS_IDEAL * rl_i and ma <= MAX_ABS_VS_IDEAL * ma_i
