@@ -526,6 +526,31 @@ __global__ __launch_bounds__(64 * fwd_waves(SHAPE), (SHAPE == Q128 ? 2 : 1)) voi
     tile_landed();
     __syncthreads();
 
+    // ---- a wavefront without a query (in a unit's last workgroup) fetches its share of the tiles, meets the others at their barriers and
+    // leaves the SIMD to the other workgroups of the CU and the power to the rest of the chip.  Out of the other wavefronts' line: in it, a call
+    // without any (48 units of 1536 tokens) took 1 % longer.  us: 320 units of 540 tokens at
+    // head_dim 64 44.8 -> 42.7, 160 of 308 at head_dim 128 19.4 -> 19.0, 160 of 960 93.0 -> 90.6, padded 160 of 3600 1056 -> 1035; calls without
+    // such wavefronts take what they took.  (The same in the backward: 2 to 3 % gained where many units end in one, 1 to 3 % lost in all small
+    // calls, whose kernels then spill and hold more code.)
+    if (__builtin_expect(qt * BR + qw * QT * 32u >= n_seq, 0)) {
+        for (uint32_t W = 0; W < n_tiles; W++) {
+            if (W + 1u < n_tiles) {
+                issue_k((W & 1u) ? kbuf0 : kbuf1, off_k);
+                if (W != 0 && qw == (W & (uint32_t)(QW - 1))) produce(W + RING_AHEAD);
+            }
+            issue_v((W & 1u) ? vbuf1 : vbuf0, off_v);
+            off_v = off_k;
+            off_k = read_offs(W + 2u);
+            tile_landed();
+            __syncthreads();
+        }
+        if constexpr (KG > 1) {  // the barriers of the merge, where the group beside it has no query either
+            if (n_tiles < (all_tiles + KG - 1) / KG) __syncthreads();
+            __syncthreads();
+            __syncthreads();
+        }
+        return;
+    }
     // ---- window 0: QK(0), then step 0 without PV
     {
         if (n_tiles > 1) issue_k(kbuf1, off_k);

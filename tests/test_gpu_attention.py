@@ -294,6 +294,20 @@ def test_workgroup_shapes(heads, N, D):
     assert np.abs(to_np64(lse[0, heads - 1]) - (m + np.log(np.exp(logits - m).sum(-1, keepdims=True)))[:, 0]).max() <= 5e-3
 
 
+# Wavefronts past a unit's last query fetch tiles and row offsets for the others and compute nothing: every row that shares a workgroup with them
+# (one to seven of them), walks of more than the 16 tiles of the offset ring, an uneven split over two groups.
+@pytest.mark.parametrize("heads,N", [(300, 33), (3, 321), (4, 1921), (12, 2465), (29, 1100), (60, 1057), (1, 2200)])
+@pytest.mark.parametrize("D", [64, 128])
+def test_last_workgroup_of_a_unit(heads, N, D):
+    import paper_2605_28691_amd as sk
+
+    w = si.make_shape("lastwg", 1, heads, D, 1, 1, N, 1, seed=N)
+    q, k, v = si.make_qkv(w)
+    rows = np.array([(0, heads - 1, n) for n in range(max(0, N - 256), N)], dtype=np.int64)
+    want = oracle.skiparse_attention_rows(*oracle_inputs(q, k, v), rows, 1, 1, N, 1, "token", w.scale)
+    assert_close_bf16(gather_rows(sk.dense_attn_fwd(*_gpu((q, k, v)), 1, 1, N, scale=w.scale), rows), want, f"heads {heads} N {N}")
+
+
 # Any-resolution grids: classes of unequal size, a smallest one of exactly a tile or less (never split) and of more.
 PADDED_GROUPS = [(1, 17, 64, 4), (1, 9, 33, 3), (3, 17, 21, 2)]  # T, H, W, s; 2 heads
 
