@@ -8,8 +8,8 @@
 //     P8 = e4m3(P * sv / sv_max * 16)          the key block's V scale is folded into the probabilities
 //     O  = (P8 v8) * sv_max / 16 / sum(P)      fp32 accumulation, bf16 result
 // Both products use v_mfma_f32_32x32x64_f8f6f4 (64-deep contraction, twice the bf16 rate), transposed as in the bf16
-// kernel (S^T = K Q^T, O^T = V^T P^T) so that each lane owns one query.  A workgroup is 4 wavefronts x 32 queries
-// (one 128-position scale block, but in the any-resolution mode); keys are walked in tiles of 64, which never straddle a block.
+// kernel (S^T = K Q^T, O^T = V^T P^T) so that each lane owns one query.  A workgroup is 4 wavefronts x 32 queries,
+// one 128-position scale block; keys are walked in tiles of 64, which never straddle one.
 //   * The probabilities leave the accumulators as 16 values per 32-key block in the accumulator's key order (4h..4h+3,
 //     8+4h..); packed to bytes, one v_permlane32_swap per 16 keys turns that into 8 consecutive keys per lane half,
 //     which is the order ds_read_b64_tr_b8 (transposing LDS read for bytes) delivers V^T in.
@@ -52,14 +52,13 @@ __device__ inline void lane_pair_f(float x, float& lo, float& hi) {
 }
 
 // Any-resolution mode (Sec. 3.2): positions run over the grid padded to multiples of s*s (the quantiser has put zero codes at the
-// padding positions).  The queries are the real positions of the class only (ClassMap): a lane that held a padding query kept its
-// wavefront in the rare path, since the equal logits of zero codes give 32 probabilities of 16, above the guard on every tile.
-// Attention alone, us, padding queries computed -> left out: 2x16 heads of 64, 9x17x21 47.5 -> 37.5; 12 heads of 64, 21x30x45 712 -> 572;
-// 4 heads of 128 338 -> 313; 40 heads of 128, 1x45x80 72 -> 59, 21x45x80 17,900 -> 17,300.
-// The keys stay positions of the padded grid, because a tile has to lie in one scale block; a padding position is a masked key (a -inf
-// bias per staged row, formed a tile ahead by one wavefront).  The bias is the initial accumulator of the logits on every tile, or is added to them where a flag says that the tile holds any: the
-// former takes 8 LDS reads a tile, the latter a test and, where it is set, 32 additions as well.  The results are the same.  Attention alone
-// (with the padding queries still computed), us, added where needed -> initial accumulator: 2x16 heads of 64, 9x17x21 54.6 -> 49.3, 12 heads of 64, 21x30x45 783 -> 712, 4 heads of 128, 21x30x45
+// padding positions); a padding position is a masked key (a -inf bias per staged row, formed a tile ahead by one wavefront) and a query that is
+// computed and not stored.  A wavefront's queries are 32 consecutive positions, padding among them, because it raises the references of its rows
+// together: over the real positions alone, 128 a workgroup, a call is up to a quarter faster, but rows keep an older reference for longer and the
+// rounding of the probabilities is 0.3 to 4.7 % further from 64 bits (on the codes; 2x16 heads of 64, 9x17x21 2.620e-2 -> 2.643e-2).
+// The bias is the initial accumulator of the logits on every tile, or is added to them where a flag says that the tile holds any: the
+// former takes 8 LDS reads a tile, the latter a test and, where it is set, 32 additions as well.  The results are the same.  Attention alone, us, added
+// where needed -> initial accumulator: 2x16 heads of 64, 9x17x21 54.6 -> 49.3, 12 heads of 64, 21x30x45 783 -> 712, 4 heads of 128, 21x30x45
 // 371 -> 338; with rows whole and the last of 24 lines padded, at head_dim 128: 40 heads, 1x45x80 73.2 -> 75.6, 12 heads, 21x45x80 5359 -> 5396.
 enum Padding : int { NO_PADDING = 0, SOME_TILES = 1, MOST_TILES = 2 };
 
@@ -98,11 +97,13 @@ __global__ __launch_bounds__(NT8) void attn_fwd_fp8_kernel(Fp8AttnArgs a, PadArg
     // one wavefront (they take turns) marks the keys of a tile: lane = key.  The padding sits at the end of H and W, so the real rows
     // and columns of a class are a prefix: two divisions a key instead of the whole index map, on the path of every tile.
     const ClassMap cm = make_class_map(a.g, pad_map, p_, q_);
-    if (PAD && qt * (32u * NW8) >= cm.n) return;  // the grid is sized for the largest class
-    auto mark_keys = [&](uint32_t t) __attribute__((always_inline)) {
-        const uint32_t j = t * KT8 + lane;
+    if (PAD && cm.n == 0u) return;  // a class without a real token
+    auto is_real = [&](uint32_t j) __attribute__((always_inline)) -> bool {
         const uint32_t r = a.g.ws.div(j), ws = j - r * a.g.ws.d, hs = r - cm.hs.div(r) * cm.hs.d;
-        const bool real = j < n_seq && ws < cm.w.d && hs < cm.h.d;
+        return j < n_seq && ws < cm.w.d && hs < cm.h.d;
+    };
+    auto mark_keys = [&](uint32_t t) __attribute__((always_inline)) {
+        const bool real = is_real(t * KT8 + lane);
         kbias[t & 1u][lane] = real ? 0.f : -INFINITY;
         if (FLAG) {
             const unsigned long long pads = __builtin_amdgcn_ballot_w64(!real);
@@ -148,17 +149,14 @@ __global__ __launch_bounds__(NT8) void attn_fwd_fp8_kernel(Fp8AttnArgs a, PadArg
     if (PAD && wave == 0) mark_keys(0);
 
     // Q fragments: lane = query lq, 32 consecutive channels starting at 64*j + 32*h
-    const uint32_t jd = qt * (32u * NW8) + wave * 32u + lq;  // PAD: counted over the real positions
-    const bool q_valid = jd < cm.n;
-    const uint32_t jc = q_valid ? jd : cm.n - 1u;
-    const uint32_t jq = PAD ? padded_position(a.g, cm, jc) : jc;
-    const size_t q_off = (size_t)jq * C;
+    const uint32_t jq = qt * (32u * NW8) + wave * 32u + lq;
+    const bool q_valid = PAD ? is_real(jq) : jq < n_seq;
+    const size_t q_off = (size_t)(q_valid ? jq : n_seq - 1u) * C;  // (where a class has padding, its last position is)
     i32x8 qf[NJ];
 #pragma unroll
     for (int j = 0; j < NJ; j++) qf[j] = *(const i32x8*)(Qg + q_off + 64 * j + 32 * h);
-    // a workgroup's 128 queries are one scale block; the real ones of a padded grid come from up to a few, a factor a lane
-    const uint32_t q_blk = PAD ? jq / 128u : qt * (32u * NW8) / 128u;
-    const float cq = a.scale * 1.4426950408889634f * a.sq[(size_t)unit * n_blk + q_blk];
+    // a workgroup's 128 queries are one scale block
+    const float cq = a.scale * 1.4426950408889634f * a.sq[(size_t)unit * n_blk + qt];
 
     float sk_cur = skp[0], sv_cur = svp[0], sk_nxt, sv_nxt;
     // largest V scale of the unit: the probabilities carry sv / sv_max, the output is multiplied by sv_max at the end
@@ -347,7 +345,8 @@ __global__ __launch_bounds__(NT8) void attn_fwd_fp8_kernel(Fp8AttnArgs a, PadArg
     lane_pair_f(l_run, llo, lhi);
     const float inv = sv_max / (P_GAIN * (llo + lhi));
     if (q_valid) {
-        const size_t row = (size_t)b0_ * (uint32_t)a.g.n_tok + (PAD ? src_token_real(a.g, cm, p_, q_, jd) : src_token(a.g, p_, q_, jd));
+        bool real;  // as q_valid says
+        const size_t row = (size_t)b0_ * (uint32_t)a.g.n_tok + (PAD ? src_token_padded(a.g, p_, q_, jq, &real) : src_token(a.g, p_, q_, jq));
         __bf16* orow = (__bf16*)a.out + row * C + (size_t)head * D;
 #pragma unroll
         for (int mt = 0; mt < MT; mt++)
@@ -365,8 +364,7 @@ template <int D, int PADDING>
 static hipError_t launch_fp8_t(const Fp8AttnArgs& a, hipStream_t stream) {
     const uint32_t s2 = a.g.mode == MODE_DENSE ? 1u : (uint32_t)(a.g.s * a.g.s);
     const uint32_t n_units = (uint32_t)a.B * s2 * (uint32_t)a.heads;
-    const uint32_t n_max = unit_sizes(a.g, PADDING != NO_PADDING, 1).n_max;
-    const uint32_t q_tiles = (n_max + 32u * NW8 - 1u) / (32u * NW8);
+    const uint32_t q_tiles = ((uint32_t)a.g.n_sub + 32u * NW8 - 1u) / (32u * NW8);
     const uint64_t total = (uint64_t)n_units * q_tiles;
     if (total > 0x7ffffff0ull) return hipErrorInvalidConfiguration;
     const uint32_t per_xcd = (uint32_t)((total + 7u) / 8u);

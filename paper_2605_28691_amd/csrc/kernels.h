@@ -101,7 +101,7 @@ struct Fp8AttnArgs {
     int head_dim;
     float scale;
     uint32_t n_blk;   // scale blocks per (subsequence, head): ceil(n_sub / 128)
-    bool pad;         // any-resolution mode: g describes the padded grid; padding positions are masked keys and no queries
+    bool pad;         // any-resolution mode: g describes the padded grid; padding positions are masked keys and queries that are not stored
     GridMap g;
 };
 hipError_t launch_attn_fp8(const Fp8AttnArgs& a, hipStream_t stream);

@@ -125,3 +125,45 @@ def ideal_attention_rows_padded(q, k, v, rows, T, H, W, s, pattern, scale):
         P8 = e4m3_round(P * (svb / sv_max * P_GAIN)[None, :])
         out[[i for i, _ in lst]] = (P8 @ vcodes) * (sv_max / P_GAIN) / P.sum(axis=1, keepdims=True)
     return out
+
+
+def lazy_reference_rows_padded(q, k, v, rows, T, H, W, s, pattern, scale):
+    """As ideal_attention_rows_padded, but with the references of the kernel's rows: 32 consecutive positions of the padded grid (padding
+    among them, as zero codes) take the keys in tiles of 64 against the reference they have, and raise it together, each to its own
+    maximum so far, when 32 scaled probabilities of any of them (keys 8i..8i+3 of the tile, or 8i+4..8i+7) add up to 448 or more."""
+    (q8, sq), (k8, sk), (v8, sv) = (oracle.quantize_fp8_padded(t, T, H, W, s, pattern) for t in (q, k, v))
+    B, nsub = q.shape[0], q8.shape[1]
+    tok_at = padded_positions(B, T, H, W, s, pattern)
+    rows = np.asarray(rows, dtype=np.int64).reshape(-1, 3)
+    at = {(int(b), int(hd), int(n)): i for i, (b, hd, n) in enumerate(rows)}
+    out = np.empty((rows.shape[0], q.shape[3]), dtype=np.float64)
+    half = np.arange(64) % 8 < 4
+    for sb in range(tok_at.shape[0]):
+        real = tok_at[sb] >= 0
+        for hd in sorted({int(r[1]) for r in rows}) if real.any() else ():
+            S = scale * np.log2(np.e) * (dequantised_unit(q8, sq, sb, hd) @ dequantised_unit(k8, sk, sb, hd).T)
+            S[:, ~real] = -np.inf
+            S = S[np.minimum(np.arange((nsub + 31) // 32 * 32), nsub - 1)].reshape(-1, 32, nsub)  # [wavefront][query][key]
+            vcodes = oracle.e4m3_decode_array(v8[sb, :, hd, :])
+            sv_max = float(sv[sb, hd].max())
+            gain = P_GAIN * sv[sb, hd, np.arange(nsub) // BLOCK].astype(np.float64) / sv_max
+            m = np.full(S.shape[:2] + (1,), -np.inf)
+            l, acc = np.zeros(m.shape), np.zeros(S.shape[:2] + (q.shape[3],))
+            for t0 in range(0, nsub, 64):
+                tile, g = S[:, :, t0 : t0 + 64], gain[t0 : t0 + 64]
+                h = half[: tile.shape[2]]
+                with np.errstate(invalid="ignore", over="ignore"):
+                    P = np.exp2(tile - m) * g
+                    fits = (P[:, :, h].sum(axis=2) < 448) & (P[:, :, ~h].sum(axis=2) < 448)
+                    new = np.where(fits.all(axis=1)[:, None, None], m, np.maximum(m, tile.max(axis=2, keepdims=True)))
+                    alpha = np.where(new == -np.inf, 1.0, np.exp2(m - new))
+                    P = np.exp2(tile - np.where(new == -np.inf, 0.0, new)) * g
+                m = new
+                l = l * alpha + (P / g).sum(axis=2, keepdims=True)
+                acc = acc * alpha + e4m3_round(P) @ vcodes[t0 : t0 + 64]
+            o = (acc * sv_max / P_GAIN / l).reshape(-1, q.shape[3])
+            for j in np.flatnonzero(real):
+                i = at.get((sb % B, hd, int(tok_at[sb, j])))
+                if i is not None:
+                    out[i] = o[j]
+    return out

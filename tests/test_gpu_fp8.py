@@ -303,8 +303,7 @@ def test_fp8_any_resolution_padding_in_some_tiles(T, H, W, pattern, D):
     test_fp8_any_resolution_small(1, 2, D, T, H, W, 2, pattern)
 
 
-# The queries of the any-resolution mode are the real positions only, 128 a workgroup whatever scale block they come from: classes of exactly two
-# workgroups (256 real positions of 384) and of two and a remainder (258), fewer than a wavefront, classes with no column at all, s = 4; the
+# Classes whose real positions are a part of the padded ones: 256 of 384, 258 of 344, fewer than a wavefront, classes with no column at all, s = 4; the
 # queries' magnitude changes along the sequence, so that every scale block has a scale of its own.
 @pytest.mark.parametrize("T,H,W,s,pattern", [(16, 9, 7, 2, "token"), (43, 5, 3, 2, "group"), (1, 5, 6, 2, "token"), (40, 9, 1, 3, "token"), (7, 20, 13, 4, "group")])
 @pytest.mark.parametrize("D", [64, 128])
@@ -326,3 +325,23 @@ def test_fp8_any_resolution_queries(T, H, W, s, pattern, D):
     ma_i, rl_i = errors(ideal, exact)
     print(f"kernel max-abs {ma:.3e} rel-L2 {rl:.3e}; ideal max-abs {ma_i:.3e} rel-L2 {rl_i:.3e}")
     assert rl <= REL_L2_VS_IDEAL * rl_i and ma <= MAX_ABS_VS_IDEAL * ma_i
+
+
+# The reference that a row's probabilities are rounded against, and with it the error of the 8-bit path, depends on which rows raise it together.
+# Against the same recipe in float64 with these references only the bf16 result (1.2e-3) and a few codes on the other side of a tie differ; rows
+# grouped otherwise (over the real positions alone, say) are 1 to 2.5e-2 apart.  A sum that is 448 up to the last bit may go either way, so a few rows may.
+@pytest.mark.parametrize("B,heads,D,T,H,W,s", [(1, 2, 64, 1, 40, 15, 2), (1, 2, 64, 9, 17, 21, 2), (2, 1, 128, 5, 21, 30, 2), (1, 2, 128, 4, 17, 29, 4)])
+@pytest.mark.parametrize("pattern", ["token", "group"])
+def test_fp8_any_resolution_references(B, heads, D, T, H, W, s, pattern):
+    import paper_2605_28691_amd as sk
+
+    w = si.make_shape("r8", B, heads, D, T, H, W, s, seed=81 + s)
+    q, k, v = si.make_qkv(w)
+    c = [sk.skiparse_quantize_fp8(t.cuda(), T, H, W, s, pattern, pad=True) for t in (q, k, v)]
+    out = sk.skiparse_attn_fwd_fp8(c[0][0], c[1][0], c[2][0], c[0][1], c[1][1], c[2][1], T, H, W, s, pattern, scale=w.scale, pad=True)
+    rows = _all_rows(B, heads, T * H * W)
+    want = emu.lazy_reference_rows_padded(*oracle_inputs(q, k, v), rows, T, H, W, s, pattern, w.scale)
+    got = gather_rows(out, rows)
+    off = np.linalg.norm(got - want, axis=1) / np.linalg.norm(want, axis=1)
+    print(f"references {pattern}: median {np.median(off):.2e}, rows above 5e-3: {(off > 5e-3).mean():.3f}")
+    assert (off > 5e-3).mean() <= 0.05
