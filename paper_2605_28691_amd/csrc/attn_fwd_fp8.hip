@@ -377,7 +377,7 @@ static hipError_t launch_fp8_t(const Fp8AttnArgs& a, hipStream_t stream) {
 template <int D>
 static hipError_t launch_fp8_d(const Fp8AttnArgs& a, hipStream_t stream) {
     if (!a.pad) return launch_fp8_t<D, NO_PADDING>(a, stream);
-    return pads_most_tiles(a.g) ? launch_fp8_t<D, MOST_TILES>(a, stream) : launch_fp8_t<D, SOME_TILES>(a, stream);
+    return pads_most_tiles(D, a.g) ? launch_fp8_t<D, MOST_TILES>(a, stream) : launch_fp8_t<D, SOME_TILES>(a, stream);
 }
 
 hipError_t launch_attn_fp8(const Fp8AttnArgs& a, hipStream_t stream) {

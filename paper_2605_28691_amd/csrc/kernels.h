@@ -23,9 +23,9 @@ inline UnitSizes unit_sizes(const GridMap& g, bool pad, uint64_t per_class) {
     return {per_class * rows * cols, make_class_map(g, m, 0, 0).n, make_class_map(g, m, s - 1u, s - 1u).n};
 }
 
-inline bool pads_most_tiles(const GridMap& g) {
+inline bool pads_most_tiles(int head_dim, const GridMap& g) {
     const uint32_t line = g.ws.d, frame = g.hpad.d / (uint32_t)g.s * line;
-    return pads_most_tiles(line, frame, line * (uint32_t)g.s != (uint32_t)g.W, g.hpad.d != (uint32_t)g.H_real);
+    return pads_most_tiles(head_dim, (uint32_t)g.n_sub, line, frame, line * (uint32_t)g.s != (uint32_t)g.W, g.hpad.d != (uint32_t)g.H_real);
 }
 
 // Row gather/scatter between the original and the sparse layout.  `to_sparse` != 0: dst is sparse.  ssp_G > 0: the sparse side is an

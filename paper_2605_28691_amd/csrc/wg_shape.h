@@ -174,9 +174,13 @@ inline int pick_bwd_pair(int head_dim, const UnitSizes& u) {
     });
 }
 
-// ---- 8-bit attention, any-resolution mode: do most tiles of 64 positions hold padding?  Where the columns are padded every line of positions ends in
-// some (lines of more than two tiles aside); where only lines are, every frame does, once in frame / 64 tiles.
-inline bool pads_most_tiles(uint32_t line, uint32_t frame, bool cols_padded, bool lines_padded) {
+// ---- 8-bit attention, any-resolution mode: do most tiles of 64 positions hold padding, on a walk of enough tiles?  Where the columns are padded every line
+// of positions ends in some (lines of more than two tiles aside); where only lines are, every frame does, once in frame / 64 tiles.  The initial accumulators
+// are waited for in front of a tile's first product, which short walks do not hide.  Attention alone, added where needed -> initial accumulator, us, units of
+// positions, head_dim 128: 360x81 8.92 -> 9.83, 160x128 8.10 -> 8.30, 128x224 10.02 -> 10.36, 80x192 9.70 -> 9.72, 80x256 11.00 -> 10.78, 12x256 9.67 -> 9.34,
+// 80x384 13.74 -> 13.01; head_dim 64: 160x128 6.45 -> 6.49, 80x192 7.45 -> 6.79, 80x320 9.37 -> 8.21.
+inline bool pads_most_tiles(int head_dim, uint32_t positions, uint32_t line, uint32_t frame, bool cols_padded, bool lines_padded) {
+    if (positions < (head_dim == 128 ? 256u : 192u)) return false;
     return (cols_padded && line <= 128u) || (lines_padded && frame <= 128u);
 }
 
