@@ -124,14 +124,15 @@ __device__ inline size_t scattered_row(const AttnArgs& a, uint32_t sb, uint32_t 
 }
 
 // Workgroup shapes (FwdShape): NW wavefronts in KG key groups take 32 * NW / KG queries.
-constexpr int fwd_waves(int shape) { return shape == Q256 || shape == Q128_SPLIT ? 8 : 4; }
-constexpr int fwd_groups(int shape) { return shape >= Q64_SPLIT ? 2 : 1; }
+constexpr int fwd_waves(int shape) { return shape == Q256 || shape == Q256_FULL || shape == Q128_SPLIT ? 8 : 4; }
+constexpr int fwd_groups(int shape) { return shape == Q64_SPLIT || shape == Q128_SPLIT ? 2 : 1; }
+constexpr int fwd_queries(int shape) { return 32 * fwd_waves(shape) / fwd_groups(shape) * ATTN_QT; }
 
 // PAD selects the any-resolution mode (Sec. 3.2), where the subsequences are those of the grid padded to multiples of s*s with the
 // padding masked: the kernel walks the real tokens of the class only (ClassMap), so that a masked key is one that is never met.  Only
 // the log-sum-exp is laid out over the padded grid (zero at the padding).
 template <int D, int SHAPE, bool PAD>
-__global__ __launch_bounds__(64 * fwd_waves(SHAPE), (SHAPE == Q128 ? 2 : 1)) void attn_fwd_bf16_kernel(AttnArgs a, PadArg<PAD> pad_map, uint32_t q_tiles, uint32_t total, uint32_t per_xcd) {
+__global__ __launch_bounds__(64 * fwd_waves(SHAPE), (fwd_queries(SHAPE) == 128 && fwd_groups(SHAPE) == 1 ? 2 : 1)) void attn_fwd_bf16_kernel(AttnArgs a, PadArg<PAD> pad_map, uint32_t q_tiles, uint32_t total, uint32_t per_xcd) {
     constexpr int NW = fwd_waves(SHAPE), KG = fwd_groups(SHAPE);
     constexpr int QT = ATTN_QT;
     constexpr int QW = NW / KG;    // wavefronts of a key group: each owns 32 queries, all walk the same keys
@@ -144,6 +145,7 @@ __global__ __launch_bounds__(64 * fwd_waves(SHAPE), (SHAPE == Q128 ? 2 : 1)) voi
     // head_dim 64 12.3 -> 11.8, 144 of 160..176 in the any-resolution mode at head_dim 128 12.65 -> 12.3).  The plain kernels of head_dim 128
     // go without: three or four registers more cost 0.3 % at 768P (110.8 -> 111.1 ms) and 0.5 % of a 13.6 us layer of 390 tokens a unit.
     constexpr bool TRIM = PAD || D == 64;
+    constexpr bool SKIP_IDLE = SHAPE != Q256_FULL && SHAPE != Q128_FULL && !(D == 128 && SHAPE == Q64_SPLIT && !PAD);  // see fwd_kernel()
     constexpr int BR = 32 * QW * QT;   // query rows per workgroup: QT tiles of 32 per wavefront
     // four separate arrays: the compiler must be able to tell that the tile being filled is not the tile being read
     __shared__ __attribute__((aligned(1024))) char kbuf0_all[KG * TL::TILE_BYTES];
@@ -528,11 +530,9 @@ __global__ __launch_bounds__(64 * fwd_waves(SHAPE), (SHAPE == Q128 ? 2 : 1)) voi
 
     // ---- a wavefront without a query (in a unit's last workgroup) fetches its share of the tiles, meets the others at their barriers and
     // leaves the SIMD to the other workgroups of the CU and the power to the rest of the chip.  Out of the other wavefronts' line: in it, a call
-    // without any (48 units of 1536 tokens) took 1 % longer.  us: 320 units of 540 tokens at
-    // head_dim 64 44.8 -> 42.7, 160 of 308 at head_dim 128 19.4 -> 19.0, 160 of 960 93.0 -> 90.6, padded 160 of 3600 1056 -> 1035; calls without
-    // such wavefronts take what they took.  (The same in the backward: 2 to 3 % gained where many units end in one, 1 to 3 % lost in all small
+    // without any (48 units of 1536 tokens) took 1 % longer.  (The same in the backward: 2 to 3 % gained where many units end in one, 1 to 3 % lost in all small
     // calls, whose kernels then spill and hold more code.)
-    if (__builtin_expect(qt * BR + qw * QT * 32u >= n_seq, 0)) {
+    if (SKIP_IDLE && __builtin_expect(qt * BR + qw * QT * 32u >= n_seq, 0)) {
         for (uint32_t W = 0; W < n_tiles; W++) {
             if (W + 1u < n_tiles) {
                 issue_k((W & 1u) ? kbuf0 : kbuf1, off_k);
@@ -693,7 +693,7 @@ __global__ __launch_bounds__(64 * fwd_waves(SHAPE), (SHAPE == Q128 ? 2 : 1)) voi
 template <int D, int SHAPE, bool PAD>
 static hipError_t launch_t(const AttnArgs& a, uint32_t n_units, uint32_t n_max, hipStream_t stream) {
     constexpr int NW = fwd_waves(SHAPE);
-    constexpr uint32_t BR = 32u * (NW / fwd_groups(SHAPE)) * ATTN_QT;
+    constexpr uint32_t BR = (uint32_t)fwd_queries(SHAPE);
     const uint32_t q_tiles = (n_max + BR - 1u) / BR;
     const uint64_t total = (uint64_t)n_units * q_tiles;
     if (total > 0x7ffffff0ull) return hipErrorInvalidConfiguration;
@@ -709,10 +709,13 @@ static hipError_t launch_shape(const AttnArgs& a, hipStream_t stream) {
     const uint32_t s2 = a.g.mode == MODE_DENSE ? 1u : (uint32_t)(a.g.s * a.g.s);
     const uint32_t n_units = (uint32_t)a.B * s2 * (uint32_t)a.heads;
     const UnitSizes u = unit_sizes(a.g, PAD, (uint64_t)a.B * (uint32_t)a.heads);
-    switch (pick_fwd_shape(D, u)) {
+    switch (fwd_kernel(D, PAD, u)) {
         case Q128: return launch_t<D, Q128, PAD>(a, n_units, u.n_max, stream);
         case Q64_SPLIT: return launch_t<D, Q64_SPLIT, PAD>(a, n_units, u.n_max, stream);
         case Q128_SPLIT: return launch_t<D, Q128_SPLIT, PAD>(a, n_units, u.n_max, stream);
+        // (the any-resolution mode has no FULL kernels)
+        case Q128_FULL: return launch_t<D, PAD ? Q128 : Q128_FULL, PAD>(a, n_units, u.n_max, stream);
+        case Q256_FULL: return launch_t<D, PAD ? Q256 : Q256_FULL, PAD>(a, n_units, u.n_max, stream);
         default: return launch_t<D, Q256, PAD>(a, n_units, u.n_max, stream);
     }
 }

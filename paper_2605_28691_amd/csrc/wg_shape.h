@@ -70,6 +70,9 @@ enum FwdShape : int {
     Q128 = 2,        // 4 wavefronts, 1 group: two (head_dim 64: three) workgroups per CU; twice as many, finer-grained workgroups
     Q64_SPLIT = 3,   // 4 wavefronts, 2 groups: four times the workgroups, half the serial chain
     Q128_SPLIT = 4,  // 8 wavefronts, 2 groups: half the chain at two wavefronts per SIMD
+    // Q256 and Q128 for units whose wavefronts all have a query: see fwd_kernel()
+    Q256_FULL = 5,
+    Q128_FULL = 6,
 };
 
 // Costs fitted to 1100 calls timed in every shape (1..2700 units of 8..80,640 tokens, plain and any-resolution): the pick is 0.1 % above the
@@ -98,6 +101,23 @@ inline int pick_fwd_shape(int head_dim, const UnitSizes& u) {
         if (!c.split) return true;
         return u.workgroups(cost[0]) < 2u * CUS && (c.shape != Q64_SPLIT || u.workgroups(c) <= CUS * (uint64_t)c.max_k);
     });
+}
+
+// The kernel of a launch.  The wavefronts past a unit's last query leave the arithmetic out; launches of the large shapes that have no such wavefront take
+// the FULL kernels, without the test for it (in the any-resolution mode units differ in size, and nearly all launches have some), and so does Q64_SPLIT at
+// head_dim 128, where it cost 0.3 to 1.2 % whatever the size.  Over 240 random calls, without -> with the test, us: 320 units of 540 tokens at head_dim 64
+// 44.8 -> 42.7, 422 of 32 4.55 -> 4.19, at head_dim 128 160 of 960 93.0 -> 90.6, 160 of 1440 185 -> 181; where every wavefront has a query 0.995 to 1.012
+// of the time (40 of 384 at head_dim 64 6.97 -> 7.04); Q64_SPLIT at head_dim 128 3 of 440 10.26 -> 10.37, 25 of 260 9.20 -> 9.25; the other shapes of two
+// groups 0.99 to 1.003; the any-resolution mode 0.93 to 1.009, the latter where few wavefronts are idle (68 units of 240 and 300 at head_dim 64).
+// At head_dim 64, three workgroups a CU, it is FULL in more than one round as well if a unit is a multiple of 16 workgroups: the short ones meet on the
+// same CUs (32 an XCD, in turn), which then take more than their share of the last round (40 of 4032 182 -> 189, 80 of 1984 94 -> 97).
+inline int fwd_kernel(int head_dim, bool pad, const UnitSizes& u) {
+    const int shape = pick_fwd_shape(head_dim, u);
+    if (pad || (shape != Q256 && shape != Q128)) return shape;
+    const uint32_t rows = shape == Q256 ? 256u : 128u, left = u.n_max % rows, per_unit = (u.n_max + rows - 1u) / rows;
+    const bool idle = left != 0 && left + 32u <= rows;
+    const bool meet = head_dim == 64 && shape == Q128 && per_unit % 16u == 0 && u.units * per_unit > 3u * CUS;
+    return idle && !meet ? shape : shape == Q256 ? Q256_FULL : Q128_FULL;
 }
 
 // ---- backward.  The dQ launch's owners are queries, the dK+dV launch's keys.

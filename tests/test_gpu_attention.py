@@ -294,9 +294,13 @@ def test_workgroup_shapes(heads, N, D):
     assert np.abs(to_np64(lse[0, heads - 1]) - (m + np.log(np.exp(logits - m).sum(-1, keepdims=True)))[:, 0]).max() <= 5e-3
 
 
-# Wavefronts past a unit's last query fetch tiles and row offsets for the others and compute nothing: every row that shares a workgroup with them
-# (one to seven of them), walks of more than the 16 tiles of the offset ring, an uneven split over two groups.
-@pytest.mark.parametrize("heads,N", [(300, 33), (3, 321), (4, 1921), (12, 2465), (29, 1100), (60, 1057), (1, 2200)])
+# Wavefronts past a unit's last query fetch tiles and row offsets for the others and compute nothing: every row that shares a
+# workgroup with them (one to seven of them), walks of more than the 16 tiles of the offset ring, an uneven split over two groups; and units in whose last,
+# incomplete workgroup every wavefront has a query.
+LAST_WORKGROUPS = [(300, 33), (3, 321), (4, 1921), (12, 2465), (29, 1100), (60, 1057), (1, 2200), (60, 1137), (194, 250), (242, 174)]
+
+
+@pytest.mark.parametrize("heads,N", LAST_WORKGROUPS)
 @pytest.mark.parametrize("D", [64, 128])
 def test_last_workgroup_of_a_unit(heads, N, D):
     import paper_2605_28691_amd as sk

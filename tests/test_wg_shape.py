@@ -160,3 +160,27 @@ def test_bias_as_initial_accumulator_only_on_walks_that_hide_it(pick):
     assert pick(long) == [1] * 5
     few = [fp8(128, 40, 21, 45, 80, 2), fp8(64, 2, 1, 6, 258, 2)]  # whole lines at the end of long frames; the end of long lines
     assert pick(few) == [0] * 2
+
+
+Q256_FULL, Q128_FULL = 5, 6  # FwdShape
+
+
+def test_no_test_for_idle_wavefronts_where_none_is_idle(pick):
+    """It costs up to 1.2 % there; at head_dim 64 it unbalances several rounds of units of 16 workgroups (40 x 4032: 4 %)."""
+    full = {(48, 1536): Q128_FULL, (48, 1520): Q128_FULL, (15, 3584): Q256_FULL, (371, 128): Q128_FULL, (30, 2304): Q128_FULL}
+    assert pick([dense("kernel", 128, *c) for c in full]) == list(full.values())
+    assert pick([dense("kernel", 64, *c) for c in ((160, 384), (487, 128), (100, 4096), (40, 4032), (34, 4032), (80, 1984))]) == [Q128_FULL] * 6
+    some = {(48, 1504): Q128, (160, 20160): Q256, (472, 480): Q128, (331, 96): Q128, (1, 32): Q128}
+    assert pick([dense("kernel", 128, *c) for c in some]) == list(some.values())
+    assert pick([dense("kernel", 64, *c) for c in ((1, 32), (40, 1984), (40, 3904), (60, 2368))]) == [Q128] * 4
+    # the any-resolution mode always has the test
+    assert pick([("kernel", 128, 1, 40, 21, 45, 80, 2, 0, 1), ("kernel", 64, 1, 4, 1, 9, 14, 2, 1, 1)]) == [Q256, Q128]
+
+
+def test_gpu_tests_reach_the_kernels_with_and_without_that_test(pick):
+    import test_gpu_attention as fwd
+
+    met = {64: set(), 128: set()}
+    for D in met:
+        met[D] = set(pick([dense("kernel", D, *c) for c in fwd.WORKGROUP_SHAPES + fwd.LAST_WORKGROUPS]))
+    assert all({Q256, Q128, Q256_FULL, Q128_FULL} <= m for m in met.values())
