@@ -600,16 +600,15 @@ static hipError_t launch_all(const BwdArgs& a, hipStream_t stream) {
     const uint32_t s2 = a.g.mode == MODE_DENSE ? 1u : (uint32_t)(a.g.s * a.g.s);
     const uint32_t n_units = (uint32_t)a.B * s2 * (uint32_t)a.heads;
     const UnitSizes u = unit_sizes(a.g, PAD, (uint64_t)a.B * (uint32_t)a.heads);
-    switch (pick_bwd_pair(D, u)) {
+    const int shape = pick_bwd_shape(D, u);
+    switch (shape) {
         case B128: return launch_both<D, B128, PAD>(a, n_units, u.n_max, stream);
         case B64_SPLIT: return launch_both<D, B64_SPLIT, PAD>(a, n_units, u.n_max, stream);
         case B128_SPLIT: return launch_both<D, B128_SPLIT, PAD>(a, n_units, u.n_max, stream);
         default: break;
     }
-    // The dQ launch forms delta, which the second one reads.  Some of these calls have a better last round in workgroups of 128 queries (24 units of
-    // 2055 tokens at head_dim 64); the other shapes of pick_bwd_shape() are for calls that have been taken above.
-    const bool small = pick_bwd_shape(false, D, u) == O128;
-    const hipError_t e = small ? launch_t<D, BWD_DQ, 4, PAD>(a, n_units, u.n_max, stream) : launch_t<D, BWD_DQ, 8, PAD>(a, n_units, u.n_max, stream);
+    // The dQ launch forms delta, which the second one reads.
+    const hipError_t e = shape == TWO_LAUNCHES_DQ128 ? launch_t<D, BWD_DQ, 4, PAD>(a, n_units, u.n_max, stream) : launch_t<D, BWD_DQ, 8, PAD>(a, n_units, u.n_max, stream);
     return e != hipSuccess ? e : launch_t<D, BWD_DKV, 8, PAD>(a, n_units, u.n_max, stream);
 }
 

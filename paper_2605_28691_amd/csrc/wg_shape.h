@@ -120,44 +120,17 @@ inline int fwd_kernel(int head_dim, bool pad, const UnitSizes& u) {
     return idle && !meet ? shape : shape == Q256 ? Q256_FULL : Q128_FULL;
 }
 
-// ---- backward.  The dQ launch's owners are queries, the dK+dV launch's keys.
+// ---- backward.  The dQ owners are queries, the dK+dV owners keys.
 enum BwdShape : int {
-    O256 = 1,       // 8 wavefronts, 1 group
-    O128 = 2,       // 4 wavefronts, 1 group
-    O64_SPLIT = 3,  // 4 wavefronts, 2 groups
-};
-
-// At head_dim 128 the dK+dV shapes with 4 wavefronts hold V in registers (one workgroup per CU).  Measured, always O256 -> picked, dQ and dK+dV
-// together, us at head_dim 128, units x tokens: 16x200 39.8 -> 23, 12x700 78 -> 42, 48x390 62 -> 43, 160x960 347 -> 328, 24x2600 495 -> 328,
-// 1x5000 411 -> 190, 1x20160 1534 -> 1150, 4x20160 3560 -> 3390; 48x960 (108), 30x8190 (3340), 12x20160 (7900) and 48x8190 (5190) keep it.
-constexpr ShapeCost DQ_COST_128[] = {{O256, 256, false, 1, 5.0f, 5.0f, 0.f, {0.f, 1.30f}},
-                                     {O128, 128, false, 2, 4.0f, 4.0f, 0.f, {0.f, 0.95f, 1.34f}},
-                                     {O64_SPLIT, 64, true, 1, 4.0f, 4.0f, 0.f, {0.f, 0.63f}}};
-constexpr ShapeCost DQ_COST_64[] = {{O256, 256, false, 1, 3.5f, 3.5f, 0.f, {0.f, 0.80f}},
-                                    {O128, 128, false, 2, 2.8f, 2.8f, 0.f, {0.f, 0.56f, 0.81f}},
-                                    {O64_SPLIT, 64, true, 2, 3.0f, 3.0f, 0.f, {0.f, 0.34f, 0.60f}}};
-constexpr ShapeCost DKV_COST_128[] = {{O256, 256, false, 1, 8.0f, 8.0f, 0.f, {0.f, 1.90f}},
-                                      {O128, 128, false, 1, 6.0f, 6.0f, 0.f, {0.f, 1.32f}},
-                                      {O64_SPLIT, 64, true, 1, 7.0f, 7.0f, 0.f, {0.f, 0.80f}}};
-constexpr ShapeCost DKV_COST_64[] = {{O256, 256, false, 1, 5.0f, 5.0f, 0.f, {0.f, 1.00f}},
-                                     {O128, 128, false, 2, 4.0f, 4.0f, 0.f, {0.f, 0.80f, 1.03f}},
-                                     {O64_SPLIT, 64, true, 1, 5.0f, 5.0f, 0.f, {0.f, 0.54f}}};
-
-// Here one figure for a round is enough (picks 0.2 % above the best shape on average over 300 calls, 6 % at worst; with linear costs in between
-// 0.4 % and 13 %), and the split shape has no limit: none of 80 random training steps took longer than with 256 owners alone, and a
-// long walk gains by it too (dK+dV of 1x80640, with dQ: 13.7 ms against 14.2).
-inline int pick_bwd_shape(bool dkv, int head_dim, const UnitSizes& u) {
-    const auto& cost = dkv ? (head_dim == 128 ? DKV_COST_128 : DKV_COST_64) : (head_dim == 128 ? DQ_COST_128 : DQ_COST_64);
-    return pick_shape(cost, u, true, [](const ShapeCost&) { return true; });
-}
-
-// Both kinds of owner in ONE launch (after a small one that forms delta): the dK+dV workgroups first, the dQ workgroups fill the chip behind them,
-// so that there is one last round instead of two and a call of few units has twice the workgroups.
-enum BwdPair : int {
-    TWO_LAUNCHES = 0,  // not in one: a launch of each kind, 256 owners a workgroup (dQ also 128: pick_bwd_shape())
-    B128 = 1,          // 4 wavefronts, 1 group, two workgroups on a CU whatever their kind
-    B64_SPLIT = 2,     // 4 wavefronts, 2 groups
-    B128_SPLIT = 3,    // 8 wavefronts, 2 groups
+    // a launch of each kind of owner, 256 a workgroup (8 wavefronts), the dQ launch forming delta;
+    TWO_LAUNCHES = 0,
+    // or both kinds in ONE launch (after a small one that forms delta): the dK+dV workgroups first, the dQ workgroups fill the chip behind them, so that there
+    // is one last round instead of two and a call of few units has twice the workgroups
+    B128 = 1,        // 4 wavefronts, 1 group, two workgroups on a CU whatever their kind
+    B64_SPLIT = 2,   // 4 wavefronts, 2 groups
+    B128_SPLIT = 3,  // 8 wavefronts, 2 groups
+    // as TWO_LAUNCHES, with 128 queries (4 wavefronts) a workgroup in the dQ launch
+    TWO_LAUNCHES_DQ128 = 4,
 };
 // us, the mean of both kinds.  Fitted to 660 calls (1..1088 units of 24..30,000 tokens, plain and any-resolution) timed in every shape: the pick is 0.5 %
 // above the best on average and 12 % at worst, and 0.84 of the two launches' time on average (1.03 at worst).  Measured, two launches -> picked,
@@ -184,8 +157,12 @@ inline bool bwd_full_rounds(int head_dim, const UnitSizes& u) {
     if (head_dim == 128) return fill >= 0.955f ? u.n_max >= 2500u : u.n_max >= 4000u && fill >= 0.935f;
     return u.n_max >= 4000u && rounds <= 6u && fill >= 0.955f;
 }
-inline int pick_bwd_pair(int head_dim, const UnitSizes& u) {
-    if (bwd_full_rounds(head_dim, u)) return TWO_LAUNCHES;
+// Which dQ launch, where there are two: 128 queries a workgroup, two on a CU, have the better last round in some calls (24 units of 2055 tokens at head_dim 64).
+// One figure for a round, however full, is enough here.
+constexpr ShapeCost DQ_COST_128[] = {{TWO_LAUNCHES, 256, false, 1, 5.0f, 5.0f, 0.f, {0.f, 1.30f}}, {TWO_LAUNCHES_DQ128, 128, false, 2, 4.0f, 4.0f, 0.f, {0.f, 0.95f, 1.34f}}};
+constexpr ShapeCost DQ_COST_64[] = {{TWO_LAUNCHES, 256, false, 1, 3.5f, 3.5f, 0.f, {0.f, 0.80f}}, {TWO_LAUNCHES_DQ128, 128, false, 2, 2.8f, 2.8f, 0.f, {0.f, 0.56f, 0.81f}}};
+inline int pick_bwd_shape(int head_dim, const UnitSizes& u) {
+    if (bwd_full_rounds(head_dim, u)) return pick_shape(head_dim == 128 ? DQ_COST_128 : DQ_COST_64, u, true, [](const ShapeCost&) { return true; });
     const UnitSizes both = {2u * u.units, u.n_max, u.n_min};
     // more rounds of the split shapes than these were never the best
     return pick_shape(head_dim == 128 ? PAIR_COST_128 : PAIR_COST_64, both, false, [&](const ShapeCost& c) {

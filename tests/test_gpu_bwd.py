@@ -350,3 +350,21 @@ def test_backward_pair_shapes(D, heads, N):
 @pytest.mark.parametrize("D,case", [(D, c) for D in PADDED_PAIR_SHAPES for c in PADDED_PAIR_SHAPES[D]])
 def test_backward_any_resolution_pair_shapes(D, case):
     test_backward_any_resolution_workgroup_shapes(*case, D)
+
+
+LONG_SHAPES = [(101, 4737)]  # heads, N: a launch of each kind at head_dim 128, dQ in 128-query workgroups
+
+
+@pytest.mark.parametrize("heads,N", LONG_SHAPES)
+def test_backward_long_shapes(heads, N):
+    import paper_2605_28691_amd as sk
+
+    w = si.make_shape("bwd_long", 1, heads, 128, 1, 1, N, 1, seed=N + heads)
+    q, k, v = si.make_qkv(w)
+    dout = si.make_dout(w)
+    _, _, dq, dk, dv = _run(sk, q, k, v, dout, 1, 1, N, 1, "token", w.scale)
+    toks = [0, 63, 64, 1000, 2431, N - 130, N - 2, N - 1]
+    for h in (0, heads // 2, heads - 1):
+        want = oracle.skiparse_attention_bwd_unit(*oracle_inputs(q, k, v), si.as_oracle_array(dout), 0, h, toks, 1, 1, N, 1, "token", w.scale)
+        for g, wnt, name in zip((dq, dk, dv), want, ("dq", "dk", "dv")):
+            assert_grad_close(to_np64(g[0, toks, h]), wnt, f"head {h} {name}")

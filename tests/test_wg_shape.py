@@ -6,7 +6,7 @@ import pytest
 
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 Q256, Q128, Q64_SPLIT, Q128_SPLIT = 1, 2, 3, 4  # FwdShape
-O256, O128, O64_SPLIT = 1, 2, 3                 # BwdShape
+TWO_LAUNCHES, B128, B64_SPLIT, B128_SPLIT, TWO_LAUNCHES_DQ128 = 0, 1, 2, 3, 4  # BwdShape
 
 
 @pytest.fixture(scope="module")
@@ -74,27 +74,26 @@ def test_gpu_tests_reach_every_shape(pick):
     import test_gpu_attention as fwd
     import test_gpu_bwd as bwd
 
-    calls = []
-    for launches, module in ((("fwd",), fwd), (("dq", "dkv"), bwd)):
-        for launch in launches:
-            for D in (64, 128):
-                calls += [(launch, D, 1, heads, 1, 1, n, 1, 0, 0) for heads, n in module.WORKGROUP_SHAPES]
-                calls += [(launch, D, 1, heads, T, H, W, s, int(pattern == "group"), 1) for heads, T, H, W, s, pattern in module.PADDED_SHAPES]
-    for T, H, W, s in fwd.PADDED_GROUPS:
-        calls += [("fwd", D, 1, 2, T, H, W, s, group, 1) for D in (64, 128) for group in (0, 1)]
-    calls += [(launch, D, B, heads, T, H, W, s, group, 1) for launch in ("dq", "dkv") for B, heads, D, T, H, W, s in bwd.PAD_CASES for group in (0, 1)]
+    calls = [("fwd", D, 1, heads, 1, 1, n, 1, 0, 0) for D in (64, 128) for heads, n in fwd.WORKGROUP_SHAPES]
+    calls += [("fwd", D, 1, heads, T, H, W, s, int(pattern == "group"), 1) for D in (64, 128) for heads, T, H, W, s, pattern in fwd.PADDED_SHAPES]
+    calls += [("fwd", D, 1, 2, T, H, W, s, group, 1) for D in (64, 128) for T, H, W, s in fwd.PADDED_GROUPS for group in (0, 1)]
+    calls += [("bwd", D, 1, heads, 1, 1, n, 1, 0, 0) for D in (64, 128) for heads, n in bwd.WORKGROUP_SHAPES + bwd.PAIR_SHAPES[D]]
+    calls += [("bwd", 128, 1, heads, 1, 1, n, 1, 0, 0) for heads, n in bwd.LONG_SHAPES]
+    calls += [("bwd", D, 1, heads, T, H, W, s, int(pattern == "group"), 1) for D in (64, 128) for heads, T, H, W, s, pattern in bwd.PADDED_SHAPES + bwd.PADDED_PAIR_SHAPES[D]]
+    calls += [("bwd", D, B, heads, T, H, W, s, group, 1) for B, heads, D, T, H, W, s in bwd.PAD_CASES for group in (0, 1)]
     met, wrapped = set(), set()
     for call, shape in zip(calls, pick(calls)):
         launch, D, _, _, T, H, W, s, group, pad = call
         largest = T * max(_classes(H, s, group)) * max(_classes(W, s, group)) if pad else T * H * W
-        groups = 2 if shape >= (Q64_SPLIT if launch == "fwd" else O64_SPLIT) else 1
+        groups = 2 if shape in ((Q64_SPLIT, Q128_SPLIT) if launch == "fwd" else (B64_SPLIT, B128_SPLIT)) else 1
         met.add((launch, D, shape, pad))
         if (largest + 63) // 64 // groups > 16:
             wrapped.add((launch, D, shape, pad))
     want = {("fwd", D, shape, pad) for D in (64, 128) for shape in (Q256, Q128, Q64_SPLIT, Q128_SPLIT) for pad in (0, 1)}
-    want |= {(launch, D, shape, pad) for launch in ("dq", "dkv") for D in (64, 128) for shape in (O256, O128, O64_SPLIT) for pad in (0, 1)}
+    want |= {("bwd", D, shape, pad) for D in (64, 128) for shape in (TWO_LAUNCHES, TWO_LAUNCHES_DQ128, B128, B64_SPLIT, B128_SPLIT) for pad in (0, 1)}
     assert met == want
-    assert wrapped == want
+    # at head_dim 128 the four units of an any-resolution call take B64_SPLIT with 32 tiles at most
+    assert wrapped == want - {("bwd", 128, B64_SPLIT, 1)}
 
 
 def rows(row_bytes, n):
@@ -112,37 +111,15 @@ def test_row_batches(pick):
     assert pick([rows(128, 2000)]) == [1]
 
 
-TWO_LAUNCHES, B128, B64_SPLIT, B128_SPLIT = 0, 1, 2, 3  # BwdPair
-
-
-def test_gpu_tests_reach_every_shape_of_the_backward_in_one_launch(pick):
-    """As above for the launch that holds both kinds of owner, and for calls that keep a launch of each kind."""
-    import test_gpu_bwd as bwd
-
-    calls = [("bwd", D, 1, heads, 1, 1, n, 1, 0, 0) for D in (64, 128) for heads, n in bwd.WORKGROUP_SHAPES + bwd.PAIR_SHAPES[D]]
-    calls += [("bwd", D, 1, heads, T, H, W, s, int(pattern == "group"), 1) for D in (64, 128) for heads, T, H, W, s, pattern in bwd.PADDED_SHAPES + bwd.PADDED_PAIR_SHAPES[D]]
-    met, wrapped = set(), set()
-    for call, shape in zip(calls, pick(calls)):
-        _, D, _, _, T, H, W, s, group, pad = call
-        largest = T * max(_classes(H, s, group)) * max(_classes(W, s, group)) if pad else T * H * W
-        met.add((D, shape, pad))
-        if (largest + 63) // 64 // (2 if shape in (B64_SPLIT, B128_SPLIT) else 1) > 16:
-            wrapped.add((D, shape, pad))
-    want = {(D, shape, pad) for D in (64, 128) for shape in (TWO_LAUNCHES, B128, B64_SPLIT, B128_SPLIT) for pad in (0, 1)}
-    assert met == want
-    # at head_dim 128 the four units of an any-resolution call take B64_SPLIT with 32 tiles at most
-    assert wrapped == want - {(128, B64_SPLIT, 1)}
-
-
 def test_two_backward_launches_only_in_full_rounds(pick):
     """A launch of each kind in 256-owner workgroups is the better one in rounds that are full (or in one that mostly is), with long walks."""
     full = [(73, 12282), (192, 4584), (313, 5512), (48, 8190), (160, 20160), (6, 7844), (3, 17728)]
-    assert pick([dense("bwd", 128, *c) for c in full]) == [TWO_LAUNCHES] * 7
+    assert all(x in (TWO_LAUNCHES, TWO_LAUNCHES_DQ128) for x in pick([dense("bwd", 128, *c) for c in full]))
     rest = [(20, 20160), (39, 5781), (414, 1824), (74, 385), (160, 960), (48, 400), (160, 2600), (12, 8190), (4, 20160)]
     assert pick([dense("bwd", 128, *c) for c in rest]) == [B128] * 9
     assert pick([dense("bwd", 128, *c) for c in ((1, 120), (8, 190), (24, 220), (1, 6116))]) == [B64_SPLIT] * 4
     assert pick([dense("bwd", 128, *c) for c in ((4, 2200), (1, 11191), (12, 1200))]) == [B128_SPLIT] * 3
-    assert pick([dense("bwd", 64, *c) for c in ((24, 2199), (7, 8474), (8, 6888))]) == [TWO_LAUNCHES] * 3
+    assert all(x in (TWO_LAUNCHES, TWO_LAUNCHES_DQ128) for x in pick([dense("bwd", 64, *c) for c in ((24, 2199), (7, 8474), (8, 6888))]))
     assert pick([dense("bwd", 64, *c) for c in ((160, 960), (572, 2563), (84, 14568))]) == [B128] * 3
     # units that a group of wavefronts has no tile in are never split
     assert all(x == B128 for x in pick([dense("bwd", D, u, n) for D in (64, 128) for u in (1, 40) for n in (1, 33, 64)]))
