@@ -517,8 +517,8 @@ __global__ __launch_bounds__(64 * both_waves(SHAPE), (SHAPE == B128 || (SHAPE ==
     __shared__ __attribute__((aligned(1024))) char own2[OWN2_LDS ? 32 * NW / KG * D * 2 : 16];
     __shared__ __attribute__((aligned(16))) float row_l[KG * 2 * BT], row_d[KG * 2 * BT];
     __shared__ __attribute__((aligned(16))) uint32_t rowoff[KG * BRING * 64];
-    const bool dkv = blockIdx.x < 8u * per_xcd;  // the longer workgroups first: what is left over at the end is short
-    const uint32_t id = dkv ? blockIdx.x : blockIdx.x - 8u * per_xcd, lin = (id & 7u) * per_xcd + (id >> 3);
+    const bool dkv = blockIdx.y == 0;  // the longer workgroups first: what is left over at the end is short
+    const uint32_t lin = (blockIdx.x & 7u) * per_xcd + (blockIdx.x >> 3);
     if (lin >= total) return;
     const BwdLds lds = {s1buf0, s1buf1, s2buf0, s2buf1, own2, row_l, row_d, rowoff};
     if (dkv) bwd_part<D, BWD_DKV, NW, KG, BT, OWN2_LDS, false, PAD>(a, pad_map, lin, o_tiles, lds);
@@ -573,12 +573,13 @@ static hipError_t launch_both(const BwdArgs& a, uint32_t n_units, uint32_t n_max
     constexpr uint32_t NW = both_waves(SHAPE), WGO = 32u * NW / both_groups(SHAPE);
     const uint32_t o_tiles = (n_max + WGO - 1u) / WGO, d_tiles = (n_max + 15u) / 16u;
     const uint64_t total = (uint64_t)n_units * o_tiles, waves = (uint64_t)n_units * d_tiles;
-    if (total > 0x3ffffff0ull || waves > 0x7ffffff0ull) return hipErrorInvalidConfiguration;
+    // a grid's dimension holds fewer than 2^32 work items: one for each kind
+    if ((total + 8u) * 64u * NW >= 1ull << 32 || (waves + 4u) * 64u >= 1ull << 32) return hipErrorInvalidConfiguration;
     const uint32_t per_xcd = (uint32_t)((total + 7u) / 8u);
     PadArg<PAD> pad_map;
     make_pad_arg(a.g, pad_map);
     attn_bwd_delta_kernel<D, PAD><<<(uint32_t)((waves + 3u) / 4u), 256, 0, stream>>>(a, pad_map, d_tiles, (uint32_t)waves);
-    attn_bwd_both_kernel<D, SHAPE, PAD><<<16u * per_xcd, 64u * NW, 0, stream>>>(a, pad_map, o_tiles, (uint32_t)total, per_xcd);
+    attn_bwd_both_kernel<D, SHAPE, PAD><<<dim3(8u * per_xcd, 2u), 64u * NW, 0, stream>>>(a, pad_map, o_tiles, (uint32_t)total, per_xcd);
     return hipGetLastError();
 }
 

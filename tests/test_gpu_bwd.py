@@ -368,3 +368,30 @@ def test_backward_long_shapes(heads, N):
         want = oracle.skiparse_attention_bwd_unit(*oracle_inputs(q, k, v), si.as_oracle_array(dout), 0, h, toks, 1, 1, N, 1, "token", w.scale)
         for g, wnt, name in zip((dq, dk, dv), want, ("dq", "dk", "dv")):
             assert_grad_close(to_np64(g[0, toks, h]), wnt, f"head {h} {name}")
+
+
+def test_backward_of_very_many_tiny_units():
+    """8,519,680 units of two tokens: workgroups of both kinds in one launch, more of each than 2^23 (twice 256 work items of them do not fit one grid
+    dimension).  Every gradient against the formulas in float32."""
+    import paper_2605_28691_amd as sk
+
+    B, heads, D, T, H, W, s = 32768, 65, 64, 2, 2, 2, 2
+    gen = torch.Generator(device="cuda").manual_seed(3)
+    q, k, v, dout = (torch.randn((B, T * H * W, heads, D), generator=gen, device="cuda", dtype=torch.bfloat16) for _ in range(4))
+    out, lse = sk.skiparse_attn_fwd_lse(q, k, v, T, H, W, s, "token")
+    grads = sk.skiparse_attn_bwd(q, k, v, out, dout, lse, T, H, W, s, "token")
+    diff, norm = [0.0] * 3, [0.0] * 3
+    for b in range(0, B, 2048):
+        x, y, z, do = (t[b : b + 2048].float().view(-1, T, H * W, heads, D) for t in (q, k, v, dout))  # a unit: the frames of one position
+        p = torch.softmax((x[:, :, None] * y[:, None]).sum(-1) * D ** -0.5, dim=2)  # [b][query][key][position][head]
+        dp = (do[:, :, None] * z[:, None]).sum(-1)
+        ds = (p * (dp - (p * dp).sum(2, keepdim=True)) * D ** -0.5)[..., None]
+        want = (ds * y[:, None]).sum(2), (ds * x[:, :, None]).sum(1), (p[..., None] * do[:, :, None]).sum(1)
+        for i, (g, w) in enumerate(zip(grads, want)):
+            d = g[b : b + 2048].float().view_as(w) - w
+            diff[i] += float(d.square().sum(dtype=torch.float64))
+            norm[i] += float(w.square().sum(dtype=torch.float64))
+            rows = w.square().sum(-1)
+            assert bool((d.square().sum(-1) <= 0.1 * rows.clamp_min(rows.mean())).all())  # no row is another's
+    for d, n in zip(diff, norm):
+        assert (d / n) ** 0.5 <= 1e-2
