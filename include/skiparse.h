@@ -46,7 +46,7 @@ enum {
     SKIPARSE_ESHAPE = -2,       /* H or W not divisible as the pattern requires, or sizes overflow 31-bit row counts */
     SKIPARSE_EUNSUPPORTED = -3, /* no kernel for this head_dim / element type */
     SKIPARSE_EWORKSPACE = -4,   /* workspace missing or smaller than skiparse_workspace_bytes() */
-    SKIPARSE_EHIP = -5          /* a kernel launch failed; see skiparse_last_hip_error() */
+    SKIPARSE_EHIP = -5          /* a kernel launch failed, or would need 2^32 work items or more; see skiparse_last_hip_error() */
 };
 
 /*

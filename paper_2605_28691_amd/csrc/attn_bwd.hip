@@ -573,12 +573,12 @@ static hipError_t launch_both(const BwdArgs& a, uint32_t n_units, uint32_t n_max
     constexpr uint32_t NW = both_waves(SHAPE), WGO = 32u * NW / both_groups(SHAPE);
     const uint32_t o_tiles = (n_max + WGO - 1u) / WGO, d_tiles = (n_max + 15u) / 16u;
     const uint64_t total = (uint64_t)n_units * o_tiles, waves = (uint64_t)n_units * d_tiles;
-    // a grid's dimension holds fewer than 2^32 work items: one for each kind
-    if ((total + 8u) * 64u * NW >= 1ull << 32 || (waves + 4u) * 64u >= 1ull << 32) return hipErrorInvalidConfiguration;
+    if (!fits_grid(total + 7u, 64u * NW) || !fits_grid((waves + 3u) / 4u, 256u)) return hipErrorInvalidConfiguration;
     const uint32_t per_xcd = (uint32_t)((total + 7u) / 8u);
     PadArg<PAD> pad_map;
     make_pad_arg(a.g, pad_map);
     attn_bwd_delta_kernel<D, PAD><<<(uint32_t)((waves + 3u) / 4u), 256, 0, stream>>>(a, pad_map, d_tiles, (uint32_t)waves);
+    // a dimension of the grid for each kind: together they could fill one
     attn_bwd_both_kernel<D, SHAPE, PAD><<<dim3(8u * per_xcd, 2u), 64u * NW, 0, stream>>>(a, pad_map, o_tiles, (uint32_t)total, per_xcd);
     return hipGetLastError();
 }
@@ -588,7 +588,7 @@ static hipError_t launch_t(const BwdArgs& a, uint32_t n_units, uint32_t n_max, h
     constexpr uint32_t WGO = 32u * NW;
     const uint32_t o_tiles = (n_max + WGO - 1u) / WGO;
     const uint64_t total = (uint64_t)n_units * o_tiles;
-    if (total > 0x7ffffff0ull) return hipErrorInvalidConfiguration;
+    if (!fits_grid(total + 7u, 64 * NW)) return hipErrorInvalidConfiguration;
     const uint32_t per_xcd = (uint32_t)((total + 7u) / 8u);
     PadArg<PAD> pad_map;
     make_pad_arg(a.g, pad_map);

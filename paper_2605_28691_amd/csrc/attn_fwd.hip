@@ -696,7 +696,7 @@ static hipError_t launch_t(const AttnArgs& a, uint32_t n_units, uint32_t n_max, 
     constexpr uint32_t BR = (uint32_t)fwd_queries(SHAPE);
     const uint32_t q_tiles = (n_max + BR - 1u) / BR;
     const uint64_t total = (uint64_t)n_units * q_tiles;
-    if (total > 0x7ffffff0ull) return hipErrorInvalidConfiguration;
+    if (!fits_grid(total + 7u, 64 * NW)) return hipErrorInvalidConfiguration;
     const uint32_t per_xcd = (uint32_t)((total + 7u) / 8u);
     PadArg<PAD> pad_map;
     make_pad_arg(a.g, pad_map);

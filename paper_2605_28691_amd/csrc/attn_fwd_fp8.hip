@@ -366,7 +366,7 @@ static hipError_t launch_fp8_t(const Fp8AttnArgs& a, hipStream_t stream) {
     const uint32_t n_units = (uint32_t)a.B * s2 * (uint32_t)a.heads;
     const uint32_t q_tiles = ((uint32_t)a.g.n_sub + 32u * NW8 - 1u) / (32u * NW8);
     const uint64_t total = (uint64_t)n_units * q_tiles;
-    if (total > 0x7ffffff0ull) return hipErrorInvalidConfiguration;
+    if (!fits_grid(total + 7u, NT8)) return hipErrorInvalidConfiguration;
     const uint32_t per_xcd = (uint32_t)((total + 7u) / 8u);
     PadArg<PADDING != NO_PADDING> pad_map;
     make_pad_arg(a.g, pad_map);

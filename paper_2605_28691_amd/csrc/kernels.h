@@ -10,6 +10,9 @@
 
 namespace skiparse {
 
+// A dimension of a grid holds fewer than 2^32 work items.  A launch of more is not refused but cut, so the launchers refuse it.
+inline bool fits_grid(uint64_t workgroups, uint32_t threads) { return workgroups * threads < 1ull << 32; }
+
 // Sizes of the units of a launch over map g, `per_class` units (batch elements x heads) a class.
 inline UnitSizes unit_sizes(const GridMap& g, bool pad, uint64_t per_class) {
     if (!pad) return {per_class * (g.mode == MODE_DENSE ? 1u : (uint32_t)(g.s * g.s)), (uint32_t)g.n_sub, (uint32_t)g.n_sub};

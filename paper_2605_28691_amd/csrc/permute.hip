@@ -67,16 +67,20 @@ __global__ __launch_bounds__(PERMUTE_WAVES * 64) void permute_short_rows_kernel(
 }
 
 template <int MAP, int UNROLL>
-static void launch_long(const void* src, void* dst, const RowArgs& g, uint32_t chunks, uint32_t n_rows, uint32_t ssp_G, hipStream_t stream) {
+static hipError_t launch_long(const void* src, void* dst, const RowArgs& g, uint32_t chunks, uint32_t n_rows, uint32_t ssp_G, hipStream_t stream) {
     const uint32_t span = row_span(chunks, n_rows, UNROLL), parts = (chunks + span - 1u) / span;
-    const uint32_t blocks = (n_rows * parts + PERMUTE_WAVES - 1) / PERMUTE_WAVES;
-    permute_rows_kernel<MAP, UNROLL><<<blocks, PERMUTE_WAVES * 64, 0, stream>>>((const u32x4*)src, (u32x4*)dst, g, make_div32(parts), span, chunks, n_rows, ssp_G);
+    const uint64_t blocks = ((uint64_t)n_rows * parts + PERMUTE_WAVES - 1) / PERMUTE_WAVES;
+    if (!fits_grid(blocks, PERMUTE_WAVES * 64)) return hipErrorInvalidConfiguration;
+    permute_rows_kernel<MAP, UNROLL><<<(uint32_t)blocks, PERMUTE_WAVES * 64, 0, stream>>>((const u32x4*)src, (u32x4*)dst, g, make_div32(parts), span, chunks, n_rows, ssp_G);
+    return hipGetLastError();
 }
 
 template <int MAP, int UNROLL>
-static void launch_short(const void* src, void* dst, const RowArgs& g, uint32_t chunks, uint32_t n_rows, uint32_t batch, uint32_t ssp_G, hipStream_t stream) {
+static hipError_t launch_short(const void* src, void* dst, const RowArgs& g, uint32_t chunks, uint32_t n_rows, uint32_t batch, uint32_t ssp_G, hipStream_t stream) {
     const uint32_t per_block = batch * PERMUTE_WAVES, blocks = (n_rows + per_block - 1) / per_block;
+    if (!fits_grid(blocks, PERMUTE_WAVES * 64)) return hipErrorInvalidConfiguration;
     permute_short_rows_kernel<MAP, UNROLL><<<blocks, PERMUTE_WAVES * 64, 0, stream>>>((const u32x4*)src, (u32x4*)dst, g, make_fastdiv32(chunks), n_rows, batch, ssp_G);
+    return hipGetLastError();
 }
 
 template <int MAP>
@@ -89,15 +93,11 @@ static hipError_t launch_rows(const void* src, void* dst, int B, const GridMap& 
     if (batch > 1u) {
         // few rows or very short ones: no more rounds than the batch has (three moves of 4608 rows of 16 to 512 B 8.3..9.9 us -> 7.7..9.2)
         const uint32_t per_wave = batch * chunks;
-        if (per_wave <= 64u) launch_short<MAP, 1>(src, dst, args, chunks, n_rows, batch, ssp_G, stream);
-        else if (per_wave <= 128u) launch_short<MAP, 2>(src, dst, args, chunks, n_rows, batch, ssp_G, stream);
-        else launch_short<MAP, 4>(src, dst, args, chunks, n_rows, batch, ssp_G, stream);
-    } else if (row_unroll(chunks) == 2u) {
-        launch_long<MAP, 2>(src, dst, args, chunks, n_rows, ssp_G, stream);
-    } else {
-        launch_long<MAP, 1>(src, dst, args, chunks, n_rows, ssp_G, stream);
+        if (per_wave <= 64u) return launch_short<MAP, 1>(src, dst, args, chunks, n_rows, batch, ssp_G, stream);
+        if (per_wave <= 128u) return launch_short<MAP, 2>(src, dst, args, chunks, n_rows, batch, ssp_G, stream);
+        return launch_short<MAP, 4>(src, dst, args, chunks, n_rows, batch, ssp_G, stream);
     }
-    return hipGetLastError();
+    return row_unroll(chunks) == 2u ? launch_long<MAP, 2>(src, dst, args, chunks, n_rows, ssp_G, stream) : launch_long<MAP, 1>(src, dst, args, chunks, n_rows, ssp_G, stream);
 }
 
 hipError_t launch_switch(const void* src, void* dst, int B, const GridMap& g_to, size_t row_bytes, hipStream_t stream) {

@@ -114,7 +114,7 @@ hipError_t launch_quantize_fp8(const void* x, void* x8, float* scales, int B, in
     const uint32_t s = g.mode == MODE_DENSE ? 1u : (uint32_t)g.s;
     const uint32_t n_blk = ((uint32_t)g.n_sub + QBLOCK - 1) / QBLOCK;
     const uint64_t blocks = (uint64_t)B * s * s * (uint32_t)heads * n_blk;
-    if (blocks > 0x7fffffffull) return hipErrorInvalidConfiguration;
+    if (!fits_grid(blocks, 256u)) return hipErrorInvalidConfiguration;
     const QuantArgs a = {make_div32(n_blk), make_div32((uint32_t)heads), make_div32((uint32_t)B), make_div32(s)};
     const uint64_t bytes = (uint64_t)B * (uint32_t)g.n_tok * (uint32_t)heads * (uint32_t)head_dim * 2u;
     if (head_dim == 128)

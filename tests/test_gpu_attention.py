@@ -364,3 +364,13 @@ def test_any_resolution_workgroup_shapes(heads, T, H, W, s, pattern, D):
     sk.skiparse_attn_fwd(*_gpu((q, k, v)), T, H, W, s, pattern, scale=w.scale, pad=True, out=out)
     assert bool((guard[:2048] == 5.0).all()) and bool((guard[2048 + q.numel() :] == 5.0).all())
     assert_close_bf16(gather_rows(out, rows), want, f"padded {pattern}")
+
+
+def test_more_workgroups_than_a_grid_holds_are_refused():
+    """17,039,360 units of one token in workgroups of 256: a launch of 2^32 work items or more is cut without an error, so the call says no."""
+    import paper_2605_28691_amd as sk
+
+    q = torch.zeros((65536, 4, 65, 64), dtype=torch.bfloat16, device="cuda")
+    with pytest.raises(sk.SkiparseError) as e:
+        sk.skiparse_attn_fwd(q, q, q, 1, 2, 2, 2, "token")
+    assert e.value.code == -5
