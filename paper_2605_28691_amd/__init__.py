@@ -8,6 +8,7 @@ from __future__ import annotations
 
 import ctypes
 import functools
+import importlib
 import os
 
 import torch
@@ -86,13 +87,13 @@ def lib() -> ctypes.CDLL:
         L.skiparse_strerror.argtypes = [i]
         L.skiparse_last_hip_error.restype = i
         L.skiparse_last_hip_error.argtypes = []
+        _bind(L)
         _lib = L
     return _lib
 
 
-# A small call is bound by what it costs to issue it (a kernel of 4 us behind 10 us of Python), so the marshalling keeps to plain
-# integers: addresses and the stream handle are converted once, by ctypes, and no Stream or c_void_p object is made for them.  torch hands
-# out the bare handle under private names only; where a release has no such names the Stream object serves.
+# A small call is bound by what it costs to issue it, so no Stream object is made for it.  torch hands out the bare handle under private names
+# only; where a release has no such names the Stream object serves.
 _raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
 _get_device = getattr(torch._C, "_cuda_getDevice", None)
 
@@ -157,15 +158,32 @@ def _general(name: str, *args) -> None:
     _failed(getattr(lib(), name)(*args), name)
 
 
-# The entry points themselves: natively marshalled where the module is there (it is built for one torch and one Python), by ctypes otherwise.
-try:
-    from . import _marshal
-except ImportError:
-    _marshal = None
-else:
-    _marshal.set_up(_general, _failed)
+# The entry points themselves: by ctypes until the library is opened, then natively marshalled where there is a module for this Python and
+# this torch.  The module is imported then and not with the package, so that a process that builds first gets what it has built.
 for _name in _TENSORS:
-    globals()["_" + _name] = functools.partial(_general, _name) if _marshal is None else getattr(_marshal, _name)
+    globals()["_" + _name] = functools.partial(_general, _name)
+
+
+def _bind(L: ctypes.CDLL) -> None:
+    """Looks for the module, and hands it the functions of the library that has been opened."""
+    global _marshal
+    try:
+        native = importlib.import_module(__name__ + "._marshal")
+    except ImportError:
+        native = None
+    if native is not None:
+        native.set_up(_general, _failed)
+        for name in _TENSORS:
+            native.bind(name, ctypes.cast(getattr(L, name), ctypes.c_void_p).value)
+            globals()["_" + name] = getattr(native, name)
+    _marshal = native
+
+
+def __getattr__(name: str):
+    if name == "_marshal":  # the native module, or None: known once the library is open
+        lib()
+        return globals()[name]
+    raise AttributeError(f"module {__name__!r} has no attribute {name!r}")
 
 
 def _dims(x: torch.Tensor, T: int, H: int, W: int):

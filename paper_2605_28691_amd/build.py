@@ -2,6 +2,7 @@
 micro-kernels the benchmark times (HIP, gfx950 only), and _marshal.so, the binding's native calls (host C++)."""
 from __future__ import annotations
 
+import importlib
 import os
 import subprocess
 import sysconfig
@@ -30,11 +31,12 @@ def build(verbose: bool = False, save_temps: bool = False) -> str:
     _build_one(PROBE_LIB, PROBE_SOURCES, verbose, False)
     _build_one(LIB, SOURCES, verbose, save_temps)
     _build_marshal(verbose)
+    importlib.invalidate_caches()
     return LIB
 
 
 def _build_marshal(verbose: bool) -> str:
-    """The CPython module: compiled against torch's headers, linked to the attention library beside it."""
+    """The CPython module, compiled against torch's headers."""
     import torch
 
     root = os.path.dirname(torch.__file__)
@@ -43,7 +45,6 @@ def _build_marshal(verbose: bool) -> str:
            "-isystem", os.path.join(root, "include"), "-isystem", os.path.join(root, "include", "torch", "csrc", "api", "include"),
            "-isystem", sysconfig.get_paths()["include"],
            os.path.join(CSRC, "marshal.cpp"), "-o", MARSHAL + ".tmp",
-           "-L" + HERE, "-l:" + os.path.basename(LIB), "-Wl,-rpath,$ORIGIN",
            "-L" + os.path.join(root, "lib"), "-ltorch_python", "-ltorch_cpu", "-lc10"]
     _run(cmd, verbose)
     os.replace(MARSHAL + ".tmp", MARSHAL)

@@ -1,15 +1,19 @@
 // The calls of the Python binding, marshalled natively: every entry point of include/skiparse.h that launches kernels as a function of a CPython
 // module, with the argument list of the C function, tensors in the places of device pointers.
 //
-// A small call is bound by what it costs to issue it: a kernel of 4 us behind 7 us of host work, of which the launch is 2.5 and ctypes, with an
-// address asked for tensor by tensor in Python, was FIG.  Here an argument costs nanoseconds.
+// A small call is bound by what it costs to issue it: a kernel of 4 us behind 3.3 us of host work, the launch among them.  By way of ctypes,
+// with an address asked for tensor by tensor in Python, it is 5.4.  Here an argument costs nanoseconds.
 //
 // Only plain arguments are taken: torch.Tensor itself, on the GPU and contiguous, int and float themselves.  With anything else, and to turn a
 // code into an exception, the module calls the functions that the binding has given it, so that what those accept, refuse and raise does not
 // depend on this module.
+//
+// The module is not linked to the library: the binding hands it the addresses in the copy that it has opened itself, so that a process that
+// rebuilds the library calls one copy only.
 #include <Python.h>
 #include <torch/csrc/autograd/python_variable.h>
 
+#include <cstring>
 #include <tuple>
 #include <utility>
 
@@ -134,11 +138,15 @@ PyObject* call(int (*fn)(A...), const char* name, PyObject* const* args, Py_ssiz
 }
 
 constexpr size_t NEVER = ~(size_t)0;
+// address of the C function: none until the binding has opened the library, and the general way is taken (which opens it)
+#define SLOT(name, none) decltype(&::name) g_##name = nullptr;
 // argument that may be None: the workspace of the forward layer, which the fused form does not need
 #define ENTRY(name, none)                                                 \
     PyObject* py_##name(PyObject*, PyObject* const* args, Py_ssize_t n) { \
-        return call<none>(name, #name, args, n);                          \
+        return g_##name ? call<none>(g_##name, #name, args, n) : general(#name, args, n); \
     }
+#define BIND(name, none) \
+    if (strcmp(what, #name) == 0) g_##name = (decltype(g_##name))address;
 #define LISTED(name, none) {#name, (PyCFunction)(void (*)(void))py_##name, METH_FASTCALL, nullptr},
 #define ENTRIES(X) \
     X(skiparse_attn_fwd, 15) \
@@ -154,6 +162,7 @@ constexpr size_t NEVER = ~(size_t)0;
     X(skiparse_attn_bwd_static, NEVER) \
     X(skiparse_quantize_fp8_ex, NEVER) \
     X(skiparse_attn_fwd_fp8_ex, NEVER)
+ENTRIES(SLOT)
 ENTRIES(ENTRY)
 
 PyObject* set_up(PyObject*, PyObject* const* args, Py_ssize_t n) {
@@ -170,7 +179,20 @@ PyObject* set_up(PyObject*, PyObject* const* args, Py_ssize_t n) {
     Py_RETURN_NONE;
 }
 
-PyMethodDef methods[] = {ENTRIES(LISTED){"set_up", (PyCFunction)(void (*)(void))set_up, METH_FASTCALL, nullptr}, {nullptr, nullptr, 0, nullptr}};
+PyObject* bind(PyObject*, PyObject* const* args, Py_ssize_t n) {
+    const char* what = n == 2 ? PyUnicode_AsUTF8(args[0]) : nullptr;
+    void* address = what != nullptr ? PyLong_AsVoidPtr(args[1]) : nullptr;
+    if (PyErr_Occurred()) return nullptr;
+    if (address == nullptr) {
+        PyErr_SetString(PyExc_TypeError, "bind(name, address)");
+        return nullptr;
+    }
+    ENTRIES(BIND)
+    Py_RETURN_NONE;
+}
+
+PyMethodDef methods[] = {ENTRIES(LISTED){"bind", (PyCFunction)(void (*)(void))bind, METH_FASTCALL, nullptr},
+                         {"set_up", (PyCFunction)(void (*)(void))set_up, METH_FASTCALL, nullptr}, {nullptr, nullptr, 0, nullptr}};
 PyModuleDef module = {PyModuleDef_HEAD_INIT, "_marshal", "Native marshalling of the binding's calls.", -1, methods, nullptr, nullptr, nullptr, nullptr};
 
 }  // namespace

@@ -1,6 +1,7 @@
 """The Python binding's own logic, without a GPU: sizes that the library computes, and the stream that calls go to."""
 import ctypes
 import os
+import shutil
 import subprocess
 import sys
 
@@ -113,3 +114,26 @@ def test_every_entry_point_is_marshalled_in_the_order_of_the_c_function():
     for name, tensors in sk._TENSORS.items():
         types = getattr(sk.lib(), name).argtypes
         assert [i for i, t in enumerate(types) if t is ctypes.c_void_p] == [i for i, _ in tensors] + [len(types) - 1]
+
+
+def _copy_of_package(tmp_path):
+    """The built package in a folder of its own, for processes that replace its files."""
+    pkg = os.path.join(tmp_path, "paper_2605_28691_amd")
+    shutil.copytree(os.path.dirname(sk._LIB_PATH), pkg, ignore=shutil.ignore_patterns("csrc", "__pycache__", "*_probe.so"))
+    return pkg
+
+
+def test_a_library_built_after_the_import_is_the_only_one(tmp_path):
+    """A process that imports the package, builds and calls runs what it has built, by every route."""
+    lib = os.path.join(_copy_of_package(tmp_path), "libskiparse.so")
+    code = f"""
+import os, shutil
+import paper_2605_28691_amd as sk
+shutil.copy({lib!r}, {lib!r} + ".tmp")
+os.replace({lib!r} + ".tmp", {lib!r})  # as a build does
+assert sk.lib() and sk._marshal is not None and sk._skiparse_permute is sk._marshal.skiparse_permute
+mapped = {{line.split(None, 5)[5].strip() for line in open("/proc/self/maps") if "libskiparse" in line}}
+assert mapped == {{{lib!r}}}, mapped  # a replaced file is listed as deleted
+"""
+    done = subprocess.run([sys.executable, "-c", code], cwd=tmp_path, stderr=subprocess.PIPE, text=True)
+    assert done.returncode == 0, done.stderr
