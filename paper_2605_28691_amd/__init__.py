@@ -164,12 +164,19 @@ for _name in _TENSORS:
     globals()["_" + _name] = functools.partial(_general, _name)
 
 
+def _torch_build() -> str:
+    """Which torch this is: the module reads tensors by the layout in the headers that it was built with."""
+    return f"{torch.__version__} {torch.version.git_version}"
+
+
 def _bind(L: ctypes.CDLL) -> None:
     """Looks for the module, and hands it the functions of the library that has been opened."""
     global _marshal
     try:
         native = importlib.import_module(__name__ + "._marshal")
     except ImportError:
+        native = None
+    if native is not None and getattr(native, "BUILT_FOR", None) != _torch_build():
         native = None
     if native is not None:
         native.set_up(_general, _failed)

@@ -1,17 +1,19 @@
 """Compiles the sources under csrc/ in-tree: libskiparse.so, the attention library, and libskiparse_probe.so, the measurement
-micro-kernels the benchmark times (HIP, gfx950 only), and _marshal.so, the binding's native calls (host C++)."""
+micro-kernels the benchmark times (HIP, gfx950 only), and the module _marshal, the binding's native calls (host C++)."""
 from __future__ import annotations
 
+import glob
 import importlib
 import os
 import subprocess
 import sysconfig
+import warnings
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libskiparse.so")
 SOURCES = ["api.hip", "permute.hip", "attn_fwd.hip", "attn_bwd.hip", "quant_fp8.hip", "attn_fwd_fp8.hip"]
-MARSHAL = os.path.join(HERE, "_marshal.so")
+MARSHAL = os.path.join(HERE, "_marshal" + sysconfig.get_config_var("EXT_SUFFIX"))  # found by the Python that it is built for
 PROBE_LIB = os.path.join(HERE, "libskiparse_probe.so")
 PROBE_SOURCES = ["mfma_probe.hip"]
 FLAGS = [
@@ -29,8 +31,13 @@ FLAGS = [
 def build(verbose: bool = False, save_temps: bool = False) -> str:
     """Builds everything; returns the path of the attention library."""
     _build_one(PROBE_LIB, PROBE_SOURCES, verbose, False)
+    for old in glob.glob(os.path.join(HERE, "_marshal*.so")):  # never an old module beside a new library
+        os.remove(old)
     _build_one(LIB, SOURCES, verbose, save_temps)
-    _build_marshal(verbose)
+    try:
+        _build_marshal(verbose)
+    except (OSError, RuntimeError) as e:  # no host compiler, or no headers of this Python or torch
+        warnings.warn(f"the native module of the binding was not built, calls go through ctypes: {e}")
     importlib.invalidate_caches()
     return LIB
 
@@ -39,9 +46,11 @@ def _build_marshal(verbose: bool) -> str:
     """The CPython module, compiled against torch's headers."""
     import torch
 
+    from . import _torch_build
+
     root = os.path.dirname(torch.__file__)
     cmd = [os.environ.get("CXX", "g++"), "-O2", "-std=c++17", "-fPIC", "-shared", "-fvisibility=hidden",
-           f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}",
+           f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}", f'-DBUILT_FOR="{_torch_build()}"',
            "-isystem", os.path.join(root, "include"), "-isystem", os.path.join(root, "include", "torch", "csrc", "api", "include"),
            "-isystem", sysconfig.get_paths()["include"],
            os.path.join(CSRC, "marshal.cpp"), "-o", MARSHAL + ".tmp",

@@ -21,6 +21,10 @@
 
 namespace {
 
+#ifndef BUILT_FOR
+#error "the torch that the headers belong to"
+#endif
+
 PyObject* g_general = nullptr;  // (name, *arguments): the same call by way of ctypes
 PyObject* g_failed = nullptr;   // (code, name): raises
 
@@ -197,4 +201,8 @@ PyModuleDef module = {PyModuleDef_HEAD_INIT, "_marshal", "Native marshalling of 
 
 }  // namespace
 
-extern "C" __attribute__((visibility("default"))) PyObject* PyInit__marshal() { return PyModule_Create(&module); }
+extern "C" __attribute__((visibility("default"))) PyObject* PyInit__marshal() {
+    PyObject* m = PyModule_Create(&module);
+    if (m != nullptr && PyModule_AddStringConstant(m, "BUILT_FOR", BUILT_FOR) != 0) Py_CLEAR(m);
+    return m;
+}

@@ -4,6 +4,7 @@ import os
 import shutil
 import subprocess
 import sys
+import sysconfig
 
 import numpy as np
 import pytest
@@ -137,3 +138,44 @@ assert mapped == {{{lib!r}}}, mapped  # a replaced file is listed as deleted
 """
     done = subprocess.run([sys.executable, "-c", code], cwd=tmp_path, stderr=subprocess.PIPE, text=True)
     assert done.returncode == 0, done.stderr
+
+
+@pytest.mark.parametrize("change, native", [("", True), ("torch.__version__ = '0.0'", False), ("torch.version.git_version = 'another'", False)])
+def test_module_is_for_one_torch(tmp_path, change, native):
+    """The module reads tensors by the layout in the headers of one torch: under another one calls go through ctypes."""
+    _copy_of_package(tmp_path)
+    code = f"""
+import torch
+{change}
+import paper_2605_28691_amd as sk
+assert (sk._marshal is not None) == {native}
+assert sk.lib() and (sk._skiparse_permute.__class__.__name__ == "partial") != {native}
+"""
+    assert subprocess.run([sys.executable, "-c", code], cwd=tmp_path).returncode == 0
+
+
+def test_module_is_for_one_python(tmp_path):
+    """Its name says which: a module without one, from another build, is taken away and never looked for."""
+    from paper_2605_28691_amd import build
+
+    assert os.path.basename(build.MARSHAL) == "_marshal" + sysconfig.get_config_var("EXT_SUFFIX") and os.path.exists(build.MARSHAL)
+    assert [n for n in os.listdir(build.HERE) if n.startswith("_marshal")] == [os.path.basename(build.MARSHAL)]
+
+
+def test_build_without_a_host_compiler(tmp_path, monkeypatch):
+    """The library is what a build has to make; without its module calls go through ctypes.  No module of an earlier build stays beside it."""
+    from paper_2605_28691_amd import build
+
+    made = []
+    for name in ("_marshal.so", os.path.basename(build.MARSHAL)):
+        (tmp_path / name).write_bytes(b"old")
+    monkeypatch.setattr(build, "HERE", str(tmp_path))
+    monkeypatch.setattr(build, "MARSHAL", str(tmp_path / os.path.basename(build.MARSHAL)))
+    monkeypatch.setattr(build, "_build_one", lambda lib, *rest: made.append((lib, sorted(p.name for p in tmp_path.iterdir()))))
+    monkeypatch.setenv("CXX", str(tmp_path / "no-such-compiler"))
+    with pytest.warns(UserWarning, match="ctypes"):
+        assert build.build() == build.LIB
+    assert made[-1] == (build.LIB, []) and not list(tmp_path.iterdir())
+    monkeypatch.setenv("CXX", "false")  # one that fails
+    with pytest.warns(UserWarning, match="ctypes"):
+        build.build()
