@@ -504,7 +504,7 @@ __global__ __launch_bounds__(64 * NW, (NW == 4 ? 2 : 1)) void attn_bwd_kernel(Bw
 }
 
 // Both kinds in one launch.  At head_dim 128 with the owners' V in LDS, tiles of 32 rows leave room for two B128 workgroups on a CU (70 KiB each) and
-// for the two groups of B128_SPLIT; each kind fits 256 registers without a spill (4 to 6 in B128_SPLIT).  48 units of 400 tokens: 35 us with the
+// for the two groups of B128_SPLIT; each kind fits 256 registers without a spill (3 to 5 values in B128_SPLIT).  48 units of 400 tokens: 35 us with the
 // launch that forms delta, against 43 in a launch of each kind, 160 of 960: 312 against 344 (605 TFLOP/s on the definition's five products).
 constexpr int both_waves(int shape) { return shape == B128_SPLIT ? 8 : 4; }
 constexpr int both_groups(int shape) { return shape == B128 ? 1 : 2; }

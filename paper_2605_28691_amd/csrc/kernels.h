@@ -64,7 +64,8 @@ struct AttnArgs {
 enum OutKind : int { OUT_AS_INPUT = 0, OUT_ORIGINAL = 1, OUT_OTHER_PATTERN = 2 };
 hipError_t launch_attn_bf16(const AttnArgs& a, hipStream_t stream);
 
-// Flash-attention backward, bf16: dQ and delta = rowsum(dO o O) in one launch, then dK and dV in one.  Addressing as in AttnArgs.
+// Flash-attention backward, bf16, in two launches: dQ and delta = rowsum(dO o O), then dK and dV; or delta, then all three gradients
+// (pick_bwd_shape()).  Addressing as in AttnArgs.
 enum BwdMode : int { BWD_DQ = 0, BWD_DKV = 1 };  // dQ (owner = query), dK and dV together (owner = key)
 struct BwdArgs {
     const void* q;

@@ -132,6 +132,7 @@ enum BwdShape : int {
     // as TWO_LAUNCHES, with 128 queries (4 wavefronts) a workgroup in the dQ launch
     TWO_LAUNCHES_DQ128 = 4,
 };
+
 // us, the mean of both kinds.  Fitted to 660 calls (1..1088 units of 24..30,000 tokens, plain and any-resolution) timed in every shape: the pick is 0.5 %
 // above the best on average and 12 % at worst, and 0.84 of the two launches' time on average (1.03 at worst).  Measured, two launches -> picked,
 // us, units x tokens, head_dim 128: 1x120 18.1 -> 12.4, 8x190 21.6 -> 14.5, 48x400 43 -> 35, 24x1000 75 -> 63.5, 1x6116 215 -> 134, 160x400 120 -> 93,
@@ -157,6 +158,7 @@ inline bool bwd_full_rounds(int head_dim, const UnitSizes& u) {
     if (head_dim == 128) return fill >= 0.955f ? u.n_max >= 2500u : u.n_max >= 4000u && fill >= 0.935f;
     return u.n_max >= 4000u && rounds <= 6u && fill >= 0.955f;
 }
+
 // Which dQ launch, where there are two: 128 queries a workgroup, two on a CU, have the better last round in some calls (24 units of 2055 tokens at head_dim 64).
 // One figure for a round, however full, is enough here.
 constexpr ShapeCost DQ_COST_128[] = {{TWO_LAUNCHES, 256, false, 1, 5.0f, 5.0f, 0.f, {0.f, 1.30f}}, {TWO_LAUNCHES_DQ128, 128, false, 2, 4.0f, 4.0f, 0.f, {0.f, 0.95f, 1.34f}}};
@@ -195,7 +197,6 @@ inline uint32_t row_batch(uint32_t chunks, uint32_t n_rows) {
     while (batch > 1u && n_rows / batch < 2048u) batch /= 2u;
     return batch;
 }
-
 
 // Longer rows: parts of 64 chunks a wavefront, or of up to 128 (two loads in flight) where parts of 64 would leave more than a fifth of the
 // lanes idle.  Permute, switch and unpermute together, us, a wavefront a row / parts of 64 / of 128: 80,640 rows of 80 chunks 110 / 121 / 105,
