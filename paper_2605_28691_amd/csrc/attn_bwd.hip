@@ -31,6 +31,7 @@
 
 #include "kernels.h"
 #include "lds_layout.h"
+#include "row_store.h"
 
 namespace skiparse {
 
@@ -132,7 +133,8 @@ __device__ __attribute__((always_inline)) inline void bwd_part(const BwdArgs& a,
     };
     auto value_at = [&](uint32_t j) __attribute__((always_inline)) -> uint32_t { return PAD ? padded_position(a.g, cm, j) : j; };
     const uint32_t jo_c = jo < n_seq ? jo : n_seq - 1u;  // an owner past the end reads the last row and stores nothing
-    const size_t own_off = (size_t)token_at(jo_c) * C;
+    const uint32_t own_tok = token_at(jo_c);
+    const size_t own_off = (size_t)own_tok * C;
     bf16x8 own1[KS], own2[OWN2_LDS ? 1 : KS];
 #pragma unroll
     for (int ks = 0; ks < KS; ks++) {
@@ -417,75 +419,68 @@ __device__ __attribute__((always_inline)) inline void bwd_part(const BwdArgs& a,
         if (t < n_t) do_tile(P0{}, std::false_type{}, t);
     }
 
-    // ---- groups: the first one adds the others' sums to its own, through the LDS of the tiles
+    // ---- two groups: one finishes dK and the other dV, or each half of dQ's channels, adding the other group's sums to its own, through the LDS of the tiles
+    constexpr int MF = KG > 1 && !DKV ? MT / 2 : MT;  // channel blocks that a wavefront finishes
+    static_assert(KG <= 2 && QW * KG <= 8, "two groups at most");
+    constexpr uint32_t PART = MF * 4 * 1024;  // of a wavefront
+    auto part = [&](uint32_t i) __attribute__((always_inline)) -> char* {
+        const uint32_t n = i % 4u;
+        return (n == 0 ? s1buf0 : n == 1 ? s1buf1 : n == 2 ? s2buf0 : s2buf1) + i / 4u * PART;
+    };
+    const uint32_t jw = ot * (uint32_t)WGO + ow * 32u, stored = rows_below(jw, n_seq);
     if constexpr (KG > 1) {
         if (n_t < (all_t + KG - 1) / KG) __syncthreads();  // a group with one tile less has passed one barrier less
-        // every tile has been read (each ends with a barrier): a wavefront's accumulator takes 4 KiB per channel block of the tile buffers
-        constexpr uint32_t PART = MT * 4 * 1024, SLOTS = 4 * KG * TILE_BYTES / PART;
-        constexpr bool AT_ONCE = QW * (DKV ? 2 : 1) <= SLOTS;  // room for dK and dV together
-        static_assert(KG == 2 && QW <= SLOTS && KG * TILE_BYTES % PART == 0, "the tile buffers hold an accumulator of every wavefront of a group");
-        auto part = [&](uint32_t i) __attribute__((always_inline)) -> char* {
-            const uint32_t n = i % 4u;
-            return (n == 0 ? lds.s1buf0 : n == 1 ? lds.s1buf1 : n == 2 ? lds.s2buf0 : lds.s2buf1) + i / 4u * PART + lane * 16u;
+        // every tile has been read (each ends with a barrier)
+        constexpr bool AT_ONCE = KG * QW <= 4 * KG * TILE_BYTES / (int)PART;  // room for both directions
+        static_assert(QW <= 4 && KG * TILE_BYTES % PART == 0 && PART >= 4096, "the tile buffers hold what every wavefront of a group leaves");
+        auto leave = [&](char* dst, const f32x16* x) __attribute__((always_inline)) {
+#pragma unroll
+            for (int m = 0; m < MF; m++)
+#pragma unroll
+                for (int g = 0; g < 4; g++) *(f32x4*)(dst + lane * 16u + (m * 4 + g) * 1024) = f32x4{x[m][4 * g], x[m][4 * g + 1], x[m][4 * g + 2], x[m][4 * g + 3]};
         };
-        auto leave = [&](char* dst, const f32x16 (&x)[MT]) __attribute__((always_inline)) {
+        auto take = [&](const char* src, f32x16* x) __attribute__((always_inline)) {
 #pragma unroll
-            for (int mt = 0; mt < MT; mt++)
-#pragma unroll
-                for (int g = 0; g < 4; g++) *(f32x4*)(dst + (mt * 4 + g) * 1024) = f32x4{x[mt][4 * g], x[mt][4 * g + 1], x[mt][4 * g + 2], x[mt][4 * g + 3]};
-        };
-        auto take = [&](const char* src, f32x16 (&x)[MT]) __attribute__((always_inline)) {
-#pragma unroll
-            for (int mt = 0; mt < MT; mt++)
+            for (int m = 0; m < MF; m++)
 #pragma unroll
                 for (int g = 0; g < 4; g++) {
-                    const f32x4 o = *(const f32x4*)(src + (mt * 4 + g) * 1024);
+                    const f32x4 o = *(const f32x4*)(src + lane * 16u + (m * 4 + g) * 1024);
 #pragma unroll
-                    for (int e = 0; e < 4; e++) x[mt][4 * g + e] += o[e];
+                    for (int e = 0; e < 4; e++) x[m][4 * g + e] += o[e];
                 }
         };
-        if (kg != 0) {
-            leave(part(ow), acc);
-            if constexpr (DKV && AT_ONCE) leave(part(QW + ow), acc2);
-        }
+        f32x16* const second = DKV ? acc2 : acc + MT - MF;  // group 1's
+        // part(ow) from group 1 to group 0, part(QW + ow) (the same one, with a barrier more, where there is no room) the other way
+        char *const to0 = part(ow), *const to1 = part(AT_ONCE ? QW + ow : ow);
+        if (kg != 0) leave(to0, acc);
+        else if (AT_ONCE) leave(to1, second);
         __syncthreads();
-        if (kg == 0) {
-            take(part(ow), acc);
-            if constexpr (DKV && AT_ONCE) take(part(QW + ow), acc2);
-        }
-        if constexpr (DKV && !AT_ONCE) {
+        if (kg == 0) take(to0, acc);
+        if (!AT_ONCE) {
             __syncthreads();
-            if (kg != 0) leave(part(ow), acc2);
+            if (kg == 0) leave(to1, second);
             __syncthreads();
-            if (kg == 0) take(part(ow), acc2);
         }
-        if (kg != 0) return;
+        if (kg != 0) take(to1, second);
+        if (stored == 0u) return;
+        // a wavefront's region: what it has taken; without room for both that is group 1's, and group 0 has the owners' second operand instead
+        static_assert(AT_ONCE || OWN2_LDS, "a region for group 0");
+        constexpr int CHP = MF * 32 >= 64 ? 64 : 32;
+        const RowDest<CHP> dest(own_tok, C, stored, lane);
+        if (kg == 0) store_rows<CHP, 32>(AT_ONCE ? to0 : own2buf + ow * 32u * RB, (const f32x16(&)[MF])*acc, a.scale, grad_g, dest, lane);
+        else store_rows<CHP, 32>(to1, (const f32x16(&)[MF])*second, DKV ? 1.0f : a.scale, DKV ? grad2_g : grad_g + D / 2, dest, lane);
+        return;
     }
 
-    // ---- epilogue: lane owns row jo; register r of block mt is channel 32*mt + 8*(r/4) + 4*h + r%4
-    if (jo < n_seq) {
-        const float f = a.scale;
-#pragma unroll
-        for (int mt = 0; mt < MT; mt++)
-#pragma unroll
-            for (int g = 0; g < 4; g++) {
-                bf16x4 o;
-#pragma unroll
-                for (int e = 0; e < 4; e++) o[e] = (__bf16)(acc[mt][g * 4 + e] * f);
-                *(bf16x4*)(grad_g + own_off + mt * 32 + g * 8 + 4 * h) = o;
-            }
-        if (DKV) {  // the second row after the first is complete, so that the L2 sees whole lines of one row at a time
-#pragma unroll
-            for (int mt = 0; mt < MT; mt++)
-#pragma unroll
-                for (int g = 0; g < 4; g++) {
-                    bf16x4 o;
-#pragma unroll
-                    for (int e = 0; e < 4; e++) o[e] = (__bf16)acc2[DKV ? mt : 0][g * 4 + e];
-                    *(bf16x4*)(grad2_g + own_off + mt * 32 + g * 8 + 4 * h) = o;
-                }
-        }
-    }
+    // ---- epilogue: lane owns row jo; every tile has been read, 4 KiB of the buffers for each wavefront
+    if (stored == 0u) return;
+    constexpr uint32_t PER_BUF = TILE_BYTES / 4096;
+    static_assert(KG > 1 || NW <= 4 * (int)PER_BUF, "a region of the tile buffers for every wavefront");
+    const uint32_t in = ow / PER_BUF;
+    char* const region = (in == 0 ? s1buf0 : in == 1 ? s1buf1 : in == 2 ? s2buf0 : s2buf1) + ow % PER_BUF * 4096u;
+    const RowDest<64> dest(own_tok, C, stored, lane);
+    store_rows<64, 32>(region, acc, a.scale, grad_g, dest, lane);
+    if constexpr (DKV) store_rows<64, 32>(region, acc2, 1.0f, grad2_g, dest, lane);
 }
 
 // A launch of one kind of owner.

@@ -47,6 +47,7 @@
 
 #include "kernels.h"
 #include "lds_layout.h"
+#include "row_store.h"
 
 namespace skiparse {
 
@@ -207,14 +208,15 @@ __global__ __launch_bounds__(64 * fwd_waves(SHAPE), (fwd_queries(SHAPE) == 128 &
     // ---- Q fragments (B operand of S^T = K Q^T): lane = query lq, 8 consecutive channels starting at 16*ks + 8*h
     bf16x8 qf[QT][KS];
     bool q_valid[QT];
-    size_t q_row_off[QT];
+    uint32_t q_token[QT];
 #pragma unroll
     for (int qi = 0; qi < QT; qi++) {
         const uint32_t jq = qt * BR + (qw * QT + qi) * 32u + lq;
         q_valid[qi] = jq < n_seq;
-        q_row_off[qi] = (size_t)token_at(q_valid[qi] ? jq : n_seq - 1u) * C;
+        q_token[qi] = token_at(q_valid[qi] ? jq : n_seq - 1u);
+        const size_t q_row_off = (size_t)q_token[qi] * C;
 #pragma unroll
-        for (int ks = 0; ks < KS; ks++) qf[qi][ks] = *(const bf16x8*)(Qg + q_row_off[qi] + ks * 16 + 8 * h);
+        for (int ks = 0; ks < KS; ks++) qf[qi][ks] = *(const bf16x8*)(Qg + q_row_off + ks * 16 + 8 * h);
     }
 
     // ---- staging: K/V tiles of 64 rows go from global memory straight into LDS (global_load_lds_dwordx4: lane l's 16 bytes
@@ -616,78 +618,76 @@ __global__ __launch_bounds__(64 * fwd_waves(SHAPE), (fwd_queries(SHAPE) == 128 &
         pv(vb, 1, preg[1]);
     }
 
-    // ---- key groups: the first one takes in the others' (reference, sum, O), through the LDS of the tiles
+    // ---- two key groups: each takes half of the channels and adds in the other's (reference, sum, O), through the LDS of the tiles
+    constexpr int MF = MT / KG;  // channel blocks that a wavefront finishes
+    static_assert(KG <= 2 && QT == 1 && QW * KG <= 8, "two groups at most, a tile buffer for each pair of wavefronts");
+    auto pair_buf = [&](uint32_t g) __attribute__((always_inline)) -> char* {
+        return (qw == 0 ? kbuf0_all : qw == 1 ? kbuf1_all : qw == 2 ? vbuf0_all : vbuf1_all) + g * TL::TILE_BYTES;
+    };
     if constexpr (KG > 1) {
         if (n_tiles < (all_tiles + KG - 1) / KG) __syncthreads();  // a group with one tile less has passed one barrier less
         __syncthreads();                                           // every tile has been read
         __shared__ float part_ml[KG][QW][2][64];
-        static_assert(QT == 1 && MT * 4 * 1024 == TL::TILE_BYTES && QW <= 4, "the accumulators of a wavefront take a tile buffer");
-        char* const bufs[4] = {kbuf0_all, kbuf1_all, vbuf0_all, vbuf1_all};
-        if (kg != 0) {
-            char* dst = (qw == 0 ? kbuf0 : qw == 1 ? kbuf1 : qw == 2 ? vbuf0 : vbuf1) + lane * 16u;
+        static_assert(MF * 4 * 1024 <= TL::TILE_BYTES && QW <= 4, "half of a wavefront's accumulators takes a group's half of a tile buffer");
+        auto leave = [&](const f32x16* x) __attribute__((always_inline)) {
+            char* const dst = pair_buf(kg) + lane * 16u;
 #pragma unroll
-            for (int mt = 0; mt < MT; mt++)
+            for (int m = 0; m < MF; m++)
 #pragma unroll
-                for (int g = 0; g < 4; g++) {
-                    f32x4 o;
-#pragma unroll
-                    for (int e = 0; e < 4; e++) o[e] = oacc[0][mt][g * 4 + e];
-                    *(f32x4*)(dst + (mt * 4 + g) * 1024) = o;
-                }
-            part_ml[kg][qw][0][lane] = m_ref[0];
-            part_ml[kg][qw][1][lane] = l_run[0];
-        }
+                for (int g = 0; g < 4; g++) *(f32x4*)(dst + (m * 4 + g) * 1024) = f32x4{x[m][4 * g], x[m][4 * g + 1], x[m][4 * g + 2], x[m][4 * g + 3]};
+        };
+        if (kg == 0) leave(oacc[0] + MT - MF);
+        else leave(oacc[0]);
+        part_ml[kg][qw][0][lane] = m_ref[0];
+        part_ml[kg][qw][1][lane] = l_run[0];
         __syncthreads();
-        if (kg != 0) return;
-        const char* src = (qw == 0 ? bufs[0] : qw == 1 ? bufs[1] : qw == 2 ? bufs[2] : bufs[3]) + lane * 16u;
+        const float mo = part_ml[kg ^ 1u][qw][0][lane], lo = part_ml[kg ^ 1u][qw][1][lane];
+        const float m_new = fmaxf(m_ref[0], mo);
+        const float w0 = m_ref[0] == m_new ? 1.0f : __builtin_amdgcn_exp2f((m_ref[0] - m_new) * c);
+        const float w1 = mo == m_new ? 1.0f : __builtin_amdgcn_exp2f((mo - m_new) * c);
+        m_ref[0] = m_new;
+        l_run[0] = l_run[0] * w0 + lo * w1;
+        auto take = [&](f32x16* x) __attribute__((always_inline)) {
+            const char* const src = pair_buf(kg ^ 1u) + lane * 16u;
 #pragma unroll
-        for (int og = 1; og < KG; og++) {
-            const float mo = part_ml[og][qw][0][lane], lo = part_ml[og][qw][1][lane];
-            const float m_new = fmaxf(m_ref[0], mo);
-            const float w0 = m_ref[0] == m_new ? 1.0f : __builtin_amdgcn_exp2f((m_ref[0] - m_new) * c);
-            const float w1 = mo == m_new ? 1.0f : __builtin_amdgcn_exp2f((mo - m_new) * c);
-            m_ref[0] = m_new;
-            l_run[0] = l_run[0] * w0 + lo * w1;
-#pragma unroll
-            for (int mt = 0; mt < MT; mt++)
+            for (int m = 0; m < MF; m++)
 #pragma unroll
                 for (int g = 0; g < 4; g++) {
-                    const f32x4 o = *(const f32x4*)(src + og * TL::TILE_BYTES + (mt * 4 + g) * 1024);
+                    const f32x4 o = *(const f32x4*)(src + (m * 4 + g) * 1024);
 #pragma unroll
-                    for (int e = 0; e < 4; e++) oacc[0][mt][g * 4 + e] = oacc[0][mt][g * 4 + e] * w0 + o[e] * w1;
+                    for (int e = 0; e < 4; e++) x[m][g * 4 + e] = x[m][g * 4 + e] * w0 + o[e] * w1;
                 }
-        }
+        };
+        if (kg == 0) take(oacc[0]);
+        else take(oacc[0] + MT - MF);
     }
 
     // ---- epilogue: O = O^T / l, rounded to bf16; lane owns query lq, register r of block mt is channel 32*mt + 8*(r/4) + 4*h + r%4
-#pragma unroll
-    for (int qi = 0; qi < QT; qi++) {
-        float llo, lhi;
-        lane_pair(l_run[qi], llo, lhi);
-        const float inv = 1.0f / (llo + lhi);
-        if (a.lse != nullptr && h == 0) {
-            // log-sum-exp of the scaled logits: the reference is in raw logit units, the sum is relative to it
-            const uint32_t jq = qt * BR + (qw * QT + qi) * 32u + lq;
-            if (jq < n_seq) lse_u[PAD ? padded_position(a.g, cm, jq) : jq] = m_ref[qi] * a.scale + __logf(llo + lhi);
-        }
-        if (q_valid[qi]) {
-            __bf16* orow = Og + q_row_off[qi];
-            if (a.out_kind != OUT_AS_INPUT) {
-                // the input is a sparse layout: bb is the subsequence (p, q, b) and this lane's query sits at position jq of it
-                const uint32_t jq = qt * BR + (qw * QT + qi) * 32u + lq;
-                orow = (__bf16*)a.out + scattered_row(a, bb, jq) * C + (size_t)head * D;
-            }
-#pragma unroll
-            for (int mt = 0; mt < MT; mt++)
-#pragma unroll
-                for (int g = 0; g < 4; g++) {
-                    bf16x4 o;
-#pragma unroll
-                    for (int e = 0; e < 4; e++) o[e] = (__bf16)(oacc[qi][mt][g * 4 + e] * inv);
-                    *(bf16x4*)(orow + mt * 32 + g * 8 + 4 * h) = o;
-                }
-        }
+    const uint32_t jw = qt * BR + qw * 32u, stored = rows_below(jw, n_seq);
+    if (stored == 0u) return;
+    float llo, lhi;
+    lane_pair(l_run[0], llo, lhi);
+    const float inv = 1.0f / (llo + lhi);
+    if (a.lse != nullptr && h == 0 && kg == 0 && q_valid[0])
+        // log-sum-exp of the scaled logits: the reference is in raw logit units, the sum is relative to it
+        lse_u[PAD ? padded_position(a.g, cm, jw + lq) : jw + lq] = m_ref[0] * a.scale + __logf(llo + lhi);
+    uint32_t row = q_token[0];
+    __bf16* dst = Og + kg * (uint32_t)(D / KG);
+    if (a.out_kind != OUT_AS_INPUT) {
+        // the input is a sparse layout: bb is the subsequence (p, q, b) and this lane's query sits at position jw + lq of it
+        dst = (__bf16*)a.out + (size_t)head * D + kg * (uint32_t)(D / KG);
+        row = (uint32_t)scattered_row(a, bb, q_valid[0] ? jw + lq : n_seq - 1u);
     }
+    // K's buffers are free here, and of the groups' buffers the half that this wavefront has taken in
+    constexpr uint32_t CHP = D / KG >= 64 ? 64 : 32, REGION = KG > 1 || 2 * TL::TILE_BYTES >= NW * 4096 ? 4096 : 2048, ROWS = REGION >= 64 * CHP ? 32 : 16;
+    static_assert(KG > 1 ? REGION <= TL::TILE_BYTES : NW * REGION <= 2 * TL::TILE_BYTES, "a region for every wavefront");
+    const uint32_t at = qw * REGION;
+    char* region;
+    if constexpr (KG > 1) region = pair_buf(kg ^ 1u);
+    else region = at < TL::TILE_BYTES ? kbuf0_all + at : kbuf1_all + (at - TL::TILE_BYTES);
+    const RowDest<CHP> dest(row, C, stored, lane);
+    if (KG == 1 || kg == 0) store_rows<CHP, ROWS>(region, (const f32x16(&)[MF])*oacc[0], inv, dst, dest, lane);
+    else store_rows<CHP, ROWS>(region, (const f32x16(&)[MF])*(oacc[0] + MT - MF), inv, dst, dest, lane);
 }
 
 template <int D, int SHAPE, bool PAD>

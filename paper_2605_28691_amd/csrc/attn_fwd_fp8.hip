@@ -21,6 +21,7 @@
 
 #include "kernels.h"
 #include "lds_layout.h"
+#include "row_store.h"
 
 namespace skiparse {
 
@@ -344,20 +345,17 @@ __global__ __launch_bounds__(NT8) void attn_fwd_fp8_kernel(Fp8AttnArgs a, PadArg
     float llo, lhi;
     lane_pair_f(l_run, llo, lhi);
     const float inv = sv_max / (P_GAIN * (llo + lhi));
-    if (q_valid) {
-        bool real;  // as q_valid says
-        const size_t row = (size_t)b0_ * (uint32_t)a.g.n_tok + (PAD ? src_token_padded(a.g, p_, q_, jq, &real) : src_token(a.g, p_, q_, jq));
-        __bf16* orow = (__bf16*)a.out + row * C + (size_t)head * D;
-#pragma unroll
-        for (int mt = 0; mt < MT; mt++)
-#pragma unroll
-            for (int g = 0; g < 4; g++) {
-                bf16x4 o;
-#pragma unroll
-                for (int e = 0; e < 4; e++) o[e] = (__bf16)(oacc[mt][g * 4 + e] * inv);
-                *(bf16x4*)(orow + mt * 32 + g * 8 + 4 * h) = o;
-            }
-    }
+    const uint32_t rows = (uint32_t)__builtin_amdgcn_ballot_w64(q_valid);
+    if (rows == 0u) return;
+    bool real;  // as q_valid says
+    const uint32_t jr = q_valid ? jq : 0u;
+    const uint32_t tok = PAD ? src_token_padded(a.g, p_, q_, jr, &real) : src_token(a.g, p_, q_, jr);
+    // every tile has been read: 4 KiB of the buffers for each wavefront
+    constexpr uint32_t PER_BUF = TILE_BYTES / 4096;
+    static_assert(NW8 <= 4 * (int)PER_BUF, "a region of the tile buffers for every wavefront");
+    const uint32_t in = wave / PER_BUF;
+    char* const region = (in == 0 ? kbuf0 : in == 1 ? kbuf1 : in == 2 ? vbuf0 : vbuf1) + wave % PER_BUF * 4096u;
+    store_rows<64, 32>(region, oacc, inv, (__bf16*)a.out + (size_t)b0_ * (uint32_t)a.g.n_tok * C + (size_t)head * D, RowDest<64>(tok, C, rows, lane), lane);
 }
 
 template <int D, int PADDING>

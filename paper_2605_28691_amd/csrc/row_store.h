@@ -1,0 +1,78 @@
+// Results leave the attention kernels through LDS.  In the accumulator layout a lane holds 4 consecutive channels of its row here and 4 there: stored
+// from there, an instruction of a wavefront writes 16 bytes to each of 32 rows, and the address unit takes such pieces one after the other.  So a wavefront
+// lays the channels down in LDS (a region of its own, no barrier) and stores whole 128-byte lines (64 where it has 32 channels), 8 rows an instruction.
+// Clocks of a workgroup from its last product until its stores have arrived, before -> after: 4 wavefronts at head_dim 128 (48 units of 390 tokens) 4990 ->
+// 2640, 8 (48 of 8190) 7510 -> 3400, dK and dV of 128 keys (48 of 400) 4950 -> 3070; two wavefronts a compute unit, where nothing queues, 1310 -> 1790.
+#pragma once
+#include <hip/hip_runtime.h>
+#include <stddef.h>
+#include <stdint.h>
+
+namespace skiparse {
+
+// Where the 32 rows of a wavefront go, CH channels at a time: a pass over them takes N instructions, instruction i rows RPI*i ...
+template <int CH>
+struct RowDest {
+    static_assert(CH == 64 || CH == 32, "channels of a pass");
+    static constexpr int LPR = CH / 8, RPI = 64 / LPR, N = 32 / RPI;  // lanes a row, rows an instruction, instructions
+    size_t off[N];  // elements
+    bool ok[N];
+    // row: number of the row that lane l % 32 owns (below 2^32: a row has 128 bytes at least), row_len: elements a row; bit r of `stored`: row r is stored
+    __device__ __attribute__((always_inline)) inline RowDest(uint32_t row, size_t row_len, uint32_t stored, uint32_t lane) {
+#pragma unroll
+        for (int i = 0; i < N; i++) {
+            const uint32_t r = RPI * i + lane / LPR;
+            off[i] = (size_t)(uint32_t)__shfl((int)row, (int)r) * row_len;
+            ok[i] = (stored >> r & 1u) != 0;
+        }
+    }
+};
+
+// acc * f, rounded to bf16, to dst + row offset: register 4*g + e of block mt is channel 32*mt + 8*g + 4*(lane/32) + e of row lane % 32.
+// buf: ROWS * CH * 2 bytes of LDS of the wavefront's own, 16-byte aligned.  Chunk c (8 channels) of row r lies at another position of the row, and with 64
+// channels its halves are exchanged in every other run of 8 rows, so that 16 lanes' 8-byte writes touch every bank once, as do the 16-byte reads.
+template <int CH, int ROWS, int BLOCKS>
+__device__ __attribute__((always_inline)) inline void store_rows(char* buf, const __attribute__((ext_vector_type(16))) float (&acc)[BLOCKS], float f, __bf16* dst, const RowDest<CH>& d, uint32_t lane) {
+    static_assert(ROWS % RowDest<CH>::RPI == 0 && 32 % ROWS == 0 && BLOCKS * 32 % CH == 0, "whole passes");
+    typedef __attribute__((ext_vector_type(4))) __bf16 bf16x4;
+    typedef __attribute__((ext_vector_type(4))) uint32_t u32x4;
+    constexpr int LPR = RowDest<CH>::LPR, RPI = RowDest<CH>::RPI;
+    const uint32_t r = lane & 31u, h = lane >> 5;
+    auto swz = [](uint32_t row) __attribute__((always_inline)) -> uint32_t { return CH == 64 ? row & 7u : row >> 2 & 3u; };
+    char* const wr = buf + (r & (uint32_t)(ROWS - 1)) * (2u * CH) + 8u * (CH == 64 ? h ^ (r >> 3 & 1u) : h);
+    const char* const rd = buf + lane / LPR * (2u * CH) + ((lane % LPR) ^ swz(lane / LPR)) * 16u;
+    __bf16* const out = dst + lane % LPR * 8u;
+#pragma unroll
+    for (int part = 0; part < 32 / ROWS; part++)
+#pragma unroll
+        for (int c = 0; c < BLOCKS * 32 / CH; c++) {
+            if (ROWS == 32 || r / ROWS == (uint32_t)part) {
+#pragma unroll
+                for (int k = 0; k < LPR; k++) {
+                    bf16x4 o;
+#pragma unroll
+                    for (int e = 0; e < 4; e++) o[e] = (__bf16)(acc[c * CH / 32 + k / 4][4 * (k % 4) + e] * f);
+                    *(bf16x4*)(wr + (((uint32_t)k ^ swz(r)) * 16u)) = o;
+                }
+            }
+            // the wavefront's LDS accesses take effect in order; the fences keep the compiler from exchanging them
+            __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+            __builtin_amdgcn_wave_barrier();
+#pragma unroll
+            for (int i = 0; i < ROWS / RPI; i++) {
+                const u32x4 x = *(const u32x4*)(rd + i * 1024);
+                const int n = part * (ROWS / RPI) + i;
+                const u32x4 y = CH == 32 || n % 2 == 0 ? x : u32x4{x[2], x[3], x[0], x[1]};
+                if (d.ok[n]) *(u32x4*)(out + d.off[n] + c * CH) = y;
+            }
+            __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+            __builtin_amdgcn_wave_barrier();
+        }
+}
+
+// of the 32 rows from `first`, those below n
+__device__ inline uint32_t rows_below(uint32_t first, uint32_t n) {
+    return first >= n ? 0u : n - first >= 32u ? ~0u : (1u << (n - first)) - 1u;
+}
+
+}  // namespace skiparse
