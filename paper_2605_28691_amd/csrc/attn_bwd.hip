@@ -63,7 +63,7 @@ struct BwdLds {
 // never met; log-sum-exp and delta are laid out over the padded grid.
 // lin: number of the workgroup in the (unit, owner tile) order.  DELTA: the dQ part forms delta (else it is there already).
 template <int D, int MODE, int NW, int KG, int BT, bool OWN2_LDS, bool DELTA, bool PAD>
-__device__ __attribute__((always_inline)) inline void bwd_part(const BwdArgs& a, const PadArg<PAD>& pad_map, uint32_t lin, uint32_t o_tiles, const BwdLds& lds) {
+__device__ __attribute__((always_inline)) inline void bwd_part(const BwdArgs& a, const PadArg<PAD>& pad_map, uint32_t lin, const UnitMap& units, const BwdLds& lds) {
     constexpr int KS = D / 16;   // MFMA steps along head_dim
     constexpr int MT = D / 32;   // 32-channel blocks of the gradient row
     constexpr int CH = D / 8;    // 16-byte chunks per row
@@ -94,20 +94,8 @@ __device__ __attribute__((always_inline)) inline void bwd_part(const BwdArgs& a,
     float (*const row_l)[BT] = (float (*)[BT])lds.row_l + kg * 2u;
     float (*const row_d)[BT] = (float (*)[BT])lds.row_d + kg * 2u;
     uint32_t* const rowoff = lds.rowoff + kg * (BRING * 64u);
-    const uint32_t unit = lin / o_tiles, ot = lin - unit * o_tiles;  // unit = (subsequence or batch element) * heads + head
-    uint32_t bb = unit / (uint32_t)a.heads, head = unit - bb * (uint32_t)a.heads;
-    if (PAD) {  // classes differ in size: neighbouring units belong to different classes, so that every XCD gets its share of each
-        const uint32_t n_bb = (uint32_t)a.B * (uint32_t)(a.g.s * a.g.s);
-        head = unit / n_bb;
-        bb = unit - head * n_bb;
-    }
-    uint32_t p = 0, q = 0, b0 = bb;
-    if (a.g.mode != MODE_DENSE) {
-        const uint32_t pq = bb / (uint32_t)a.B;
-        b0 = bb - pq * (uint32_t)a.B;
-        p = pq / (uint32_t)a.g.s;
-        q = pq - p * (uint32_t)a.g.s;
-    }
+    const UnitAt at_unit = units.at<PAD>(lin);  // any-resolution mode: classes differ in size, so heads are the slow index and every XCD gets its share of each
+    const uint32_t ot = at_unit.tile, bb = at_unit.bb, head = at_unit.head, p = at_unit.p, q = at_unit.q, b0 = at_unit.b;
     const ClassMap cm = make_class_map(a.g, pad_map, p, q);
     const uint32_t n_seq = PAD ? __builtin_amdgcn_readfirstlane(cm.n) : (uint32_t)a.g.n_sub;
     if (PAD && ot * (uint32_t)WGO >= n_seq) return;  // the grid is sized for the largest class
@@ -125,43 +113,11 @@ __device__ __attribute__((always_inline)) inline void bwd_part(const BwdArgs& a,
     __bf16* grad_g = (__bf16*)(MODE == BWD_DQ ? a.dq : a.dk) + unit_off;
     __bf16* grad2_g = (__bf16*)a.dv + unit_off;  // DKV: the second gradient
 
-    // ---- owner row: operands in registers (B operands: lane = owner lq, 8 consecutive channels starting at 16*ks + 8*h)
-    const uint32_t jo = ot * (uint32_t)WGO + ow * 32u + lq;
     // token at position j of this unit, and where its log-sum-exp and delta are
     auto token_at = [&](uint32_t j) __attribute__((always_inline)) -> uint32_t {
         return PAD ? src_token_real(a.g, cm, p, q, j) : src_token(a.g, p, q, j);
     };
     auto value_at = [&](uint32_t j) __attribute__((always_inline)) -> uint32_t { return PAD ? padded_position(a.g, cm, j) : j; };
-    const uint32_t jo_c = jo < n_seq ? jo : n_seq - 1u;  // an owner past the end reads the last row and stores nothing
-    const uint32_t own_tok = token_at(jo_c);
-    const size_t own_off = (size_t)own_tok * C;
-    bf16x8 own1[KS], own2[OWN2_LDS ? 1 : KS];
-#pragma unroll
-    for (int ks = 0; ks < KS; ks++) {
-        own1[ks] = *(const bf16x8*)(own1_g + own_off + ks * 16 + 8 * h);
-        if (!OWN2_LDS) own2[OWN2_LDS ? 0 : ks] = *(const bf16x8*)(own2_g + own_off + ks * 16 + 8 * h);
-    }
-    float own_l = 0.f, own_d = 0.f;  // dQ: the owner is a query
-    if (MODE == BWD_DQ && !DELTA) {
-        const uint32_t at = value_at(jo_c);
-        own_d = delta_u[at];
-        own_l = lse_u[at] * LOG2E;
-    }
-    if (MODE == BWD_DQ && DELTA) {
-        // delta of the row: its dO is here, O is read for nothing else.  Kept for the dK+dV launch, which streams the queries.
-        const __bf16* o_g = (const __bf16*)a.out + unit_off + own_off;
-        float sum = 0.f;
-#pragma unroll
-        for (int ks = 0; ks < KS; ks++) {
-            const bf16x8 of = *(const bf16x8*)(o_g + ks * 16 + 8 * h);
-#pragma unroll
-            for (int e = 0; e < 8; e++) sum = fmaf((float)of[e], (float)own2[OWN2_LDS ? 0 : ks][e], sum);
-        }
-        const uint32_t at = value_at(jo_c);
-        own_d = sum + __shfl_xor(sum, 32);
-        own_l = lse_u[at] * LOG2E;
-        if (jo < n_seq && h == 0 && kg == 0) delta_u[at] = own_d;
-    }
     const float c = a.scale * LOG2E;  // exp(x*scale - L) = exp2(x*c - L*log2e)
     const float inv_scale = 1.0f / a.scale;
 
@@ -224,6 +180,49 @@ __device__ __attribute__((always_inline)) inline void bwd_part(const BwdArgs& a,
     };
     auto tile_landed = [&]() __attribute__((always_inline)) { asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); };
 
+    // ---- tile 0 is asked for before anything else is formed: every wavefront finds its row offsets for itself (lane = row) and hands them round its lanes
+    {
+        const uint32_t j = tile0 * BT + lane;
+        const uint32_t mine = token_at(j < n_seq ? j : n_seq - 1u) * row_bytes;
+        RowOffs o;
+#pragma unroll
+        for (int i = 0; i < IPW; i++) o.off[i] = (uint32_t)__shfl((int)mine, (int)st_row[i]) + st_cb[i];
+        issue_tile(0, o, s1buf0, s2buf0);
+    }
+
+    // ---- owner row: operands in registers (B operands: lane = owner lq, 8 consecutive channels starting at 16*ks + 8*h)
+    const uint32_t jo = ot * (uint32_t)WGO + ow * 32u + lq;
+    const uint32_t jo_c = jo < n_seq ? jo : n_seq - 1u;  // an owner past the end reads the last row and stores nothing
+    const uint32_t own_tok = token_at(jo_c);
+    const size_t own_off = (size_t)own_tok * C;
+    bf16x8 own1[KS], own2[OWN2_LDS ? 1 : KS];
+#pragma unroll
+    for (int ks = 0; ks < KS; ks++) {
+        own1[ks] = *(const bf16x8*)(own1_g + own_off + ks * 16 + 8 * h);
+        if (!OWN2_LDS) own2[OWN2_LDS ? 0 : ks] = *(const bf16x8*)(own2_g + own_off + ks * 16 + 8 * h);
+    }
+    float own_l = 0.f, own_d = 0.f;  // dQ: the owner is a query
+    if (MODE == BWD_DQ && !DELTA) {
+        const uint32_t at = value_at(jo_c);
+        own_d = delta_u[at];
+        own_l = lse_u[at] * LOG2E;
+    }
+    if (MODE == BWD_DQ && DELTA) {
+        // delta of the row: its dO is here, O is read for nothing else.  Kept for the dK+dV launch, which streams the queries.
+        const __bf16* o_g = (const __bf16*)a.out + unit_off + own_off;
+        float sum = 0.f;
+#pragma unroll
+        for (int ks = 0; ks < KS; ks++) {
+            const bf16x8 of = *(const bf16x8*)(o_g + ks * 16 + 8 * h);
+#pragma unroll
+            for (int e = 0; e < 8; e++) sum = fmaf((float)of[e], (float)own2[OWN2_LDS ? 0 : ks][e], sum);
+        }
+        const uint32_t at = value_at(jo_c);
+        own_d = sum + __shfl_xor(sum, 32);
+        own_l = lse_u[at] * LOG2E;
+        if (jo < n_seq && h == 0 && kg == 0) delta_u[at] = own_d;
+    }
+
     f32x16 acc[MT], acc2[DKV ? MT : 1];  // acc2: dV in the DKV launch
 #pragma unroll
     for (int mt = 0; mt < MT; mt++)
@@ -269,13 +268,11 @@ __device__ __attribute__((always_inline)) inline void bwd_part(const BwdArgs& a,
         }
     }
     const char* const own2_lds = own2buf + (OWN2_LDS ? ow * 32u * RB : 0u) - grp;  // read at a_rd()
-    for (uint32_t t = ow; t < (uint32_t)BRING_AHEAD; t += QW) produce(t);
-    __syncthreads();
-    issue_tile(0, read_offs(0), s1buf0, s2buf0);
-    RowOffs off_next = read_offs(1);
+    for (uint32_t t = BT == 64 ? 1u + ow : ow; t < (uint32_t)BRING_AHEAD; t += QW) produce(t);
     store_rowvals(0);
     tile_landed();
     __syncthreads();
+    RowOffs off_next = read_offs(1);
     // one tile: enqueue the loads of the next tile into the other buffers, compute on this one, wait, barrier.  The parity of
     // the tile (which buffers) is a compile-time constant.  Tile t also forms the row offsets of tile t + BRING_AHEAD (written
     // here, first read in tile t + BRING_AHEAD - 2; the slot's previous tenant, tile t + BRING_AHEAD - BRING, was last read in tile
@@ -485,7 +482,7 @@ __device__ __attribute__((always_inline)) inline void bwd_part(const BwdArgs& a,
 
 // A launch of one kind of owner.
 template <int D, int MODE, int NW, bool PAD>
-__global__ __launch_bounds__(64 * NW, (NW == 4 ? 2 : 1)) void attn_bwd_kernel(BwdArgs a, PadArg<PAD> pad_map, uint32_t o_tiles, uint32_t total, uint32_t per_xcd) {
+__global__ __launch_bounds__(64 * NW, (NW == 4 ? 2 : 1)) void attn_bwd_kernel(BwdArgs a, PadArg<PAD> pad_map, UnitMap units, uint32_t total, uint32_t per_xcd) {
     constexpr bool OWN2_LDS = MODE == BWD_DKV;
     constexpr int TILE = BT64 * D * 2;
     // separate arrays so that the compiler can tell the tile being filled from the one being read
@@ -493,9 +490,10 @@ __global__ __launch_bounds__(64 * NW, (NW == 4 ? 2 : 1)) void attn_bwd_kernel(Bw
     __shared__ __attribute__((aligned(1024))) char own2[OWN2_LDS ? 32 * NW * D * 2 : 16];  // V rows of the owners, swizzled like a tile
     __shared__ __attribute__((aligned(16))) float row_l[2 * BT64], row_d[2 * BT64];
     __shared__ __attribute__((aligned(16))) uint32_t rowoff[BRING * 64];
+    asm volatile("" ::SKIPARSE_ARG_UNITS(units), "s"(total), "s"(per_xcd), SKIPARSE_ARG_GRID(a.g), "s"(a.q), "s"(a.k), "s"(a.v), "s"(a.out), "s"(a.dout), "s"(a.lse), "s"(a.delta), "s"(a.dq), "s"(a.dk), "s"(a.dv), "s"(a.heads), "s"(a.scale));
     const uint32_t lin = (blockIdx.x & 7u) * per_xcd + (blockIdx.x >> 3);  // each XCD owns a contiguous range of the (unit, owner tile) order
     if (lin >= total) return;
-    bwd_part<D, MODE, NW, 1, BT64, OWN2_LDS, true, PAD>(a, pad_map, lin, o_tiles, {s1buf0, s1buf1, s2buf0, s2buf1, own2, row_l, row_d, rowoff});
+    bwd_part<D, MODE, NW, 1, BT64, OWN2_LDS, true, PAD>(a, pad_map, lin, units, {s1buf0, s1buf1, s2buf0, s2buf1, own2, row_l, row_d, rowoff});
 }
 
 // Both kinds in one launch.  At head_dim 128 with the owners' V in LDS, tiles of 32 rows leave room for two B128 workgroups on a CU (70 KiB each) and
@@ -504,7 +502,7 @@ __global__ __launch_bounds__(64 * NW, (NW == 4 ? 2 : 1)) void attn_bwd_kernel(Bw
 constexpr int both_waves(int shape) { return shape == B128_SPLIT ? 8 : 4; }
 constexpr int both_groups(int shape) { return shape == B128 ? 1 : 2; }
 template <int D, int SHAPE, bool PAD>
-__global__ __launch_bounds__(64 * both_waves(SHAPE), (SHAPE == B128 || (SHAPE == B64_SPLIT && D == 64) ? 2 : 1)) void attn_bwd_both_kernel(BwdArgs a, PadArg<PAD> pad_map, uint32_t o_tiles, uint32_t total, uint32_t per_xcd) {
+__global__ __launch_bounds__(64 * both_waves(SHAPE), (SHAPE == B128 || (SHAPE == B64_SPLIT && D == 64) ? 2 : 1)) void attn_bwd_both_kernel(BwdArgs a, PadArg<PAD> pad_map, UnitMap units, uint32_t total, uint32_t per_xcd) {
     constexpr int NW = both_waves(SHAPE), KG = both_groups(SHAPE);
     constexpr bool OWN2_LDS = D == 128 && SHAPE != B64_SPLIT;
     constexpr int BT = OWN2_LDS ? 32 : BT64, TILE = BT * D * 2;
@@ -512,30 +510,25 @@ __global__ __launch_bounds__(64 * both_waves(SHAPE), (SHAPE == B128 || (SHAPE ==
     __shared__ __attribute__((aligned(1024))) char own2[OWN2_LDS ? 32 * NW / KG * D * 2 : 16];
     __shared__ __attribute__((aligned(16))) float row_l[KG * 2 * BT], row_d[KG * 2 * BT];
     __shared__ __attribute__((aligned(16))) uint32_t rowoff[KG * BRING * 64];
+    asm volatile("" ::SKIPARSE_ARG_UNITS(units), "s"(total), "s"(per_xcd), SKIPARSE_ARG_GRID(a.g), "s"(a.q), "s"(a.k), "s"(a.v), "s"(a.out), "s"(a.dout), "s"(a.lse), "s"(a.delta), "s"(a.dq), "s"(a.dk), "s"(a.dv), "s"(a.heads), "s"(a.scale));
     const bool dkv = blockIdx.y == 0;  // the longer workgroups first: what is left over at the end is short
     const uint32_t lin = (blockIdx.x & 7u) * per_xcd + (blockIdx.x >> 3);
     if (lin >= total) return;
     const BwdLds lds = {s1buf0, s1buf1, s2buf0, s2buf1, own2, row_l, row_d, rowoff};
-    if (dkv) bwd_part<D, BWD_DKV, NW, KG, BT, OWN2_LDS, false, PAD>(a, pad_map, lin, o_tiles, lds);
-    else bwd_part<D, BWD_DQ, NW, KG, BT, false, false, PAD>(a, pad_map, lin, o_tiles, lds);
+    if (dkv) bwd_part<D, BWD_DKV, NW, KG, BT, OWN2_LDS, false, PAD>(a, pad_map, lin, units, lds);
+    else bwd_part<D, BWD_DQ, NW, KG, BT, false, false, PAD>(a, pad_map, lin, units, lds);
 }
 
 // delta = rowsum(dO o O) of every query, for the launch of both kinds.  A wavefront takes 16 rows of a unit, lane i finding row i, with all loads
 // in flight at once.  HBM-bound where it is not a launch's latency: 160 units of 960 tokens at head_dim 128 take 14 us of 312.
 template <int D, bool PAD>
-__global__ __launch_bounds__(256) void attn_bwd_delta_kernel(BwdArgs a, PadArg<PAD> pad_map, uint32_t tiles, uint32_t total) {
+__global__ __launch_bounds__(256) void attn_bwd_delta_kernel(BwdArgs a, PadArg<PAD> pad_map, UnitMap units, uint32_t total) {
     constexpr int CH = D / 8, RPI = 64 / CH, N = 16 / RPI;  // lanes a row, rows an instruction, instructions
+    asm volatile("" ::SKIPARSE_ARG_UNITS(units), "s"(total), SKIPARSE_ARG_GRID(a.g), "s"(a.out), "s"(a.dout), "s"(a.delta), "s"(a.heads));
     const uint32_t lane = threadIdx.x & 63u, id = __builtin_amdgcn_readfirstlane(blockIdx.x * 4u + (threadIdx.x >> 6));
     if (id >= total) return;
-    const uint32_t unit = id / tiles, j0 = (id - unit * tiles) * 16u;
-    const uint32_t bb = unit / (uint32_t)a.heads, head = unit - bb * (uint32_t)a.heads;
-    uint32_t p = 0, q = 0, b0 = bb;
-    if (a.g.mode != MODE_DENSE) {
-        const uint32_t pq = bb / (uint32_t)a.B;
-        b0 = bb - pq * (uint32_t)a.B;
-        p = pq / (uint32_t)a.g.s;
-        q = pq - p * (uint32_t)a.g.s;
-    }
+    const UnitAt at_unit = units.at<false>(id);
+    const uint32_t unit = at_unit.unit, j0 = at_unit.tile * 16u, head = at_unit.head, p = at_unit.p, q = at_unit.q, b0 = at_unit.b;
     const ClassMap cm = make_class_map(a.g, pad_map, p, q);
     const uint32_t n_seq = PAD ? cm.n : (uint32_t)a.g.n_sub;
     if (j0 >= n_seq) return;
@@ -572,9 +565,9 @@ static hipError_t launch_both(const BwdArgs& a, uint32_t n_units, uint32_t n_max
     const uint32_t per_xcd = (uint32_t)((total + 7u) / 8u);
     PadArg<PAD> pad_map;
     make_pad_arg(a.g, pad_map);
-    attn_bwd_delta_kernel<D, PAD><<<(uint32_t)((waves + 3u) / 4u), 256, 0, stream>>>(a, pad_map, d_tiles, (uint32_t)waves);
+    attn_bwd_delta_kernel<D, PAD><<<(uint32_t)((waves + 3u) / 4u), 256, 0, stream>>>(a, pad_map, make_unit_map<false>(a.g, d_tiles, (uint32_t)a.B, (uint32_t)a.heads), (uint32_t)waves);
     // a dimension of the grid for each kind: together they could fill one
-    attn_bwd_both_kernel<D, SHAPE, PAD><<<dim3(8u * per_xcd, 2u), 64u * NW, 0, stream>>>(a, pad_map, o_tiles, (uint32_t)total, per_xcd);
+    attn_bwd_both_kernel<D, SHAPE, PAD><<<dim3(8u * per_xcd, 2u), 64u * NW, 0, stream>>>(a, pad_map, make_unit_map<PAD>(a.g, o_tiles, (uint32_t)a.B, (uint32_t)a.heads), (uint32_t)total, per_xcd);
     return hipGetLastError();
 }
 
@@ -587,7 +580,7 @@ static hipError_t launch_t(const BwdArgs& a, uint32_t n_units, uint32_t n_max, h
     const uint32_t per_xcd = (uint32_t)((total + 7u) / 8u);
     PadArg<PAD> pad_map;
     make_pad_arg(a.g, pad_map);
-    attn_bwd_kernel<D, MODE, NW, PAD><<<8u * per_xcd, 64 * NW, 0, stream>>>(a, pad_map, o_tiles, (uint32_t)total, per_xcd);
+    attn_bwd_kernel<D, MODE, NW, PAD><<<8u * per_xcd, 64 * NW, 0, stream>>>(a, pad_map, make_unit_map<PAD>(a.g, o_tiles, (uint32_t)a.B, (uint32_t)a.heads), (uint32_t)total, per_xcd);
     return hipGetLastError();
 }
 

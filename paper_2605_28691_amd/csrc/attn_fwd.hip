@@ -133,7 +133,7 @@ constexpr int fwd_queries(int shape) { return 32 * fwd_waves(shape) / fwd_groups
 // padding masked: the kernel walks the real tokens of the class only (ClassMap), so that a masked key is one that is never met.  Only
 // the log-sum-exp is laid out over the padded grid (zero at the padding).
 template <int D, int SHAPE, bool PAD>
-__global__ __launch_bounds__(64 * fwd_waves(SHAPE), (fwd_queries(SHAPE) == 128 && fwd_groups(SHAPE) == 1 ? 2 : 1)) void attn_fwd_bf16_kernel(AttnArgs a, PadArg<PAD> pad_map, uint32_t q_tiles, uint32_t total, uint32_t per_xcd) {
+__global__ __launch_bounds__(64 * fwd_waves(SHAPE), (fwd_queries(SHAPE) == 128 && fwd_groups(SHAPE) == 1 ? 2 : 1)) void attn_fwd_bf16_kernel(AttnArgs a, PadArg<PAD> pad_map, UnitMap units, uint32_t total, uint32_t per_xcd) {
     constexpr int NW = fwd_waves(SHAPE), KG = fwd_groups(SHAPE);
     constexpr int QT = ATTN_QT;
     constexpr int QW = NW / KG;    // wavefronts of a key group: each owns 32 queries, all walk the same keys
@@ -155,6 +155,7 @@ __global__ __launch_bounds__(64 * fwd_waves(SHAPE), (fwd_queries(SHAPE) == 128 &
     __shared__ __attribute__((aligned(1024))) char vbuf1_all[KG * TL::TILE_BYTES];
     __shared__ __attribute__((aligned(16))) uint32_t rowoff_all[KG][RING][KT];        // byte offsets of the rows of the next tiles
 
+    asm volatile("" ::SKIPARSE_ARG_UNITS(units), "s"(total), "s"(per_xcd), SKIPARSE_ARG_GRID(a.g), "s"(a.q), "s"(a.k), "s"(a.v), "s"(a.out), "s"(a.heads), "s"(a.scale), "s"(a.lse), "s"(a.out_kind));
     const uint32_t tid = threadIdx.x, lane = tid & 63u, wave = uniform(tid >> 6);
     const uint32_t lq = lane & 31u, h = lane >> 5;
     const uint32_t kg = KG == 1 ? 0u : wave / QW, qw = KG == 1 ? wave : wave % QW;  // key group, wavefront of the group
@@ -169,26 +170,14 @@ __global__ __launch_bounds__(64 * fwd_waves(SHAPE), (fwd_queries(SHAPE) == 128 &
     const uint32_t xcd = blockIdx.x & 7u, idx = blockIdx.x >> 3;
     const uint32_t lin = xcd * per_xcd + idx;
     if (lin >= total) return;
-    const uint32_t unit = lin / q_tiles, qt = lin - unit * q_tiles;
-    uint32_t bb = unit / (uint32_t)a.heads, head = unit - bb * (uint32_t)a.heads;
-    if (PAD) {  // classes differ in size: neighbouring units belong to different classes, so that every XCD gets its share of each
-        const uint32_t n_bb = (uint32_t)a.B * (uint32_t)(a.g.s * a.g.s);
-        head = unit / n_bb;
-        bb = unit - head * n_bb;
-    }
-    uint32_t p = 0, q = 0, b0 = bb;
-    if (a.g.mode != MODE_DENSE) {
-        const uint32_t pq = bb / (uint32_t)a.B;
-        b0 = bb - pq * (uint32_t)a.B;
-        p = pq / (uint32_t)a.g.s;
-        q = pq - p * (uint32_t)a.g.s;
-    }
+    const UnitAt at_unit = units.at<PAD>(lin);  // any-resolution mode: classes differ in size, so heads are the slow index and every XCD gets its share of each
+    const uint32_t qt = at_unit.tile, bb = at_unit.bb, head = at_unit.head, p = at_unit.p, q = at_unit.q, b0 = at_unit.b;
     const ClassMap cm = make_class_map(a.g, pad_map, p, q);
     const uint32_t n_seq = PAD ? uniform(cm.n) : (uint32_t)a.g.n_sub;
     float* const lse_u = a.lse + (size_t)(bb * (uint32_t)a.heads + head) * (uint32_t)a.g.n_sub;
     if (PAD) {
         if (a.lse != nullptr)
-            for (uint32_t j = qt * (64u * NW) + tid; j < (uint32_t)a.g.n_sub; j += q_tiles * (64u * NW)) {
+            for (uint32_t j = qt * (64u * NW) + tid; j < (uint32_t)a.g.n_sub; j += units.tiles.d * (64u * NW)) {
                 bool real;
                 (void)src_token_padded(a.g, p, q, j, &real);
                 if (!real) lse_u[j] = 0.f;
@@ -204,20 +193,6 @@ __global__ __launch_bounds__(64 * fwd_waves(SHAPE), (fwd_queries(SHAPE) == 128 &
     const __bf16* Kg = (const __bf16*)a.k + unit_off;
     const __bf16* Vg = (const __bf16*)a.v + unit_off;
     __bf16* Og = (__bf16*)a.out + unit_off;
-
-    // ---- Q fragments (B operand of S^T = K Q^T): lane = query lq, 8 consecutive channels starting at 16*ks + 8*h
-    bf16x8 qf[QT][KS];
-    bool q_valid[QT];
-    uint32_t q_token[QT];
-#pragma unroll
-    for (int qi = 0; qi < QT; qi++) {
-        const uint32_t jq = qt * BR + (qw * QT + qi) * 32u + lq;
-        q_valid[qi] = jq < n_seq;
-        q_token[qi] = token_at(q_valid[qi] ? jq : n_seq - 1u);
-        const size_t q_row_off = (size_t)q_token[qi] * C;
-#pragma unroll
-        for (int ks = 0; ks < KS; ks++) qf[qi][ks] = *(const bf16x8*)(Qg + q_row_off + ks * 16 + 8 * h);
-    }
 
     // ---- staging: K/V tiles of 64 rows go from global memory straight into LDS (global_load_lds_dwordx4: lane l's 16 bytes
     // land at the instruction's LDS base + 16*l, so one instruction of a wavefront fills RPI whole rows).  A wavefront issues IPW
@@ -261,6 +236,33 @@ __global__ __launch_bounds__(64 * fwd_waves(SHAPE), (fwd_queries(SHAPE) == 128 &
     auto issue_k = [&](char* buf, const RowOffs& o) __attribute__((always_inline)) { issue_tile(Kg, buf, o); };
     auto issue_v = [&](char* buf, const RowOffs& o) __attribute__((always_inline)) { issue_tile(Vg, buf, o); };
     auto tile_landed = [&]() __attribute__((always_inline)) { asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); };
+
+    // ---- what the first window needs is asked for before anything else is formed: K tile 0, whose row offsets every wavefront finds for itself (lane = row) and
+    // hands round its lanes, then Q.  Through the ring, K waited for an evaluation of the map for every tile of the ring, a barrier and an LDS read.
+    auto own_offs = [&](uint32_t tile) __attribute__((always_inline)) -> RowOffs {
+        const uint32_t j = (tile0 + tile) * KT + lane;
+        const uint32_t mine = token_at(j < n_seq ? j : n_seq - 1u) * row_bytes;
+        RowOffs o;
+#pragma unroll
+        for (int i = 0; i < TL::IPW; i++) o.off[i] = (uint32_t)__shfl((int)mine, (int)st_row[i]) + st_cb[i];
+        return o;
+    };
+    RowOffs off_v = own_offs(0);  // offsets of the tile whose V is fetched next
+    issue_k(kbuf0, off_v);
+
+    // ---- Q fragments (B operand of S^T = K Q^T): lane = query lq, 8 consecutive channels starting at 16*ks + 8*h
+    bf16x8 qf[QT][KS];
+    bool q_valid[QT];
+    uint32_t q_token[QT];
+#pragma unroll
+    for (int qi = 0; qi < QT; qi++) {
+        const uint32_t jq = qt * BR + (qw * QT + qi) * 32u + lq;
+        q_valid[qi] = jq < n_seq;
+        q_token[qi] = token_at(q_valid[qi] ? jq : n_seq - 1u);
+        const size_t q_row_off = (size_t)q_token[qi] * C;
+#pragma unroll
+        for (int ks = 0; ks < KS; ks++) qf[qi][ks] = *(const bf16x8*)(Qg + q_row_off + ks * 16 + 8 * h);
+    }
 
     // ---- running state: every lane tracks its own query (lanes l and l^32 hold the same m_ref; l_run is a partial sum)
     f32x16 oacc[QT][MT];
@@ -521,14 +523,11 @@ __global__ __launch_bounds__(64 * fwd_waves(SHAPE), (fwd_queries(SHAPE) == 128 &
     // K tile W+1 (into the K buffer that window W-1 read) and of V tile W (into the V buffer that window W-1 read); they have half
     // a window to land and are waited for just before the window's closing barrier.  The row offsets of tile W+2 are picked up
     // from the ring in window W (so that the LDS read is not waited for), and tile W+RING_AHEAD's are formed by wavefront W % QW of the group.
-    // ---- prologue: offsets of tiles 0..RING_AHEAD, K tile 0
-    for (uint32_t t = qw; t <= (uint32_t)RING_AHEAD && (!TRIM || t < n_tiles); t += QW) produce(t);
-    __syncthreads();
-    RowOffs off_v = read_offs(0);  // offsets of the tile whose V is fetched next
-    issue_k(kbuf0, off_v);
-    RowOffs off_k = read_offs(1);  // offsets of the tile whose K is fetched next (past the group's last tile: read, never used)
+    // ---- prologue: offsets of tiles 1..RING_AHEAD
+    for (uint32_t t = 1u + qw; t <= (uint32_t)RING_AHEAD && (!TRIM || t < n_tiles); t += QW) produce(t);
     tile_landed();
     __syncthreads();
+    RowOffs off_k = read_offs(1);  // offsets of the tile whose K is fetched next (past the group's last tile: read, never used)
 
     // ---- a wavefront without a query (in a unit's last workgroup) fetches its share of the tiles, meets the others at their barriers and
     // leaves the SIMD to the other workgroups of the CU and the power to the rest of the chip.  Out of the other wavefronts' line: in it, a call
@@ -555,8 +554,8 @@ __global__ __launch_bounds__(64 * fwd_waves(SHAPE), (fwd_queries(SHAPE) == 128 &
     }
     // ---- window 0: QK(0), then step 0 without PV
     {
-        if (n_tiles > 1) issue_k(kbuf1, off_k);
         issue_v(vbuf0, off_v);
+        if (n_tiles > 1) issue_k(kbuf1, off_k);
         off_v = off_k;
         off_k = read_offs(2);
         qk(kbuf0, 0, sreg[0]);
@@ -700,7 +699,8 @@ static hipError_t launch_t(const AttnArgs& a, uint32_t n_units, uint32_t n_max, 
     const uint32_t per_xcd = (uint32_t)((total + 7u) / 8u);
     PadArg<PAD> pad_map;
     make_pad_arg(a.g, pad_map);
-    attn_fwd_bf16_kernel<D, SHAPE, PAD><<<8u * per_xcd, 64 * NW, 0, stream>>>(a, pad_map, q_tiles, (uint32_t)total, per_xcd);
+    const UnitMap units = make_unit_map<PAD>(a.g, q_tiles, (uint32_t)a.B, (uint32_t)a.heads);
+    attn_fwd_bf16_kernel<D, SHAPE, PAD><<<8u * per_xcd, 64 * NW, 0, stream>>>(a, pad_map, units, (uint32_t)total, per_xcd);
     return hipGetLastError();
 }
 

@@ -65,7 +65,7 @@ enum Padding : int { NO_PADDING = 0, SOME_TILES = 1, MOST_TILES = 2 };
 
 template <int D, int PADDING>
 __attribute__((amdgpu_waves_per_eu(waves_per_simd8(D), waves_per_simd8(D))))
-__global__ __launch_bounds__(NT8) void attn_fwd_fp8_kernel(Fp8AttnArgs a, PadArg<PADDING != NO_PADDING> pad_map, uint32_t q_tiles, uint32_t total, uint32_t per_xcd) {
+__global__ __launch_bounds__(NT8) void attn_fwd_fp8_kernel(Fp8AttnArgs a, PadArg<PADDING != NO_PADDING> pad_map, UnitMap units, uint32_t total, uint32_t per_xcd) {
     constexpr bool PAD = PADDING != NO_PADDING, FLAG = PADDING == SOME_TILES;
     constexpr int NJ = D / 64;         // 64-channel MFMA steps of S^T = K Q^T
     constexpr int MT = D / 32;         // 32-channel blocks of O^T
@@ -85,16 +85,15 @@ __global__ __launch_bounds__(NT8) void attn_fwd_fp8_kernel(Fp8AttnArgs a, PadArg
     __shared__ __attribute__((aligned(16))) float kbias[2][KT8];  // PAD only: 0 for a real key of the tile, -inf for padding
     __shared__ uint32_t kany[2];                                  // FLAG only: non-zero if the tile holds any padding
 
+    asm volatile("" ::SKIPARSE_ARG_UNITS(units), "s"(total), "s"(per_xcd), SKIPARSE_ARG_GRID(a.g), "s"(a.q8), "s"(a.k8), "s"(a.v8), "s"(a.sq), "s"(a.sk), "s"(a.sv), "s"(a.out), "s"(a.heads), "s"(a.scale), "s"(a.n_blk));
     const uint32_t tid = threadIdx.x, lane = tid & 63u, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const uint32_t lq = lane & 31u, h = lane >> 5;
     const uint32_t xcd = blockIdx.x & 7u, idx = blockIdx.x >> 3;
     const uint32_t lin = xcd * per_xcd + idx;  // each XCD owns a contiguous range of the (unit, tile) order
     if (lin >= total) return;
-    const uint32_t unit = lin / q_tiles, qt = lin - unit * q_tiles;  // unit = sb * heads + head
-    const uint32_t sb = unit / (uint32_t)a.heads, head = unit - sb * (uint32_t)a.heads;
+    const UnitAt at_unit = units.at<false>(lin);  // unit = sb * heads + head
+    const uint32_t unit = at_unit.unit, qt = at_unit.tile, sb = at_unit.bb, head = at_unit.head, b0_ = at_unit.b, p_ = at_unit.p, q_ = at_unit.q;
     const uint32_t n_seq = (uint32_t)a.g.n_sub, n_blk = a.n_blk;
-    const uint32_t pq_ = sb / (uint32_t)a.B, b0_ = sb - pq_ * (uint32_t)a.B;
-    const uint32_t p_ = a.g.mode == MODE_DENSE ? 0u : pq_ / (uint32_t)a.g.s, q_ = a.g.mode == MODE_DENSE ? 0u : pq_ - p_ * (uint32_t)a.g.s;
     // one wavefront (they take turns) marks the keys of a tile: lane = key.  The padding sits at the end of H and W, so the real rows
     // and columns of a class are a prefix: two divisions a key instead of the whole index map, on the path of every tile.
     const ClassMap cm = make_class_map(a.g, pad_map, p_, q_);
@@ -368,7 +367,7 @@ static hipError_t launch_fp8_t(const Fp8AttnArgs& a, hipStream_t stream) {
     const uint32_t per_xcd = (uint32_t)((total + 7u) / 8u);
     PadArg<PADDING != NO_PADDING> pad_map;
     make_pad_arg(a.g, pad_map);
-    attn_fwd_fp8_kernel<D, PADDING><<<8u * per_xcd, NT8, 0, stream>>>(a, pad_map, q_tiles, (uint32_t)total, per_xcd);
+    attn_fwd_fp8_kernel<D, PADDING><<<8u * per_xcd, NT8, 0, stream>>>(a, pad_map, make_unit_map<false>(a.g, q_tiles, (uint32_t)a.B, (uint32_t)a.heads), (uint32_t)total, per_xcd);
     return hipGetLastError();
 }
 

@@ -266,6 +266,45 @@ inline Div32 make_div32(uint32_t d) {
     return {d, (uint32_t)m, (uint32_t)(m >> 32), d <= 1u ? 1u : 0u};
 }
 
+// Which unit, and which of its tiles, workgroup `lin` of the (unit, tile) order has.  The divisions are multiplications on the scalar unit: four divisions by
+// run-time constants in a row stood in front of every workgroup's first address.
+struct UnitAt {
+    uint32_t unit, tile;    // unit = number in the order of the units
+    uint32_t bb, head;      // subsequence (p, q, b) or batch element, and head
+    uint32_t p, q, b;       // class and batch element
+};
+struct UnitMap {
+    Div32 tiles;  // tiles of a unit
+    Div32 inner;  // heads; with heads slow the subsequences, so that neighbouring units belong to different classes
+    Div32 B, s;
+    template <bool HEADS_SLOW>
+    __host__ __device__ inline UnitAt at(uint32_t lin) const {
+        UnitAt u;
+        u.unit = tiles.div(lin);
+        u.tile = lin - u.unit * tiles.d;
+        const uint32_t slow = inner.div(u.unit), fast = u.unit - slow * inner.d;
+        u.bb = HEADS_SLOW ? fast : slow;
+        u.head = HEADS_SLOW ? slow : fast;
+        const uint32_t pq = B.div(u.bb);
+        u.b = u.bb - pq * B.d;
+        u.p = s.div(pq);
+        u.q = pq - u.p * s.d;
+        return u;
+    }
+};
+// (a dense map has s = 1, so that p = q = 0)
+template <bool HEADS_SLOW>
+inline UnitMap make_unit_map(const GridMap& g, uint32_t tiles, uint32_t B, uint32_t heads) {
+    const uint32_t s = (uint32_t)g.s;
+    return {make_div32(tiles), make_div32(HEADS_SLOW ? B * s * s : heads), make_div32(B), make_div32(s)};
+}
+
+// A kernel's arguments are asked for at once and waited for once: left to itself the compiler reads them where they are needed, and three or four loads from
+// memory, one waiting for the other, stand in front of a workgroup's first address (35 units of 225 tokens at head_dim 64: 6.39 us so, 6.02 at once).
+#define SKIPARSE_ARG_DIV32(x) "s"((x).d), "s"((x).lo), "s"((x).hi), "s"((x).one)
+#define SKIPARSE_ARG_UNITS(u) SKIPARSE_ARG_DIV32((u).tiles), SKIPARSE_ARG_DIV32((u).inner), SKIPARSE_ARG_DIV32((u).B), SKIPARSE_ARG_DIV32((u).s)
+#define SKIPARSE_ARG_GRID(g) "s"((g).W), "s"((g).n_tok), "s"((g).n_sub), "s"((g).a), "s"((g).b), "s"((g).cmul), "s"((g).ws.d), "s"((g).ws.mul), "s"((g).ws.one), "s"((g).sdiv.mul), "s"((g).sdiv.one)
+
 // What the row numbers of both sides are made of, for destination rows of one RowMap.
 struct RowArgs {
     Div32 n_row;    // rows of a subsequence (destination sparse) or of a batch element (destination original)

@@ -113,6 +113,23 @@ int main() {
         if (f.div(last) != last / d) { printf("fastdiv %u fails at the top of its range\n", d); return 1; }
         }
     }
+    // the number of a workgroup taken apart as integer divisions do it, both orders of the units
+    for (uint32_t tiles : {1u, 3u, 79u, 158u})
+        for (uint32_t B : {1u, 2u, 36u})
+            for (uint32_t heads : {1u, 5u, 40u})
+                for (uint32_t s : {1u, 2u, 3u}) {
+                    GridMap g = s == 1 ? make_dense_gridmap(10) : make_gridmap(1, 2 * (int)(s * s), 2 * (int)(s * s), (int)s, false);
+                    const UnitMap by_unit = make_unit_map<false>(g, tiles, B, heads), by_head = make_unit_map<true>(g, tiles, B, heads);
+                    for (uint32_t lin = 0; lin < tiles * B * s * s * heads; lin++) {
+                        const uint32_t unit = lin / tiles, n_bb = B * s * s;
+                        const UnitAt a = by_unit.at<false>(lin), h = by_head.at<true>(lin);
+                        const bool ok = a.unit == unit && a.tile == lin % tiles && a.bb == unit / heads && a.head == unit % heads && a.p == unit / heads / B / s && a.q == unit / heads / B % s &&
+                                        a.b == unit / heads % B && h.unit == unit && h.tile == lin % tiles && h.head == unit / n_bb && h.bb == unit % n_bb && h.p == unit % n_bb / B / s &&
+                                        h.q == unit % n_bb / B % s && h.b == unit % n_bb % B;
+                        if (!ok) { printf("unit map: tiles %u B %u heads %u s %u workgroup %u\n", tiles, B, heads, s, lin); return 1; }
+                        checked++;
+                    }
+                }
     printf("ok %ld checks\n", checked);
     return 0;
 }
