@@ -31,7 +31,7 @@
 
 #include "kernels.h"
 #include "lds_layout.h"
-#include "row_store.h"
+#include "row_io.h"
 
 namespace skiparse {
 

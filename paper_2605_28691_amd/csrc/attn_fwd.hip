@@ -47,7 +47,7 @@
 
 #include "kernels.h"
 #include "lds_layout.h"
-#include "row_store.h"
+#include "row_io.h"
 
 namespace skiparse {
 
@@ -251,18 +251,12 @@ __global__ __launch_bounds__(64 * fwd_waves(SHAPE), (fwd_queries(SHAPE) == 128 &
     issue_k(kbuf0, off_v);
 
     // ---- Q fragments (B operand of S^T = K Q^T): lane = query lq, 8 consecutive channels starting at 16*ks + 8*h
+    const uint32_t jq = qt * BR + qw * 32u + lq;
+    const bool q_valid = jq < n_seq;
+    const uint32_t q_token = token_at(q_valid ? jq : n_seq - 1u);
+    RowLoad<D> q_rows;
+    q_rows.issue(Qg, q_token, C, lane);
     bf16x8 qf[QT][KS];
-    bool q_valid[QT];
-    uint32_t q_token[QT];
-#pragma unroll
-    for (int qi = 0; qi < QT; qi++) {
-        const uint32_t jq = qt * BR + (qw * QT + qi) * 32u + lq;
-        q_valid[qi] = jq < n_seq;
-        q_token[qi] = token_at(q_valid[qi] ? jq : n_seq - 1u);
-        const size_t q_row_off = (size_t)q_token[qi] * C;
-#pragma unroll
-        for (int ks = 0; ks < KS; ks++) qf[qi][ks] = *(const bf16x8*)(Qg + q_row_off + ks * 16 + 8 * h);
-    }
 
     // ---- running state: every lane tracks its own query (lanes l and l^32 hold the same m_ref; l_run is a partial sum)
     f32x16 oacc[QT][MT];
@@ -526,6 +520,12 @@ __global__ __launch_bounds__(64 * fwd_waves(SHAPE), (fwd_queries(SHAPE) == 128 &
     // ---- prologue: offsets of tiles 1..RING_AHEAD
     for (uint32_t t = 1u + qw; t <= (uint32_t)RING_AHEAD && (!TRIM || t < n_tiles); t += QW) produce(t);
     tile_landed();
+    {   // Q's fragments, through V's buffers: V tile 0 is not asked for before the barrier
+        constexpr uint32_t REGION = 2 * KG * TL::TILE_BYTES >= NW * 4096 ? 4096 : 2048;
+        static_assert(NW * REGION <= 2 * KG * TL::TILE_BYTES, "a region for every wavefront");
+        const uint32_t at = wave * REGION;
+        q_rows.template fragments<REGION / 128>(at < KG * TL::TILE_BYTES ? vbuf0_all + at : vbuf1_all + (at - KG * TL::TILE_BYTES), qf[0], lane);
+    }
     __syncthreads();
     RowOffs off_k = read_offs(1);  // offsets of the tile whose K is fetched next (past the group's last tile: read, never used)
 
@@ -667,15 +667,15 @@ __global__ __launch_bounds__(64 * fwd_waves(SHAPE), (fwd_queries(SHAPE) == 128 &
     float llo, lhi;
     lane_pair(l_run[0], llo, lhi);
     const float inv = 1.0f / (llo + lhi);
-    if (a.lse != nullptr && h == 0 && kg == 0 && q_valid[0])
+    if (a.lse != nullptr && h == 0 && kg == 0 && q_valid)
         // log-sum-exp of the scaled logits: the reference is in raw logit units, the sum is relative to it
         lse_u[PAD ? padded_position(a.g, cm, jw + lq) : jw + lq] = m_ref[0] * a.scale + __logf(llo + lhi);
-    uint32_t row = q_token[0];
+    uint32_t row = q_token;
     __bf16* dst = Og + kg * (uint32_t)(D / KG);
     if (a.out_kind != OUT_AS_INPUT) {
         // the input is a sparse layout: bb is the subsequence (p, q, b) and this lane's query sits at position jw + lq of it
         dst = (__bf16*)a.out + (size_t)head * D + kg * (uint32_t)(D / KG);
-        row = (uint32_t)scattered_row(a, bb, q_valid[0] ? jw + lq : n_seq - 1u);
+        row = (uint32_t)scattered_row(a, bb, q_valid ? jw + lq : n_seq - 1u);
     }
     // K's buffers are free here, and of the groups' buffers the half that this wavefront has taken in
     constexpr uint32_t CHP = D / KG >= 64 ? 64 : 32, REGION = KG > 1 || 2 * TL::TILE_BYTES >= NW * 4096 ? 4096 : 2048, ROWS = REGION >= 64 * CHP ? 32 : 16;
@@ -684,9 +684,11 @@ __global__ __launch_bounds__(64 * fwd_waves(SHAPE), (fwd_queries(SHAPE) == 128 &
     char* region;
     if constexpr (KG > 1) region = pair_buf(kg ^ 1u);
     else region = at < TL::TILE_BYTES ? kbuf0_all + at : kbuf1_all + (at - TL::TILE_BYTES);
-    const RowDest<CHP> dest(row, C, stored, lane);
-    if (KG == 1 || kg == 0) store_rows<CHP, ROWS>(region, (const f32x16(&)[MF])*oacc[0], inv, dst, dest, lane);
-    else store_rows<CHP, ROWS>(region, (const f32x16(&)[MF])*(oacc[0] + MT - MF), inv, dst, dest, lane);
+    uint32_t lane_out = lane;  // formed anew: what Q's loads have formed of the same lane would be kept in ten registers through the whole walk
+    asm volatile("" : "+v"(lane_out));
+    const RowDest<CHP> dest(row, C, stored, lane_out);
+    if (KG == 1 || kg == 0) store_rows<CHP, ROWS>(region, (const f32x16(&)[MF])*oacc[0], inv, dst, dest, lane_out);
+    else store_rows<CHP, ROWS>(region, (const f32x16(&)[MF])*(oacc[0] + MT - MF), inv, dst, dest, lane_out);
 }
 
 template <int D, int SHAPE, bool PAD>

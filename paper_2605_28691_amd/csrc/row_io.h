@@ -1,4 +1,6 @@
-// Results leave the attention kernels through LDS.  In the accumulator layout a lane holds 4 consecutive channels of its row here and 4 there: stored
+// How the attention kernels move the rows that a wavefront owns.
+//
+// Results leave through LDS.  In the accumulator layout a lane holds 4 consecutive channels of its row here and 4 there: stored
 // from there, an instruction of a wavefront writes 16 bytes to each of 32 rows, and the address unit takes such pieces one after the other.  So a wavefront
 // lays the channels down in LDS (a region of its own, no barrier) and stores whole 128-byte lines (64 where it has 32 channels), 8 rows an instruction.
 // Clocks of a workgroup from its last product until its stores have arrived, before -> after: 4 wavefronts at head_dim 128 (48 units of 390 tokens) 4990 ->
@@ -7,6 +9,8 @@
 #include <hip/hip_runtime.h>
 #include <stddef.h>
 #include <stdint.h>
+
+#include "lds_layout.h"
 
 namespace skiparse {
 
@@ -69,6 +73,50 @@ __device__ __attribute__((always_inline)) inline void store_rows(char* buf, cons
             __builtin_amdgcn_wave_barrier();
         }
 }
+
+// The way in: a wavefront's 32 rows as B operands (lane = row lane % 32, 8 consecutive channels starting at 16*ks + 8*(lane/32)).  Loaded in that shape an
+// instruction takes 32 bytes of each of 32 rows; here it takes 128 bytes of 8, and the fragments are picked up from LDS.  Forward calls, us, loaded as fragments ->
+// so: 12 units of 132 tokens 8.06 -> 7.94, 9.32 -> 9.01 and 13.16 -> 12.91 in chains, 48 of 390 12.39 -> 12.34.  The backward kernels load fragments: with this
+// their registers are allotted another way, and the whole training step of 48 units of 8190 tokens takes 6560 instead of 6200.
+template <int D>
+struct RowLoad {
+    typedef __attribute__((ext_vector_type(8))) __bf16 bf16x8;
+    static constexpr int NC = D / 64;
+    bf16x8 x[NC][4];
+    // row, row_len as in RowDest; src: the unit's first row
+    __device__ __attribute__((always_inline)) inline void issue(const __bf16* src, uint32_t row, size_t row_len, uint32_t lane) {
+#pragma unroll
+        for (int i = 0; i < 4; i++) {
+            const __bf16* const at = src + (size_t)(uint32_t)__shfl((int)row, (int)(8 * i + (lane >> 3))) * row_len + (lane & 7u) * 8u;
+#pragma unroll
+            for (int c = 0; c < NC; c++) x[c][i] = *(const bf16x8*)(at + c * 64);
+        }
+    }
+    // buf: ROWS * 128 bytes of LDS of the wavefront's own.  Rows of 64 channels in the layout of a head_dim 64 tile.
+    template <int ROWS>
+    __device__ __attribute__((always_inline)) inline void fragments(char* buf, bf16x8 (&f)[D / 16], uint32_t lane) const {
+        static_assert(ROWS == 32 || ROWS == 16, "rows of a pass");
+        const uint32_t r = lane & 31u, h = lane >> 5;
+        char* const wr = buf + (lane >> 3) * 128u;  // rows 8 apart differ in the swizzle
+        const char* const rd = buf + (r & (uint32_t)(ROWS - 1)) * 128u;
+#pragma unroll
+        for (int c = 0; c < NC; c++)
+#pragma unroll
+            for (int part = 0; part < 32 / ROWS; part++) {
+#pragma unroll
+                for (int i = 0; i < ROWS / 8; i++)
+                    *(bf16x8*)(wr + i * 1024 + (((lane & 7u) ^ lds_swizzle<64>(8u * i + (lane >> 3))) * 16u)) = x[c][part * (ROWS / 8) + i];
+                __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+                __builtin_amdgcn_wave_barrier();
+                if (ROWS == 32 || r / ROWS == (uint32_t)part) {
+#pragma unroll
+                    for (int k = 0; k < 4; k++) f[4 * c + k] = *(const bf16x8*)(rd + (((2u * k + h) ^ lds_swizzle<64>(r)) * 16u));
+                }
+                __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+                __builtin_amdgcn_wave_barrier();
+            }
+    }
+};
 
 // of the 32 rows from `first`, those below n
 __device__ inline uint32_t rows_below(uint32_t first, uint32_t n) {
