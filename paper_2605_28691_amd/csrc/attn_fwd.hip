@@ -21,7 +21,7 @@
 //     matrix pipe and the vector ALU overlap within one wavefront as well as across the two on a SIMD.
 //   * In the steady state the instruction order of a step is written out by hand and fixed with scheduling fences:
 //     MFMAs of the two products alternate (so consecutive MFMAs never depend on each other), each followed by its share
-//     of the exponentials, and every LDS fragment is read four MFMAs before its use (across the two steps of a window too).
+//     of the exponentials, and every LDS fragment is read four or eight MFMAs before its use (across the two steps of a window too).
 //   * Reference maximum without a per-block maximum: the exponentials are taken against the reference the row already
 //     has; the common path computes no maximum at all.  The guard is the row sum: if 16 probabilities of a lane add up
 //     to 2^16 or more (always on the first block, where the reference is -inf) the wavefront takes a rare path that finds
@@ -67,7 +67,9 @@ constexpr int ATTN_QT = 1;       // 32-query tiles per wavefront
 constexpr int RING_AHEAD = 8;    // row offsets are formed this many tiles ahead, by one wavefront per window in turn
 constexpr int RING = 16;         // tiles of row offsets kept in LDS: a slot is rewritten RING - RING_AHEAD windows after its last use
 static_assert((RING & (RING - 1)) == 0 && RING >= RING_AHEAD + 4, "ring sizes");
-constexpr int LDS_AHEAD = 4;     // MFMA groups by which the LDS fragment reads run ahead in the steady state
+// MFMA groups by which the LDS fragment reads run ahead in the steady state.  With two wavefronts a SIMD 4 cover the latency; a single one waits for reads less
+// often with 8 (48 units of 390 tokens 12.35 -> 12.13 us, training step of 48 of 400 42.4 -> 41.7; calls of several rounds as before), where the registers are there.
+constexpr int lds_ahead(int D, int shape) { return shape == Q256 || shape == Q256_FULL || (D == 128 && shape == Q128_SPLIT) ? 4 : 8; }
 constexpr float RESCALE_LOG2 = 8.0f;  // the reference maximum is only raised when it grew by more than 2^8
 
 // QW: wavefronts that share a tile (and fetch it together)
@@ -402,10 +404,11 @@ __global__ __launch_bounds__(64 * fwd_waves(SHAPE), (fwd_queries(SHAPE) == 128 &
     // if a lane's 16 probabilities add up to 2^16 or more (always on the first block, where the reference is -inf), the
     // wavefront takes the rare path, which finds the true maximum, redoes the block's exponentials against it and rescales
     // O and l.  Probabilities up to 2^16 are harmless: bf16 keeps their relative precision and O, l are fp32.
-    // LDS fragments are read two MFMA groups ahead and every fragment feeds the MFMAs of all QT query tiles.
+    // LDS fragments are read LDS_AHEAD MFMA groups ahead and every fragment feeds the MFMAs of all QT query tiles.
     // MFMA groups of a step alternate between the two products (PV, QK, PV, QK, ...: as many of each), so consecutive MFMAs never
     // depend on each other: group g is PV group g/2 when g is even and QK group g/2 when g is odd.
     constexpr int NPV = 2 * MT, NQK = KS, NG = NPV + NQK;
+    constexpr int LDS_AHEAD = lds_ahead(D, SHAPE);
     static_assert(NPV == NQK, "the two products have the same number of MFMA groups");
     // LDS fragment of group g of the step with parity PAR (its PV and QK both work on the half PAR ^ 1 of their tiles)
     auto read_frag = [&](auto PARC, const char* kb, const char* vb, int g) __attribute__((always_inline)) -> bf16x8 {
