@@ -75,9 +75,10 @@ __device__ __attribute__((always_inline)) inline void bwd_part(const BwdArgs& a,
     constexpr bool DKV = MODE == BWD_DKV; // dK and dV together: two accumulators
     // LDS fragments are read AH MFMA groups before their use and the order is pinned with scheduling fences, so that an MFMA
     // waits only for its own operands (left to itself the compiler issues each read right before the MFMA that needs it).
-    // The dK+dV launch with 8 wavefronts has almost no registers to spare: 1 group ahead in the first two products and 2 in the last
-    // two is what fits without spilling into the MFMA chains (deeper variants measure 2-14 % slower).
-    constexpr int AH_A = OWN2_LDS ? 1 : 4, AH_C = OWN2_LDS ? 2 : 4;
+    // The dK+dV part with the owners' V in LDS has almost no registers to spare: 1 group ahead in the first two products and 2 (8 wavefronts) or 3 (4) in the
+    // last two is what fits without spilling into the MFMA chains.  160 units of 960 tokens, training step, us: 375 with 1 and 2, 366 with 1 and 3 or 4, 372 with
+    // 2 and 4; 48 of 400 40.3 / 39.85 / 40.1 / 40.5.  With 8 wavefronts deeper variants measured 2 to 14 % slower.
+    constexpr int AH_A = OWN2_LDS ? 1 : 4, AH_C = OWN2_LDS ? (NW == 4 ? 3 : 2) : 4;
     constexpr int TILE_BYTES = BT * RB;
     static_assert(IPW >= 1 && IPW * QW * RPI == BT, "a tile's instructions are spread evenly over the wavefronts");
     static_assert(BT == 64 || BT == 32, "tiles of one or two blocks of 32 rows");
