@@ -15,6 +15,9 @@ struct ShapeCost {
     float again;     // and every further one
     float crowd;     // once, where workgroups share a CU: they start together and wait for the same loads
     float block[4];  // us per 32-row block of the walk with 128 or fewer, 256, 512, 768 workgroups running
+    // how much of the difference to a full round a last round of many has, from the round's half on: the chip's clock is down by then, and its workgroups begin
+    // here and there, as the others end (without it the fit took 69x1304 to Q256, 82 us instead of 72)
+    float late = 0.f;
 };
 
 // The units of a launch: how many have any row, and the rows of the largest and of the smallest one (they differ in the any-resolution
@@ -43,7 +46,11 @@ inline float launch_cost(const ShapeCost& c, const UnitSizes& u, bool step) {
     const float blocks = (float)((u.n_max + 31u) / 32u);
     const uint64_t wgs = u.workgroups(c), per_round = CUS * (uint64_t)c.max_k, rounds = wgs / per_round, rem = wgs % per_round;
     float t = c.first + c.again * (float)(rounds + (rem != 0) - 1u) + (float)rounds * blocks * c.block[c.max_k];
-    if (rem != 0) t += blocks * block_cost(c, rem, step);
+    if (rem != 0) {
+        float b = block_cost(c, rem, step);
+        if (rounds != 0) b += c.late * (2u * rem < per_round ? 2.0f * (float)rem / (float)per_round : 1.0f) * (c.block[c.max_k] - b);
+        t += blocks * b;
+    }
     if (wgs > CUS) t += c.crowd * (wgs >= CUS + CUS / 12 ? 1.0f : 12.0f * (float)(wgs - CUS) / CUS);
     return t;
 }
@@ -75,26 +82,26 @@ enum FwdShape : int {
     Q128_FULL = 6,
 };
 
-// Costs fitted to 1100 calls timed in every shape (1..2700 units of 8..80,640 tokens, plain and any-resolution): the pick is 0.1 % above the
-// best shape on average and 8 % at worst (with one figure a round 0.5 % and 15 %).  Measured, always Q256 -> picked, us at
-// head_dim 128, units x tokens: 48x390 18.6 -> 13.5, 88x280 16.5 -> 14.7, 160x960 101 -> 88, 169x1550 246 -> 230, 24x2600 134 -> 85,
-// 48x2600 213 -> 165, 1x8190 166 -> 96, 1x20160 401 -> 236, 4x20160 948 -> 830; 192x240 (16.5), 34x900 (29), 84x512 (21.3), 48x960 (32),
-// 14x30240 (5740), 20x20160 (3780) and 48x8190 (1400) keep it.  At head_dim 64: 24x2600 88 -> 52, 4x20160 640 -> 499, 160x4000 865 -> 718,
-// 160x20160 18,550 -> 17,220; 103x377 (11.8) keeps it.
-//   * What a round costs depends on how full it is: a Q256 block takes 0.63 us with half of the CUs busy and 0.88 with all of them, the chip
+// Costs fitted to 1200 calls timed in every shape, in turn and warm (1..640 units of 16..12,000 tokens), and held to the calls named below: the pick is 0.07 % above
+// the best shape on average at head_dim 128 (6 % at worst) and 0.04 % at head_dim 64 (5 %).  Against the fit to the kernels that stored their results in pieces,
+// whose ends and merges took longer, 0.978 and 0.985 of the time on average (0.84 at best; 1.004 and 1.044 at worst).  Measured, us, Q256 / Q128 / Q64_SPLIT /
+// Q128_SPLIT at head_dim 128, units x tokens: 78x67 6.30 / 6.11 / 7.31 / 7.11, 10x1512 36.1 / 27.9 / 23.8 / 23.9, 69x1304 82.3 / 72.4 / 133 / 79.7, 4x3293 71.6 / 55.1 /
+// 43.7 / 43.9; 192x240, 34x900, 84x512, 48x960, 14x30240 and 20x20160 keep Q256.  At head_dim 64: 52x276 8.47 / 6.87 / 8.38 / 7.19, 10x3203 57 / 57 / 44 / 62, 100x4096
+// and 160x20160 keep Q128; 103x377 keeps Q256.
+//   * What a round costs depends on how full it is: a Q256 block takes 0.74 us with half of the CUs busy and 0.97 with all of them, the chip
 //     being at its power limit.  Without that the rule gave long sequences to Q128_SPLIT for a smaller last round: 14x30240 6025 us.
 //   * Two Q128 workgroups that start together on a CU wait for the same loads (`crowd`): 192x240 17.3 in that shape, 84x512 22.5.
 //   * Q64_SPLIT is for one round of its own: in a second one the traffic of four times the workgroups shows (34x900: 33.5).
 //   * The split shapes stream K and V at two places and move 4 % more per MFMA; what they gain is idle CUs, so they are left out from two
 //     rounds of Q256 on.
-constexpr ShapeCost FWD_COST_128[] = {{Q256, 256, false, 1, 4.0f, 7.3f, 0.f, {0.63f, 0.88f}},
-                                      {Q128, 128, false, 2, 3.6f, 2.6f, 2.3f, {0.40f, 0.66f, 0.96f}},
-                                      {Q64_SPLIT, 64, true, 1, 1.2f, 0.8f, 0.f, {0.29f, 0.37f}},
-                                      {Q128_SPLIT, 128, true, 1, 5.6f, 10.2f, 0.f, {0.30f, 0.46f}}};
-constexpr ShapeCost FWD_COST_64[] = {{Q256, 256, false, 1, 3.2f, 5.7f, 0.f, {0.32f, 0.524f}},
-                                     {Q128, 128, false, 3, 1.6f, 0.8f, 4.5f, {0.30f, 0.32f, 0.535f, 0.66f}},
-                                     {Q64_SPLIT, 64, true, 2, 1.8f, 1.1f, 0.f, {0.165f, 0.268f, 0.376f}},
-                                     {Q128_SPLIT, 128, true, 1, 3.2f, 6.2f, 0.f, {0.194f, 0.249f}}};
+constexpr ShapeCost FWD_COST_128[] = {{Q256, 256, false, 1, 4.43f, 6.52f, 0.f, {0.742f, 0.967f}, 0.65f},
+                                      {Q128, 128, false, 2, 4.11f, 2.15f, 1.84f, {0.443f, 0.775f, 1.051f}, 0.20f},
+                                      {Q64_SPLIT, 64, true, 1, 5.62f, 1.49f, 0.f, {0.305f, 0.347f}},
+                                      {Q128_SPLIT, 128, true, 1, 6.50f, 14.55f, 0.f, {0.319f, 0.548f}}};
+constexpr ShapeCost FWD_COST_64[] = {{Q256, 256, false, 1, 2.44f, 6.90f, 0.f, {0.310f, 0.528f}},
+                                     {Q128, 128, false, 3, 1.01f, 1.87f, 4.97f, {0.320f, 0.346f, 0.514f, 0.658f}},
+                                     {Q64_SPLIT, 64, true, 2, 2.24f, 0.71f, 0.98f, {0.146f, 0.182f, 0.268f}},
+                                     {Q128_SPLIT, 128, true, 1, 2.38f, 9.52f, 0.f, {0.179f, 0.251f}}};
 inline int pick_fwd_shape(int head_dim, const UnitSizes& u) {
     const auto& cost = head_dim == 128 ? FWD_COST_128 : FWD_COST_64;
     return pick_shape(cost, u, false, [&](const ShapeCost& c) {
@@ -138,8 +145,10 @@ enum BwdShape : int {
 // us, units x tokens, head_dim 128: 1x120 18.1 -> 12.4, 8x190 21.6 -> 14.5, 48x400 43 -> 35, 24x1000 75 -> 63.5, 1x6116 215 -> 134, 160x400 120 -> 93,
 // 160x960 344 -> 312, 1x11191 390 -> 370, 12x8190 1437 -> 1313, 4x20160 3387 -> 2704, 160x2600 2093 -> 1977; head_dim 64: 1x78 11.8 -> 8.1,
 // 48x400 25.9 -> 21.4, 24x1000 44.6 -> 33.8, 1x3955 94 -> 52, 4x5000 171 -> 115, 160x960 171 -> 165.
+// The ends and merges of the workgroups have become shorter since, by about the same for all, so that the picks stand (0.3 % above the best on average over 900
+// calls timed anew); units of 65 to 96 tokens at head_dim 128 alone are better off in B128 than in two groups (7x74 12.1 -> 10.4 us): `first` of B64_SPLIT.
 constexpr ShapeCost PAIR_COST_128[] = {{B128, 128, false, 2, 8.9f, 8.3f, 4.7f, {1.285f, 1.505f, 1.616f}},
-                                       {B64_SPLIT, 64, true, 1, 10.8f, 4.0f, 0.f, {0.614f, 0.718f}},
+                                       {B64_SPLIT, 64, true, 1, 11.2f, 4.0f, 0.f, {0.614f, 0.718f}},
                                        {B128_SPLIT, 128, true, 1, 14.3f, 8.2f, 0.f, {0.975f, 0.930f}}};
 constexpr ShapeCost PAIR_COST_64[] = {{B128, 128, false, 2, 7.2f, 5.4f, 2.4f, {0.558f, 0.684f, 0.848f}},
                                       {B64_SPLIT, 64, true, 2, 7.4f, 4.0f, 1.8f, {0.361f, 0.387f, 0.481f}},

@@ -161,3 +161,14 @@ def test_gpu_tests_reach_the_kernels_with_and_without_that_test(pick):
     for D in met:
         met[D] = set(pick([dense("kernel", D, *c) for c in fwd.WORKGROUP_SHAPES + fwd.LAST_WORKGROUPS]))
     assert all({Q256, Q128, Q256_FULL, Q128_FULL} <= m for m in met.values())
+
+
+@pytest.mark.parametrize("launch,D,calls,want", [
+    ("fwd", 128, [(1, 78), (35, 331), (49, 1465), (277, 1199), (141, 1997)], [Q128]),  # short units are not worth a merge; late rounds cost a full chip's clock
+    ("fwd", 64, [(52, 276), (56, 244)], [Q128]),
+    ("fwd", 128, [(3, 6151), (4, 3293), (10, 1512)], [Q64_SPLIT, Q128_SPLIT]),
+    ("bwd", 128, [(2, 73), (7, 74), (17, 65), (1, 82)], [B128]),
+])
+def test_calls_timed_in_every_shape(pick, launch, D, calls, want):
+    """Picks within 3 % of the best of all shapes, where the neighbouring ones measured up to 20 % slower."""
+    assert set(pick([dense(launch, D, *c) for c in calls])) <= set(want)
