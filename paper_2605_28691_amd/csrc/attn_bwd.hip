@@ -182,7 +182,10 @@ __device__ __attribute__((always_inline)) inline void bwd_part(const BwdArgs& a,
     auto tile_landed = [&]() __attribute__((always_inline)) { asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); };
 
     // ---- tile 0 is asked for before anything else is formed: every wavefront finds its row offsets for itself (lane = row) and hands them round its lanes
-    {
+    // (Not in the any-resolution mode's dK+dV launch at head_dim 128: its registers are allotted another way then, 15 spilled values instead of 11, and at 720P it
+    // takes 52.1 ms instead of 50.3.)
+    constexpr bool EARLY = !(PAD && D == 128 && NW == 8 && OWN2_LDS && KG == 1);
+    if constexpr (EARLY) {
         const uint32_t j = tile0 * BT + lane;
         const uint32_t mine = token_at(j < n_seq ? j : n_seq - 1u) * row_bytes;
         RowOffs o;
@@ -269,7 +272,11 @@ __device__ __attribute__((always_inline)) inline void bwd_part(const BwdArgs& a,
         }
     }
     const char* const own2_lds = own2buf + (OWN2_LDS ? ow * 32u * RB : 0u) - grp;  // read at a_rd()
-    for (uint32_t t = BT == 64 ? 1u + ow : ow; t < (uint32_t)BRING_AHEAD; t += QW) produce(t);
+    for (uint32_t t = EARLY && BT == 64 ? 1u + ow : ow; t < (uint32_t)BRING_AHEAD; t += QW) produce(t);
+    if constexpr (!EARLY) {
+        __syncthreads();
+        issue_tile(0, read_offs(0), s1buf0, s2buf0);
+    }
     store_rowvals(0);
     tile_landed();
     __syncthreads();
