@@ -433,6 +433,7 @@ __device__ __attribute__((always_inline)) inline void bwd_part(const BwdArgs& a,
         return (n == 0 ? s1buf0 : n == 1 ? s1buf1 : n == 2 ? s2buf0 : s2buf1) + i / 4u * PART;
     };
     const uint32_t jw = ot * (uint32_t)WGO + ow * 32u, stored = rows_below(jw, n_seq);
+    const bool few = !DELTA && n_seq - ot * (uint32_t)WGO <= BWD_DIRECT_ROWS;  // of the workgroup's rows; the launches of one kind are for long units
     if constexpr (KG > 1) {
         if (n_t < (all_t + KG - 1) / KG) __syncthreads();  // a group with one tile less has passed one barrier less
         // every tile has been read (each ends with a barrier)
@@ -468,6 +469,13 @@ __device__ __attribute__((always_inline)) inline void bwd_part(const BwdArgs& a,
         }
         if (kg != 0) take(to1, second);
         if (stored == 0u) return;
+        if (few) {
+            if (stored >> lq & 1u) {
+                if (kg == 0) store_own_row((const f32x16(&)[MF])*acc, a.scale, grad_g, own_tok, C, lane);
+                else store_own_row((const f32x16(&)[MF])*second, DKV ? 1.0f : a.scale, DKV ? grad2_g : grad_g + D / 2, own_tok, C, lane);
+            }
+            return;
+        }
         // a wavefront's region: what it has taken; without room for both that is group 1's, and group 0 has the owners' second operand instead
         static_assert(AT_ONCE || OWN2_LDS, "a region for group 0");
         constexpr int CHP = MF * 32 >= 64 ? 64 : 32;
@@ -479,6 +487,13 @@ __device__ __attribute__((always_inline)) inline void bwd_part(const BwdArgs& a,
 
     // ---- epilogue: lane owns row jo; every tile has been read, 4 KiB of the buffers for each wavefront
     if (stored == 0u) return;
+    if (few) {
+        if (stored >> lq & 1u) {
+            store_own_row(acc, a.scale, grad_g, own_tok, C, lane);
+            if constexpr (DKV) store_own_row(acc2, 1.0f, grad2_g, own_tok, C, lane);
+        }
+        return;
+    }
     constexpr uint32_t PER_BUF = TILE_BYTES / 4096;
     static_assert(KG > 1 || NW <= 4 * (int)PER_BUF, "a region of the tile buffers for every wavefront");
     const uint32_t in = ow / PER_BUF;

@@ -256,9 +256,15 @@ __global__ __launch_bounds__(64 * fwd_waves(SHAPE), (fwd_queries(SHAPE) == 128 &
     const uint32_t jq = qt * BR + qw * 32u + lq;
     const bool q_valid = jq < n_seq;
     const uint32_t q_token = token_at(q_valid ? jq : n_seq - 1u);
+    const bool few = n_seq - qt * BR <= FWD_DIRECT_ROWS;  // of the workgroup's rows
     RowLoad<D> q_rows;
-    q_rows.issue(Qg, q_token, C, lane);
     bf16x8 qf[QT][KS];
+    if (few) {
+#pragma unroll
+        for (int ks = 0; ks < KS; ks++) qf[0][ks] = *(const bf16x8*)(Qg + (size_t)q_token * C + ks * 16 + 8 * h);
+    } else {
+        q_rows.issue(Qg, q_token, C, lane);
+    }
 
     // ---- running state: every lane tracks its own query (lanes l and l^32 hold the same m_ref; l_run is a partial sum)
     f32x16 oacc[QT][MT];
@@ -525,7 +531,7 @@ __global__ __launch_bounds__(64 * fwd_waves(SHAPE), (fwd_queries(SHAPE) == 128 &
     // ---- prologue: offsets of tiles 1..RING_AHEAD
     for (uint32_t t = 1u + qw; t <= (uint32_t)RING_AHEAD && (!TRIM || t < n_tiles); t += QW) produce(t);
     tile_landed();
-    {   // Q's fragments, through V's buffers: V tile 0 is not asked for before the barrier
+    if (!few) {  // Q's fragments, through V's buffers: V tile 0 is not asked for before the barrier
         constexpr uint32_t REGION = 2 * KG * TL::TILE_BYTES >= NW * 4096 ? 4096 : 2048;
         static_assert(NW * REGION <= 2 * KG * TL::TILE_BYTES, "a region for every wavefront");
         const uint32_t at = wave * REGION;
@@ -678,6 +684,13 @@ __global__ __launch_bounds__(64 * fwd_waves(SHAPE), (fwd_queries(SHAPE) == 128 &
         // the input is a sparse layout: bb is the subsequence (p, q, b) and this lane's query sits at position jw + lq of it
         dst = (__bf16*)a.out + (size_t)head * D + kg * (uint32_t)(D / KG);
         row = (uint32_t)scattered_row(a, bb, q_valid ? jw + lq : n_seq - 1u);
+    }
+    if (few) {
+        if (stored >> lq & 1u) {
+            if (KG == 1 || kg == 0) store_own_row((const f32x16(&)[MF])*oacc[0], inv, dst, row, C, lane);
+            else store_own_row((const f32x16(&)[MF])*(oacc[0] + MT - MF), inv, dst, row, C, lane);
+        }
+        return;
     }
     // K's buffers are free here, and of the groups' buffers the half that this wavefront has taken in
     constexpr uint32_t CHP = D / KG >= 64 ? 64 : 32, REGION = KG > 1 || 2 * TL::TILE_BYTES >= NW * 4096 ? 4096 : 2048, ROWS = REGION >= 64 * CHP ? 32 : 16;

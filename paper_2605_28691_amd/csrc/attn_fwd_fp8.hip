@@ -63,7 +63,8 @@ __device__ inline void lane_pair_f(float x, float& lo, float& hi) {
 // 371 -> 338; with rows whole and the last of 24 lines padded, at head_dim 128: 40 heads, 1x45x80 73.2 -> 75.6, 12 heads, 21x45x80 5359 -> 5396.
 enum Padding : int { NO_PADDING = 0, SOME_TILES = 1, MOST_TILES = 2 };
 
-template <int D, int PADDING>
+// FEW: units of few positions, whose rows are stored directly.  (A kernel of its own: with a branch at its end the one of head_dim 128 spilled 72 values, in the loop.)
+template <int D, int PADDING, bool FEW>
 __attribute__((amdgpu_waves_per_eu(waves_per_simd8(D), waves_per_simd8(D))))
 __global__ __launch_bounds__(NT8) void attn_fwd_fp8_kernel(Fp8AttnArgs a, PadArg<PADDING != NO_PADDING> pad_map, UnitMap units, uint32_t total, uint32_t per_xcd) {
     constexpr bool PAD = PADDING != NO_PADDING, FLAG = PADDING == SOME_TILES;
@@ -349,15 +350,20 @@ __global__ __launch_bounds__(NT8) void attn_fwd_fp8_kernel(Fp8AttnArgs a, PadArg
     bool real;  // as q_valid says
     const uint32_t jr = q_valid ? jq : 0u;
     const uint32_t tok = PAD ? src_token_padded(a.g, p_, q_, jr, &real) : src_token(a.g, p_, q_, jr);
-    // every tile has been read: 4 KiB of the buffers for each wavefront
-    constexpr uint32_t PER_BUF = TILE_BYTES / 4096;
-    static_assert(NW8 <= 4 * (int)PER_BUF, "a region of the tile buffers for every wavefront");
-    const uint32_t in = wave / PER_BUF;
-    char* const region = (in == 0 ? kbuf0 : in == 1 ? kbuf1 : in == 2 ? vbuf0 : vbuf1) + wave % PER_BUF * 4096u;
-    store_rows<64, 32>(region, oacc, inv, (__bf16*)a.out + (size_t)b0_ * (uint32_t)a.g.n_tok * C + (size_t)head * D, RowDest<64>(tok, C, rows, lane), lane);
+    __bf16* const out = (__bf16*)a.out + (size_t)b0_ * (uint32_t)a.g.n_tok * C + (size_t)head * D;
+    if constexpr (FEW) {
+        if (q_valid) store_own_row(oacc, inv, out, tok, C, lane);
+    } else {
+        // every tile has been read: 4 KiB of the buffers for each wavefront
+        constexpr uint32_t PER_BUF = TILE_BYTES / 4096;
+        static_assert(NW8 <= 4 * (int)PER_BUF, "a region of the tile buffers for every wavefront");
+        const uint32_t in = wave / PER_BUF;
+        char* const region = (in == 0 ? kbuf0 : in == 1 ? kbuf1 : in == 2 ? vbuf0 : vbuf1) + wave % PER_BUF * 4096u;
+        store_rows<64, 32>(region, oacc, inv, out, RowDest<64>(tok, C, rows, lane), lane);
+    }
 }
 
-template <int D, int PADDING>
+template <int D, int PADDING, bool FEW>
 static hipError_t launch_fp8_t(const Fp8AttnArgs& a, hipStream_t stream) {
     const uint32_t s2 = a.g.mode == MODE_DENSE ? 1u : (uint32_t)(a.g.s * a.g.s);
     const uint32_t n_units = (uint32_t)a.B * s2 * (uint32_t)a.heads;
@@ -367,14 +373,16 @@ static hipError_t launch_fp8_t(const Fp8AttnArgs& a, hipStream_t stream) {
     const uint32_t per_xcd = (uint32_t)((total + 7u) / 8u);
     PadArg<PADDING != NO_PADDING> pad_map;
     make_pad_arg(a.g, pad_map);
-    attn_fwd_fp8_kernel<D, PADDING><<<8u * per_xcd, NT8, 0, stream>>>(a, pad_map, make_unit_map<false>(a.g, q_tiles, (uint32_t)a.B, (uint32_t)a.heads), (uint32_t)total, per_xcd);
+    attn_fwd_fp8_kernel<D, PADDING, FEW><<<8u * per_xcd, NT8, 0, stream>>>(a, pad_map, make_unit_map<false>(a.g, q_tiles, (uint32_t)a.B, (uint32_t)a.heads), (uint32_t)total, per_xcd);
     return hipGetLastError();
 }
 
 template <int D>
 static hipError_t launch_fp8_d(const Fp8AttnArgs& a, hipStream_t stream) {
-    if (!a.pad) return launch_fp8_t<D, NO_PADDING>(a, stream);
-    return pads_most_tiles(D, a.g) ? launch_fp8_t<D, MOST_TILES>(a, stream) : launch_fp8_t<D, SOME_TILES>(a, stream);
+    const bool few = (uint32_t)a.g.n_sub <= FWD_DIRECT_ROWS;
+    if (!a.pad) return few ? launch_fp8_t<D, NO_PADDING, true>(a, stream) : launch_fp8_t<D, NO_PADDING, false>(a, stream);
+    if (pads_most_tiles(D, a.g)) return launch_fp8_t<D, MOST_TILES, false>(a, stream);  // (never in units of few positions)
+    return few ? launch_fp8_t<D, SOME_TILES, true>(a, stream) : launch_fp8_t<D, SOME_TILES, false>(a, stream);
 }
 
 hipError_t launch_attn_fp8(const Fp8AttnArgs& a, hipStream_t stream) {

@@ -74,6 +74,29 @@ __device__ __attribute__((always_inline)) inline void store_rows(char* buf, cons
         }
 }
 
+// The same from where the channels are: row, row_len as in RowDest, `row` being the lane's own.  For workgroups of few rows, whose stores do not queue and which
+// the way through LDS only delays.
+template <int BLOCKS>
+__device__ __attribute__((always_inline)) inline void store_own_row(const __attribute__((ext_vector_type(16))) float (&acc)[BLOCKS], float f, __bf16* dst, uint32_t row, size_t row_len, uint32_t lane) {
+    typedef __attribute__((ext_vector_type(4))) __bf16 bf16x4;
+    asm volatile("" : "+v"(row), "+v"(lane));  // formed here: else the address is kept in registers through the whole walk (3 spilled values in the backward's B128)
+    __bf16* const at = dst + (size_t)row * row_len + (lane >> 5) * 4u;
+#pragma unroll
+    for (int mt = 0; mt < BLOCKS; mt++)
+#pragma unroll
+        for (int g = 0; g < 4; g++) {
+            bf16x4 o;
+#pragma unroll
+            for (int e = 0; e < 4; e++) o[e] = (__bf16)(acc[mt][4 * g + e] * f);
+            *(bf16x4*)(at + mt * 32 + g * 8) = o;
+        }
+}
+
+// Rows of a workgroup up to which they are moved directly, and, in the forward, queries loaded as fragments.  us in a row, through LDS / directly, head_dim 128:
+// forward, 4 units of 16 tokens 4.47 / 3.93, of 32 4.41 / 4.04, of 40 5.12 / 4.82 (200 of 56: 5.32 / 5.45); backward, 4 of 16 7.26 / 6.94, of 32 7.47 / 7.20, but 200 of
+// 40 11.6 / 12.4; 8-bit, 8 of 32 5.2 / 4.8.
+constexpr uint32_t FWD_DIRECT_ROWS = 48, BWD_DIRECT_ROWS = 32;
+
 // The way in: a wavefront's 32 rows as B operands (lane = row lane % 32, 8 consecutive channels starting at 16*ks + 8*(lane/32)).  Loaded in that shape an
 // instruction takes 32 bytes of each of 32 rows; here it takes 128 bytes of 8, and the fragments are picked up from LDS.  Forward calls, us, loaded as fragments ->
 // so: 12 units of 132 tokens 8.06 -> 7.94, 9.32 -> 9.01 and 13.16 -> 12.91 in chains, 48 of 390 12.39 -> 12.34.  The backward kernels load fragments: with this

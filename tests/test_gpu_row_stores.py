@@ -1,5 +1,6 @@
-"""The rows that a wavefront moves through LDS, 8 or 16 an instruction: units that end inside, at and behind such a run of rows, in every kind of attention
-kernel, against the oracle.  Rows that a unit does not have belong to the next unit here, so one too many would be seen there."""
+"""The rows that a wavefront moves: through LDS, 8 or 16 an instruction, or, in workgroups of few rows, directly.  Units that end inside, at and behind a run of
+rows.  Every result lies inside a larger buffer of NaN: a row that is not written stays NaN, one that is written outside the tensor is found there.  (A row
+too many inside a unit is not an error that could be seen: an owner past the end has the last row's number and values.)"""
 import numpy as np
 import pytest
 import torch
@@ -12,11 +13,104 @@ from _util import assert_close_bf16, errors, oracle_inputs, to_np64
 pytestmark = pytest.mark.gpu
 
 LENGTHS = [1, 7, 8, 9, 15, 16, 17, 24, 31, 32, 33, 71, 95, 129, 200]
+GUARD = 32 * 1024  # elements in front of and behind a tensor
+
+
+class Guarded:
+    """A bf16 tensor of NaN inside a buffer of NaN."""
+
+    def __init__(self, shape):
+        n = int(np.prod(shape))
+        self.buf = torch.full((n + 2 * GUARD,), float("nan"), dtype=torch.bfloat16, device="cuda")
+        self.t = self.buf[GUARD : GUARD + n].view(shape)
+
+    def check(self, what):
+        assert not torch.isnan(self.t).any(), f"{what}: a row was not written"
+        assert torch.isnan(self.buf[:GUARD]).all() and torch.isnan(self.buf[GUARD + self.t.numel() :]).all(), f"{what}: written outside the tensor"
+        return self.t
 
 
 def _inputs(n, heads, D, batch=2):
     g = torch.Generator().manual_seed(n * 8 + heads)
     return [torch.randn((batch, n, heads, D), generator=g).to(torch.bfloat16) for _ in range(4)]
+
+
+def _device_inputs(shape, seed):
+    g = torch.Generator(device="cuda").manual_seed(seed)
+    return [torch.randn(shape, generator=g, device="cuda").to(torch.bfloat16) for _ in range(4)]
+
+
+def _exact_rows(q, k, v, dout, rows, out, grads):
+    """Attention over the tokens `rows` of every batch element and head, in 64 bits, into out and grads."""
+    scale = q.shape[3] ** -0.5
+    for b in range(q.shape[0]):
+        for a in range(q.shape[2]):
+            qd, kd, vd, do = (t[b, rows, a].double() for t in (q, k, v, dout))
+            p = torch.softmax(qd @ kd.t().contiguous() * scale, dim=1)
+            out[b, rows, a] = p @ vd
+            if grads:
+                ds = p * (do @ vd.t().contiguous() - (do * out[b, rows, a]).sum(dim=1, keepdim=True))
+                for grad, x in zip(grads, (ds @ kd * scale, ds.t().contiguous() @ qd * scale, p.t().contiguous() @ do)):
+                    grad[b, rows, a] = x
+
+
+def _assert_rows(got, want, n, what):
+    """bf16 factors and a bf16 result: 2.5e-3 in all, and no row further off than a few times that; over one key dq and dk are 0 but for the rounding of delta
+    (out and dO in bf16: 2^-9 of |dO||v|)."""
+    diff = (got.double() - want).flatten(0, -2).norm(dim=1)
+    size = want.flatten(0, -2).norm(dim=1).square().mean().sqrt()
+    if n == 1 and what in ("dq", "dk"):
+        assert (got.double() - want).abs().max() <= 2.0 ** -7 * got.shape[-1] ** 0.5, what
+    else:
+        assert diff.square().mean().sqrt() <= 1e-2 * size and diff.max() <= 5e-2 * size, (what, n, (diff.max() / size).item())
+
+
+def _check_dense(units, n, D, backward):
+    q, k, v, dout = _device_inputs((1, n, units, D), 1000 * units + n)
+    want = [torch.empty(q.shape, dtype=torch.float64, device="cuda") for _ in range(4 if backward else 1)]
+    _exact_rows(q, k, v, dout, slice(0, n), want[0], want[1:])
+    out = Guarded(q.shape)
+    if not backward:
+        sk.dense_attn_fwd(q, k, v, 1, 1, n, out=out.t)
+        return _assert_rows(out.check(f"out {n}"), want[0], n, "out")
+    _, lse = sk.skiparse_attn_fwd_lse(q, k, v, 1, 1, n, 1, "token", out=out.t)
+    grads = [Guarded(q.shape) for _ in range(3)]
+    sk.skiparse_attn_bwd(q, k, v, out.check(f"out {n}"), dout, lse, 1, 1, n, 1, "token", dq=grads[0].t, dk=grads[1].t, dv=grads[2].t)
+    for name, x, w in zip(("dq", "dk", "dv"), grads, want[1:]):
+        _assert_rows(x.check(f"{name} {n}"), w, n, name)
+
+
+# launch, head_dim, kernel (FwdShape or BwdShape), units, tokens in front of the last workgroup's
+FEW = [("fwd", 64, 1, 104, 256), ("fwd", 64, 2, 3, 0), ("fwd", 64, 3, 2, 256), ("fwd", 64, 4, 40, 384),
+       ("fwd", 128, 1, 96, 256), ("fwd", 128, 2, 3, 0), ("fwd", 128, 3, 2, 384), ("fwd", 128, 4, 32, 512),
+       ("bwd", 64, 1, 3, 0), ("bwd", 64, 1, 200, 0), ("bwd", 64, 2, 2, 64), ("bwd", 64, 3, 8, 1792),
+       ("bwd", 128, 1, 3, 0), ("bwd", 128, 1, 200, 0), ("bwd", 128, 2, 2, 128), ("bwd", 128, 3, 24, 384)]
+FEW_ROWS = [1, 16, 31, 32, 33, 48, 49]  # both sides of the lines at 32 and 48
+
+
+@pytest.mark.parametrize("launch,D,kernel,units,before", FEW)
+def test_workgroups_of_few_rows(launch, D, kernel, units, before):
+    for rows in FEW_ROWS:
+        _check_dense(units, before + rows, D, launch == "bwd")
+
+
+@pytest.mark.parametrize("D", [64, 128])
+@pytest.mark.parametrize("pad", [False, True])
+def test_quantised_units_of_few_rows(D, pad):
+    """One class of 1 to 49 positions; in the any-resolution mode classes of W/2 and (W + 1)/2 real tokens a line."""
+    for W in FEW_ROWS:
+        T, H, W, s = (1, 3, W, 2) if pad else (1, 1, W, 1)
+        q, k, v, dout = _device_inputs((2, H * W, 3, D), W)
+        (q8, sq), (k8, sk_), (v8, sv) = (sk.skiparse_quantize_fp8(t, T, H, W, s, "token", pad=pad) for t in (q, k, v))
+        out = Guarded(q.shape)
+        sk.skiparse_attn_fwd_fp8(q8, k8, v8, sq, sk_, sv, T, H, W, s, "token", out=out.t, pad=pad)
+        want = torch.empty(q.shape, dtype=torch.float64, device="cuda")
+        n = torch.arange(H * W, device="cuda").view(H, W)
+        for rows in (n[i::s, j::s].reshape(-1) for i in range(s) for j in range(s)):
+            if rows.numel():
+                _exact_rows(q, k, v, dout, rows, want, [])
+        diff = out.check(f"out {W}").double() - want
+        assert diff.norm() <= 1e-1 * want.norm(), W  # E4M3 on N(0,1) values: 5e-2
 
 
 @pytest.mark.parametrize("n", LENGTHS)

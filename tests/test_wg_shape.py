@@ -172,3 +172,11 @@ def test_gpu_tests_reach_the_kernels_with_and_without_that_test(pick):
 def test_calls_timed_in_every_shape(pick, launch, D, calls, want):
     """Picks within 3 % of the best of all shapes, where the neighbouring ones measured up to 20 % slower."""
     assert set(pick([dense(launch, D, *c) for c in calls])) <= set(want)
+
+
+def test_row_store_tests_reach_their_kernels(pick):
+    """Every kind of kernel with a last workgroup of few rows, on both sides of the lines at which rows are moved directly."""
+    import test_gpu_row_stores as rows
+
+    for launch, D, kernel, units, before in rows.FEW:
+        assert pick([dense(launch, D, units, before + n) for n in rows.FEW_ROWS]) == [kernel] * len(rows.FEW_ROWS), (launch, D, kernel)
