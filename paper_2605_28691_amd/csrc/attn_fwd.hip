@@ -143,10 +143,10 @@ __global__ __launch_bounds__(64 * fwd_waves(SHAPE), (fwd_queries(SHAPE) == 128 &
     using TL = Tile<D, QW>;
     constexpr int KS = D / 16;     // MFMA steps along head_dim for S^T = K Q^T
     constexpr int MT = D / 32;     // 32-row blocks of O^T
-    // Small calls: offsets are formed for the tiles that exist only (those past the group's last tile are read but address nothing), and
-    // keys are compared with the end only in the block that holds it: 1 to 6 % of a small launch (us, 103 units of 377 tokens at
-    // head_dim 64 12.3 -> 11.8, 144 of 160..176 in the any-resolution mode at head_dim 128 12.65 -> 12.3).  The plain kernels of head_dim 128
-    // go without: three or four registers more cost 0.3 % at 768P (110.8 -> 111.1 ms) and 0.5 % of a 13.6 us layer of 390 tokens a unit.
+    // Small calls: the prologue forms offsets for the tiles that exist only (those past the group's last tile are read but address nothing).  With the test of
+    // mask_end(), which all kernels have by now, it gave 1 to 6 % of a small launch (us, 103 units of 377 tokens at head_dim 64 12.3 -> 11.8, 144 of 160..176 in
+    // the any-resolution mode at head_dim 128 12.65 -> 12.3) and cost the plain kernels of head_dim 128, which go without, three or four registers: 0.3 % at 768P
+    // (110.8 -> 111.1 ms) and 0.5 % of a 13.6 us layer of 390 tokens a unit, in kernels that have been allotted anew since.
     constexpr bool TRIM = PAD || D == 64;
     constexpr bool SKIP_IDLE = SHAPE != Q256_FULL && SHAPE != Q128_FULL && !(D == 128 && SHAPE == Q64_SPLIT && !PAD);  // see fwd_kernel()
     constexpr int BR = 32 * QW * QT;   // query rows per workgroup: QT tiles of 32 per wavefront
@@ -375,14 +375,10 @@ __global__ __launch_bounds__(64 * fwd_waves(SHAPE), (fwd_queries(SHAPE) == 128 &
             for (int r = 0; r < 16; r++) s[r] = key0 + 8 * (r >> 2) + 4 * h + (r & 3) < n_seq ? s[r] : -INFINITY;
         }
     };
-    // One pipeline step for block b = 2W-1 (PAR = 1) or 2W (PAR = 0) of window W: K tile W in kb, V tile W-1 in vb.
-    //   QK(b+1) -> sreg[PAR^1]   softmax(b): sreg[PAR] -> preg[PAR]   PV(b-1) with preg[PAR^1]
-    // Generic form, used for the first and last windows (optional QK / PV, key masking); instruction order is left to
-    // the compiler.  The steady-state windows use step_manual below.
-    auto step = [&](auto DO_QK, auto DO_PV, auto PARC, uint32_t blk, const char* kb, const char* vb) __attribute__((always_inline)) {
+    // softmax of a block outside the pipelined steps, sreg[PAR] -> preg[PAR], by the true maximum and with keys past the end masked.  Where it raises the
+    // reference, O is rescaled after PV(b-1) and before PV(b).
+    auto softmax = [&](auto PARC, uint32_t blk) __attribute__((always_inline)) {
         constexpr int PAR = decltype(PARC)::value;
-        apply_pending();
-        if (decltype(DO_QK)::value) qk(kb, PAR ^ 1, sreg[PAR ^ 1]);
         unsigned long long grow_mask = 0;
 #pragma unroll
         for (int qi = 0; qi < QT; qi++) {
@@ -403,11 +399,11 @@ __global__ __launch_bounds__(64 * fwd_waves(SHAPE), (fwd_queries(SHAPE) == 128 &
             const float mc_use = m_use == -INFINITY ? 0.f : m_use * c;
             l_run[qi] = fmaf(l_run[qi], alpha_pending[qi], exps(s, mc_use, preg[PAR][qi]));
         }
-        if (decltype(DO_PV)::value) pv(vb, PAR ^ 1, preg[PAR ^ 1]);
-        pending = grow_mask != 0;  // O is rescaled at the start of the next step: after PV(b-1), before PV(b)
+        pending = grow_mask != 0;
     };
-    // Hand-ordered version of a full, unmasked step: the instruction order is fixed group by group with scheduling
-    // fences, and the exponentials are taken against the reference the row already has, so the common path computes no
+    // One pipeline step for block b = 2W-1 (PAR = 1) or 2W (PAR = 0) of window W: K tile W in kb, V tile W-1 in vb.
+    //   QK(b+1) -> sreg[PAR^1]   softmax(b): sreg[PAR] -> preg[PAR]   PV(b-1) with preg[PAR^1]
+    // The instruction order is fixed group by group with scheduling fences, and the exponentials are taken against the reference the row already has, so the common path computes no
     // maximum at all: per key only fma, exp, half a bf16 pack and an add (row sum).  The guard is the row sum itself:
     // if a lane's 16 probabilities add up to 2^16 or more (always on the first block, where the reference is -inf), the
     // wavefront takes the rare path, which finds the true maximum, redoes the block's exponentials against it and rescales
@@ -563,20 +559,22 @@ __global__ __launch_bounds__(64 * fwd_waves(SHAPE), (fwd_queries(SHAPE) == 128 &
         }
         return;
     }
-    // ---- window 0: QK(0), then step 0 without PV
+    // ---- window 0: QK(0), QK(1) and the softmax of block 0
     {
         issue_v(vbuf0, off_v);
         if (n_tiles > 1) issue_k(kbuf1, off_k);
         off_v = off_k;
         off_k = read_offs(2);
         qk(kbuf0, 0, sreg[0]);
-        step(T_{}, F_{}, P0{}, 0u, kbuf0, vbuf0);
+        qk(kbuf0, 1, sreg[1]);
+        softmax(P0{}, 0u);
         tile_landed();
         __syncthreads();
     }
     // ---- windows 1 .. n_tiles-1.  The parity of W selects the buffers at compile time.  The last one (MAY_END: windows that can be it) has no K tile to ask for,
     // and the block that it takes the exponentials of in its second step may hold keys past the end.  (As two steps of the generic kind, which waited for V's tile
-    // in front of their LDS reads, and with the softmax and PV of a last block that has no key, 48 units of 390 tokens took 12.13 us instead of 11.62.)
+    // in front of their LDS reads, and with the softmax and PV of a last block that has no key, 48 units of 390 tokens took 12.13 us instead of 11.62.  Windows that
+    // can be the last form no offsets for a tile that does not exist: few units of 390 tokens 10.6 -> 10.2, of 520 11.5 -> 11.0.)
     auto window = [&](auto WP, auto MAY_END, uint32_t Wn) __attribute__((always_inline)) {
         constexpr int WPAR = decltype(WP)::value;  // Wn & 1
         char* const kb = WPAR ? kbuf1 : kbuf0;           // K tile Wn
@@ -590,7 +588,7 @@ __global__ __launch_bounds__(64 * fwd_waves(SHAPE), (fwd_queries(SHAPE) == 128 &
         // the L2 misses quadruple (measured: 2.4e8 instead of 5.7e7 per call, and 1.6 % more time); spreading the issues over the
         // MFMA groups is slower still (each issue stalls the wavefront).
         const RowOffs off_ahead = read_offs(Wn + 2u);
-        if (qw == (Wn & (uint32_t)(QW - 1))) produce(Wn + RING_AHEAD);
+        if (qw == (Wn & (uint32_t)(QW - 1)) && (!decltype(MAY_END)::value || Wn + RING_AHEAD < n_tiles)) produce(Wn + RING_AHEAD);
         const Frags pre = first_frags(P1{}, kb, vb);
         Frags mid, none;
         step_manual(P1{}, T_{}, kb, vb, pre, mid);
@@ -612,16 +610,16 @@ __global__ __launch_bounds__(64 * fwd_waves(SHAPE), (fwd_queries(SHAPE) == 128 &
         window(P1{}, T_{}, W);
         W++;
     }
-    // ---- final window (W == n_tiles): softmax of the last block, the last two PVs; where the last tile has 32 keys at most, the PV of its first block
+    // ---- final window (W == n_tiles): the PV of the last tile's first block, then softmax and PV of its second, if it has a key.  (As two
+    // ways, each with its own copy of the first PV, 400 units of 48 tokens at head_dim 64 took 4.89 us instead of 4.75, 100 of 16 at head_dim 128 4.02 instead of 3.95.)
     {
         const char* vb = (W & 1u) ? vbuf0 : vbuf1;  // V tile W-1
+        apply_pending();
+        pv(vb, 0, preg[0]);
         if (tile0 * KT + (2u * W - 1u) * 32u < n_seq) {
-            step(F_{}, T_{}, P1{}, 2u * W - 1u, nullptr, vb);
+            softmax(P1{}, 2u * W - 1u);
             apply_pending();
             pv(vb, 1, preg[1]);
-        } else {
-            apply_pending();
-            pv(vb, 0, preg[0]);
         }
     }
 

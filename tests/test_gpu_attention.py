@@ -93,6 +93,27 @@ def test_peaky_and_shifted_logits():
     assert_close_bf16(to_np64(out), want, "peaky")
 
 
+@pytest.mark.parametrize("heads", [2, 60])
+@pytest.mark.parametrize("D", [64, 128])
+def test_maximum_grows_in_a_last_tile_of_few_keys(heads, D):
+    """715 keys: the last tile holds 11, masked in front of a pipelined step.  Their norm is eight times that of the others, so that the row sums pass the guard
+    there and the step is redone on a block that holds -inf; one row in two meets them with small logits and stays."""
+    import paper_2605_28691_amd as sk
+
+    N = 715
+    g = torch.Generator().manual_seed(heads + D)
+    q, k, v = (torch.randn((1, N, heads, D), generator=g) for _ in range(3))
+    k[:, N - 11 :] *= 8.0
+    q[:, ::2] *= 0.1
+    q, k, v = (t.to(torch.bfloat16) for t in (q, k, v))
+    scale = 2.0 * D ** -0.5
+    want = oracle.attention(*oracle_inputs(q, k, v), scale)
+    logits = (q[0, 1::2, 0].float() @ k[0, :, 0].float().t().contiguous()) * scale
+    assert (logits[:, N - 11 :].amax(dim=1) - logits[:, : N - 11].amax(dim=1)).max() > 16  # far above 2^16 of the old reference's 1
+    out = sk.dense_attn_fwd(*_gpu((q, k, v)), 1, 1, N, scale=scale)
+    assert_close_bf16(to_np64(out), want, "last tile")
+
+
 def test_run_to_run_determinism_and_canaries():
     import paper_2605_28691_amd as sk
 
