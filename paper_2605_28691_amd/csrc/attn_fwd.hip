@@ -239,20 +239,9 @@ __global__ __launch_bounds__(64 * fwd_waves(SHAPE), (fwd_queries(SHAPE) == 128 &
     auto issue_v = [&](char* buf, const RowOffs& o) __attribute__((always_inline)) { issue_tile(Vg, buf, o); };
     auto tile_landed = [&]() __attribute__((always_inline)) { asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); };
 
-    // ---- what the first window needs is asked for before anything else is formed: K tile 0, whose row offsets every wavefront finds for itself (lane = row) and
-    // hands round its lanes, then Q.  Through the ring, K waited for an evaluation of the map for every tile of the ring, a barrier and an LDS read.
-    auto own_offs = [&](uint32_t tile) __attribute__((always_inline)) -> RowOffs {
-        const uint32_t j = (tile0 + tile) * KT + lane;
-        const uint32_t mine = token_at(j < n_seq ? j : n_seq - 1u) * row_bytes;
-        RowOffs o;
-#pragma unroll
-        for (int i = 0; i < TL::IPW; i++) o.off[i] = (uint32_t)__shfl((int)mine, (int)st_row[i]) + st_cb[i];
-        return o;
-    };
-    RowOffs off_v = own_offs(0);  // offsets of the tile whose V is fetched next
-    issue_k(kbuf0, off_v);
-
-    // ---- Q fragments (B operand of S^T = K Q^T): lane = query lq, 8 consecutive channels starting at 16*ks + 8*h
+    // ---- what the first window needs is asked for before anything else is formed: Q, then K tile 0, whose offsets take two trips between the lanes.  (K first, 16
+    // units of 16, 64 and 160 tokens at head_dim 64 take 3.18, 3.82 and 4.89 us instead of 3.09, 3.72 and 4.80.)
+    // Q fragments (B operand of S^T = K Q^T): lane = query lq, 8 consecutive channels starting at 16*ks + 8*h
     const uint32_t jq = qt * BR + qw * 32u + lq;
     const bool q_valid = jq < n_seq;
     const uint32_t q_token = token_at(q_valid ? jq : n_seq - 1u);
@@ -265,6 +254,19 @@ __global__ __launch_bounds__(64 * fwd_waves(SHAPE), (fwd_queries(SHAPE) == 128 &
     } else {
         q_rows.issue(Qg, q_token, C, lane);
     }
+
+    // ---- K tile 0: every wavefront finds its row offsets for itself (lane = row) and hands them round its lanes.  Through the ring, K waited for an evaluation of
+    // the map for every tile of the ring, a barrier and an LDS read.
+    auto own_offs = [&](uint32_t tile) __attribute__((always_inline)) -> RowOffs {
+        const uint32_t j = (tile0 + tile) * KT + lane;
+        const uint32_t mine = token_at(j < n_seq ? j : n_seq - 1u) * row_bytes;
+        RowOffs o;
+#pragma unroll
+        for (int i = 0; i < TL::IPW; i++) o.off[i] = (uint32_t)__shfl((int)mine, (int)st_row[i]) + st_cb[i];
+        return o;
+    };
+    RowOffs off_v = own_offs(0);  // offsets of the tile whose V is fetched next
+    issue_k(kbuf0, off_v);
 
     // ---- running state: every lane tracks its own query (lanes l and l^32 hold the same m_ref; l_run is a partial sum)
     f32x16 oacc[QT][MT];
