@@ -575,8 +575,9 @@ __global__ __launch_bounds__(64 * fwd_waves(SHAPE), (fwd_queries(SHAPE) == 128 &
     }
     // ---- windows 1 .. n_tiles-1.  The parity of W selects the buffers at compile time.  The last one (MAY_END: windows that can be it) has no K tile to ask for,
     // and the block that it takes the exponentials of in its second step may hold keys past the end.  (As two steps of the generic kind, which waited for V's tile
-    // in front of their LDS reads, and with the softmax and PV of a last block that has no key, 48 units of 390 tokens took 12.13 us instead of 11.62.  Windows that
-    // can be the last form no offsets for a tile that does not exist: few units of 390 tokens 10.6 -> 10.2, of 520 11.5 -> 11.0.)
+    // in front of their LDS reads, and with the softmax and PV of a last block that has no key, 48 units of 390 tokens took 12.13 us instead of 11.62.  Offsets are
+    // formed for tiles past the last as well: with a test for them 48 units of 390 tokens took 11.34 us instead of 11.08, 200 of 300 21.7 instead of 21.4, and two
+    // groups the same.)
     auto window = [&](auto WP, auto MAY_END, uint32_t Wn) __attribute__((always_inline)) {
         constexpr int WPAR = decltype(WP)::value;  // Wn & 1
         char* const kb = WPAR ? kbuf1 : kbuf0;           // K tile Wn
@@ -590,7 +591,7 @@ __global__ __launch_bounds__(64 * fwd_waves(SHAPE), (fwd_queries(SHAPE) == 128 &
         // the L2 misses quadruple (measured: 2.4e8 instead of 5.7e7 per call, and 1.6 % more time); spreading the issues over the
         // MFMA groups is slower still (each issue stalls the wavefront).
         const RowOffs off_ahead = read_offs(Wn + 2u);
-        if (qw == (Wn & (uint32_t)(QW - 1)) && (!decltype(MAY_END)::value || Wn + RING_AHEAD < n_tiles)) produce(Wn + RING_AHEAD);
+        if (qw == (Wn & (uint32_t)(QW - 1))) produce(Wn + RING_AHEAD);
         const Frags pre = first_frags(P1{}, kb, vb);
         Frags mid, none;
         step_manual(P1{}, T_{}, kb, vb, pre, mid);
