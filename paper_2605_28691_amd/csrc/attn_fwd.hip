@@ -130,12 +130,21 @@ __device__ inline size_t scattered_row(const AttnArgs& a, uint32_t sb, uint32_t 
 constexpr int fwd_waves(int shape) { return shape == Q256 || shape == Q256_FULL || shape == Q128_SPLIT ? 8 : 4; }
 constexpr int fwd_groups(int shape) { return shape == Q64_SPLIT || shape == Q128_SPLIT ? 2 : 1; }
 constexpr int fwd_queries(int shape) { return 32 * fwd_waves(shape) / fwd_groups(shape) * ATTN_QT; }
+// Workgroups of a shape that its rule counts on a CU: the compiler is held to the registers that they leave each other (Q128 at head_dim 64: 168, of which 165
+// are in use; with a few more a third of the workgroups would wait while the rule still planned for them).  Where a workgroup was told that it has a SIMD's registers
+// to itself, Q64_SPLIT at head_dim 64, the accumulators went to accumulation registers and were copied: 16 units of 250 tokens 5.64 us, so 5.03, 3 of 1600 10.3 and 9.3.
+constexpr int fwd_per_cu(int D, int shape) {
+    const int of = shape == Q256_FULL ? Q256 : shape == Q128_FULL ? Q128 : shape;
+    for (const ShapeCost& c : D == 128 ? FWD_COST_128 : FWD_COST_64)
+        if (c.shape == of) return c.max_k;
+    return 1;
+}
 
 // PAD selects the any-resolution mode (Sec. 3.2), where the subsequences are those of the grid padded to multiples of s*s with the
 // padding masked: the kernel walks the real tokens of the class only (ClassMap), so that a masked key is one that is never met.  Only
 // the log-sum-exp is laid out over the padded grid (zero at the padding).
 template <int D, int SHAPE, bool PAD>
-__global__ __launch_bounds__(64 * fwd_waves(SHAPE), (fwd_queries(SHAPE) == 128 && fwd_groups(SHAPE) == 1 ? 2 : 1)) void attn_fwd_bf16_kernel(AttnArgs a, PadArg<PAD> pad_map, UnitMap units, uint32_t total, uint32_t per_xcd) {
+__global__ __launch_bounds__(64 * fwd_waves(SHAPE), fwd_waves(SHAPE) / 4 * fwd_per_cu(D, SHAPE)) void attn_fwd_bf16_kernel(AttnArgs a, PadArg<PAD> pad_map, UnitMap units, uint32_t total, uint32_t per_xcd) {
     constexpr int NW = fwd_waves(SHAPE), KG = fwd_groups(SHAPE);
     constexpr int QT = ATTN_QT;
     constexpr int QW = NW / KG;    // wavefronts of a key group: each owns 32 queries, all walk the same keys
