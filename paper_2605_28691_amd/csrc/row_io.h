@@ -34,7 +34,8 @@ struct RowDest {
 
 // acc * f, rounded to bf16, to dst + row offset: register 4*g + e of block mt is channel 32*mt + 8*g + 4*(lane/32) + e of row lane % 32.
 // buf: ROWS * CH * 2 bytes of LDS of the wavefront's own, 16-byte aligned.  Chunk c (8 channels) of row r lies at another position of the row, and with 64
-// channels its halves are exchanged in every other run of 8 rows, so that 16 lanes' 8-byte writes touch every bank once, as do the 16-byte reads.
+// channels its halves are exchanged in every other run of 8 rows, so that no two of 16 lanes
+// write to one bank, 8 bytes each, and 16 lanes' 16-byte reads touch every bank once.
 template <int CH, int ROWS, int BLOCKS>
 __device__ __attribute__((always_inline)) inline void store_rows(char* buf, const __attribute__((ext_vector_type(16))) float (&acc)[BLOCKS], float f, __bf16* dst, const RowDest<CH>& d, uint32_t lane) {
     static_assert(ROWS % RowDest<CH>::RPI == 0 && 32 % ROWS == 0 && BLOCKS * 32 % CH == 0, "whole passes");
@@ -46,6 +47,9 @@ __device__ __attribute__((always_inline)) inline void store_rows(char* buf, cons
     char* const wr = buf + (r & (uint32_t)(ROWS - 1)) * (2u * CH) + 8u * (CH == 64 ? h ^ (r >> 3 & 1u) : h);
     const char* const rd = buf + lane / LPR * (2u * CH) + ((lane % LPR) ^ swz(lane / LPR)) * 16u;
     __bf16* const out = dst + lane % LPR * 8u;
+    // other lanes may have read the region last; the wavefront's LDS accesses take effect in order, and the fences keep the compiler from exchanging them
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
 #pragma unroll
     for (int part = 0; part < 32 / ROWS; part++)
 #pragma unroll
@@ -59,7 +63,6 @@ __device__ __attribute__((always_inline)) inline void store_rows(char* buf, cons
                     *(bf16x4*)(wr + (((uint32_t)k ^ swz(r)) * 16u)) = o;
                 }
             }
-            // the wavefront's LDS accesses take effect in order; the fences keep the compiler from exchanging them
             __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
             __builtin_amdgcn_wave_barrier();
 #pragma unroll
@@ -142,7 +145,7 @@ struct RowLoad {
 };
 
 // of the 32 rows from `first`, those below n
-__device__ inline uint32_t rows_below(uint32_t first, uint32_t n) {
+__host__ __device__ inline uint32_t rows_below(uint32_t first, uint32_t n) {
     return first >= n ? 0u : n - first >= 32u ? ~0u : (1u << (n - first)) - 1u;
 }
 

@@ -3,7 +3,8 @@
 //      byte ii*1024 + 16*l) puts every (row, chunk) exactly once at row*RB + ((chunk ^ swz(row)) * 16);
 //   2. the fragment read addresses and the transposing read addresses the kernels use point at the chunks they mean;
 //   3. both kinds of read are free of bank conflicts (64 banks of 4 bytes; a 16-byte read is served 16 lanes at a time, an
-//      8-byte transposing read 32 lanes at a time).
+//      8-byte transposing read 32 lanes at a time);
+// and of which of a wavefront's 32 rows lie in a unit (rows_below() in row_io.h).
 // Built and run by tests/test_host_logic.py with hipcc (host pass only); prints "ok" or the first failure.
 #include <cstdio>
 #include <cstdlib>
@@ -14,6 +15,7 @@
 #include <hip/hip_runtime.h>
 
 #include "../paper_2605_28691_amd/csrc/lds_layout.h"
+#include "../paper_2605_28691_amd/csrc/row_io.h"
 
 using namespace skiparse;
 
@@ -133,8 +135,16 @@ static int check8() {
     return 0;
 }
 
+static int check_rows_below() {
+    for (uint32_t n : {0u, 1u, 15u, 31u, 32u, 33u, 63u, 64u, 65u, 400u, 0xffffffffu})
+        for (uint32_t first : {0u, 1u, 31u, 32u, 33u, 64u, 96u, 368u, 399u, 400u, 0xffffffe0u})
+            for (uint32_t r = 0; r < 32; r++)
+                if ((rows_below(first, n) >> r & 1u) != ((uint64_t)first + r < n)) return printf("row %u from %u of %u\n", r, first, n), 1;
+    return 0;
+}
+
 int main() {
-    if (check<128>() || check<64>() || check8<128>() || check8<64>()) return 1;
+    if (check<128>() || check<64>() || check8<128>() || check8<64>() || check_rows_below()) return 1;
     printf("ok\n");
     return 0;
 }
