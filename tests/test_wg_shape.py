@@ -175,8 +175,20 @@ def test_calls_timed_in_every_shape(pick, launch, D, calls, want):
 
 
 def test_row_store_tests_reach_their_kernels(pick):
-    """Every kind of kernel with a last workgroup of few rows, on both sides of the lines at which rows are moved directly."""
+    """Every kernel with every kind of remainder, and with a last workgroup of few rows, on both sides of the lines at which rows are moved directly."""
     import test_gpu_row_stores as rows
 
-    for launch, D, kernel, units, before in rows.FEW:
-        assert pick([dense(launch, D, units, before + n) for n in rows.FEW_ROWS]) == [kernel] * len(rows.FEW_ROWS), (launch, D, kernel)
+    for cases, last in ((rows.FEW, rows.FEW_ROWS), (rows.KERNELS, rows.LAST)):
+        for launch, D, kernel, units, before in cases:
+            assert pick([dense(launch, D, units, before + n) for n in last]) == [kernel] * len(last), (launch, D, kernel)
+    for launch, D, kernel, heads, W in rows.PADDED:
+        assert pick([(launch, D, 1, heads, 1, 3, W + more, 2, 0, 1) for more in rows.LINES]) == [kernel] * len(rows.LINES), (launch, D, kernel)
+    for D, kernel, heads, before in rows.LAYOUTS:
+        calls = [("fwd", D, 1, heads, 1, H, W, 2, group, 0) for n in rows.LAST for H, W, group in ((2, 2 * (before + n), 0), (4, before + 4 * n, 1))]
+        assert pick(calls[::2]) == [kernel] * len(rows.LAST) and kernel in pick(calls[1::2]), (D, kernel)
+    both = {(launch, D, shape) for launch in ("kernel",) for D in (64, 128) for shape in range(1, 7)} | {("bwd", D, shape) for D in (64, 128) for shape in range(5)}
+    assert {c[:3] for c in rows.KERNELS} == both
+    # (128 queries a workgroup of the dQ launch: at head_dim 128 no any-resolution call of this size)
+    assert {c[:3] for c in rows.PADDED} == {("fwd", D, shape) for D in (64, 128) for shape in range(1, 5)} | {("bwd", D, shape) for D in (64, 128) for shape in range(5)} - {("bwd", 128, 4)}
+    fp8 = [("fp8", D, 1, 3, 1, 3, W, 2, 0, 1) for D in (64, 128) for W in rows.POSITIONS]
+    assert pick(fp8[: len(fp8) // 2]).count(1) and pick(fp8[len(fp8) // 2 :]).count(1)
