@@ -669,8 +669,9 @@ __global__ __launch_bounds__(64 * fwd_waves(SHAPE), fwd_waves(SHAPE) / 4 * fwd_p
         const float w0 = m_ref[0] == m_new ? 1.0f : __builtin_amdgcn_exp2f((m_ref[0] - m_new) * c);
         const float w1 = mo == m_new ? 1.0f : __builtin_amdgcn_exp2f((mo - m_new) * c);
         m_ref[0] = m_new;
-        l_run[0] = l_run[0] * w0 + lo * w1;
-        auto take = [&](f32x16* x) __attribute__((always_inline)) {
+        l_run[0] = kg == 0 ? fmaf(l_run[0], w0, lo * w1) : fmaf(lo, w1, l_run[0] * w0);
+        // rounded as if the first group finished them all: a channel's bits do not depend on which group it falls to
+        auto take = [&](auto FIRSTC, f32x16* x) __attribute__((always_inline)) {
             const char* const src = pair_buf(kg ^ 1u) + lane * 16u;
 #pragma unroll
             for (int m = 0; m < MF; m++)
@@ -678,11 +679,11 @@ __global__ __launch_bounds__(64 * fwd_waves(SHAPE), fwd_waves(SHAPE) / 4 * fwd_p
                 for (int g = 0; g < 4; g++) {
                     const f32x4 o = *(const f32x4*)(src + (m * 4 + g) * 1024);
 #pragma unroll
-                    for (int e = 0; e < 4; e++) x[m][g * 4 + e] = x[m][g * 4 + e] * w0 + o[e] * w1;
+                    for (int e = 0; e < 4; e++) x[m][g * 4 + e] = decltype(FIRSTC)::value ? fmaf(o[e], w1, x[m][g * 4 + e] * w0) : fmaf(x[m][g * 4 + e], w0, o[e] * w1);
                 }
         };
-        if (kg == 0) take(oacc[0]);
-        else take(oacc[0] + MT - MF);
+        if (kg == 0) take(T_{}, oacc[0]);
+        else take(F_{}, oacc[0] + MT - MF);
     }
 
     // ---- epilogue: O = O^T / l, rounded to bf16; lane owns query lq, register r of block mt is channel 32*mt + 8*(r/4) + 4*h + r%4

@@ -137,6 +137,17 @@ def test_largest_probability_at_the_end_of_a_walk_is_not_rounded(at, heads, D):
     assert wrong <= 0.02 if at > 650 else (out.float() / want.float() - 1).abs().max() <= 2.0 ** -7, wrong
 
 
+@pytest.mark.parametrize("D,heads,N", [(64, 2, 715), (64, 40, 520), (128, 2, 715), (128, 40, 520)])
+def test_channels_of_two_key_groups_are_rounded_alike(D, heads, N):
+    """Each group finishes half of the channels: with the halves of v exchanged, those of the result are."""
+    import paper_2605_28691_amd as sk
+
+    g = torch.Generator(device="cuda").manual_seed(N)
+    q, k, v = (torch.randn((1, N, heads, D), generator=g, device="cuda").to(torch.bfloat16) for _ in range(3))
+    out = sk.dense_attn_fwd(q, k, v, 1, 1, N)
+    assert torch.equal(sk.dense_attn_fwd(q, k, v.roll(D // 2, dims=3), 1, 1, N), out.roll(D // 2, dims=3))
+
+
 def test_run_to_run_determinism_and_canaries():
     import paper_2605_28691_amd as sk
 
