@@ -77,7 +77,8 @@ __device__ __attribute__((always_inline)) inline void bwd_part(const BwdArgs& a,
     // waits only for its own operands (left to itself the compiler issues each read right before the MFMA that needs it).
     // The dK+dV part with the owners' V in LDS has almost no registers to spare: 1 group ahead in the first two products and 2 (8 wavefronts) or 3 (4) in the
     // last two is what fits without spilling into the MFMA chains.  160 units of 960 tokens, training step, us: 375 with 1 and 2, 366 with 1 and 3 or 4, 372 with
-    // 2 and 4; 48 of 400 40.3 / 39.85 / 40.1 / 40.5.  With 8 wavefronts deeper variants measured 2 to 14 % slower.
+    // 2 and 4; 48 of 400 40.3 / 39.85 / 40.1 / 40.5.  With 8 wavefronts 1 and 3 make no difference (48 units of 8190 tokens 6340 either way), and deeper variants
+    // measured 2 to 14 % slower.
     constexpr int AH_A = OWN2_LDS ? 1 : 4, AH_C = OWN2_LDS ? (NW == 4 ? 3 : 2) : 4;
     constexpr int TILE_BYTES = BT * RB;
     static_assert(IPW >= 1 && IPW * QW * RPI == BT, "a tile's instructions are spread evenly over the wavefronts");
@@ -520,8 +521,8 @@ __global__ __launch_bounds__(64 * NW, (NW == 4 ? 2 : 1)) void attn_bwd_kernel(Bw
 }
 
 // Both kinds in one launch.  At head_dim 128 with the owners' V in LDS, tiles of 32 rows leave room for two B128 workgroups on a CU (70 KiB each) and
-// for the two groups of B128_SPLIT; each kind fits 256 registers without a spill (3 to 5 values in B128_SPLIT).  48 units of 400 tokens: 35 us with the
-// launch that forms delta, against 43 in a launch of each kind, 160 of 960: 312 against 344 (605 TFLOP/s on the definition's five products).
+// for the two groups of B128_SPLIT; each kind fits 256 registers without a spill (4 or 5 values in B128_SPLIT).  48 units of 400 tokens: 30 us with the
+// launch that forms delta, 160 of 960: 290 (650 TFLOP/s on the definition's five products); 35 and 312 when it was compared with a launch of each kind, 43 and 344.
 constexpr int both_waves(int shape) { return shape == B128_SPLIT ? 8 : 4; }
 constexpr int both_groups(int shape) { return shape == B128 ? 1 : 2; }
 template <int D, int SHAPE, bool PAD>
@@ -543,7 +544,7 @@ __global__ __launch_bounds__(64 * both_waves(SHAPE), (SHAPE == B128 || (SHAPE ==
 }
 
 // delta = rowsum(dO o O) of every query, for the launch of both kinds.  A wavefront takes 16 rows of a unit, lane i finding row i, with all loads
-// in flight at once.  HBM-bound where it is not a launch's latency: 160 units of 960 tokens at head_dim 128 take 14 us of 312.
+// in flight at once.  HBM-bound where it is not a launch's latency: 160 units of 960 tokens at head_dim 128 take 13 us of 290.
 template <int D, bool PAD>
 __global__ __launch_bounds__(256) void attn_bwd_delta_kernel(BwdArgs a, PadArg<PAD> pad_map, UnitMap units, uint32_t total) {
     constexpr int CH = D / 8, RPI = 64 / CH, N = 16 / RPI;  // lanes a row, rows an instruction, instructions

@@ -26,7 +26,7 @@
 //     has; the common path computes no maximum at all.  The guard is the row sum: if 16 probabilities of a lane add up
 //     to 2^16 or more (always on the first block, where the reference is -inf) the wavefront takes a rare path that finds
 //     the true maximum, redoes the block against it and rescales l; O is rescaled at the start of the next step in a
-//     block that holds only the in-place multiplies.  Numerator and denominator always use the same reference, so the
+//     block that holds only the in-place multiplies.  In a walk's first and last windows the reference is raised from a growth of 2^8 on.  Numerator and denominator always use the same reference, so the
 //     result is exact up to rounding; probabilities up to 2^16 keep their relative precision in bf16, O and l are fp32.
 //   * K and V tiles of 64 keys go from global memory straight into LDS (global_load_lds_dwordx4, no staging registers,
 //     no LDS store instructions), double buffered, K one tile ahead of V (a window of two steps reads K tile W and V tile

@@ -84,14 +84,16 @@ enum FwdShape : int {
 
 // Costs fitted to 1200 calls timed in every shape, in turn and warm (1..640 units of 16..12,000 tokens), and held to the calls named below: the pick is 0.07 % above
 // the best shape on average at head_dim 128 (6 % at worst) and 0.04 % at head_dim 64 (5 %).  Against the fit to the kernels that stored their results in pieces,
-// whose ends and merges took longer, 0.978 and 0.985 of the time on average (0.84 at best; 1.004 and 1.044 at worst).  Measured, us, Q256 / Q128 / Q64_SPLIT /
+// whose ends and merges took longer, 0.978 and 0.985 of the time on average (0.84 at best; at worst 1.004, 10x1512 and 4x3293, and 1.044, 63x1574 at head_dim 64, which
+// moved from Q128 to Q256: 65.5 us against 62.7).  Since then Q64_SPLIT at head_dim 64 takes 0.88 to 0.92 of its time here, and the costs are as fitted.  Measured, us, Q256 / Q128 / Q64_SPLIT /
 // Q128_SPLIT at head_dim 128, units x tokens: 78x67 6.30 / 6.11 / 7.31 / 7.11, 10x1512 36.1 / 27.9 / 23.8 / 23.9, 69x1304 82.3 / 72.4 / 133 / 79.7, 4x3293 71.6 / 55.1 /
 // 43.7 / 43.9; 192x240, 34x900, 84x512, 48x960, 14x30240 and 20x20160 keep Q256.  At head_dim 64: 52x276 8.47 / 6.87 / 8.38 / 7.19, 10x3203 57 / 57 / 44 / 62, 100x4096
 // and 160x20160 keep Q128; 103x377 keeps Q256.
 //   * What a round costs depends on how full it is: a Q256 block takes 0.74 us with half of the CUs busy and 0.97 with all of them, the chip
-//     being at its power limit.  Without that the rule gave long sequences to Q128_SPLIT for a smaller last round: 14x30240 6025 us.
-//   * Two Q128 workgroups that start together on a CU wait for the same loads (`crowd`): 192x240 17.3 in that shape, 84x512 22.5.
-//   * Q64_SPLIT is for one round of its own: in a second one the traffic of four times the workgroups shows (34x900: 33.5).
+//     being at its power limit.  Without that the rule gave long sequences to Q128_SPLIT for a smaller last round.
+//   * Two Q128 workgroups that start together on a CU wait for the same loads (`crowd`).
+//   * Q64_SPLIT is for one round of its own: in a second one the traffic of four times the workgroups shows.
+//     (The earlier kernels, Q256 / the other one: 14x30240 5740 / 6025, 192x240 16.5 / 17.3, 84x512 21.3 / 22.5, 34x900 29 / 33.5.)
 //   * The split shapes stream K and V at two places and move 4 % more per MFMA; what they gain is idle CUs, so they are left out from two
 //     rounds of Q256 on.
 constexpr ShapeCost FWD_COST_128[] = {{Q256, 256, false, 1, 4.43f, 6.52f, 0.f, {0.742f, 0.967f}, 0.65f},
