@@ -85,7 +85,9 @@ enum FwdShape : int {
 // Costs fitted to 1200 calls timed in every shape, in turn and warm (1..640 units of 16..12,000 tokens), and held to the calls named below: the pick is 0.07 % above
 // the best shape on average at head_dim 128 (6 % at worst) and 0.04 % at head_dim 64 (5 %).  Against the fit to the kernels that stored their results in pieces,
 // whose ends and merges took longer, 0.978 and 0.985 of the time on average (0.84 at best; at worst 1.004, 10x1512 and 4x3293, and 1.044, 63x1574 at head_dim 64, which
-// moved from Q128 to Q256: 65.5 us against 62.7).  Since then Q64_SPLIT at head_dim 64 takes 0.88 to 0.92 of its time here, and the costs are as fitted.  Measured, us, Q256 / Q128 / Q64_SPLIT /
+// moved from Q128 to Q256: 65.5 us against 62.7).  Q64_SPLIT at
+// head_dim 64 has become 8 to 12 % faster since (fwd_per_cu() in attn_fwd.hip), and its row is fitted to 1000 calls timed anew: 0.24 % above the best on average and 11 %
+// at worst, where the old one was 0.54 and 30 % (3x5414 50.4 us in Q128_SPLIT, 41.6 in Q64_SPLIT).  Measured, us, Q256 / Q128 / Q64_SPLIT /
 // Q128_SPLIT at head_dim 128, units x tokens: 78x67 6.30 / 6.11 / 7.31 / 7.11, 10x1512 36.1 / 27.9 / 23.8 / 23.9, 69x1304 82.3 / 72.4 / 133 / 79.7, 4x3293 71.6 / 55.1 /
 // 43.7 / 43.9; 192x240, 34x900, 84x512, 48x960, 14x30240 and 20x20160 keep Q256.  At head_dim 64: 52x276 8.47 / 6.87 / 8.38 / 7.19, 10x3203 57 / 57 / 44 / 62, 100x4096
 // and 160x20160 keep Q128; 103x377 keeps Q256.
@@ -102,7 +104,7 @@ constexpr ShapeCost FWD_COST_128[] = {{Q256, 256, false, 1, 4.43f, 6.52f, 0.f, {
                                       {Q128_SPLIT, 128, true, 1, 6.50f, 14.55f, 0.f, {0.319f, 0.548f}}};
 constexpr ShapeCost FWD_COST_64[] = {{Q256, 256, false, 1, 2.44f, 6.90f, 0.f, {0.310f, 0.528f}},
                                      {Q128, 128, false, 3, 1.01f, 1.87f, 4.97f, {0.320f, 0.346f, 0.514f, 0.658f}},
-                                     {Q64_SPLIT, 64, true, 2, 2.24f, 0.71f, 0.98f, {0.146f, 0.182f, 0.268f}},
+                                     {Q64_SPLIT, 64, true, 2, 2.32f, 0.48f, 0.56f, {0.095f, 0.179f, 0.282f}},
                                      {Q128_SPLIT, 128, true, 1, 2.38f, 9.52f, 0.f, {0.179f, 0.251f}}};
 inline int pick_fwd_shape(int head_dim, const UnitSizes& u) {
     const auto& cost = head_dim == 128 ? FWD_COST_128 : FWD_COST_64;
