@@ -4,7 +4,8 @@
 // from there, an instruction of a wavefront writes 16 bytes to each of 32 rows, and the address unit takes such pieces one after the other.  So a wavefront
 // lays the channels down in LDS (a region of its own, no barrier) and stores whole 128-byte lines (64 where it has 32 channels), 8 rows an instruction.
 // Clocks of a workgroup from its last product until its stores have arrived, before -> after: 4 wavefronts at head_dim 128 (48 units of 390 tokens) 4990 ->
-// 2640, 8 (48 of 8190) 7510 -> 3400, dK and dV of 128 keys (48 of 400) 4950 -> 3070; two wavefronts a compute unit, where nothing queues, 1310 -> 1790.
+// 2640, 8 (48 of 8190) 7510 -> 3400, dK and dV of 128 keys (48 of 400) 4950 -> 3070; two wavefronts a compute unit, where nothing queues, 1310 -> 1790 (units
+// that short store their rows directly, see FWD_DIRECT_ROWS and BWD_DIRECT_ROWS).
 #pragma once
 #include <hip/hip_runtime.h>
 #include <stddef.h>
