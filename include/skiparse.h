@@ -141,7 +141,10 @@ int skiparse_attn_fwd_sparse(const void* q, const void* k, const void* v, void* 
  *   all inside every subsequence.  q, k, v, out, dout, dq, dk, dv: ORIGINAL layout [B][T*H*W][heads][head_dim] bf16; out and lse
  *   must be what skiparse_attn_fwd_lse produced for the same q, k, v, scale and flags.  P and dS are rounded to bf16 for the
  *   matrix products, accumulation is fp32, the gradients are rounded to bf16.  Deterministic (no atomics).
- *   workspace: skiparse_bwd_workspace_bytes() bytes of device memory (one float per position and head).
+ *   workspace: skiparse_bwd_workspace_bytes() bytes of device memory: one float per position and head (skiparse_lse_bytes()
+ *   rounded up to 256), and for large problems at head_dim 128 as much again as two bf16 tensors, in which the unfinished dq is
+ *   passed along workgroups (float32), so that all gradients take one walk.  Given the first part alone those problems are
+ *   computed by the kernels of the small ones, 1.03 to 1.19 times slower; the results differ in rounding only (about 4e-4 relative).
  *   No gradient buffer may overlap any other argument.  s = 1 gives the gradients of full attention.
  * flags: 0, or SKIPARSE_PAD for the any-resolution mode (Sec. 3.2; the paper trains at 720x1280, a grid that needs the padding):
  *   H and W arbitrary, positions j then run over the grid padded to multiples of s*s (lse of a padding position is 0), padding
@@ -159,8 +162,8 @@ int skiparse_attn_bwd(const void* q, const void* k, const void* v, const void* o
  * The backward pass for callers that cannot allocate device memory (code under HIP graph capture, tight serving or training
  * loops, harnesses that forbid hipMalloc): skiparse_attn_bwd with the delta workspace taken from a static device array inside the
  * library instead of a caller's buffer.  The call allocates nothing and frees nothing; inputs, outputs and results are exactly
- * those of skiparse_attn_bwd.
- *   Limit: the workspace the call would need (skiparse_bwd_workspace_bytes()) must not exceed SKIPARSE_STATIC_SCRATCH_BYTES
+ * those of skiparse_attn_bwd with a workspace of one float per position and head.
+ *   Limit: one float per position and head (skiparse_lse_bytes()) must not exceed SKIPARSE_STATIC_SCRATCH_BYTES
  *   (16 MiB = 4,194,304 positions x heads x subsequences; the 768P shape with 40 heads needs 12.9 MB); larger problems are
  *   rejected with SKIPARSE_EWORKSPACE and must use skiparse_attn_bwd.  Every GPU the library is used on holds the array until
  *   the process ends.

@@ -352,7 +352,8 @@ def skiparse_bwd_workspace_bytes(B, heads, T, H, W, D, s, pattern: str, pad: boo
 def skiparse_attn_bwd(q, k, v, out, dout, lse, T: int, H: int, W: int, s: int, pattern: str, scale: float = 0.0,
                       dq=None, dk=None, dv=None, workspace: torch.Tensor | None = None, pad: bool = False):
     """Gradients (dq, dk, dv) of the Skiparse attention layer; out and lse come from skiparse_attn_fwd_lse (same pad flag).  A
-    uint8 device workspace of skiparse_bwd_workspace_bytes() bytes is allocated with torch if none is passed."""
+    uint8 device workspace of skiparse_bwd_workspace_bytes() bytes is allocated with torch if none is passed; a smaller one, down to
+    one float per position and head, selects kernels that need no more (slower on large problems at head_dim 128)."""
     B, heads, D = _dims(q, T, H, W)
     dq = torch.empty_like(q) if dq is None else dq
     dk = torch.empty_like(q) if dk is None else dk

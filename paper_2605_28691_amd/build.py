@@ -12,7 +12,7 @@ import warnings
 HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libskiparse.so")
-SOURCES = ["api.hip", "permute.hip", "attn_fwd.hip", "attn_bwd.hip", "quant_fp8.hip", "attn_fwd_fp8.hip"]
+SOURCES = ["api.hip", "permute.hip", "attn_fwd.hip", "attn_bwd.hip", "attn_bwd_chain.hip", "quant_fp8.hip", "attn_fwd_fp8.hip"]
 MARSHAL = os.path.join(HERE, "_marshal" + sysconfig.get_config_var("EXT_SUFFIX"))  # found by the Python that it is built for
 PROBE_LIB = os.path.join(HERE, "libskiparse_probe.so")
 PROBE_SOURCES = ["mfma_probe.hip"]

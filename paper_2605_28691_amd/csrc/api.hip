@@ -359,8 +359,20 @@ int skiparse_attn_fwd_lse(const void* q, const void* k, const void* v, void* out
     return finish(launch_attn_bf16(a, (hipStream_t)stream));
 }
 
+// Whether the backward passes dQ along workgroups where it has the workspace for it, and what they share there.
+static bool bwd_chain(int B, int heads, int head_dim, const GridMap& g, bool pad, BwdChain* w) {
+    const UnitSizes u = unit_sizes(g, pad, (uint64_t)B * (uint32_t)heads);
+    if (!bwd_chain(head_dim, u)) return false;
+    *w = make_bwd_chain((uint32_t)B * (g.mode == MODE_DENSE ? 1u : (uint32_t)(g.s * g.s)) * (uint32_t)heads, u.n_max);
+    return true;
+}
+
 size_t skiparse_bwd_workspace_bytes(int B, int heads, int T, int H, int W, int head_dim, int s, int pattern, unsigned flags) {
-    return align256(skiparse_lse_bytes(B, heads, T, H, W, head_dim, s, pattern, flags));
+    const size_t delta = align256(skiparse_lse_bytes(B, heads, T, H, W, head_dim, s, pattern, flags));
+    if (delta == 0) return 0;
+    BwdChain w;
+    const bool pad = (flags & SKIPARSE_PAD) != 0 && s > 1;
+    return delta + (bwd_chain(B, heads, head_dim, make_gridmap(T, H, W, s, pattern, pad), pad, &w) ? w.bytes(head_dim) : 0);
 }
 
 // Shared by skiparse_attn_bwd (caller's workspace) and skiparse_attn_bwd_static (workspace == nullptr: the library's static scratch,
@@ -385,13 +397,20 @@ static int attn_bwd_common(const void* q, const void* k, const void* v, const vo
     for (void* y : outs)
         if (!y || misaligned(y)) return SKIPARSE_EINVAL;
     if (!lse || ((uintptr_t)lse & 3u)) return SKIPARSE_EINVAL;
-    const size_t need = align256(lse_bytes);
+    size_t need = align256(lse_bytes);
+    const GridMap g = make_gridmap(T, H, W, s, pattern, pad);
+    BwdChain chain;
+    const bool chained = !use_static && bwd_chain(B, heads, head_dim, g, pad, &chain) && workspace_bytes >= need + chain.bytes(head_dim);
     if (use_static) {
         if (need > STATIC_SCRATCH_BYTES) return SKIPARSE_EWORKSPACE;  // the problem is larger than the static scratch
         rc = static_scratch(&workspace);
         if (rc != SKIPARSE_OK) return rc;
     } else if (!workspace || workspace_bytes < need || misaligned(workspace)) {
         return SKIPARSE_EWORKSPACE;
+    }
+    if (chained) {
+        chain.place((char*)workspace + need);
+        need += chain.bytes(head_dim);
     }
     // no gradient may alias an input, another gradient, the log-sum-exp or the workspace
     for (int i = 0; i < 3; i++) {
@@ -411,8 +430,8 @@ static int attn_bwd_common(const void* q, const void* k, const void* v, const vo
     a.B = B; a.heads = heads; a.head_dim = head_dim;
     a.scale = scale > 0.f ? scale : 1.0f / sqrtf((float)head_dim);
     a.pad = pad;
-    a.g = make_gridmap(T, H, W, s, pattern, pad);
-    return finish(launch_attn_bwd_bf16(a, (hipStream_t)stream));
+    a.g = g;
+    return finish(chained ? launch_attn_bwd_chain(a, chain, (hipStream_t)stream) : launch_attn_bwd_bf16(a, (hipStream_t)stream));
 }
 
 int skiparse_attn_bwd(const void* q, const void* k, const void* v, const void* out, const void* dout, const float* lse, void* dq,

@@ -15,7 +15,8 @@
 // result is deterministic.  dK and dV share one walk (S and dP are formed once for both: 7 matrix products in all against the
 // 5 of the definition); their two accumulators take 128 registers at head_dim 128, so the owner's V rows are kept in LDS where two
 // wavefronts share a SIMD.
-//   * The large problems whose rounds of workgroups are full take a launch of each kind in workgroups of 256 owners, the least traffic per MFMA.
+// Large problems at head_dim 128 whose caller has the workspace for it are one walk instead (attn_bwd_chain.hip, five products).
+//   * Other large problems whose rounds of workgroups are full take a launch of each kind in workgroups of 256 owners, the least traffic per MFMA.
 //     All others take ONE launch in smaller workgroups, the dK+dV ones first: a launch of each kind leaves the chip half idle in its last
 //     round, which is the only one of a small problem, and two workgroups of different kinds on a CU overlap one's elementwise arithmetic
 //     with the other's MFMAs.  Few units walk the streamed rows in two groups of wavefronts, half each, that add their accumulators
@@ -545,17 +546,22 @@ __global__ __launch_bounds__(64 * both_waves(SHAPE), (SHAPE == B128 || (SHAPE ==
 
 // delta = rowsum(dO o O) of every query, for the launch of both kinds.  A wavefront takes 16 rows of a unit, lane i finding row i, with all loads
 // in flight at once.  HBM-bound where it is not a launch's latency: 160 units of 960 tokens at head_dim 128 take 13 us of 290.
-template <int D, bool PAD>
-__global__ __launch_bounds__(256) void attn_bwd_delta_kernel(BwdArgs a, PadArg<PAD> pad_map, UnitMap units, uint32_t total) {
+// CHAIN: for attn_bwd_chain.hip, what its steps start their products with instead, and its control words cleared.
+struct NoChain {};
+template <int D, bool PAD, typename Chain>
+__global__ __launch_bounds__(256) void attn_bwd_delta_kernel(BwdArgs a, PadArg<PAD> pad_map, UnitMap units, uint32_t total, Chain chain) {
+    constexpr bool CHAIN = std::is_same<Chain, BwdChain>::value;
     constexpr int CH = D / 8, RPI = 64 / CH, N = 16 / RPI;  // lanes a row, rows an instruction, instructions
     asm volatile("" ::SKIPARSE_ARG_UNITS(units), "s"(total), SKIPARSE_ARG_GRID(a.g), "s"(a.out), "s"(a.dout), "s"(a.delta), "s"(a.heads));
+    if constexpr (CHAIN)
+        for (uint32_t i = blockIdx.x * 256u + threadIdx.x; i < chain.n_ctl(); i += gridDim.x * 256u) chain.ctl[i] = 0u;
     const uint32_t lane = threadIdx.x & 63u, id = __builtin_amdgcn_readfirstlane(blockIdx.x * 4u + (threadIdx.x >> 6));
     if (id >= total) return;
     const UnitAt at_unit = units.at<false>(id);
     const uint32_t unit = at_unit.unit, j0 = at_unit.tile * 16u, head = at_unit.head, p = at_unit.p, q = at_unit.q, b0 = at_unit.b;
     const ClassMap cm = make_class_map(a.g, pad_map, p, q);
     const uint32_t n_seq = PAD ? cm.n : (uint32_t)a.g.n_sub;
-    if (j0 >= n_seq) return;
+    if (j0 >= (CHAIN ? (n_seq + CHAIN_STEP - 1u) / CHAIN_STEP * CHAIN_STEP : n_seq)) return;
     const uint32_t jl = j0 + (lane & 15u), jc = jl < n_seq ? jl : n_seq - 1u;
     const uint32_t tok = PAD ? src_token_real(a.g, cm, p, q, jc) : src_token(a.g, p, q, jc), at = PAD ? padded_position(a.g, cm, jc) : jc;
     const size_t C = (size_t)a.heads * D, base = (size_t)b0 * (uint32_t)a.g.n_tok * C + (size_t)head * D + lane % CH * 8u;
@@ -568,6 +574,7 @@ __global__ __launch_bounds__(256) void attn_bwd_delta_kernel(BwdArgs a, PadArg<P
         d[i] = *(const bf16x8*)(do_g + row);
     }
     float* delta_u = a.delta + (size_t)unit * (uint32_t)a.g.n_sub;
+    const float* lse_u = a.lse + (size_t)unit * (uint32_t)a.g.n_sub;
 #pragma unroll
     for (int i = 0; i < N; i++) {
         float sum = 0.f;
@@ -576,20 +583,41 @@ __global__ __launch_bounds__(256) void attn_bwd_delta_kernel(BwdArgs a, PadArg<P
 #pragma unroll
         for (int off = 1; off < CH; off <<= 1) sum += __shfl_xor(sum, off);
         const uint32_t r = i * RPI + lane / CH, pos = (uint32_t)__shfl((int)at, (int)r);
-        if (lane % CH == 0 && j0 + r < n_seq) delta_u[pos] = sum;
+        if constexpr (CHAIN) {
+            if (lane % CH == 0) {
+                const uint32_t j = j0 + r;
+                float* const at = chain.vals + ((size_t)unit * chain.n_steps + j / CHAIN_STEP) * (2u * CHAIN_STEP) + j % CHAIN_STEP;
+                at[0] = j < n_seq ? -lse_u[pos] * (1.0f / a.scale) : -INFINITY;
+                at[CHAIN_STEP] = j < n_seq ? -sum : 0.f;
+            }
+        } else if (lane % CH == 0 && j0 + r < n_seq) {
+            delta_u[pos] = sum;
+        }
     }
+}
+
+template <int D, bool PAD, typename Chain>
+static hipError_t launch_delta(const BwdArgs& a, uint32_t n_units, uint32_t n_rows, const Chain& chain, hipStream_t stream) {
+    const uint32_t d_tiles = (n_rows + 15u) / 16u;
+    const uint64_t waves = (uint64_t)n_units * d_tiles;
+    if (!fits_grid((waves + 3u) / 4u, 256u)) return hipErrorInvalidConfiguration;
+    PadArg<PAD> pad_map;
+    make_pad_arg(a.g, pad_map);
+    attn_bwd_delta_kernel<D, PAD, Chain><<<(uint32_t)((waves + 3u) / 4u), 256, 0, stream>>>(a, pad_map, make_unit_map<false>(a.g, d_tiles, (uint32_t)a.B, (uint32_t)a.heads), (uint32_t)waves, chain);
+    return hipGetLastError();
 }
 
 template <int D, int SHAPE, bool PAD>
 static hipError_t launch_both(const BwdArgs& a, uint32_t n_units, uint32_t n_max, hipStream_t stream) {
     constexpr uint32_t NW = both_waves(SHAPE), WGO = 32u * NW / both_groups(SHAPE);
-    const uint32_t o_tiles = (n_max + WGO - 1u) / WGO, d_tiles = (n_max + 15u) / 16u;
-    const uint64_t total = (uint64_t)n_units * o_tiles, waves = (uint64_t)n_units * d_tiles;
-    if (!fits_grid(total + 7u, 64u * NW) || !fits_grid((waves + 3u) / 4u, 256u)) return hipErrorInvalidConfiguration;
+    const uint32_t o_tiles = (n_max + WGO - 1u) / WGO;
+    const uint64_t total = (uint64_t)n_units * o_tiles;
+    if (!fits_grid(total + 7u, 64u * NW)) return hipErrorInvalidConfiguration;
     const uint32_t per_xcd = (uint32_t)((total + 7u) / 8u);
     PadArg<PAD> pad_map;
     make_pad_arg(a.g, pad_map);
-    attn_bwd_delta_kernel<D, PAD><<<(uint32_t)((waves + 3u) / 4u), 256, 0, stream>>>(a, pad_map, make_unit_map<false>(a.g, d_tiles, (uint32_t)a.B, (uint32_t)a.heads), (uint32_t)waves);
+    const hipError_t e = launch_delta<D, PAD>(a, n_units, n_max, NoChain{}, stream);
+    if (e != hipSuccess) return e;
     // a dimension of the grid for each kind: together they could fill one
     attn_bwd_both_kernel<D, SHAPE, PAD><<<dim3(8u * per_xcd, 2u), 64u * NW, 0, stream>>>(a, pad_map, make_unit_map<PAD>(a.g, o_tiles, (uint32_t)a.B, (uint32_t)a.heads), (uint32_t)total, per_xcd);
     return hipGetLastError();
@@ -610,8 +638,7 @@ static hipError_t launch_t(const BwdArgs& a, uint32_t n_units, uint32_t n_max, h
 
 template <int D, bool PAD>
 static hipError_t launch_all(const BwdArgs& a, hipStream_t stream) {
-    const uint32_t s2 = a.g.mode == MODE_DENSE ? 1u : (uint32_t)(a.g.s * a.g.s);
-    const uint32_t n_units = (uint32_t)a.B * s2 * (uint32_t)a.heads;
+    const uint32_t n_units = bwd_units(a);
     const UnitSizes u = unit_sizes(a.g, PAD, (uint64_t)a.B * (uint32_t)a.heads);
     const int shape = pick_bwd_shape(D, u);
     switch (shape) {
@@ -623,6 +650,10 @@ static hipError_t launch_all(const BwdArgs& a, hipStream_t stream) {
     // The dQ launch forms delta, which the second one reads.
     const hipError_t e = shape == TWO_LAUNCHES_DQ128 ? launch_t<D, BWD_DQ, 4, PAD>(a, n_units, u.n_max, stream) : launch_t<D, BWD_DQ, 8, PAD>(a, n_units, u.n_max, stream);
     return e != hipSuccess ? e : launch_t<D, BWD_DKV, 8, PAD>(a, n_units, u.n_max, stream);
+}
+
+hipError_t launch_bwd_chain_start(const BwdArgs& a, const BwdChain& w, hipStream_t stream) {
+    return a.pad ? launch_delta<128, true>(a, w.n_units, w.n_steps * CHAIN_STEP, w, stream) : launch_delta<128, false>(a, w.n_units, w.n_steps * CHAIN_STEP, w, stream);
 }
 
 hipError_t launch_attn_bwd_bf16(const BwdArgs& a, hipStream_t stream) {

@@ -1,0 +1,146 @@
+"""GPU: the backward in one walk, dQ passed along the workgroups of a unit, at sizes that the rule gives it to: units that end inside a step of 32 queries and inside a
+block of 256 keys, odd and even numbers of steps, both kinds of map, the any-resolution mode.  Against the gradients in float64 on sampled units, and on every unit
+against the kernels that it stands in for, which a workspace of one float per position and head selects.
+
+Tolerances: those of the bf16 backward (relative L2 1e-2, 3e-2 of the largest value) against float64.  Between the two paths P and dS differ by float32 rounding in
+front of their rounding to bf16, so that few of them round the other way: 4e-4 measured at 20,000 keys, 1e-3 allowed."""
+import pytest
+import torch
+
+import paper_2605_28691_amd as sk
+
+pytestmark = pytest.mark.gpu
+
+DENSE = [  # heads, N
+    (64, 2048),   # whole blocks and steps
+    (64, 2017),   # one query in the last step
+    (64, 2015),   # an odd number of steps
+    (224, 2049),  # one key in the last block
+    (512, 1000),  # many rounds of short walks
+]
+GRIDS = [  # B, heads, T, H, W, s, pattern, pad
+    (1, 16, 21, 32, 40, 2, "group", False),
+    (2, 8, 21, 30, 40, 2, "token", False),
+    (1, 16, 21, 33, 37, 2, "token", True),
+    (1, 16, 21, 33, 38, 2, "group", True),
+]
+CASES = [(1, heads, 1, 1, N, 1, "token", False) for heads, N in DENSE] + GRIDS
+
+
+def _delta_only(lse):
+    """A workspace of one float per position and head."""
+    return torch.empty((lse.numel() * 4 + 255) // 256 * 256, dtype=torch.uint8, device="cuda")
+
+
+def _inputs(B, heads, T, H, W, s, pattern, pad, seed=1):
+    gen = torch.Generator(device="cuda").manual_seed(seed)
+    q, k, v, dout = (torch.randn((B, T * H * W, heads, 128), generator=gen, device="cuda").to(torch.bfloat16) for _ in range(4))
+    out, lse = sk.skiparse_attn_fwd_lse(q, k, v, T, H, W, s, pattern, pad=pad)
+    assert sk.skiparse_bwd_workspace_bytes(B, heads, T, H, W, 128, s, pattern, pad) > _delta_only(lse).numel()  # one walk
+    return q, k, v, out, dout, lse
+
+
+def _rows(T, H, W, s, pattern, p, q):
+    step = s if pattern == "group" else 1
+    n = torch.arange(T * H * W, device="cuda").view(T, H, W)
+    return n[:, torch.arange(H, device="cuda") // step % s == p][:, :, torch.arange(W, device="cuda") // step % s == q].reshape(-1)
+
+
+def _float64(q, k, v, dout):
+    kt, vt = k.t().contiguous(), v.t().contiguous()
+    scale = q.shape[1] ** -0.5
+    prob = torch.softmax((q @ kt) * scale, dim=1)
+    ds = prob * (dout @ vt - (dout * (prob @ v)).sum(dim=1, keepdim=True))
+    return (ds @ k) * scale, (ds.t().contiguous() @ q) * scale, prob.t().contiguous() @ dout
+
+
+@pytest.mark.parametrize("B,heads,T,H,W,s,pattern,pad", CASES)
+def test_one_walk_gives_the_gradients(B, heads, T, H, W, s, pattern, pad):
+    q, k, v, out, dout, lse = _inputs(B, heads, T, H, W, s, pattern, pad)
+    at = (T, H, W, s, pattern)
+    before = sk.skiparse_attn_bwd(q, k, v, out, dout, lse, *at, pad=pad, workspace=_delta_only(lse))
+    work = torch.full((sk.skiparse_bwd_workspace_bytes(B, heads, T, H, W, 128, s, pattern, pad),), 0xFF, dtype=torch.uint8, device="cuda")  # NaN and huge counts
+    guard = 4096
+    buf = torch.full((3, q.numel() + 2 * guard), float("nan"), dtype=torch.bfloat16, device="cuda")
+    got = [b[guard:-guard].view(q.shape) for b in buf]
+    for _ in range(2):  # the second call finds the first one's workspace
+        sk.skiparse_attn_bwd(q, k, v, out, dout, lse, *at, pad=pad, workspace=work, dq=got[0], dk=got[1], dv=got[2])
+        assert torch.isnan(buf[:, :guard]).all() and torch.isnan(buf[:, -guard:]).all()
+        for g, b, name in zip(got, before, ("dq", "dk", "dv")):
+            diff = (g.float() - b.float()).pow(2).sum(dim=(1, 3)).sqrt() / b.float().pow(2).sum(dim=(1, 3)).sqrt()
+            assert float(diff.max()) <= 1e-3, f"{name}: {float(diff.max()):.2e}"
+    again = sk.skiparse_attn_bwd(q, k, v, out, dout, lse, *at, pad=pad)
+    assert all(torch.equal(a, g) for a, g in zip(again, got))
+    for b, h, p in ((0, 0, 0), (B - 1, heads - 1, s - 1)):
+        rows = _rows(T, H, W, s, pattern, p, p)
+        want = _float64(*(t[b, rows, h].double() for t in (q, k, v, dout)))
+        for g, ref, name in zip(got, want, ("dq", "dk", "dv")):
+            d = g[b, rows, h].double() - ref
+            assert float(d.norm() / ref.norm()) <= 1e-2 and float(d.abs().max() / ref.abs().max()) <= 3e-2, name
+
+
+def test_static_scratch_gives_what_a_workspace_of_its_size_gives():
+    q, k, v, out, dout, lse = _inputs(*GRIDS[0])
+    at = GRIDS[0][2:7]
+    want = sk.skiparse_attn_bwd(q, k, v, out, dout, lse, *at, workspace=_delta_only(lse))
+    got = tuple(torch.full_like(q, float("nan")) for _ in range(3))
+    sk.skiparse_attn_bwd_static(q, k, v, out, dout, lse, *got, *at)
+    assert all(torch.equal(a, b) for a, b in zip(got, want))
+
+
+def test_two_streams_with_workspaces_of_their_own():
+    """Workgroups of either call may hold CUs that the other one waits for."""
+    sets = [_inputs(*GRIDS[0], seed=1), _inputs(*GRIDS[2], seed=2)]
+    calls = [(GRIDS[0][2:7], False), (GRIDS[2][2:7], True)]
+    want = [sk.skiparse_attn_bwd(*x, *at, pad=pad) for x, (at, pad) in zip(sets, calls)]
+    torch.cuda.synchronize()
+    streams = [torch.cuda.Stream() for _ in sets]
+    got = [None, None]
+    for _ in range(3):
+        for i, (x, (at, pad)) in enumerate(zip(sets, calls)):
+            with torch.cuda.stream(streams[i]):
+                got[i] = sk.skiparse_attn_bwd(*x, *at, pad=pad)
+        torch.cuda.synchronize()
+        for g, w in zip(got, want):
+            assert all(torch.equal(a, b) for a, b in zip(g, w))
+
+
+def test_replayed_from_a_graph():
+    q, k, v, out, dout, lse = _inputs(1, 64, 1, 1, 2017, 1, "token", False)
+    at = (1, 1, 2017, 1, "token")
+    work = torch.empty(sk.skiparse_bwd_workspace_bytes(1, 64, 1, 1, 2017, 128, 1, "token"), dtype=torch.uint8, device="cuda")
+    grads = [torch.empty_like(q) for _ in range(3)]
+
+    def step():
+        sk.skiparse_attn_fwd_lse(q, k, v, *at, out=out, lse=lse)
+        sk.skiparse_attn_bwd(q, k, v, out, dout, lse, *at, workspace=work, dq=grads[0], dk=grads[1], dv=grads[2])
+
+    step()
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        step()
+    for trial in range(3):
+        gen = torch.Generator(device="cuda").manual_seed(10 + trial)
+        for t in (q, k, v, dout):
+            t.copy_(torch.randn(t.shape, generator=gen, device="cuda"))
+        for t in grads:
+            t.fill_(float("nan"))
+        graph.replay()
+        torch.cuda.synchronize()
+        got = [t.clone() for t in grads]
+        o2, l2 = sk.skiparse_attn_fwd_lse(q, k, v, *at)
+        want = sk.skiparse_attn_bwd(q, k, v, o2, dout, l2, *at)
+        torch.cuda.synchronize()
+        assert all(torch.equal(a, b) for a, b in zip(got, want)), trial
+
+
+@pytest.mark.parametrize("heads,N", [(101, 4737), (48, 8190)])
+def test_launches_of_one_kind_still_serve_small_workspaces(heads, N):
+    """The kernels of 256 and of 128 queries a workgroup in a launch of their own, which one walk has replaced where there is room for it."""
+    q, k, v, out, dout, lse = _inputs(1, heads, 1, 1, N, 1, "token", False)
+    got = sk.skiparse_attn_bwd(q, k, v, out, dout, lse, 1, 1, N, 1, "token", workspace=_delta_only(lse))
+    for h in (0, heads - 1):
+        want = _float64(*(t[0, :, h].double() for t in (q, k, v, dout)))
+        for g, ref, name in zip(got, want, ("dq", "dk", "dv")):
+            assert float((g[0, :, h].double() - ref).norm() / ref.norm()) <= 1e-2, name
