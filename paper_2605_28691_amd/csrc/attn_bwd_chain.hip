@@ -6,14 +6,16 @@
 // products over its own 256 keys, and leaves them for workgroup i+1; the last one rounds them to bf16 into dq.  No atomics on the sums and one order, that of
 // the keys: the result is deterministic.
 //   * Why: at 160 units of 20,160 tokens the two launches took 41 ms (dQ) and 58 (dK+dV) of matrix products at the board's power limit, a quarter of them S and dP
-//     formed a second time; one walk takes 85 (976 TFLOP/s on the definition), 48 units of 8190 tokens 4.28 instead of 4.95.
+//     formed a second time; one walk takes 82 (1010 TFLOP/s on the definition), 48 units of 8190 tokens 4.15 instead of 4.95, 160 of 960 0.27 instead of 0.28.
 //   * What bounds it: a step takes about 4700 clocks at 1.77 GHz (the power limit; 2.1 at the same step count before the waits below were gone), 2560 of which are the
-//     80 products of a SIMD; LDS reads take half of the clocks, and 200 to 300 are waits for the workgroup in front.  Without the sums' way through memory 74.7 ms.
+//     80 products of a SIMD; LDS reads take half of the clocks, and some 200 are waits for the workgroup in front.  Without the sums' way through memory 74.7 ms.
 //   * A unit's workgroups run on ONE XCD, whose L2 the sums pass through: workgroups take their work from a queue of the XCD that they find themselves on, so
 //     that no placement is assumed.  A store is there for the XCD's other CUs once vmcnt says so (the vector L1 writes through); the reader's loads go past its own
 //     L1.  Of 130 GB of sums about a quarter leave the L2 before they are read.
 //   * The sums are asked for between the products of dV of the step before, and used in the first products of the next: the loads are not waited for, and the flag
-//     that allows them (progress of the workgroup in front, published after each second step) was asked for at that step's start.
+//     that allows them was asked for at that step's start.  A wavefront follows the one with its number in the workgroup in front, which says so itself when its
+//     stores have arrived, half a step after them: one flag a workgroup, behind the step's barrier, left the next one further behind and made it wait for the slowest
+//     wavefront (64 units of 3000 tokens 904 us instead of 801, 48 of 8190 4210 instead of 4110).
 //   * LDS, 147 KiB: K of the owners (B operand of S for their wavefront, A operand of dQ for all), two steps of Q and dO, three of dS.  dQ of two steps is formed at
 //     once, so that each of the 8 wavefronts has a tile of 32 queries x 32 channels and all have the same work: half of the wavefronts each step, in turn,
 //     left the others waiting at the barrier (5300 clocks a step instead of 4660).
@@ -170,7 +172,7 @@ __device__ __attribute__((always_inline)) inline void chain_task(const BwdArgs& 
     // ---- the chain: sums of step t of this unit, 16 KiB: [channel block][register / 4][lane][4]
     const uint32_t cb = wave & 3u, half = wave >> 2;
     float* const part_u = w.part + (size_t)at_unit.unit * w.n_steps * (STEP * D);
-    uint32_t* const done = w.ctl + CHAIN_SLOTS + CHAIN_XCCS * (w.n_units + 1u) + lin;  // steps that this workgroup has left; [-1]: that the one before it has
+    uint32_t* const done = w.ctl + CHAIN_SLOTS + CHAIN_XCCS * (w.n_units + 1u) + lin * CHAIN_FLAGS + wave;  // steps that this wavefront has left; [-CHAIN_FLAGS]: that of the workgroup before
     uint32_t seen = 0;
     bool lost = false;
     auto wait_for = [&](uint32_t steps) __attribute__((always_inline)) {
@@ -178,7 +180,7 @@ __device__ __attribute__((always_inline)) inline void chain_task(const BwdArgs& 
 #pragma unroll 1
         while (have < steps && !lost) {
             __builtin_amdgcn_s_sleep(1);
-            seen = __hip_atomic_load(done - 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            seen = __hip_atomic_load(done - CHAIN_FLAGS, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
             have = __builtin_amdgcn_readfirstlane(seen);
             lost = ++tries >= MOST_TRIES;
         }
@@ -276,7 +278,7 @@ __device__ __attribute__((always_inline)) inline void chain_task(const BwdArgs& 
         off_next = read_offs(t + 2u);
         if (PARITY == 0 && wave == (t / 2u & (uint32_t)(NW - 1))) produce(t / 2u + RING_AHEAD);
         if (more) issue_tile(t + 1u, off_now, PARITY ? lds.q0 : lds.q1, PARITY ? lds.do0 : lds.do1, PARITY ? lds.vals0 : lds.vals1);
-        if ((PARITY == 1 || !more) && !first) seen = __hip_atomic_load(done - 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        if ((PARITY == 1 || !more) && !first) seen = __hip_atomic_load(done - CHAIN_FLAGS, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         if (PARITY == 0 && t != 0u) pass_on(t - 2u + half, lds.ds + (half ? ds_behind(ds_at) : ds_ahead(ds_at)));
         f32x16 m1, m2;
 #pragma unroll
@@ -348,15 +350,18 @@ __device__ __attribute__((always_inline)) inline void chain_task(const BwdArgs& 
             }
             __builtin_amdgcn_sched_barrier(0);
             if (cidx == MT - 1) {
+                if (PARITY == 0 && t != 0u) {
+                    landed();  // the sums that this wavefront has left, half a step ago
+                    if (lane == 0u) __hip_atomic_store(done, t, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                }
                 asm volatile("" : "=v"(x));  // not the sums that have left
                 if (PARITY == 1) take_sums(t - 1u + half, t + 1u);
                 else if (!more && half == 0u) take_sums(t, t + 1u);
                 __builtin_amdgcn_sched_barrier(0);
             }
         }
-        landed();  // the next step's rows, and the sums that this wavefront has left
+        landed();  // the next step's rows
         __syncthreads();
-        if (PARITY == 0 && tid == 0u) __hip_atomic_store(done, t, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         ds_at = ds_ahead(ds_at);
     };
     using P0 = std::integral_constant<int, 0>;
@@ -374,8 +379,8 @@ __device__ __attribute__((always_inline)) inline void chain_task(const BwdArgs& 
         pass_on(n_t - 2u + half, lds.ds + (half ? ds_behind(ds_at) : ds_ahead(ds_at)));
     }
     landed();
+    if (lane == 0u) __hip_atomic_store(done, n_t, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     __syncthreads();
-    if (tid == 0u) __hip_atomic_store(done, n_t, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 
     const uint32_t stored = rows_below(ot * (uint32_t)OWNERS + wave * 32u, n_seq);
     if (stored == 0u) return;

@@ -91,7 +91,8 @@ hipError_t launch_attn_bwd_bf16(const BwdArgs& a, hipStream_t stream);
 // The same gradients in one walk that passes dQ along the workgroups of a unit (attn_bwd_chain.hip): what they share in the workspace.
 constexpr uint32_t CHAIN_XCCS = 16;  // values of the XCC number
 // ctl: a ticket counter of every XCC, 128 bytes apart; how many groups of units are taken; every XCC's groups, 0 where not taken yet, else number + 1; every
-// workgroup's progress
+// wavefront's progress
+constexpr uint32_t CHAIN_FLAGS = 8;  // wavefronts of a workgroup
 constexpr uint32_t CHAIN_NEXT = 32u * CHAIN_XCCS, CHAIN_SLOTS = CHAIN_NEXT + 32u;
 struct BwdChain {
     uint32_t* ctl;      // cleared by the launch that forms delta
@@ -99,7 +100,7 @@ struct BwdChain {
     float* part;        // [unit][step][32 queries x head_dim] sums of dQ
     uint32_t n_units, n_blk, n_steps;              // blocks of keys and steps of the largest unit
     uint32_t together, per_group, n_groups;        // units handed out together, their blocks, and how many times
-    __host__ __device__ uint32_t n_ctl() const { return CHAIN_SLOTS + CHAIN_XCCS * (n_units + 1u) + n_units * n_blk; }
+    __host__ __device__ uint32_t n_ctl() const { return CHAIN_SLOTS + CHAIN_XCCS * (n_units + 1u) + n_units * n_blk * CHAIN_FLAGS; }
     size_t ctl_bytes() const { return ((size_t)n_ctl() * 4u + 255u) & ~(size_t)255u; }
     size_t vals_bytes() const { return (size_t)n_units * n_steps * CHAIN_STEP * 8u; }
     size_t bytes(int head_dim) const { return ctl_bytes() + vals_bytes() + (size_t)n_units * n_steps * CHAIN_STEP * (uint32_t)head_dim * 4u; }
@@ -114,7 +115,7 @@ inline BwdChain make_bwd_chain(uint32_t n_units, uint32_t n_max) {
     w.n_units = n_units;
     w.n_blk = (n_max + CHAIN_OWNERS - 1u) / CHAIN_OWNERS;
     w.n_steps = (n_max + CHAIN_STEP - 1u) / CHAIN_STEP;
-    w.together = chain_together(n_units);
+    w.together = chain_together(n_units, n_max);
     w.per_group = w.together * w.n_blk;
     w.n_groups = (n_units + w.together - 1u) / w.together;
     return w;

@@ -188,31 +188,25 @@ inline int pick_bwd_shape(int head_dim, const UnitSizes& u) {
 
 // ---- all gradients in one walk, dQ passed along a unit's workgroups (attn_bwd_chain.hip)
 constexpr uint32_t XCDS = 8, CHAIN_OWNERS = 256, CHAIN_STEP = 32;  // keys of a workgroup, queries of a step
-// Units handed to an XCD at a time, whose workgroups take turns on its CUs.  One unit at a time makes a chain of 32 workgroups, each of which starts behind the one
-// before it and waits where that one was late; many units at a time find less in the L2.  160 units of 20,160 tokens (20 an XCD), ms, by 1, 2, 4 and 10: 90.6, 89.3,
-// 86.2, 96.5 (the last in an earlier state, in which 4 took 95.4).  Of 1 to 4 the number that leaves the busiest XCD the fewest units, or the larger one.
-inline uint32_t chain_together(uint64_t units) {
-    uint32_t best = 1u;
-    uint64_t least = ~0ull;
-    for (uint32_t n = 1; n <= 4u; n++) {
-        const uint64_t longest = ((units + n - 1u) / n + XCDS - 1u) / XCDS * n;
-        if (longest <= least) {
-            best = n;
-            least = longest;
-        }
-    }
-    return best;
+// Units handed to an XCD at a time, whose workgroups take turns on its CUs.  One unit makes a chain of 32 workgroups, each of which starts behind the one before it
+// and waits where that one was late; of several less is found in the L2, which long walks pay for.  us, by 1 / 2 / 4, units x tokens: 64x3000 830 / 810 / 776,
+// 160x4200 3964 / 3965 / 3887, 160x6000 7609 / 7642 / 7619, 48x8190 4221 / 4152 / 5239 (6 units an XCD), 64x12000 12,359 / 11,958 / 12,226, 160x12000 29,202 / 29,180 /
+// 30,213, 32x20160 16,521 / 17,005 / 16,963, 160x20160 82,409 / 83,608 / 84,902.  Never so many that the busiest XCD has more units than by one.
+inline uint32_t chain_together(uint64_t units, uint32_t n_max) {
+    const uint64_t least = (units + XCDS - 1u) / XCDS;
+    for (uint32_t n = n_max >= 16000u ? 1u : n_max >= 7000u ? 2u : 4u; n > 1u; n--)
+        if (((units + n - 1u) / n + XCDS - 1u) / XCDS * n == least) return n;
+    return 1u;
 }
-// An XCD's CUs take its units' workgroups in rounds.  Where those are largely filled, and there are two or more of long walks, or many, one walk takes 0.84 to 0.97 of
-// what the shapes above take: measured at 140 sizes, us, those -> one walk, units x tokens: 160x20160 99,590 -> 85,200, 48x8190 4950 -> 4280, 64x7960 6450 -> 5430,
-// 480x960 898 -> 793, 40x2857 574 -> 559; the other way 160x960 288 -> 298, 32x4098 (0.67 filled) 941 -> 978, 20x20160 (0.77) 13,106 -> 13,469, 8x8190 (one
-// round) 816 -> 859, 64x1827 394 -> 394.
+// An XCD's CUs take its units' workgroups in rounds.  Two rounds or more, three quarters full, take 0.79 to 0.99 of the time of the shapes above, if a chain is not
+// 32 workgroups on a short walk.  Measured at 220 sizes, us, those -> one walk, units x tokens: 160x20160 99,590 -> 82,400, 48x8190 4950 -> 4150, 160x2048 and
+// 320x1921 0.79 of the time, 480x960 898 -> 746, 64x3000 934 -> 776, 80x2396 0.95, 160x921 0.99; the other way 12x20064 (0.74 full) 1.03, 48x1780
+// (0.65) 1.02, 40x2048 (0.63) 1.13, 40x2991 (chains of 32) 1.07, 24x2432 (one round) 1.01.
 inline bool bwd_chain(int head_dim, const UnitSizes& u) {
     if (head_dim != 128 || u.units == 0) return false;
-    const uint64_t together = chain_together(u.units), longest = ((u.units + together - 1u) / together + XCDS - 1u) / XCDS * together;
-    const uint64_t rounds = (longest * ((u.n_max + CHAIN_OWNERS - 1u) / CHAIN_OWNERS) + CUS / XCDS - 1u) / (CUS / XCDS);
+    const uint64_t rounds = ((u.units + XCDS - 1u) / XCDS * ((u.n_max + CHAIN_OWNERS - 1u) / CHAIN_OWNERS) + CUS / XCDS - 1u) / (CUS / XCDS);
     const double fill = (double)u.units * 0.5 * ((double)u.n_max + (double)u.n_min) / ((double)CHAIN_OWNERS * (double)(CUS * rounds));
-    return fill >= 0.86 && ((rounds >= 2u && u.n_max >= 2000u) || (rounds >= 8u && u.n_max >= 900u));
+    return fill >= 0.75 && rounds >= 2u && u.n_max >= 900u && (u.n_max >= 4000u || chain_together(u.units, u.n_max) > 1u);
 }
 
 // ---- 8-bit attention, any-resolution mode: do most tiles of 64 positions hold padding, on a walk of enough tiles?  Where the columns are padded every line
