@@ -144,7 +144,7 @@ int skiparse_attn_fwd_sparse(const void* q, const void* k, const void* v, void* 
  *   workspace: skiparse_bwd_workspace_bytes() bytes of device memory: one float per position and head (skiparse_lse_bytes()
  *   rounded up to 256), and for large problems at head_dim 128 as much again as two bf16 tensors, in which the unfinished dq is
  *   passed along workgroups (float32), so that all gradients take one walk.  Given the first part alone those problems are
- *   computed by the kernels of the small ones, 1.01 to 1.27 times slower; the results differ in rounding only (about 4e-4 relative).
+ *   computed by the kernels of the small ones, 1.02 to 1.22 times slower; the results differ in rounding only (about 4e-4 relative).
  *   No gradient buffer may overlap any other argument.  s = 1 gives the gradients of full attention.
  * flags: 0, or SKIPARSE_PAD for the any-resolution mode (Sec. 3.2; the paper trains at 720x1280, a grid that needs the padding):
  *   H and W arbitrary, positions j then run over the grid padded to multiples of s*s (lse of a padding position is 0), padding

@@ -6,7 +6,7 @@
 // products over its own 256 keys, and leaves them for workgroup i+1; the last one rounds them to bf16 into dq.  No atomics on the sums and one order, that of
 // the keys: the result is deterministic.
 //   * Why: at 160 units of 20,160 tokens the two launches took 41 ms (dQ) and 58 (dK+dV) of matrix products at the board's power limit, a quarter of them S and dP
-//     formed a second time; one walk takes 82 (1010 TFLOP/s on the definition), 48 units of 8190 tokens 4.15 instead of 4.95, 160 of 960 0.27 instead of 0.28.
+//     formed a second time; one walk takes 81 (1030 TFLOP/s on the definition), 48 units of 8190 tokens 4.1 instead of 4.8.
 //   * What bounds it: a step takes about 4700 clocks at 1.77 GHz (the power limit; 2.1 at the same step count before the waits below were gone), 2560 of which are the
 //     80 products of a SIMD; LDS reads take half of the clocks, and some 200 are waits for the workgroup in front.  Without the sums' way through memory 74.7 ms.
 //   * A unit's workgroups run on ONE XCD, whose L2 the sums pass through: workgroups take their work from a queue of the XCD that they find themselves on, so

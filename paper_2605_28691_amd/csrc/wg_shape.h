@@ -198,15 +198,16 @@ inline uint32_t chain_together(uint64_t units, uint32_t n_max) {
         if (((units + n - 1u) / n + XCDS - 1u) / XCDS * n == least) return n;
     return 1u;
 }
-// An XCD's CUs take its units' workgroups in rounds.  Two rounds or more, three quarters full, take 0.79 to 0.99 of the time of the shapes above, if a chain is not
-// 32 workgroups on a short walk.  Measured at 220 sizes, us, those -> one walk, units x tokens: 160x20160 99,590 -> 82,400, 48x8190 4950 -> 4150, 160x2048 and
-// 320x1921 0.79 of the time, 480x960 898 -> 746, 64x3000 934 -> 776, 80x2396 0.95, 160x921 0.99; the other way 12x20064 (0.74 full) 1.03, 48x1780
-// (0.65) 1.02, 40x2048 (0.63) 1.13, 40x2991 (chains of 32) 1.07, 24x2432 (one round) 1.01.
+// An XCD's CUs take its units' workgroups in rounds.  Two rounds or more that are largely filled take 0.84 to 0.98 of the time of the shapes above; chains of 32
+// workgroups want longer walks.  Measured at 200 sizes, units x tokens: 160x20160 98.2 -> 80.6 ms, 48x8190 4817 -> 4092 us, 480x960 (0.88 full) 0.89 of the time,
+// 64x2907 0.87, 48x4200 (0.77) 0.95, 64x2315 (0.75) 0.96; the other way 12x8116 (0.74) 1.09, 48x3000 (0.73) 1.03, 160x1017 (0.83) 1.02, 20x20160 (0.77, chains of 32)
+// 1.04, 40x3000 (0.92, chains of 32) 1.13, 24x2343 (one round) 1.03.
 inline bool bwd_chain(int head_dim, const UnitSizes& u) {
     if (head_dim != 128 || u.units == 0) return false;
     const uint64_t rounds = ((u.units + XCDS - 1u) / XCDS * ((u.n_max + CHAIN_OWNERS - 1u) / CHAIN_OWNERS) + CUS / XCDS - 1u) / (CUS / XCDS);
     const double fill = (double)u.units * 0.5 * ((double)u.n_max + (double)u.n_min) / ((double)CHAIN_OWNERS * (double)(CUS * rounds));
-    return fill >= 0.75 && rounds >= 2u && u.n_max >= 900u && (u.n_max >= 4000u || chain_together(u.units, u.n_max) > 1u);
+    const bool together = chain_together(u.units, u.n_max) > 1u;
+    return rounds >= 2u && u.n_max >= (together ? 900u : 4000u) && fill >= (together && u.n_max >= 2000u ? 0.75 : 0.84);
 }
 
 // ---- 8-bit attention, any-resolution mode: do most tiles of 64 positions hold padding, on a walk of enough tiles?  Where the columns are padded every line
