@@ -326,7 +326,7 @@ def main() -> int:
         extras["chain_token_to_group_tflops"] = round(flops / c_ms / 1e9, 2)
         del qs, ks, vs, os_
     if "bwd" in sections:
-        # training step of the layer: forward that keeps the log-sum-exp, then dQ (with delta) and dK, dV (two launches)
+        # training step of the layer: forward that keeps the log-sum-exp, then dQ, dK and dV
         dout = si.make_dout(w).cuda()
         lse = torch.empty((s * s * w.B, w.heads, w.Nsub), dtype=torch.float32, device="cuda")
         grads = [torch.empty_like(qd) for _ in range(3)]
@@ -339,7 +339,10 @@ def main() -> int:
         extras["bwd_ms"] = round(b_ms, 4)
         extras["bwd_ms_median_min"] = [round(b_t["median"], 4), round(b_t["min"], 4)]
         extras["bwd_effective_tflops"] = round(2.5 * flops / b_ms / 1e9, 2)  # five matrix products of the definition (forward has two)
-        extras["bwd_executed_tflops"] = round(3.5 * flops / b_ms / 1e9, 2)   # seven are executed (S and dP are formed in both launches)
+        # executed: five in one walk, which needs more than a float per position and head; else seven (S and dP are formed twice)
+        products = 5 if wsb.numel() > (lse.numel() * 4 + 255) // 256 * 256 else 7
+        extras["bwd_products_executed"] = products
+        extras["bwd_executed_tflops"] = round(products / 2 * flops / b_ms / 1e9, 2)
         extras["bwd_frac_of_bf16_peak_effective"] = round(2.5 * flops / b_ms / 1e9 / PEAK_BF16_TFLOPS, 4)
         del dout, lse, grads, wsb
     if "pad" in sections and w.name == "768p":
@@ -488,7 +491,7 @@ def main() -> int:
         others["attn_fwd_fp8_kernel"] = {"bound": "mfma", "achieved": c5["attn_tflops"], "peak": PEAK_FP8_TFLOPS, "unit": "TFLOP/s",
                                          "frac": c5["frac_of_fp8_mfma_peak"]}
     if "bwd_ms" in extras:
-        others["attn_bwd_kernel (dQ + dK,dV launches, 7 products executed)"] = {
+        others[f"attention backward ({extras['bwd_products_executed']} products executed)"] = {
             "bound": "mfma", "achieved": extras["bwd_executed_tflops"], "peak": PEAK_BF16_TFLOPS, "unit": "TFLOP/s",
             "frac": round(extras["bwd_executed_tflops"] / PEAK_BF16_TFLOPS, 4), "frac_on_the_5_product_definition": extras["bwd_frac_of_bf16_peak_effective"]}
     if others:

@@ -6,12 +6,12 @@
 // products over its own 256 keys, and leaves them for workgroup i+1; the last one rounds them to bf16 into dq.  No atomics on the sums and one order, that of
 // the keys: the result is deterministic.
 //   * Why: at 160 units of 20,160 tokens the two launches took 41 ms (dQ) and 58 (dK+dV) of matrix products at the board's power limit, a quarter of them S and dP
-//     formed a second time; one walk takes 81 (1030 TFLOP/s on the definition), 48 units of 8190 tokens 4.1 instead of 4.8.
-//   * What bounds it: a step takes about 4700 clocks at 1.77 GHz (the power limit; 2.1 at the same step count before the waits below were gone), 2560 of which are the
-//     80 products of a SIMD; LDS reads take half of the clocks, and some 200 are waits for the workgroup in front.  Without the sums' way through memory 74.7 ms.
+//     formed a second time; one walk takes 80 (1040 TFLOP/s on the definition), 48 units of 8190 tokens 4.1 instead of 4.8.
+//   * What bounds it: a step takes about 4900 clocks at 1.9 GHz (power: 2.4 on zeros), 2560 of which are the 80 products of a SIMD (matrix pipe 52 % busy, LDS 47, vector
+//     ALU 32), and some 200 are waits for the workgroup in front.  Without the sums' way through memory it took 74.7 ms where it took 85.
 //   * A unit's workgroups run on ONE XCD, whose L2 the sums pass through: workgroups take their work from a queue of the XCD that they find themselves on, so
 //     that no placement is assumed.  A store is there for the XCD's other CUs once vmcnt says so (the vector L1 writes through); the reader's loads go past its own
-//     L1.  Of 130 GB of sums about a quarter leave the L2 before they are read.
+//     L1.  Of 130 GB of sums about a fifth leave the L2 (28.6 GB written).
 //   * The sums are asked for between the products of dV of the step before, and used in the first products of the next: the loads are not waited for, and the flag
 //     that allows them was asked for at that step's start.  A wavefront follows the one with its number in the workgroup in front, which says so itself when its
 //     stores have arrived, half a step after them: one flag a workgroup, behind the step's barrier, left the next one further behind and made it wait for the slowest
