@@ -16,7 +16,7 @@
 //     that allows them was asked for at that step's start.  A wavefront follows the one with its number in the workgroup in front, which says so itself when its
 //     stores have arrived, half a step after them: one flag a workgroup, behind the step's barrier, left the next one further behind and made it wait for the slowest
 //     wavefront (64 units of 3000 tokens 904 us instead of 801, 48 of 8190 4210 instead of 4110).
-//   * LDS, 147 KiB: K of the owners (B operand of S for their wavefront, A operand of dQ for all), two steps of Q and dO, three of dS.  dQ of two steps is formed at
+//   * LDS, 149 KiB: K of the owners (B operand of S for their wavefront, A operand of dQ for all), two steps of Q and dO, three of dS.  dQ of two steps is formed at
 //     once, so that each of the 8 wavefronts has a tile of 32 queries x 32 channels and all have the same work: half of the wavefronts each step, in turn,
 //     left the others waiting at the barrier (5300 clocks a step instead of 4660).
 //   * The initial logits and dP of the queries (-lse / scale, -delta) are formed by the launch in front, laid out as the steps read them, and come straight into LDS
