@@ -145,7 +145,8 @@ int skiparse_attn_fwd_sparse(const void* q, const void* k, const void* v, void* 
  *   rounded up to 256), and for large problems at head_dim 128 as much again as two bf16 tensors, in which the unfinished dq is
  *   passed along workgroups (float32), so that all gradients take one walk.  Given the first part alone those problems are
  *   computed by the kernels of the small ones, 1.02 to 1.22 times slower; the results differ in rounding only (about 4e-4 relative).
- *   No gradient buffer may overlap any other argument.  s = 1 gives the gradients of full attention.
+ *   No gradient buffer may overlap any other argument, and the workspace's first part none of the tensors; where its rest overlaps
+ *   one, as in a buffer that holds both, the rest is not used.  s = 1 gives the gradients of full attention.
  * flags: 0, or SKIPARSE_PAD for the any-resolution mode (Sec. 3.2; the paper trains at 720x1280, a grid that needs the padding):
  *   H and W arbitrary, positions j then run over the grid padded to multiples of s*s (lse of a padding position is 0), padding
  *   positions are masked keys and have no gradients.

@@ -397,10 +397,7 @@ static int attn_bwd_common(const void* q, const void* k, const void* v, const vo
     for (void* y : outs)
         if (!y || misaligned(y)) return SKIPARSE_EINVAL;
     if (!lse || ((uintptr_t)lse & 3u)) return SKIPARSE_EINVAL;
-    size_t need = align256(lse_bytes);
-    const GridMap g = make_gridmap(T, H, W, s, pattern, pad);
-    BwdChain chain;
-    const bool chained = !use_static && bwd_chain(B, heads, head_dim, g, pad, &chain) && workspace_bytes >= need + chain.bytes(head_dim);
+    const size_t need = align256(lse_bytes);
     if (use_static) {
         if (need > STATIC_SCRATCH_BYTES) return SKIPARSE_EWORKSPACE;  // the problem is larger than the static scratch
         rc = static_scratch(&workspace);
@@ -408,21 +405,32 @@ static int attn_bwd_common(const void* q, const void* k, const void* v, const vo
     } else if (!workspace || workspace_bytes < need || misaligned(workspace)) {
         return SKIPARSE_EWORKSPACE;
     }
-    if (chained) {
-        chain.place((char*)workspace + need);
-        need += chain.bytes(head_dim);
-    }
     // no gradient may alias an input, another gradient, the log-sum-exp or the workspace
     for (int i = 0; i < 3; i++) {
         for (const void* x : ins)
             if (overlap(outs[i], x, bytes)) return SKIPARSE_EINVAL;
         for (int j = i + 1; j < 3; j++)
             if (overlap(outs[i], outs[j], bytes)) return SKIPARSE_EINVAL;
-        if (overlap2(outs[i], bytes, lse, lse_bytes) || overlap2(outs[i], bytes, workspace, need)) return SKIPARSE_EINVAL;
+        if (overlap2(outs[i], bytes, lse, lse_bytes)) return SKIPARSE_EINVAL;
     }
-    for (const void* x : ins)
-        if (overlap2(workspace, need, x, bytes)) return SKIPARSE_EINVAL;
-    if (overlap2(workspace, need, lse, lse_bytes)) return SKIPARSE_EINVAL;
+    // whether an argument lies in the first n bytes of the workspace
+    auto holds_argument = [&](size_t n) {
+        for (const void* x : ins)
+            if (overlap2(workspace, n, x, bytes)) return true;
+        for (const void* y : outs)
+            if (overlap2(workspace, n, y, bytes)) return true;
+        return overlap2(workspace, n, lse, lse_bytes);
+    };
+    if (holds_argument(need)) return SKIPARSE_EINVAL;
+    const GridMap g = make_gridmap(T, H, W, s, pattern, pad);
+    BwdChain chain;
+    bool chained = !use_static && bwd_chain(B, heads, head_dim, g, pad, &chain);
+    if (chained) {
+        // the call does without the rest: a workspace that is the front of a buffer whose rest holds tensors of the call is no error
+        const size_t all = need + chain.bytes(head_dim);
+        chained = workspace_bytes >= all && !holds_argument(all);
+        chain.place((char*)workspace + need);
+    }
     BwdArgs a;
     a.q = q; a.k = k; a.v = v; a.out = out; a.dout = dout; a.lse = lse;
     a.delta = (float*)workspace;

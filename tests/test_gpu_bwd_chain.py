@@ -135,6 +135,22 @@ def test_replayed_from_a_graph():
         assert all(torch.equal(a, b) for a, b in zip(got, want)), trial
 
 
+def test_workspace_at_the_front_of_a_buffer_that_holds_the_gradients():
+    """Only its first part, one float per position and head, must be free of the call's tensors: where the rest is not, the call does without it."""
+    q, k, v, out, dout, lse = _inputs(*GRIDS[0])
+    at = GRIDS[0][2:7]
+    least = _delta_only(lse).numel()
+    want = sk.skiparse_attn_bwd(q, k, v, out, dout, lse, *at, workspace=_delta_only(lse))
+    arena = torch.full((least + 4 * q.numel() * 2,), 0xFF, dtype=torch.uint8, device="cuda")
+    assert arena.numel() >= sk.skiparse_bwd_workspace_bytes(1, 16, 21, 32, 40, 128, 2, "group")
+    tensors = [arena[least + i * q.numel() * 2 :][: q.numel() * 2].view(torch.bfloat16).view(q.shape) for i in range(4)]
+    tensors[3].copy_(q)
+    got = sk.skiparse_attn_bwd(tensors[3], k, v, out, dout, lse, *at, workspace=arena, dq=tensors[0], dk=tensors[1], dv=tensors[2])
+    assert all(torch.equal(a, b) for a, b in zip(got, want)) and torch.equal(tensors[3], q)
+    with pytest.raises(sk.SkiparseError):
+        sk.skiparse_attn_bwd(q, k, v, out, dout, lse, *at, workspace=arena, dq=arena[: q.numel() * 2].view(torch.bfloat16).view(q.shape))
+
+
 @pytest.mark.parametrize("heads,N", [(101, 4737), (48, 8190)])
 def test_launches_of_one_kind_still_serve_small_workspaces(heads, N):
     """The kernels of 256 and of 128 queries a workgroup in a launch of their own, which one walk has replaced where there is room for it."""
