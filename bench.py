@@ -330,7 +330,7 @@ def main() -> int:
         dout = si.make_dout(w).cuda()
         lse = torch.empty((s * s * w.B, w.heads, w.Nsub), dtype=torch.float32, device="cuda")
         grads = [torch.empty_like(qd) for _ in range(3)]
-        wsb = torch.empty(sk.skiparse_bwd_workspace_bytes(w.B, w.heads, T, H, W, w.D, s, "token"), dtype=torch.uint8, device="cuda")
+        wsb = torch.empty(sk.skiparse_bwd_walk_workspace_bytes(w.B, w.heads, T, H, W, w.D, s, "token"), dtype=torch.uint8, device="cuda")
         fl_ms = time_calls(lambda: sk.skiparse_attn_fwd_lse(qd, kd, vd, T, H, W, s, "token", scale=w.scale, out=out, lse=lse), it)["avg"]
         b_t = time_calls(lambda: sk.skiparse_attn_bwd(qd, kd, vd, out, dout, lse, T, H, W, s, "token", scale=w.scale, dq=grads[0], dk=grads[1],
                                                       dv=grads[2], workspace=wsb), 5)
@@ -374,7 +374,7 @@ def main() -> int:
             dop = torch.randn(shp, generator=g, device="cuda", dtype=torch.bfloat16)
             opl, lsep = sk.skiparse_attn_fwd_lse(qp, kp, vp, T, Hp_real, W, s, "token", scale=w.scale, out=op, pad=True)
             gp = [torch.empty_like(qp) for _ in range(3)]
-            wsp = torch.empty(sk.skiparse_bwd_workspace_bytes(w.B, w.heads, T, Hp_real, W, w.D, s, "token", pad=True), dtype=torch.uint8, device="cuda")
+            wsp = torch.empty(sk.skiparse_bwd_walk_workspace_bytes(w.B, w.heads, T, Hp_real, W, w.D, s, "token", pad=True), dtype=torch.uint8, device="cuda")
             pb_ms = time_calls(lambda: sk.skiparse_attn_bwd(qp, kp, vp, opl, dop, lsep, T, Hp_real, W, s, "token", scale=w.scale, dq=gp[0],
                                                             dk=gp[1], dv=gp[2], workspace=wsp, pad=True), 3)["avg"]
             extras["pad720p_bwd_ms"] = round(pb_ms, 4)

@@ -141,12 +141,13 @@ int skiparse_attn_fwd_sparse(const void* q, const void* k, const void* v, void* 
  *   all inside every subsequence.  q, k, v, out, dout, dq, dk, dv: ORIGINAL layout [B][T*H*W][heads][head_dim] bf16; out and lse
  *   must be what skiparse_attn_fwd_lse produced for the same q, k, v, scale and flags.  P and dS are rounded to bf16 for the
  *   matrix products, accumulation is fp32, the gradients are rounded to bf16.  Deterministic (no atomics).
- *   workspace: skiparse_bwd_workspace_bytes() bytes of device memory: one float per position and head (skiparse_lse_bytes()
- *   rounded up to 256), and for large problems at head_dim 128 as much again as two bf16 tensors, in which the unfinished dq is
- *   passed along workgroups (float32), so that all gradients take one walk.  Given the first part alone those problems are
- *   computed by the kernels of the small ones, 1.02 to 1.22 times slower; the results differ in rounding only (about 4e-4 relative).
- *   No gradient buffer may overlap any other argument, and the workspace's first part none of the tensors; where its rest overlaps
- *   one, as in a buffer that holds both, the rest is not used.  s = 1 gives the gradients of full attention.
+ *   workspace: skiparse_bwd_workspace_bytes() bytes of device memory (one float per position and head), or, for large problems at
+ *   head_dim 128, skiparse_bwd_walk_workspace_bytes(): as much again as two bf16 tensors, in which the unfinished dq is passed along
+ *   workgroups (float32), so that all gradients take one walk, in 0.82 to 0.98 of the time.  The results of the two differ in rounding
+ *   only (about 4e-4 relative).  Where one walk would be no gain both functions give the same size.
+ *   No gradient buffer may overlap any other argument, nor may the first skiparse_bwd_workspace_bytes() bytes of the workspace;
+ *   where the rest of it does, as in a buffer that holds both, the rest is not used.
+ *   s = 1 gives the gradients of full attention.
  * flags: 0, or SKIPARSE_PAD for the any-resolution mode (Sec. 3.2; the paper trains at 720x1280, a grid that needs the padding):
  *   H and W arbitrary, positions j then run over the grid padded to multiples of s*s (lse of a padding position is 0), padding
  *   positions are masked keys and have no gradients.
@@ -155,6 +156,7 @@ size_t skiparse_lse_bytes(int B, int heads, int T, int H, int W, int head_dim, i
 int skiparse_attn_fwd_lse(const void* q, const void* k, const void* v, void* out, float* lse, int B, int heads, int T, int H, int W,
                           int head_dim, int s, int pattern, float scale, int dtype, unsigned flags, void* stream);
 size_t skiparse_bwd_workspace_bytes(int B, int heads, int T, int H, int W, int head_dim, int s, int pattern, unsigned flags);
+size_t skiparse_bwd_walk_workspace_bytes(int B, int heads, int T, int H, int W, int head_dim, int s, int pattern, unsigned flags);
 int skiparse_attn_bwd(const void* q, const void* k, const void* v, const void* out, const void* dout, const float* lse, void* dq,
                       void* dk, void* dv, int B, int heads, int T, int H, int W, int head_dim, int s, int pattern, float scale,
                       int dtype, unsigned flags, void* workspace, size_t workspace_bytes, void* stream);
@@ -163,8 +165,8 @@ int skiparse_attn_bwd(const void* q, const void* k, const void* v, const void* o
  * The backward pass for callers that cannot allocate device memory (code under HIP graph capture, tight serving or training
  * loops, harnesses that forbid hipMalloc): skiparse_attn_bwd with the delta workspace taken from a static device array inside the
  * library instead of a caller's buffer.  The call allocates nothing and frees nothing; inputs, outputs and results are exactly
- * those of skiparse_attn_bwd with a workspace of one float per position and head.
- *   Limit: one float per position and head (skiparse_lse_bytes()) must not exceed SKIPARSE_STATIC_SCRATCH_BYTES
+ * those of skiparse_attn_bwd with a workspace of skiparse_bwd_workspace_bytes() bytes.
+ *   Limit: the workspace the call would need (skiparse_bwd_workspace_bytes()) must not exceed SKIPARSE_STATIC_SCRATCH_BYTES
  *   (16 MiB = 4,194,304 positions x heads x subsequences; the 768P shape with 40 heads needs 12.9 MB); larger problems are
  *   rejected with SKIPARSE_EWORKSPACE and must use skiparse_attn_bwd.  Every GPU the library is used on holds the array until
  *   the process ends.

@@ -67,6 +67,8 @@ def lib() -> ctypes.CDLL:
         L.skiparse_attn_fwd_lse.argtypes = [vp] * 5 + [i] * 8 + [f, i, u, vp]
         L.skiparse_bwd_workspace_bytes.restype = sz
         L.skiparse_bwd_workspace_bytes.argtypes = [i] * 8 + [u]
+        L.skiparse_bwd_walk_workspace_bytes.restype = sz
+        L.skiparse_bwd_walk_workspace_bytes.argtypes = [i] * 8 + [u]
         L.skiparse_attn_bwd.restype = i
         L.skiparse_attn_bwd.argtypes = [vp] * 9 + [i] * 8 + [f, i, u, vp, sz, vp]
         L.skiparse_attn_bwd_static.restype = i
@@ -346,20 +348,26 @@ def skiparse_attn_fwd_lse(q, k, v, T: int, H: int, W: int, s: int, pattern: str,
 
 
 def skiparse_bwd_workspace_bytes(B, heads, T, H, W, D, s, pattern: str, pad: bool = False) -> int:
+    """Bytes that skiparse_attn_bwd cannot do without."""
     return _bytes("skiparse_bwd_workspace_bytes", B, heads, T, H, W, D, s, PATTERNS[pattern], PAD if pad else 0)
+
+
+def skiparse_bwd_walk_workspace_bytes(B, heads, T, H, W, D, s, pattern: str, pad: bool = False) -> int:
+    """Bytes with which skiparse_attn_bwd is fastest: more than the least for large problems at head_dim 128."""
+    return _bytes("skiparse_bwd_walk_workspace_bytes", B, heads, T, H, W, D, s, PATTERNS[pattern], PAD if pad else 0)
 
 
 def skiparse_attn_bwd(q, k, v, out, dout, lse, T: int, H: int, W: int, s: int, pattern: str, scale: float = 0.0,
                       dq=None, dk=None, dv=None, workspace: torch.Tensor | None = None, pad: bool = False):
     """Gradients (dq, dk, dv) of the Skiparse attention layer; out and lse come from skiparse_attn_fwd_lse (same pad flag).  A
-    uint8 device workspace of skiparse_bwd_workspace_bytes() bytes is allocated with torch if none is passed; a smaller one, down to
-    one float per position and head, selects kernels that need no more (slower on large problems at head_dim 128)."""
+    uint8 device workspace of skiparse_bwd_walk_workspace_bytes() bytes is allocated with torch if none is passed; a smaller one, down to
+    skiparse_bwd_workspace_bytes(), selects kernels that need no more (slower on large problems at head_dim 128)."""
     B, heads, D = _dims(q, T, H, W)
     dq = torch.empty_like(q) if dq is None else dq
     dk = torch.empty_like(q) if dk is None else dk
     dv = torch.empty_like(q) if dv is None else dv
     if workspace is None:
-        workspace = torch.empty(max(skiparse_bwd_workspace_bytes(B, heads, T, H, W, D, s, pattern, pad), 1), dtype=torch.uint8, device=q.device)
+        workspace = torch.empty(max(skiparse_bwd_walk_workspace_bytes(B, heads, T, H, W, D, s, pattern, pad), 1), dtype=torch.uint8, device=q.device)
     _skiparse_attn_bwd(q, k, v, out, dout, lse, dq, dk, dv, B, heads, T, H, W, D, s, PATTERNS[pattern], float(scale), _DTYPES[q.dtype],
                        PAD if pad else 0, workspace, workspace.numel() * workspace.element_size(), _stream())
     return dq, dk, dv
@@ -368,7 +376,8 @@ def skiparse_attn_bwd(q, k, v, out, dout, lse, T: int, H: int, W: int, s: int, p
 def skiparse_attn_bwd_static(q, k, v, out, dout, lse, dq, dk, dv, T: int, H: int, W: int, s: int, pattern: str, scale: float = 0.0,
                              pad: bool = False):
     """skiparse_attn_bwd for callers that cannot allocate: the delta workspace is the library's static device array, and this
-    wrapper allocates nothing either (dq, dk, dv must be passed).  Problems above the array's size raise (code -4)."""
+    wrapper allocates nothing either (dq, dk, dv must be passed).  Results are those of skiparse_attn_bwd with a workspace of
+    skiparse_bwd_workspace_bytes() bytes; problems that need more than the array's size raise (code -4)."""
     B, heads, D = _dims(q, T, H, W)
     _skiparse_attn_bwd_static(q, k, v, out, dout, lse, dq, dk, dv, B, heads, T, H, W, D, s, PATTERNS[pattern], float(scale),
                               _DTYPES[q.dtype], PAD if pad else 0, _stream())

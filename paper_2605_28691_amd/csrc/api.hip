@@ -368,7 +368,11 @@ static bool bwd_chain(int B, int heads, int head_dim, const GridMap& g, bool pad
 }
 
 size_t skiparse_bwd_workspace_bytes(int B, int heads, int T, int H, int W, int head_dim, int s, int pattern, unsigned flags) {
-    const size_t delta = align256(skiparse_lse_bytes(B, heads, T, H, W, head_dim, s, pattern, flags));
+    return align256(skiparse_lse_bytes(B, heads, T, H, W, head_dim, s, pattern, flags));
+}
+
+size_t skiparse_bwd_walk_workspace_bytes(int B, int heads, int T, int H, int W, int head_dim, int s, int pattern, unsigned flags) {
+    const size_t delta = skiparse_bwd_workspace_bytes(B, heads, T, H, W, head_dim, s, pattern, flags);
     if (delta == 0) return 0;
     BwdChain w;
     const bool pad = (flags & SKIPARSE_PAD) != 0 && s > 1;

@@ -247,6 +247,18 @@ def test_static_scratch_backward_rejects_what_does_not_fit(lib):
     assert lib.skiparse_attn_bwd_static(*ptrs, 1, 2, 2, 8, 8, 64, 2, 0, f, 0, 4, None) == -1   # unknown flag
 
 
+def test_least_workspace_of_the_backward_decides_about_the_static_scratch(lib):
+    """skiparse_bwd_workspace_bytes() is what the call cannot do without, one float per position and head: what fits the static scratch by it is
+    taken there.  What makes large problems faster is a size of its own."""
+    fits = [(1, 48, 1, 1, 8190, 128, 1, 0, 0), (1, 40, 21, 48, 80, 128, 2, 0, 0), (1, 40, 21, 45, 80, 128, 2, 0, 2), (1, 40, 1, 48, 80, 128, 2, 1, 0), (1, 48, 1, 1, 8190, 64, 1, 0, 0)]
+    more = [True, True, True, False, False]
+    for call, faster_with_more in zip(fits, more):
+        least, walk = lib.skiparse_bwd_workspace_bytes(*call), lib.skiparse_bwd_walk_workspace_bytes(*call)
+        assert least == (lib.skiparse_lse_bytes(*call) + 255) // 256 * 256 <= lib.skiparse_static_scratch_bytes()
+        assert (walk > least) == faster_with_more and (faster_with_more or walk == least)
+    assert lib.skiparse_bwd_walk_workspace_bytes(1, 2, 2, 7, 8, 64, 2, 0, 0) == 0  # bad shape
+
+
 def test_ssp_entry_points_reject_bad_arguments(lib):
     p, q = ctypes.c_void_p(FAKE), ctypes.c_void_p(FAKE + (1 << 30))
     for fn in (lib.skiparse_ssp_pack, lib.skiparse_ssp_unpack):

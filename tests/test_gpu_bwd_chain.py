@@ -36,7 +36,7 @@ def _inputs(B, heads, T, H, W, s, pattern, pad, seed=1):
     gen = torch.Generator(device="cuda").manual_seed(seed)
     q, k, v, dout = (torch.randn((B, T * H * W, heads, 128), generator=gen, device="cuda").to(torch.bfloat16) for _ in range(4))
     out, lse = sk.skiparse_attn_fwd_lse(q, k, v, T, H, W, s, pattern, pad=pad)
-    assert sk.skiparse_bwd_workspace_bytes(B, heads, T, H, W, 128, s, pattern, pad) > _delta_only(lse).numel()  # one walk
+    assert sk.skiparse_bwd_walk_workspace_bytes(B, heads, T, H, W, 128, s, pattern, pad) > _delta_only(lse).numel()  # one walk
     return q, k, v, out, dout, lse
 
 
@@ -59,7 +59,7 @@ def test_one_walk_gives_the_gradients(B, heads, T, H, W, s, pattern, pad):
     q, k, v, out, dout, lse = _inputs(B, heads, T, H, W, s, pattern, pad)
     at = (T, H, W, s, pattern)
     before = sk.skiparse_attn_bwd(q, k, v, out, dout, lse, *at, pad=pad, workspace=_delta_only(lse))
-    work = torch.full((sk.skiparse_bwd_workspace_bytes(B, heads, T, H, W, 128, s, pattern, pad),), 0xFF, dtype=torch.uint8, device="cuda")  # NaN and huge counts
+    work = torch.full((sk.skiparse_bwd_walk_workspace_bytes(B, heads, T, H, W, 128, s, pattern, pad),), 0xFF, dtype=torch.uint8, device="cuda")  # NaN and huge counts
     guard = 4096
     buf = torch.full((3, q.numel() + 2 * guard), float("nan"), dtype=torch.bfloat16, device="cuda")
     got = [b[guard:-guard].view(q.shape) for b in buf]
@@ -108,7 +108,7 @@ def test_two_streams_with_workspaces_of_their_own():
 def test_replayed_from_a_graph():
     q, k, v, out, dout, lse = _inputs(1, 64, 1, 1, 2017, 1, "token", False)
     at = (1, 1, 2017, 1, "token")
-    work = torch.empty(sk.skiparse_bwd_workspace_bytes(1, 64, 1, 1, 2017, 128, 1, "token"), dtype=torch.uint8, device="cuda")
+    work = torch.empty(sk.skiparse_bwd_walk_workspace_bytes(1, 64, 1, 1, 2017, 128, 1, "token"), dtype=torch.uint8, device="cuda")
     grads = [torch.empty_like(q) for _ in range(3)]
 
     def step():
@@ -142,7 +142,7 @@ def test_workspace_at_the_front_of_a_buffer_that_holds_the_gradients():
     least = _delta_only(lse).numel()
     want = sk.skiparse_attn_bwd(q, k, v, out, dout, lse, *at, workspace=_delta_only(lse))
     arena = torch.full((least + 4 * q.numel() * 2,), 0xFF, dtype=torch.uint8, device="cuda")
-    assert arena.numel() >= sk.skiparse_bwd_workspace_bytes(1, 16, 21, 32, 40, 128, 2, "group")
+    assert arena.numel() >= sk.skiparse_bwd_walk_workspace_bytes(1, 16, 21, 32, 40, 128, 2, "group")
     tensors = [arena[least + i * q.numel() * 2 :][: q.numel() * 2].view(torch.bfloat16).view(q.shape) for i in range(4)]
     tensors[3].copy_(q)
     got = sk.skiparse_attn_bwd(tensors[3], k, v, out, dout, lse, *at, workspace=arena, dq=tensors[0], dk=tensors[1], dv=tensors[2])
