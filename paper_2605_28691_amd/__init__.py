@@ -357,17 +357,29 @@ def skiparse_bwd_walk_workspace_bytes(B, heads, T, H, W, D, s, pattern: str, pad
     return _bytes("skiparse_bwd_walk_workspace_bytes", B, heads, T, H, W, D, s, PATTERNS[pattern], PAD if pad else 0)
 
 
+def _bwd_workspace(device, *call) -> torch.Tensor:
+    """For the fastest kernels (1.7 GB at 160 units of 20,160 positions), or where that is not to be had for the others (13 MB there)."""
+    least, walk = skiparse_bwd_workspace_bytes(*call), skiparse_bwd_walk_workspace_bytes(*call)
+    if walk > least:
+        try:
+            return torch.empty(walk, dtype=torch.uint8, device=device)
+        except torch.cuda.OutOfMemoryError:
+            pass
+    return torch.empty(max(least, 1), dtype=torch.uint8, device=device)
+
+
 def skiparse_attn_bwd(q, k, v, out, dout, lse, T: int, H: int, W: int, s: int, pattern: str, scale: float = 0.0,
                       dq=None, dk=None, dv=None, workspace: torch.Tensor | None = None, pad: bool = False):
     """Gradients (dq, dk, dv) of the Skiparse attention layer; out and lse come from skiparse_attn_fwd_lse (same pad flag).  A
     uint8 device workspace of skiparse_bwd_walk_workspace_bytes() bytes is allocated with torch if none is passed; a smaller one, down to
-    skiparse_bwd_workspace_bytes(), selects kernels that need no more (slower on large problems at head_dim 128)."""
+    skiparse_bwd_workspace_bytes(), selects kernels that need no more (slower on large problems at head_dim 128), as does a device that
+    has no room for it.  The two round differently: pass a workspace where every call has to give the same bits."""
     B, heads, D = _dims(q, T, H, W)
     dq = torch.empty_like(q) if dq is None else dq
     dk = torch.empty_like(q) if dk is None else dk
     dv = torch.empty_like(q) if dv is None else dv
     if workspace is None:
-        workspace = torch.empty(max(skiparse_bwd_walk_workspace_bytes(B, heads, T, H, W, D, s, pattern, pad), 1), dtype=torch.uint8, device=q.device)
+        workspace = _bwd_workspace(q.device, B, heads, T, H, W, D, s, pattern, pad)
     _skiparse_attn_bwd(q, k, v, out, dout, lse, dq, dk, dv, B, heads, T, H, W, D, s, PATTERNS[pattern], float(scale), _DTYPES[q.dtype],
                        PAD if pad else 0, workspace, workspace.numel() * workspace.element_size(), _stream())
     return dq, dk, dv

@@ -46,6 +46,35 @@ def test_sizes_refuse_what_is_no_integer():
             sk.skiparse_bwd_workspace_bytes(1, 2, 2, bad, 8, 64, 2, "token")
 
 
+@pytest.mark.parametrize("D, more", [(128, True), (64, False)])
+def test_backward_without_room_for_its_faster_kernels(monkeypatch, D, more):
+    """No workspace passed: where the memory for one walk is not there, the call takes what it cannot do without, as it always did."""
+    at = (1, 1, 8190, 1, "token")
+    q = torch.empty((1, 8190, 48, D), dtype=torch.bfloat16, device="meta")
+    lse = torch.empty((1, 48, 8190), device="meta")
+    least, walk = (f(1, 48, 1, 1, 8190, D, 1, "token") for f in (sk.skiparse_bwd_workspace_bytes, sk.skiparse_bwd_walk_workspace_bytes))
+    assert (walk > least) == more
+    used, free, empty = [], [walk], torch.empty
+
+    def with_limit(n, **kwargs):
+        if n > free[0]:
+            raise torch.cuda.OutOfMemoryError(f"{n} bytes")
+        return empty(n, **kwargs)
+
+    monkeypatch.setattr(torch, "empty", with_limit)
+    monkeypatch.setattr(sk, "_stream", lambda: 0)
+    monkeypatch.setattr(sk, "_skiparse_attn_bwd", lambda *args: used.append(args[-3:-1]))
+    for free[0], want in ((walk, walk), (walk - 1, least), (least, least)):
+        if not more and free[0] < least:
+            continue
+        sk.skiparse_attn_bwd(q, q, q, q, q, lse, *at)
+        assert used.pop()[1] == want
+    free[0] = least - 1
+    with pytest.raises(torch.cuda.OutOfMemoryError):
+        sk.skiparse_attn_bwd(q, q, q, q, q, lse, *at)
+    assert not used
+
+
 def test_stream_of_a_forked_child_is_refused():
     """torch refuses the GPU in a child forked from a process that has used it; so does a call whose tensors are all there already."""
     code = """
