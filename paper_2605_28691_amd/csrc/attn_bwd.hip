@@ -549,7 +549,7 @@ __global__ __launch_bounds__(64 * both_waves(SHAPE), (SHAPE == B128 || (SHAPE ==
 
 // delta = rowsum(dO o O) of every query, for the launch of both kinds.  A wavefront takes 16 rows of a unit, lane i finding row i, with all loads
 // in flight at once.  HBM-bound where it is not a launch's latency: 160 units of 960 tokens at head_dim 128 take 13 us of 290.
-// CHAIN: for attn_bwd_chain.hip, what its steps start their products with instead, and its control words cleared.
+// CHAIN: for attn_bwd_chain.hip, what its steps start their products with instead, its control words cleared, and the gradients of every block of keys marked as missing.
 struct NoChain {};
 template <int D, bool PAD, typename Chain>
 __global__ __launch_bounds__(256) void attn_bwd_delta_kernel(BwdArgs a, PadArg<PAD> pad_map, UnitMap units, uint32_t total, Chain chain) {
@@ -575,6 +575,13 @@ __global__ __launch_bounds__(256) void attn_bwd_delta_kernel(BwdArgs a, PadArg<P
         const size_t row = (size_t)(uint32_t)__shfl((int)tok, (int)(i * RPI + lane / CH)) * C;
         o[i] = *(const bf16x8*)(o_g + row);
         d[i] = *(const bf16x8*)(do_g + row);
+    }
+    if constexpr (CHAIN) {
+        // One value of every block of keys is no number until the walk has written the block: what it were to leave out (take_task() in attn_bwd_chain.hip) would show.
+        if (lane == 0u && j0 % CHAIN_OWNERS == 0u) {
+            const size_t first = base + (size_t)tok * C;
+            ((__bf16*)a.dq)[first] = ((__bf16*)a.dk)[first] = ((__bf16*)a.dv)[first] = (__bf16)__builtin_nanf("");
+        }
     }
     float* delta_u = a.delta + (size_t)unit * (uint32_t)a.g.n_sub;
     const float* lse_u = a.lse + (size_t)unit * (uint32_t)a.g.n_sub;

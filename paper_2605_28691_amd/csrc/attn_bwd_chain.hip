@@ -61,7 +61,9 @@ struct Lds {
 };
 
 // The next (unit, block of keys) of this XCD.  Units are handed out a group at a time, blocks of a group in the order of the keys with the group's units in turn.
-// Every wait is for a workgroup that holds an earlier ticket of the same XCD: one that runs already, whose own waits are for still earlier ones.
+// Every wait is for a workgroup that holds an earlier ticket of the same XCD: one that runs already, whose own waits are for still earlier ones.  A wait for the
+// group's number that ran out all the same would drop the block: its dk and dv, and dq of a unit's last block, keep the NaN of the launch in front, and the block
+// behind it finds no sums (see leave_sums).
 __device__ inline uint32_t take_task(const BwdChain& w, uint32_t xcc) {
     const uint32_t n = __hip_atomic_fetch_add(w.ctl + xcc * 32u, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     const uint32_t g = n / w.per_group, r = n - g * w.per_group;
@@ -213,7 +215,7 @@ __device__ __attribute__((always_inline)) inline void chain_task(const BwdArgs& 
         }
     };
     auto leave_sums = [&](uint32_t t, f32x16& x) __attribute__((always_inline)) {
-        if (lost) x[0] = __builtin_nanf("");  // no wait ends so (see take_task); if one did, dq would say it
+        if (lost) x[0] = __builtin_nanf("");  // no wait for the workgroup in front ends so; if one did, dq would say it
         if (!last) {
             const auto rsrc = part_rsrc(t);
 #pragma unroll

@@ -120,7 +120,7 @@ inline BwdChain make_bwd_chain(uint32_t n_units, uint32_t n_max) {
     w.n_groups = (n_units + w.together - 1u) / w.together;
     return w;
 }
-// Forms w.vals and clears w.ctl, in front of the walk.
+// Forms w.vals, clears w.ctl and marks every block of the gradients as missing, in front of the walk.
 hipError_t launch_bwd_chain_start(const BwdArgs& a, const BwdChain& w, hipStream_t stream);
 hipError_t launch_attn_bwd_chain(const BwdArgs& a, const BwdChain& w, hipStream_t stream);
 

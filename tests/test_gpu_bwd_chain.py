@@ -4,6 +4,8 @@ against the kernels that it stands in for, which a workspace of one float per po
 
 Tolerances: those of the bf16 backward (relative L2 1e-2, 3e-2 of the largest value) against float64.  Between the two paths P and dS differ by float32 rounding in
 front of their rounding to bf16, so that few of them round the other way: 4e-4 measured at 20,000 keys, 1e-3 allowed."""
+import ctypes
+
 import pytest
 import torch
 
@@ -133,6 +135,42 @@ def test_replayed_from_a_graph():
         want = sk.skiparse_attn_bwd(q, k, v, o2, dout, l2, *at)
         torch.cuda.synchronize()
         assert all(torch.equal(a, b) for a, b in zip(got, want)), trial
+
+
+@pytest.mark.parametrize("case", [CASES[3], *GRIDS[1:]])
+def test_what_the_walk_does_not_come_to_is_not_a_number(case):
+    """A workgroup whose bounded wait runs out drops its block of keys, and the call has returned long before.  The walk is taken out of a captured call, so that it
+    drops every block: each has NaN in its first row of all gradients, from the launch in front."""
+    T, H, W, s, pattern, pad = case[2:]
+    q, k, v, out, dout, lse = _inputs(*case)
+    grads = [torch.empty_like(q) for _ in range(3)]
+    work = torch.empty(sk.skiparse_bwd_walk_workspace_bytes(*case[:2], T, H, W, 128, s, pattern, pad), dtype=torch.uint8, device="cuda")
+
+    def call():
+        sk.skiparse_attn_bwd(q, k, v, out, dout, lse, T, H, W, s, pattern, pad=pad, workspace=work, dq=grads[0], dk=grads[1], dv=grads[2])
+
+    call()
+    assert not any(torch.isnan(g).any() for g in grads)
+    graph = torch.cuda.CUDAGraph(keep_graph=True)
+    with torch.cuda.graph(graph):
+        call()
+    hip, handle, count = ctypes.CDLL("libamdhip64.so"), ctypes.c_void_p(graph.raw_cuda_graph()), ctypes.c_size_t(2)
+    nodes, first = (ctypes.c_void_p * 2)(), (ctypes.c_void_p * 2)()
+    assert hip.hipGraphGetNodes(handle, nodes, ctypes.byref(count)) == 0 and count.value == 2
+    assert hip.hipGraphGetRootNodes(handle, first, ctypes.byref(count)) == 0 and count.value == 1
+    walk = [n for n in nodes if n != first[0]]
+    assert len(walk) == 1 and hip.hipGraphDestroyNode(ctypes.c_void_p(walk[0])) == 0
+    graph.instantiate()
+    for g in grads:
+        g.fill_(1.0)
+    graph.replay()
+    torch.cuda.synchronize()
+    blocks = torch.cat([_rows(T, H, W, s, pattern, p, r)[::256] for p in range(s) for r in range(s)])
+    for g in grads:
+        want = torch.ones_like(g)
+        want[:, blocks, :, 0] = float("nan")
+        same = bool(torch.where(torch.isnan(want), torch.isnan(g), g == want).all())
+        assert same
 
 
 def test_workspace_at_the_front_of_a_buffer_that_holds_the_gradients():
