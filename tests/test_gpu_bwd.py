@@ -37,10 +37,10 @@ def assert_grad_close(got, want, what):
     return max_abs, rel_l2
 
 
-def _run(sk, q, k, v, dout, T, H, W, s, pattern, scale):
+def _run(sk, q, k, v, dout, T, H, W, s, pattern, scale, workspace=None):
     qg, kg, vg, dg = (t.cuda() for t in (q, k, v, dout))
     out, lse = sk.skiparse_attn_fwd_lse(qg, kg, vg, T, H, W, s, pattern, scale=scale)
-    dq, dk, dv = sk.skiparse_attn_bwd(qg, kg, vg, out, dg, lse, T, H, W, s, pattern, scale=scale)
+    dq, dk, dv = sk.skiparse_attn_bwd(qg, kg, vg, out, dg, lse, T, H, W, s, pattern, scale=scale, workspace=workspace)
     return out, lse, dq, dk, dv
 
 
@@ -352,17 +352,21 @@ def test_backward_any_resolution_pair_shapes(D, case):
     test_backward_any_resolution_workgroup_shapes(*case, D)
 
 
-LONG_SHAPES = [(101, 4737)]  # heads, N: a launch of each kind at head_dim 128, dQ in 128-query workgroups
+# heads, N: at head_dim 128 on the least workspace a launch of each kind, dQ in 128-query workgroups; one walk where there is more
+LONG_SHAPES = [(101, 4737)]
+LONG_WORKSPACES = ["skiparse_bwd_workspace_bytes", "skiparse_bwd_walk_workspace_bytes"]
 
 
+@pytest.mark.parametrize("bytes_of", LONG_WORKSPACES)
 @pytest.mark.parametrize("heads,N", LONG_SHAPES)
-def test_backward_long_shapes(heads, N):
+def test_backward_long_shapes(heads, N, bytes_of):
     import paper_2605_28691_amd as sk
 
     w = si.make_shape("bwd_long", 1, heads, 128, 1, 1, N, 1, seed=N + heads)
     q, k, v = si.make_qkv(w)
     dout = si.make_dout(w)
-    _, _, dq, dk, dv = _run(sk, q, k, v, dout, 1, 1, N, 1, "token", w.scale)
+    work = torch.empty(getattr(sk, bytes_of)(1, heads, 1, 1, N, 128, 1, "token"), dtype=torch.uint8, device="cuda")
+    _, _, dq, dk, dv = _run(sk, q, k, v, dout, 1, 1, N, 1, "token", w.scale, work)
     toks = [0, 63, 64, 1000, 2431, N - 130, N - 2, N - 1]
     for h in (0, heads // 2, heads - 1):
         want = oracle.skiparse_attention_bwd_unit(*oracle_inputs(q, k, v), si.as_oracle_array(dout), 0, h, toks, 1, 1, N, 1, "token", w.scale)

@@ -13,6 +13,7 @@ from _util import assert_close_bf16, errors, oracle_inputs, to_np64
 pytestmark = pytest.mark.gpu
 
 LENGTHS = [1, 7, 8, 9, 15, 16, 17, 24, 31, 32, 33, 71, 95, 129, 200]
+WORKSPACES = [sk.skiparse_bwd_workspace_bytes, sk.skiparse_bwd_walk_workspace_bytes]
 GUARD = 32 * 1024  # elements in front of and behind a tensor
 
 
@@ -81,10 +82,12 @@ def _check(heads, H, W, s, pad, D, backward):
         sk.skiparse_attn_fwd(q, k, v, 1, H, W, s, "token", out=out.t, pad=pad)
         return _assert_rows(out.check(f"out {W}"), want[0], H * W, "out")
     _, lse = sk.skiparse_attn_fwd_lse(q, k, v, 1, H, W, s, "token", out=out.t, pad=pad)
-    grads = [Guarded(q.shape) for _ in range(3)]
-    sk.skiparse_attn_bwd(q, k, v, out.check(f"out {W}"), dout, lse, 1, H, W, s, "token", dq=grads[0].t, dk=grads[1].t, dv=grads[2].t, pad=pad)
-    for name, x, w in zip(("dq", "dk", "dv"), grads, want[1:]):
-        _assert_rows(x.check(f"{name} {W}"), w, H * W, name)
+    for size in sorted({f(1, heads, 1, H, W, D, s, "token", pad) for f in WORKSPACES}):  # where they differ, the larger one selects another kernel
+        grads = [Guarded(q.shape) for _ in range(3)]
+        sk.skiparse_attn_bwd(q, k, v, out.check(f"out {W}"), dout, lse, 1, H, W, s, "token", dq=grads[0].t, dk=grads[1].t, dv=grads[2].t, pad=pad,
+                             workspace=torch.empty(size, dtype=torch.uint8, device="cuda"))
+        for name, x, w in zip(("dq", "dk", "dv"), grads, want[1:]):
+            _assert_rows(x.check(f"{name} {W}"), w, H * W, name)
 
 
 # launch, head_dim, kernel (FwdShape or BwdShape), units, tokens in front of the last workgroup's

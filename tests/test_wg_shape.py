@@ -81,6 +81,10 @@ def test_gpu_tests_reach_every_shape(pick):
     calls += [("bwd", 128, 1, heads, 1, 1, n, 1, 0, 0) for heads, n in bwd.LONG_SHAPES]
     calls += [("bwd", D, 1, heads, T, H, W, s, int(pattern == "group"), 1) for D in (64, 128) for heads, T, H, W, s, pattern in bwd.PADDED_SHAPES + bwd.PADDED_PAIR_SHAPES[D]]
     calls += [("bwd", D, B, heads, T, H, W, s, group, 1) for B, heads, D, T, H, W, s in bwd.PAD_CASES for group in (0, 1)]
+    # a call that is one walk where it has the workspace reaches its shape only on the least one
+    assert "skiparse_bwd_workspace_bytes" in bwd.LONG_WORKSPACES
+    long = {("bwd", 128, 1, heads, 1, 1, n, 1, 0, 0) for heads, n in bwd.LONG_SHAPES}
+    assert [c for c, walk in zip(calls, pick([("chain", *c[1:]) for c in calls])) if walk and c[0] == "bwd" and c not in long] == []
     met, wrapped = set(), set()
     for call, shape in zip(calls, pick(calls)):
         launch, D, _, _, T, H, W, s, group, pad = call
@@ -178,6 +182,7 @@ def test_row_store_tests_reach_their_kernels(pick):
     """Every kernel with every kind of remainder, and with a last workgroup of few rows, on both sides of the lines at which rows are moved directly."""
     import test_gpu_row_stores as rows
 
+    assert "skiparse_bwd_workspace_bytes" in [f.__name__ for f in rows.WORKSPACES]  # the shapes of "bwd" are those of the least workspace
     for cases, last in ((rows.FEW, rows.FEW_ROWS), (rows.KERNELS, rows.LAST)):
         for launch, D, kernel, units, before in cases:
             assert pick([dense(launch, D, units, before + n) for n in last]) == [kernel] * len(last), (launch, D, kernel)
