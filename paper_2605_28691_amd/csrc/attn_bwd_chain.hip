@@ -50,7 +50,6 @@ constexpr int RING_AHEAD = 8, RING = 16;  // row offsets are formed this many gr
 constexpr float LOG2E = 1.4426950408889634f;
 constexpr int TILE = STEP * RB;         // bytes of a step's rows of one tensor
 constexpr int DS_TILE = OWNERS * STEP * 2;
-constexpr uint32_t NONE = ~0u, SKIP = ~0u - 1u;
 constexpr uint32_t MOST_TRIES = 1u << 22;  // of a wait for another workgroup, at about a microsecond each: no wait comes near it
 constexpr int SC1 = 16;                    // cache policy of a buffer load: past the vector L1, which other CUs' stores do not reach
 
@@ -60,14 +59,14 @@ struct Lds {
     uint32_t* rowoff;
 };
 
-// The next (unit, block of keys) of this XCD.  Units are handed out a group at a time, blocks of a group in the order of the keys with the group's units in turn.
+// The next (unit, block of keys) of this XCD.  Units are handed out a group at a time (BwdChain::task()).
 // Every wait is for a workgroup that holds an earlier ticket of the same XCD: one that runs already, whose own waits are for still earlier ones.  A wait for the
 // group's number that ran out all the same would drop the block: its dk and dv, and dq of a unit's last block, keep the NaN of the launch in front, and the block
 // behind it finds no sums (see leave_sums).
 __device__ inline uint32_t take_task(const BwdChain& w, uint32_t xcc) {
     const uint32_t n = __hip_atomic_fetch_add(w.ctl + xcc * 32u, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     const uint32_t g = n / w.per_group, r = n - g * w.per_group;
-    if (g > w.n_groups) return NONE;  // no XCD has more than all groups and one that was refused
+    if (g > w.n_groups) return CHAIN_NONE;  // no XCD has more than all groups and one that was refused
     uint32_t* const slot = w.ctl + CHAIN_SLOTS + xcc * (w.n_units + 1u) + g;
     uint32_t id;
     if (r == 0u) {
@@ -76,11 +75,9 @@ __device__ inline uint32_t take_task(const BwdChain& w, uint32_t xcc) {
     } else {
         uint32_t tries = 0;
         while ((id = __hip_atomic_load(slot, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) == 0u && ++tries < MOST_TRIES) __builtin_amdgcn_s_sleep(1);
-        if (id == 0u) return NONE;
+        if (id == 0u) return CHAIN_NONE;
     }
-    if (id > w.n_groups) return NONE;
-    const uint32_t blk = r / w.together, unit = (id - 1u) * w.together + (r - blk * w.together);
-    return unit < w.n_units ? unit * w.n_blk + blk : SKIP;
+    return w.task(id, r);
 }
 
 template <bool PAD>
@@ -408,8 +405,8 @@ __global__ __launch_bounds__(64 * NW, 1) void attn_bwd_chain_kernel(BwdArgs a, P
         if (tid == 0u) task = take_task(w, xcc);
         __syncthreads();
         const uint32_t lin = __builtin_amdgcn_readfirstlane(task);
-        if (lin == NONE) return;
-        if (lin == SKIP) continue;
+        if (lin == CHAIN_NONE) return;
+        if (lin == CHAIN_SKIP) continue;
         chain_task<PAD>(a, pad_map, w, units, lin, tid, {q0, q1, do0, do1, k, ds, vals0, vals1, rowoff});
     }
 }

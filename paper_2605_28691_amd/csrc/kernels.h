@@ -94,12 +94,19 @@ constexpr uint32_t CHAIN_XCCS = 16;  // values of the XCC number
 // wavefront's progress
 constexpr uint32_t CHAIN_FLAGS = 8;  // wavefronts of a workgroup
 constexpr uint32_t CHAIN_NEXT = 32u * CHAIN_XCCS, CHAIN_SLOTS = CHAIN_NEXT + 32u;
+constexpr uint32_t CHAIN_NONE = ~0u, CHAIN_SKIP = ~0u - 1u;  // no more work; the last group has no such unit
 struct BwdChain {
     uint32_t* ctl;      // cleared by the launch that forms delta
     float* vals;        // [unit][step][2][32]: the initial logits, -lse / scale, and dP, -delta, of the queries; -inf and 0 past the end
     float* part;        // [unit][step][32 queries x head_dim] sums of dQ
     uint32_t n_units, n_blk, n_steps;              // blocks of keys and steps of the largest unit
     uint32_t together, per_group, n_groups;        // units handed out together, their blocks, and how many times
+    // The work of ticket r of the group with number id (from 1): unit * n_blk + block.  Blocks come in the order of the keys, with the group's units in turn.
+    __host__ __device__ uint32_t task(uint32_t id, uint32_t r) const {
+        if (id > n_groups) return CHAIN_NONE;
+        const uint32_t blk = r / together, unit = (id - 1u) * together + (r - blk * together);
+        return unit < n_units ? unit * n_blk + blk : CHAIN_SKIP;
+    }
     __host__ __device__ uint32_t n_ctl() const { return CHAIN_SLOTS + CHAIN_XCCS * (n_units + 1u) + n_units * n_blk * CHAIN_FLAGS; }
     size_t ctl_bytes() const { return ((size_t)n_ctl() * 4u + 255u) & ~(size_t)255u; }
     size_t vals_bytes() const { return (size_t)n_units * n_steps * CHAIN_STEP * 8u; }

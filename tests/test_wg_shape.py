@@ -208,7 +208,19 @@ def test_one_walk_of_the_backward_where_its_rounds_are_full(pick):
     assert pick([("chain", 128, 1, 40, 21, 45, 80, 2, 0, 1), ("chain", 128, 1, 64, 30, 2, 7, 4, 1, 1), ("chain", 64, 1, 160, 1, 1, 20160, 1, 0, 0)]) == [1, 0, 0]
 
 
+def test_queue_of_one_walk_hands_out_every_block_once(pick):
+    """Whatever the units' number and the blocks', and however the workgroups are placed."""
+    calls = [dense("queue", 128, units, n) for units in (1, 7, 8, 13, 20, 25, 48, 63, 160, 515) for n in (1, 256, 900, 2900, 7000, 8190, 20160)]
+    assert all(pick(calls))
+
+
 def test_gpu_tests_of_one_walk_are_given_to_it(pick):
+    """All of them, units handed out 1 to 4 at a time, with and without a last group of fewer units, and chains of more workgroups than an XCD has CUs."""
     import test_gpu_bwd_chain as chain
 
-    assert pick([("chain", 128, B, heads, T, H, W, s, int(pattern == "group"), int(pad)) for B, heads, T, H, W, s, pattern, pad in chain.CASES]) == [1] * len(chain.CASES)
+    calls = [(128, B, heads, T, H, W, s, int(pattern == "group"), int(pad)) for B, heads, T, H, W, s, pattern, pad in chain.CASES]
+    assert pick([("chain", *c) for c in calls]) == [1] * len(calls)
+    together = pick([("queue", *c) for c in calls])
+    units = [c[1] * c[2] * c[6] ** 2 for c in calls]
+    assert set(together) == {1, 2, 3, 4} and {n for n, u in zip(together, units) if u % n} == {2, 3, 4}
+    assert [c for c, n in zip(calls, together) if n == 1 and c[3] * c[4] * c[5] > 32 * 256]
