@@ -140,7 +140,7 @@ int skiparse_attn_fwd_sparse(const void* q, const void* k, const void* v, void* 
  *   dv = P^T dout,  dq = scale dS k,  dk = scale dS^T q,  dS = P o (dout v^T - rowsum(dout o out)),  P = exp(scale q k^T - lse),
  *   all inside every subsequence.  q, k, v, out, dout, dq, dk, dv: ORIGINAL layout [B][T*H*W][heads][head_dim] bf16; out and lse
  *   must be what skiparse_attn_fwd_lse produced for the same q, k, v, scale and flags.  P and dS are rounded to bf16 for the
- *   matrix products, accumulation is fp32, the gradients are rounded to bf16.  Deterministic (no atomics).
+ *   matrix products, accumulation is fp32, the gradients are rounded to bf16.  Deterministic (no atomics on sums).
  *   workspace: skiparse_bwd_workspace_bytes() bytes of device memory (one float per position and head), or, for large problems at
  *   head_dim 128, skiparse_bwd_walk_workspace_bytes(): as much again as two bf16 tensors, in which the unfinished dq is passed along
  *   workgroups (float32), so that all gradients take one walk, in 0.82 to 0.98 of the time.  The results of the two differ in rounding

@@ -167,8 +167,8 @@ __device__ __attribute__((always_inline)) inline void bwd_part(const BwdArgs& a,
         }
         if (DKV && gtid < BT) {
             // log-sum-exp and delta of the streamed queries.  Nothing is done with them here: multiplied at once they were waited for, and the other wavefronts waited
-            // for this one at the tile's end (us: 48 units of 400 tokens 29.0 -> 27.7, 24 of 1000 56.6 -> 51.6, 1 of 6116 123 -> 110, 160 of 960 285 -> 273, at
-            // head_dim 64 1 of 3955 50.8 -> 42.5).
+            // for this one at the tile's end (us of the whole backward: 48 units of 400 tokens 28.1 -> 27.4, 24 of 1000 56.0 -> 51.8, 1 of 6116 125 -> 110, 160 of 960
+            // 283 -> 273, on two launches 48 of 8190 4990 -> 4840 and 160 of 20,160 99.9 -> 97.6 ms, at head_dim 64 1 of 3955 51.1 -> 42.7).
             const uint32_t jj = (tile0 + t) * BT + gtid;
             const uint32_t at = value_at(jj < n_seq ? jj : n_seq - 1u);
             rl = lse_u[at];

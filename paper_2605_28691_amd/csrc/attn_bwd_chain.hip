@@ -5,15 +5,17 @@
 // the unit's workgroups: workgroup i takes the float32 sums that workgroup i-1 has left for these 32 queries, starts its accumulators with them, adds the
 // products over its own 256 keys, and leaves them for workgroup i+1; the last one rounds them to bf16 into dq.  No atomics on the sums and one order, that of
 // the keys: the result is deterministic.
-//   * Why: at 160 units of 20,160 tokens the two launches took 41 ms (dQ) and 58 (dK+dV) of matrix products at the board's power limit, a quarter of them S and dP
-//     formed a second time; one walk takes 80 (1040 TFLOP/s on the definition), 48 units of 8190 tokens 4.1 instead of 4.8.
-//   * What bounds it: a step takes about 4900 clocks at 1.9 GHz (power: 2.4 on zeros), 2560 of which are the 80 products of a SIMD (matrix pipe 52 % busy, LDS 47, vector
-//     ALU 32), and some 200 are waits for the workgroup in front.  Without the sums' way through memory it took 74.7 ms where it took 85.
+//   * Why: at 160 units of 20,160 tokens the two launches take 41 ms (dQ) and 54 (dK+dV) of matrix products at the board's power limit, two sevenths of them S and dP
+//     formed a second time; one walk takes 80 (1040 TFLOP/s on the definition), 48 units of 8190 tokens 4.1 instead of 4.65.
+//   * What bounds it: a step takes about 4850 clocks at 1.88 GHz, 2560 of which are the 80 products of a SIMD (matrix pipe 53 % busy, LDS 48, vector ALU 32).  The clock
+//     is down, but the power limit is not all: busy x clock is 0.99 GHz where the two launches reach 1.17 and 1.19, and on zeros, at 2.38 GHz, a step takes 5300 clocks (69.5
+//     ms; the two launches 70.5): it waits for memory, which the clock does not speed up.  Without the sums' way through memory it took 74.7 ms where it took 85.
 //   * A unit's workgroups run on ONE XCD, whose L2 the sums pass through: workgroups take their work from a queue of the XCD that they find themselves on, so
 //     that no placement is assumed.  A store is there for the XCD's other CUs once vmcnt says so (the vector L1 writes through); the reader's loads go past its own
 //     L1.  Of 130 GB of sums about a fifth leave the L2 (28.6 GB written).
-//   * The sums are asked for between the products of dV of the step before, and used in the first products of the next: the loads are not waited for, and the flag
-//     that allows them was asked for at that step's start.  A wavefront follows the one with its number in the workgroup in front, which says so itself when its
+//   * The sums are asked for between the products of dV of the step before (the flag that allows them at that step's start) and used in the first products of the next.
+//     The last 12 products of the step hide them; what is left of their way is waited for with the next step's rows, at its end.
+//     A wavefront follows the one with its number in the workgroup in front, which says so itself when its
 //     stores have arrived, half a step after them: one flag a workgroup, behind the step's barrier, left the next one further behind and made it wait for the slowest
 //     wavefront (64 units of 3000 tokens 904 us instead of 801, 48 of 8190 4210 instead of 4110).
 //   * LDS, 149 KiB: K of the owners (B operand of S for their wavefront, A operand of dQ for all), two steps of Q and dO, three of dS.  dQ of two steps is formed at

@@ -158,7 +158,8 @@ constexpr ShapeCost PAIR_COST_64[] = {{B128, 128, false, 2, 7.2f, 5.4f, 2.4f, {0
                                       {B64_SPLIT, 64, true, 2, 7.4f, 4.0f, 1.8f, {0.361f, 0.387f, 0.481f}},
                                       {B128_SPLIT, 128, true, 1, 11.6f, 6.1f, 0.f, {0.372f, 0.426f}}};
 // Workgroups of 256 owners, in a launch of each kind, take 4 to 7 % less per row and block (head_dim 64: 1 to 4 %), but only their full rounds show
-// it: the share of the chip's rounds that holds owners has to be near one, or there is a single, largely filled round of a long walk.  Measured, one launch
+// it: the share of the chip's rounds that holds owners has to be near one, or there is a single, largely filled round of a long walk.  (At head_dim 128 the larger ones
+// come here on the least workspace only: bwd_chain().)  Measured, one launch
 // in B128 -> two of 256 owners, us: 73x12282 1.00 -> 0.932, 192x4584 0.953, 48x8190 5295 -> 5081, 84x3740 2026 -> 1918, 582x2734 7870 -> 7700, 160x20160 105,350 -> 102,340, 6x7844 (162 workgroups)
 // 0.900; the other way 20x20160 13,570 -> 13,940, 39x5781 1.011, 414x1824 1.058, 74x385 1.246.
 inline bool bwd_full_rounds(int head_dim, const UnitSizes& u) {
@@ -191,15 +192,17 @@ constexpr uint32_t XCDS = 8, CHAIN_OWNERS = 256, CHAIN_STEP = 32;  // keys of a 
 // Units handed to an XCD at a time, whose workgroups take turns on its CUs.  One unit makes a chain of 32 workgroups, each of which starts behind the one before it
 // and waits where that one was late; of several less is found in the L2, which long walks pay for.  us, by 1 / 2 / 4, units x tokens: 64x3000 830 / 810 / 776,
 // 160x4200 3964 / 3965 / 3887, 160x6000 7609 / 7642 / 7619, 48x8190 4221 / 4152 / 5239 (6 units an XCD), 64x12000 12,359 / 11,958 / 12,226, 160x12000 29,202 / 29,180 /
-// 30,213, 32x20160 16,521 / 17,005 / 16,963, 160x20160 82,409 / 83,608 / 84,902.  Never so many that the busiest XCD has more units than by one.
+// 30,213, 32x20160 16,521 / 17,005 / 16,963, 160x20160 82,409 / 83,608 / 84,902.  The upper line rests on
+// the last three sizes alone and lies somewhere between 12,000 tokens, where one and two are equal, and 20,160.  Never so many that the busiest XCD has more units than by one.
 inline uint32_t chain_together(uint64_t units, uint32_t n_max) {
     const uint64_t least = (units + XCDS - 1u) / XCDS;
     for (uint32_t n = n_max >= 16000u ? 1u : n_max >= 7000u ? 2u : 4u; n > 1u; n--)
         if (((units + n - 1u) / n + XCDS - 1u) / XCDS * n == least) return n;
     return 1u;
 }
-// An XCD's CUs take its units' workgroups in rounds.  Two rounds or more that are largely filled take 0.84 to 0.98 of the time of the shapes above; chains of 32
-// workgroups want longer walks.  Measured at 200 sizes, units x tokens: 160x20160 98.2 -> 80.6 ms, 48x8190 4817 -> 4092 us, 480x960 (0.88 full) 0.89 of the time,
+// An XCD's CUs take its units' workgroups in rounds.  Two rounds or more that are largely filled take 0.82 to 0.98 of the time of the shapes above; chains of 32
+// workgroups want longer walks.  Measured at 200 sizes, units x tokens: 160x20160 98.2 -> 80.6 ms, 48x8190 4817 -> 4092 us (0.85 and 0.88 of the time since the two
+// launches have gained as well: 95.1 ms, 4650), 480x960 (0.88 full) 0.89 of the time,
 // 64x2907 0.87, 48x4200 (0.77) 0.95, 64x2315 (0.75) 0.96; the other way 12x8116 (0.74) 1.09, 48x3000 (0.73) 1.03, 160x1017 (0.83) 1.02, 20x20160 (0.77, chains of 32)
 // 1.04, 40x3000 (0.92, chains of 32) 1.13, 24x2343 (one round) 1.03.
 inline bool bwd_chain(int head_dim, const UnitSizes& u) {
