@@ -207,7 +207,8 @@ def test_what_the_walk_does_not_come_to_is_not_a_number(case):
     graph = torch.cuda.CUDAGraph(keep_graph=True)
     with torch.cuda.graph(graph):
         call()
-    hip, handle, count = ctypes.CDLL("libamdhip64.so"), ctypes.c_void_p(graph.raw_cuda_graph()), ctypes.c_size_t(2)
+    # the runtime that the library is linked to
+    hip, handle, count = ctypes.CDLL(sk._LIB_PATH), ctypes.c_void_p(graph.raw_cuda_graph()), ctypes.c_size_t(2)
     nodes, first = (ctypes.c_void_p * 2)(), (ctypes.c_void_p * 2)()
     assert hip.hipGraphGetNodes(handle, nodes, ctypes.byref(count)) == 0 and count.value == 2
     assert hip.hipGraphGetRootNodes(handle, first, ctypes.byref(count)) == 0 and count.value == 1
